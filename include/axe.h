@@ -176,9 +176,12 @@ int axe_gemm(const axe_gemm_desc_t* g, const void* d_A, const void* d_B, void* d
  * Shapes: the 64 x 64 tile takes any M and N.  The 256 x 256 tile needs K a multiple of 64 (fp8: 128); with fp8
  * inputs a 16-bit output and M and N multiples of 256; with 16-bit inputs a 16-bit or an fp32 output, any M and
  * any N that is a multiple of 8 (fp32 output: of 4) -- edges that do not fill a tile are cut off by the buffer
- * bounds (plain operands only).  Left to itself the library takes the large tile once
- * M x N reaches 5 x 2^20 elements (fp8: 2^20); below that the 64 x 64 tiles are faster (a single large tile
- * takes as long as several rounds of small ones). */
+ * bounds (plain operands only).
+ * Left to itself (tile_hint 0) the library answers AXE_TILE_64x64x32 for every problem the large tiles do not pay for, and
+ * then launches whichever of a family of tiles from 16 x 16 to 256 x 128 loads the fewest rows per compute unit over
+ * all rounds of tiles (few rows of A: narrow tiles with K dealt to up to eight waves), or the 64 x 64 kernel itself for
+ * K up to 256; the large tiles are taken when they load no more.  axe_gemm_describe reports the tile that runs.
+ * tile_hint AXE_TILE_64x64x32 always means the 64 x 64 kernel. */
 int axe_gemm_tile(const axe_gemm_desc_t* g);
 
 /* ---------------------------------------------------------------------------------------------
@@ -203,9 +206,7 @@ int axe_gemm_tile(const axe_gemm_desc_t* g);
  * (the grouped form of B by (G, K, N) has one iter per block); leading dimensions, offsets and the group
  * stride multiples of 16 bytes; N a multiple of 256, K a multiple of 64.
  * One launch, work found on the device from d_group_rows; nothing is allocated and no scratch memory
- * is used.  G = 1 with d_group_rows = {0, M} is a dense GEMM; with few rows (M <= 64) that is the way to
- * the weight-streaming kernel (8192 x 8192 bf16 weights, M = 16: 33 us, against 125 us of axe_gemm's
- * 64 x 64 kernel). */
+ * is used.  G = 1 with d_group_rows = {0, M} is a dense GEMM (axe_gemm is the faster way to it). */
 typedef struct {
   int64_t      M, N, K;
   int32_t      G;
@@ -321,7 +322,9 @@ int axe_gemm_grouped_pair_static(const axe_gemm_grouped_desc_t* g1, const axe_ge
  * "reg" (index of the element inside the lane's fragment / accumulator / per-thread loop).
  * In the thread maps of operands that are loaded straight into LDS by the 256 x 256 kernels the
  * swizzle key spans the wave id; those maps are stated on the thread id, folded into the "lane"
- * axis as lane + 64 * wave (extent 64 * waves), with "wave" unused.
+ * axis as lane + 64 * wave (extent 64 * waves), with "wave" unused; so they are for the smaller tiles the library chooses
+ * by itself (where a single wave loads the tile: lane + 64 * piece).  Those of them whose wave groups take alternate
+ * K-tiles are described by their first group's K-tile; group p has the wave ids and the LDS block of p groups further on.
  * AXE_EUNSUPPORTED is never returned for a descriptor axe_gemm accepts. */
 enum {
   AXE_DESC_A_G2L_THREADS = 0, /* (BM, BK) tile of A  -> wave, lane, reg : who fetches which element  */

@@ -8,6 +8,7 @@
 #include "../../include/axe.h"
 #include "host_layout.h"
 #include "kernels.h"
+#include "tile_family.h"
 
 using namespace axe;
 
@@ -372,6 +373,7 @@ struct GemmPlan {
   GemmArgs args;
   bool fp8;
   int tile;           // AXE_TILE_*
+  int member;         // of the tile family (tile_family.h) when tile is AXE_TILE_64x64x32 and the library chose it; -1: the 64x64 kernel
   bool ragged;        // 256x256 tile on a shape with ragged edges (M, N no multiples of 256)
   int64_t oa, ob, oc; // element offsets of the operands inside their buffers
   int eb, cb;         // bytes per element of A / B and of C
@@ -539,6 +541,34 @@ int blocked_2d(const axe_layout_t* L, int mem_axis, int64_t d0, int64_t d1, bool
   return AXE_OK;
 }
 
+// What a launch on tiles of tm x tn costs, in bytes of an operand row that one compute unit loads per K-tile: every round of
+// tiles over the compute units takes the time of loading its (tm + tn) rows (the L2 -> CU path bounds all of these
+// kernels; a 256 x 256 tile's matrix work takes as long as its loads do).  Rows that do not exist are not loaded.
+int64_t tile_cost(int64_t M, int64_t N, int64_t tm, int64_t tn) {
+  const int64_t cus = cu_count(), tiles = ((M + tm - 1) / tm) * ((N + tn - 1) / tn);
+  return (tiles + cus - 1) / cus * (std::min(tm, M) + std::min(tn, N));
+}
+
+// The cheapest member of the tile family for a problem, or -1 when its rows are too far apart for 32-bit offsets inside a
+// tile (the 64 x 64 kernel takes those).  At equal cost the one with fewer rounds (fewer prologues), then the smaller one
+// (the larger would only pad).  AXE_TILE_MEMBER forces one, for experiments.
+int family_member(int64_t M, int64_t N, int eb, int64_t lda, int64_t ldb, int64_t* cost) {
+  *cost = INT64_MAX;
+  if (256 * lda * eb >= (int64_t(1) << 30) || 256 * ldb * eb >= (int64_t(1) << 30)) return -1;
+  const int forced = env_int("AXE_TILE_MEMBER", -1);
+  int best = -1;
+  int64_t best_tiles = 0;
+  for (int f = 0; f < kTileFamilySize; ++f) {
+    const TileShape& t = kTileFamily[f];
+    const int64_t tiles = ((M + t.tm - 1) / t.tm) * ((N + t.tn - 1) / t.tn), cus = cu_count();
+    if (tiles >= (int64_t(1) << 31) || (forced >= 0 && f != forced)) continue;
+    const int64_t c = tile_cost(M, N, t.tm, t.tn);
+    if (c > *cost || (c == *cost && (tiles + cus - 1) / cus >= (best_tiles + cus - 1) / cus)) continue;
+    best = f, *cost = c, best_tiles = tiles;
+  }
+  return best;
+}
+
 int plan_gemm(const axe_gemm_desc_t* g, const void* dA, const void* dB, void* dC, GemmPlan& P, bool need_ptrs) {
   if (!g) {
     set_error("axe_gemm: descriptor is NULL");
@@ -642,6 +672,7 @@ int plan_gemm(const axe_gemm_desc_t* g, const void* dA, const void* dB, void* dC
   const bool ragged_ok = !fp8 && (g->K % 64 == 0) && (g->N % cvec == 0) && (ldc % cvec == 0) && pitch_ok &&
                          256 * ldc * ob < (int64_t(1) << 31) && g->N <= 2048 * 256 && g->M < (int64_t(1) << 31);
   int tile = g->tile_hint;
+  bool large_ok = big_ok || ragged_ok;                             // the 256 x 256 tile can serve the problem
   if (row_scaled) {
     // one scale per row of A: the 64 x 64 kernel folds it per lane (fp32 or E8M0); the 256 x 256 kernel on the matrix
     // cores' scale path takes E8M0 row codes a window of 8 K-tiles at a time
@@ -654,7 +685,7 @@ int plan_gemm(const axe_gemm_desc_t* g, const void* dA, const void* dB, void* dC
       set_error("axe_gemm: one scale per row of A is served by the 64x64 and the 256x256 kernels");
       return AXE_EUNSUPPORTED;
     }
-    if (tile == AXE_TILE_AUTO && !rows_big) tile = AXE_TILE_64x64x32;
+    large_ok = rows_big;
   }
   if (blocked) {
     if (fp8 || !big_ok || !block_ok(opa) || !block_ok(opb) || (tile != AXE_TILE_AUTO && tile != AXE_TILE_256x256x64)) {
@@ -664,24 +695,28 @@ int plan_gemm(const axe_gemm_desc_t* g, const void* dA, const void* dB, void* dC
     }
     tile = AXE_TILE_256x256x64;
   }
+  P.member = -1;
   if (tile == AXE_TILE_AUTO) {
-    tile = big_ok ? AXE_TILE_256x256x64 : (n224_ok ? AXE_TILE_256x224x64 : AXE_TILE_64x64x32);
-    // 16-bit inputs: the large tile only once the 64 x 64 tiles of C would take more than about four rounds on the
-    // chip (measured, bf16, K = 1024 .. 4096: 768 x 768 12 vs 27 us, 1000 x 1000 12 vs 27 us, 2000 x 2000 41 vs 47 us,
-    // 4000 x 4000 388 vs 107 us -- a single large tile takes 27 - 47 us on its own, the small tiles' time grows
-    // with M x N); with ragged edges as well as without
-    static const int64_t large_min = [] { const char* v = getenv("AXE_LARGE_TILE_MIN_ELEMS"); return v ? atoll(v) : int64_t(5) << 20; }();
-    // (fp8: the 64 x 64 kernel is slower per tile; measured crossover near 1024 x 1024 -- 256^3: 8 vs 14 us,
-    //  1024^3: 19 vs 20 us, 2048^3: 91 vs 30 us)
-    const bool large = g->M * g->N >= (fp8 ? std::min<int64_t>(large_min, int64_t(1) << 20) : large_min);
-    if (!large) tile = AXE_TILE_64x64x32;
-    if (tile == AXE_TILE_64x64x32 && ragged_ok && large) tile = AXE_TILE_256x256x64;
-    if (big_ok && n224_ok && tile != AXE_TILE_64x64x32) {
-      // both fit: the launch runs ceil(tiles / compute units) rounds of tiles one after the other,
-      // each as long as the tile is wide; take the narrower tile when that is shorter in total
-      const int64_t cus = axe::cu_count(), gm = g->M / 256;
-      const int64_t t256 = (gm * (g->N / 256) + cus - 1) / cus * 256, t224 = (gm * (g->N / 224) + cus - 1) / cus * 224;
-      if (t224 < t256) tile = AXE_TILE_256x224x64;
+    // The large tiles (one workgroup per compute unit, 256 x 256 or 256 x 224) or the family of smaller ones, whichever
+    // costs less.  Measured, us, large tile / cheapest member -- bf16: 2048 x 2048 x 2048 39 / 20, 1024 x 3584 x 8192 129 / 59,
+    // 2048 x 4096 x 2048 40 / 34, 4096 x 4096 x 2048 52 / 70; fp8 with fp32 block scales: 1024 x 1024 x 2048 27 / 7,
+    // 2048 x 4096 x 2048 30 / 24, 4096 x 4096 x 2048 36 / 46.  Two lines are older than this rule and stand as what
+    // axe_gemm_tile has promised: problems of at most two K-tiles go by the elements of C (bf16 2304 x 2304 x 128 11.5 us on the
+    // large tile), and E8M0 codes per row of A take the large tile from 2048 x 2048 on (26 us at K = 2048, against 13).
+    int64_t family_cost;
+    P.member = family_member(g->M, g->N, eb, lda, ldb, &family_cost);
+    const int64_t t256 = large_ok && !(n224_ok && !big_ok) ? tile_cost(std::max<int64_t>(g->M, 256), std::max<int64_t>(g->N, 256), 256, 256) : INT64_MAX;
+    const int64_t t224 = n224_ok ? tile_cost(g->M, g->N, 256, 224) / 480 * 448 : INT64_MAX;   // (matrix work goes with the width)
+    const bool large = P.member < 0 || g->K <= 2 * bk ? g->M * g->N >= (fp8 ? int64_t(1) << 20 : int64_t(5) << 20)
+                                                      : std::min(t256, t224) <= family_cost || (row_scaled && g->M * g->N >= int64_t(4) << 20);
+    if (large && (large_ok || n224_ok)) {
+      tile = t224 < t256 ? AXE_TILE_256x224x64 : AXE_TILE_256x256x64;
+      P.member = -1;
+    } else {
+      tile = AXE_TILE_64x64x32;
+      // up to four K-tiles the burst variant of the 64 x 64 kernel is the faster one where it fits (graph replays, us, burst /
+      // cheapest member: 256^3 3.4 / 3.6, 512 x 512 x 128 2.7 / 4.0, 1024 x 1024 x 256 3.7 / 4.4; K = 512: 4.8 / 3.6, 5.1 / 5.0)
+      if (!fp8 && g->K <= 256 && small_preload_fits(g->M, g->N, g->K, lda, ldb, ldc)) P.member = -1;
     }
   }
   P.ragged = tile == AXE_TILE_256x256x64 && !big_ok && !blocked && ragged_ok;
@@ -701,8 +736,8 @@ int plan_gemm(const axe_gemm_desc_t* g, const void* dA, const void* dB, void* dC
     return AXE_EINVAL;
   }
   P.tile = tile;
-  const int64_t bm = tile == AXE_TILE_64x64x32 ? 64 : 256;
-  const int64_t bn = tile == AXE_TILE_64x64x32 ? 64 : (tile == AXE_TILE_256x224x64 ? 224 : 256);
+  const int64_t bm = P.member >= 0 ? kTileFamily[P.member].tm : (tile == AXE_TILE_64x64x32 ? 64 : 256);
+  const int64_t bn = P.member >= 0 ? kTileFamily[P.member].tn : (tile == AXE_TILE_64x64x32 ? 64 : (tile == AXE_TILE_256x224x64 ? 224 : 256));
   P.args.grid_m = (int32_t)((g->M + bm - 1) / bm);
   P.args.grid_n = (int32_t)((g->N + bn - 1) / bn);
   P.args.tile_n = (int32_t)bn;
@@ -713,7 +748,7 @@ int plan_gemm(const axe_gemm_desc_t* g, const void* dA, const void* dB, void* dC
   P.args.a_blk_stride = opa.rb ? opa.rb_stride : bm * lda;
   P.args.b_blk_stride = opb.rb ? opb.rb_stride : bn * ldb;
   if (P.ragged) P.args.groups = 1, P.args.tile_m = 256;            // one group of all rows, no offsets array
-  if (P.args.grid_m > 65535) {
+  if ((P.member >= 0 ? (g->M + 255) / 256 : P.args.grid_m) > 65535) {
     set_error("axe_gemm: M too large for one launch");
     return AXE_EUNSUPPORTED;
   }
@@ -1120,6 +1155,8 @@ int axe_gemm(const axe_gemm_desc_t* g, const void* d_A, const void* d_B, void* d
         // power-of-two scales (or none) ride on the matrix cores' scale operands; arbitrary fp32 scales are folded on the vector ALU
         : (P.args.scale_e8m0 || !P.args.scale_a ? launch_gemm_fp8_e8m0_256(P.args, (hipStream_t)stream)
                                                 : launch_gemm_fp8_256(P.args, (hipStream_t)stream));
+  else if (P.member >= 0)
+    e = P.fp8 ? launch_gemm_tiles_fp8(P.member, P.args, (hipStream_t)stream) : launch_gemm_tiles_16bit(P.member, P.args, (hipStream_t)stream);
   else
     e = launch_gemm_small(P.args, P.fp8, (hipStream_t)stream);
   return e == hipSuccess ? AXE_OK : hip_fail(e, "axe_gemm");
@@ -1133,3 +1170,8 @@ int axe_gemm_tile(const axe_gemm_desc_t* g) {
 }
 
 }  // extern "C"
+
+int axe::gemm_family_member(const axe_gemm_desc_t* g) {
+  GemmPlan P;
+  return plan_gemm(g, nullptr, nullptr, nullptr, P, false) ? -1 : P.member;
+}

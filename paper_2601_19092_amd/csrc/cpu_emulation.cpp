@@ -206,6 +206,8 @@ hipError_t launch_relayout_generic(const GenericRelayoutPlan& p, int unit, const
   return hipSuccess;
 }
 
+hipError_t launch_gemm_tiles_16bit(int, const GemmArgs&, hipStream_t) { return hipErrorNotSupported; }
+hipError_t launch_gemm_tiles_fp8(int, const GemmArgs&, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_gemm_small(const GemmArgs&, bool, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_gemm_bf16_256(const GemmArgs&, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_gemm_bf16_256_grouped(const GemmArgs&, hipStream_t) { return hipErrorNotSupported; }
@@ -236,13 +238,14 @@ extern "C" int axe_hostcheck_transposes_elementwise(void) { return axe::g_transp
 // Test hook: a layout axe_gemm_describe reports, evaluated at every point of its tile (through axe_layout_eval and
 // the host-memory stand-in above), against the index functions of tile_maps.h that the kernels compute their
 // addresses with.  Geometry (tile T x TN x BK, element bytes, waves, wave columns, element offset of the B region in
-// an LDS stage, workgroup grid columns for the accumulator layout) comes from the caller.  Returns the number of
+// an LDS stage, workgroup grid columns for the accumulator layout; flags: 1 = paired stores, 2 = a tile of at most 64 rows
+// that is loaded straight into LDS) comes from the caller.  Returns the number of
 // points that differ (0 = the described layout is the kernels' map), or a negative error code.
 #include "../../include/axe.h"
 #include "tile_maps.h"
 
 extern "C" int axe_hostcheck_describe_vs_tile_maps(const axe_gemm_desc_t* g, int32_t which, int32_t T, int32_t TN, int32_t BK,
-                                                   int32_t EB, int32_t NW, int32_t WN, int64_t b_off, int32_t paired_stores) {
+                                                   int32_t EB, int32_t NW, int32_t WN, int64_t b_off, int32_t flags) {
   namespace maps = axe::maps;
   enum { M_ = 0, LDS = 1, WG = 2, WAVE = 3, LANE = 4, REG = 5, NAX = 6 };
   axe_layout_t L;
@@ -257,7 +260,7 @@ extern "C" int axe_hostcheck_describe_vs_tile_maps(const axe_gemm_desc_t* g, int
   std::vector<int64_t> pts((size_t)(n * ER * NAX));
   if (int rc = axe_layout_eval(&L, 2, shape, n, nullptr, pts.data(), nullptr)) return rc;
   const int CE = maps::kChunkBytes / EB, CH = BK / CE, WM = NW / WN, F = maps::kFrag;
-  const bool big = T > 64, fp8 = EB == 1;
+  const bool paired_stores = flags & 1, big = T > 64 || (flags & 2), fp8 = EB == 1;
   const bool is_b = which == AXE_DESC_B_G2L_THREADS || which == AXE_DESC_B_LDS || which == AXE_DESC_B_OPERAND;
   int bad = 0;
   for (int64_t x = 0; x < n; ++x) {
@@ -273,9 +276,9 @@ extern "C" int axe_hostcheck_describe_vs_tile_maps(const axe_gemm_desc_t* g, int
       } else if (which == AXE_DESC_A_G2L_THREADS || which == AXE_DESC_B_G2L_THREADS) {
         if (big) {
           const int RPL = maps::kRowsPerLoad;
-          const int w = (r / RPL) % NW, i = r / (RPL * NW), lr = r % RPL;
-          if (maps::piece_row(w, i, lr, NW) != r) ++bad;
-          want[LANE] = 64 * w + maps::kLargeChunks * lr + maps::lds_chunk_pos(r, chunk, CH);   // thread id: wave folded into the lane axis
+          const int w = (r / RPL) % NW, i = NW == 1 ? 0 : r / (RPL * NW), lr = r % RPL;
+          if (maps::piece_row(w, r / (RPL * NW), lr, NW) != r) ++bad;
+          want[LANE] = 64 * (NW == 1 ? r / RPL : w) + maps::kLargeChunks * lr + maps::lds_chunk_pos(r, chunk, CH);   // thread id: wave folded into the lane axis
           want[REG] = i * CE + e;
         } else {
           const int c = r * CH + chunk, t = c % 256;

@@ -20,6 +20,7 @@
 
 #include "../../include/axe.h"
 #include "host_layout.h"
+#include "tile_family.h"
 #include "tile_maps.h"
 
 namespace {
@@ -126,6 +127,15 @@ Geo geometry(bool big, bool fp8, bool mx, int tile_n, bool out32) {
   return g;
 }
 
+// A member of the tile family: the K-tile of its first wave group (tile_family.h; group p is waves WM WN p ... and the
+// LDS block p (T + TN) rows further on, and takes the K-tiles p, p + wk, ...).
+Geo family_geometry(const axe::TileShape& m, bool fp8) {
+  Geo g = geometry(true, fp8, false, m.tn, true);
+  g.T = m.tm, g.WM = m.wm, g.WN = m.wn;
+  g.b_off = (int64_t)g.T * g.BK;
+  return g;
+}
+
 // (rows, k) tile of an operand: which thread fetches which element from HBM.
 int g2l_threads(const Geo& g, bool is_b, L2& out) {
   const int64_t R = is_b ? g.TN : g.T;
@@ -140,9 +150,10 @@ int g2l_threads(const Geo& g, bool is_b, L2& out) {
     const int RPL = maps::kRowsPerLoad, P = maps::lds_key_period(g.CH);
     atom = L2(P, {{P / RPL, 64, LANE}, {RPL, g.CH, LANE}}, g.BK, {{g.CH, 1, LANE}, {g.CE, 1, REG}});
     atom.swz(LANE, ilog2(g.CH), 0, ilog2(g.CH) + maps::kKeyShift);
-    // pieces i = 0 .. NI - 1 of a wave go to consecutive registers, wave pairs to consecutive 128-lane blocks
+    // pieces i = 0 .. NI - 1 of a wave go to consecutive registers, wave pairs to consecutive 128-lane blocks; where one
+    // wave loads the whole tile the key's bit comes from its piece index instead, and the lane axis counts lane + 64 piece
     const int64_t NI = R / (RPL * NW), pairs = NW / (P / RPL);
-    grid = L2(NI * pairs, {{NI, 1, REG}, {pairs, 1, LANE}}, 1, {});
+    grid = NW == 1 ? L2(R / P, {{R / P, 1, LANE}}, 1, {}) : L2(NI * pairs, {{NI, 1, REG}, {pairs, 1, LANE}}, 1, {});
   } else {
     // thread t fetches chunk t (+ 256 p) of the tile in row-major chunk order: a pass of one wave covers 64 / CH rows
     const int RPW = 64 / g.CH, PER = (64 * g.CH) / 256;
@@ -312,8 +323,10 @@ extern "C" int axe_gemm_describe(const axe_gemm_desc_t* g, int32_t which, axe_la
   }
   const bool big = tile != AXE_TILE_64x64x32;
   const bool mx = g->in_dtype == AXE_FP8_E4M3 && (!g->d_scale_a || g->scale_dtype == AXE_SCALE_E8M0);
-  const Geo geo = geometry(big, g->in_dtype == AXE_FP8_E4M3, mx, tile == AXE_TILE_256x224x64 ? 224 : (big ? 256 : 64),
-                           g->out_dtype == AXE_F32);
+  const int member = axe::gemm_family_member(g);
+  const Geo geo = member >= 0 ? family_geometry(axe::kTileFamily[member], g->in_dtype == AXE_FP8_E4M3)
+                              : geometry(big, g->in_dtype == AXE_FP8_E4M3, mx, tile == AXE_TILE_256x224x64 ? 224 : (big ? 256 : 64),
+                                         g->out_dtype == AXE_F32);
   L2 b;
   if (int rc = build(geo, which, (g->M + geo.T - 1) / geo.T, (g->N + geo.TN - 1) / geo.TN, false, b)) return rc;
   return emit(b, "axe_gemm_describe", out, shape, rank, arena, arena_bytes);

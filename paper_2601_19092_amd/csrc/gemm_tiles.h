@@ -1,0 +1,356 @@
+// GEMM on small and medium tiles for gfx950 (device code): one kernel body, its tile, wave grid and K split template
+// parameters (tile_family.h).  It serves what the 256-row kernels are too coarse for: a decode step's handful of rows,
+// prefill chunks, edges that fill no large tile, and fp8 with scales the matrix cores' scale path cannot carry.
+//
+// Bound: the L2 -> CU path.  A K-step of a TM x TN tile moves (TM + TN) x 128 bytes for TM x TN x 128 bytes' worth of
+// products; at the 21 - 25 TB/s the L2s deliver (about 86 GB/s per CU) a 128 x 128 tile's K-step takes 370 ns, of which the
+// matrix cores need 240.  Hence tiles as large as the problem can fill the chip with, every load instruction 8 rows of
+// whole 128-byte lines straight into LDS (buffer_load ... lds: no registers, no ds_write), and a ring deep enough to keep
+// 96 - 128 KiB in flight per CU.
+//
+// Tile movements (tile_maps.h, the image of the 256-row kernels):
+//   HBM -> LDS  : pieces of 8 rows x 128 bytes, one wave instruction each; the XOR swizzle is applied on the global side.
+//   LDS layout  : a stage holds one K-tile (128 bytes of K) of TM rows of A and TN rows of B for each of the WK wave
+//                 groups; 16-byte chunk c of row r at chunk position c ^ ((r >> 1) & 7).
+//   LDS -> VGPR : lane l reads row l % 16 of a fragment, chunks l / 16 and l / 16 + 4 (16-bit inputs: two MFMAs
+//                 16x16x32; fp8: the 32 bytes of one MFMA 16x16x128).
+//   MFMA        : operands swapped (B rows first), so a lane's accumulator fragment holds 4 consecutive columns of a row.
+//
+// Pipeline.  The loads of stage s + NST are issued while stage s is multiplied; the wait at the head of a step, for stage
+// s + 1, is counted (the loads of the NST - 2 stages after it stay in flight) and followed by one workgroup barrier -- or none
+// when a wave group is a single wave, which then reads only what it loaded itself.  Chunks past K, rows past the
+// operand's end and stages past the last K-tile get an offset no descriptor reaches: they load as zeros at no traffic,
+// and the counts stay the same.
+//   The fragments of stage s + 1 are read before stage s is multiplied: two waves per SIMD alone do not cover the LDS
+// latency (128 x 128, bf16 2048^3: 20.8 us without, 18.5 with).  Eight waves of 32 x 64 on a 128 x 128 tile beat four of
+// 64 x 64 (28 us), two K groups of 64 x 64 waves (24.7), sixteen of 32 x 32 (20.3) and two workgroups per CU with two stages
+// each (27.6 there, level on 512 tiles).
+//
+// Measured, us, against the 64 x 64 kernel that served these problems: bf16 16 x 3584 x 8192 91.5 -> 11.4 (58.9 MB, 5.2 TB/s),
+// 64 x 3584 x 8192 94 -> 15, 512 x 3584 x 8192 101 -> 40, fp16 2000 x 2000 x 2048 39 -> 20 (800 TFLOP/s), fp8 with one fp32 scale per
+// row 1000 x 3584 x 8192 365 -> 37 (1590 TFLOP/s), fp8 E8M0 256 x 512 x 6400 105 -> 7.6; and against the large tile: fp8
+// 1024 x 3584 x 8192 76 -> 36, bf16 2048 x 4096 x 2048 40 -> 34.
+//
+// Scales (fp8).  A K-tile is one 128-deep scale block: its product is formed alone and folded into the sum on the vector
+// ALU with the row's scale times the column block's (fp32, or E8M0 codes decoded as 2^(code - 127)).
+#pragma once
+#include <hip/hip_runtime.h>
+
+#include "device_types.h"
+#include "gemm_common.h"
+#include "kernels.h"
+#include "tile_family.h"
+#include "tile_maps.h"
+
+namespace axe {
+namespace tiles {
+
+typedef __attribute__((address_space(3))) void* lds_ptr;
+typedef __attribute__((address_space(3))) uint8_t* lds_u8;
+typedef __attribute__((ext_vector_type(2))) unsigned int u32x2;
+
+template <int DT>
+__device__ __forceinline__ uint32_t pack2(float lo, float hi) {
+  if constexpr (DT == 1) {
+    typedef __attribute__((ext_vector_type(2))) _Float16 f16x2;
+    const f16x2 v = {(_Float16)lo, (_Float16)hi};
+    return __builtin_bit_cast(uint32_t, v);
+  } else {
+    return pack_bf16(lo, hi);
+  }
+}
+
+template <int N>
+__device__ __forceinline__ void wait_loads() {                     // all but this wave's last N loads have landed; its LDS reads are done
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N) : "memory");
+}
+
+// DT: 0 bf16, 1 fp16, 2 fp8 e4m3.  SC (fp8): 0 unscaled, 1 fp32 scales, 2 E8M0 codes.
+template <int DT, int SC, int TM, int TN, int WM, int WN, int WK, int NST>
+__global__ __launch_bounds__(64 * WM * WN * WK) void gemm_tiles_kernel(GemmArgs g) {
+  constexpr int EB = DT == 2 ? 1 : 2;
+  constexpr int kRow = maps::kLargeRowBytes;
+  constexpr int NG = WM * WN;                                      // waves of a group
+  constexpr int MF = TM / WM / 16, NF = TN / WN / 16;              // fragments of a wave
+  constexpr int PA = TM / 8 / NG, PB = TN / 8 / NG;                // pieces of A and of B per wave and stage
+  constexpr int kLoads = PA + PB;
+  constexpr int kGroup = (TM + TN) * kRow, kStage = WK * kGroup;   // bytes of a group's K-tile, of a stage
+  constexpr int U = SC ? 4 : 2;                                    // stages per trip of the main loop
+  static_assert(TM % (16 * WM) == 0 && TN % (16 * WN) == 0 && (TM / 8) % NG == 0 && (TN / 8) % NG == 0, "whole fragments and pieces");
+  static_assert(NST * kStage <= 160 * 1024 && (WK - 1) * TM * TN * 4 <= NST * kStage, "the ring, and then the partial sums, fit LDS");
+  static_assert((NST - 1) * kLoads <= 63, "the counted wait");
+  __shared__ __attribute__((aligned(1024))) uint8_t lds_mem[NST * kStage];
+  const lds_u8 lds3 = (lds_u8)lds_mem;
+
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int kpart = w / NG, wg = w % NG;                           // group, wave inside the group
+  const int wm = wg / WN, wn = wg % WN;
+
+  int tm, tn;
+  tile_of_block((int)blockIdx.x, (int)gridDim.x, g.grid_m, g.grid_n, tm, tn);
+  const int64_t m0 = (int64_t)tm * TM, n0 = (int64_t)tn * TN;
+  const int rows = g.M - m0 < TM ? (int)(g.M - m0) : TM, cols = g.N - n0 < TN ? (int)(g.N - n0) : TN;
+
+  const int kbytes = (int)(g.K * EB);                              // bytes of K per row
+  const int nk = (kbytes + kRow - 1) / kRow;                       // K-tiles
+  const int a_pitch = (int)(g.lda * EB), b_pitch = (int)(g.ldb * EB);
+  const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc((void*)((const uint8_t*)g.A + m0 * g.lda * EB), 0,
+                                                                      (rows - 1) * a_pitch + kbytes, 0x00020000);
+  const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc((void*)((const uint8_t*)g.B + n0 * g.ldb * EB), 0,
+                                                                      (cols - 1) * b_pitch + kbytes, 0x00020000);
+
+  // ---- HBM -> LDS: this wave's pieces of a K-tile: of A, then of B
+  constexpr int kOutside = 0x7fff0000;                             // past the end of every descriptor (the host keeps them below 2^30 bytes)
+  const int lr = lane / maps::kLargeChunks, lp = lane % maps::kLargeChunks;
+  int voff[kLoads], kchunk[kLoads];                                // offset of the lane's chunk in the operand, and inside its row
+#pragma unroll
+  for (int i = 0; i < kLoads; ++i) {
+    const bool is_a = i < PA;
+    const int row = maps::piece_row(wg, is_a ? i : i - PA, lr, NG);
+    kchunk[i] = maps::lds_chunk_pos(row, lp, maps::kLargeChunks) * maps::kChunkBytes;
+    voff[i] = row < (is_a ? rows : cols) ? row * (is_a ? a_pitch : b_pitch) + kchunk[i] : kOutside;
+  }
+  auto issue = [&](int s, int slot) __attribute__((always_inline)) {
+    const int kt = s * WK + kpart;
+    const int left = kbytes - kt * kRow;                           // bytes of K from this K-tile on
+    const lds_u8 base = lds3 + slot * kStage + kpart * kGroup;
+    const int soff = left > 0 ? kt * kRow : 0;
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) {
+      const bool is_a = i < PA;
+      const int off = kchunk[i] < left ? voff[i] : kOutside;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(is_a ? ra : rb, (lds_ptr)(base + (is_a ? 0 : TM * kRow) + maps::piece_row(wg, is_a ? i : i - PA, 0, NG) * kRow),
+                                               16, off, soff, 0, 0);
+      AXE_PARANOID_WAIT();
+    }
+  };
+
+  // ---- LDS -> VGPR
+  const int fr = lane % maps::kFrag, fq = lane / maps::kFrag;
+  const int pos0 = maps::lds_chunk_pos(fr, maps::operand_chunk_fp8(0, fq), maps::kLargeChunks) * maps::kChunkBytes;
+  const int pos1 = maps::lds_chunk_pos(fr, maps::operand_chunk_fp8(1, fq), maps::kLargeChunks) * maps::kChunkBytes;
+  const int fa_off = kpart * kGroup + (wm * (TM / WM) + fr) * kRow, fb_off = kpart * kGroup + (TM + wn * (TN / WN) + fr) * kRow;
+  auto read = [&](lds_u8 p) __attribute__((always_inline)) -> i32x4 { return *(__attribute__((address_space(3))) const i32x4*)p; };
+
+  f32x4 acc[MF][NF];
+#pragma unroll
+  for (int i = 0; i < MF; ++i)
+#pragma unroll
+    for (int j = 0; j < NF; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  // ---- scales.  Lane (fr, fq) holds, for each of its fragment rows, the product of the row's and the column block's scale in
+  //      the K-tile of stage s0 + fq; two swaps between lane groups hand every lane those of all four stages of a trip.
+  //      One load per fragment row and one for the column block serve four stages; they are issued a trip ahead.
+  constexpr int kScaleLoads = SC ? MF + 1 : 0;
+  constexpr int SB = SC == 2 ? 1 : 4;                              // bytes of a stored scale
+  const bool by_row = g.scale_a_rows == 1;
+  __amdgpu_buffer_rsrc_t rsa, rsb;
+  int sa_off[SC ? MF : 1], sb_off = 0;
+  if constexpr (SC != 0) {
+    const int64_t a0 = by_row ? m0 : m0 / 128, b0 = n0 / 128;
+    rsa = __builtin_amdgcn_make_buffer_rsrc((void*)((const uint8_t*)g.scale_a + a0 * g.nkb * SB), 0, (by_row ? rows : (rows + 127) / 128) * g.nkb * SB, 0x00020000);
+    rsb = __builtin_amdgcn_make_buffer_rsrc((void*)((const uint8_t*)g.scale_b + b0 * g.nkb * SB), 0, g.nkb * SB, 0x00020000);
+#pragma unroll
+    for (int i = 0; i < MF; ++i) {
+      const int r = wm * (TM / WM) + i * 16 + fr;                  // (rows past the end: any value, they are never stored)
+      sa_off[i] = (by_row ? r : r / 128) * g.nkb * SB;
+    }
+  }
+  static_assert((TM <= 128 || TM % 128 == 0) && TN <= 128, "row blocks of scales start with a tile or inside one, a tile lies in one column block");
+  uint32_t sa_raw[SC ? MF : 1], sb_raw = 0;
+  auto fetch_scales = [&](int s0) __attribute__((always_inline)) {
+    if constexpr (SC != 0) {
+      asm volatile("" ::: "memory");                               // the waits below count these loads: they stay where they are
+      const int kt = (s0 + fq) * WK + kpart;
+      const int o = (kt < nk ? kt : nk - 1) * SB;
+      auto load = [&](__amdgpu_buffer_rsrc_t r, int off) -> uint32_t {
+        if constexpr (SC == 2) return __builtin_amdgcn_raw_buffer_load_b8(r, off, 0, 0);
+        else return __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0);
+      };
+      sb_raw = load(rsb, sb_off + o);
+#pragma unroll
+      for (int i = 0; i < MF; ++i) sa_raw[i] = load(rsa, sa_off[i] + o);
+      asm volatile("" ::: "memory");
+    }
+  };
+  auto scale_value = [](uint32_t raw) __attribute__((always_inline)) -> float {
+    return __builtin_bit_cast(float, SC == 2 ? raw << 23 : raw);
+  };
+  float sc[SC ? MF : 1][4];
+  auto spread_scales = [&](int s0) __attribute__((always_inline)) {
+    if constexpr (SC != 0) {
+      const bool in = (s0 + fq) * WK + kpart < nk;                 // stages past the last one multiply zeros by zero
+#pragma unroll
+      for (int i = 0; i < MF; ++i) {
+        const uint32_t v = in ? __builtin_bit_cast(uint32_t, scale_value(sa_raw[i]) * scale_value(sb_raw)) : 0u;
+        const auto h = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+        const auto q0 = __builtin_amdgcn_permlane16_swap(h[0], h[0], false, false);
+        const auto q2 = __builtin_amdgcn_permlane16_swap(h[1], h[1], false, false);
+        sc[i][0] = __builtin_bit_cast(float, (uint32_t)q0[0]), sc[i][1] = __builtin_bit_cast(float, (uint32_t)q0[1]);
+        sc[i][2] = __builtin_bit_cast(float, (uint32_t)q2[0]), sc[i][3] = __builtin_bit_cast(float, (uint32_t)q2[1]);
+      }
+    }
+  };
+
+  struct Frags {
+    i32x4 a[MF][2], b[NF][2];
+  };
+  auto read_frags = [&](Frags& f, int slot) __attribute__((always_inline)) {
+    const lds_u8 base = lds3 + slot * kStage;
+#pragma unroll
+    for (int j = 0; j < NF; ++j) f.b[j][0] = read(base + fb_off + j * 16 * kRow + pos0), f.b[j][1] = read(base + fb_off + j * 16 * kRow + pos1);
+#pragma unroll
+    for (int i = 0; i < MF; ++i) f.a[i][0] = read(base + fa_off + i * 16 * kRow + pos0), f.a[i][1] = read(base + fa_off + i * 16 * kRow + pos1);
+  };
+  auto multiply = [&](const Frags& f, int u) __attribute__((always_inline)) {
+    if constexpr (DT != 2) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int i = 0; i < MF; ++i)
+#pragma unroll
+          for (int j = 0; j < NF; ++j)
+            if constexpr (DT == 1) {
+              typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
+              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, f.b[j][h]), __builtin_bit_cast(f16x8, f.a[i][h]), acc[i][j], 0, 0, 0);
+            } else {
+              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, f.b[j][h]), __builtin_bit_cast(bf16x8, f.a[i][h]), acc[i][j], 0, 0, 0);
+            }
+    } else {
+      auto wide = [](const i32x4* p) { return i32x8{p[0][0], p[0][1], p[0][2], p[0][3], p[1][0], p[1][1], p[1][2], p[1][3]}; };
+#pragma unroll
+      for (int i = 0; i < MF; ++i) {
+        if constexpr (SC != 0) {
+          f32x4 p[NF];
+#pragma unroll
+          for (int j = 0; j < NF; ++j)
+            p[j] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(wide(f.b[j]), wide(f.a[i]), f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0, 0, 0, 0);
+#pragma unroll
+          for (int j = 0; j < NF; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[i][j][e] = __builtin_fmaf(sc[i][u], p[j][e], acc[i][j][e]);
+        } else {
+#pragma unroll
+          for (int j = 0; j < NF; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(wide(f.b[j]), wide(f.a[i]), acc[i][j], 0, 0, 0, 0, 0, 0);
+        }
+      }
+    }
+  };
+
+  const int ns = (nk + WK - 1) / WK;                               // stages
+  fetch_scales(0);
+#pragma unroll
+  for (int s = 0; s < NST; ++s) issue(s, s);
+  Frags f[2];
+  wait_loads<(NST - 1) * kLoads>();
+  if constexpr (NG > 1) wg_barrier();
+  AXE_PARANOID_SYNC();
+  read_frags(f[0], 0);
+
+  int cur = 0;                                                     // slot of the stage whose fragments are in f[u & 1]
+  for (int s0 = 0; s0 < ns; s0 += U) {
+    spread_scales(s0);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {                                  // (stages past the last one multiply zeros)
+      // stage s + 1 has landed, everybody's reads of stage s are done: its slot takes stage s + NST.  (The scales fetched
+      // at the head of the trip are younger than the stages up to s0 + NST - 1.)
+      if (u >= 1 && u <= NST - 2) wait_loads<(NST - 2) * kLoads + kScaleLoads>();
+      else wait_loads<(NST - 2) * kLoads>();
+      if constexpr (NG > 1) wg_barrier();
+      AXE_PARANOID_SYNC();
+      const int nxt = cur + 1 == NST ? 0 : cur + 1;
+      read_frags(f[(u + 1) & 1], nxt);
+      if (u == 0) fetch_scales(s0 + U);
+      issue(s0 + u + NST, cur);
+      multiply(f[u & 1], u);
+      cur = nxt;
+    }
+  }
+
+  // ---- the groups' sums meet in LDS: group 0 adds them in the order of the groups
+  if constexpr (WK > 1) {
+    wait_loads<0>();                                               // (the zeros of stages past the end have landed, too)
+    wg_barrier();
+    typedef __attribute__((address_space(3))) f32x4* lds_f32x4;
+    auto slot = [&](int part, int i, int j) -> lds_f32x4 {
+      return (lds_f32x4)(lds3 + (((part - 1) * NG + wg) * MF * NF + i * NF + j) * 1024 + lane * 16);
+    };
+    if (kpart > 0) {
+#pragma unroll
+      for (int i = 0; i < MF; ++i)
+#pragma unroll
+        for (int j = 0; j < NF; ++j) *slot(kpart, i, j) = acc[i][j];
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    wg_barrier();
+    if (kpart > 0) return;
+#pragma unroll
+    for (int part = 1; part < WK; ++part)
+#pragma unroll
+      for (int i = 0; i < MF; ++i)
+#pragma unroll
+        for (int j = 0; j < NF; ++j) acc[i][j] += *slot(part, i, j);
+  }
+
+  // ---- VGPR -> HBM: lane holds C[m][n .. n + 3]
+  const bool whole = (g.ldc & 3) == 0;
+#pragma unroll
+  for (int i = 0; i < MF; ++i) {
+    const int64_t m = m0 + wm * (TM / WM) + i * 16 + fr;
+    if (m >= g.M) continue;
+#pragma unroll
+    for (int j = 0; j < NF; ++j) {
+      const int64_t n = n0 + wn * (TN / WN) + j * 16 + maps::kAccCols * fq;
+      if (g.out_bf16) {
+        uint16_t* C = (uint16_t*)g.C + m * g.ldc + n;
+        const u32x2 d = {pack2<DT>(acc[i][j][0], acc[i][j][1]), pack2<DT>(acc[i][j][2], acc[i][j][3])};
+        if (n + 3 < g.N && whole) {
+          *(u32x2*)C = d;
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (n + e < g.N) C[e] = (uint16_t)(d[e >> 1] >> (16 * (e & 1)));
+        }
+      } else {
+        float* C = (float*)g.C + m * g.ldc + n;
+        if (n + 3 < g.N && whole) {
+          *(f32x4*)C = acc[i][j];
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (n + e < g.N) C[e] = acc[i][j][e];
+        }
+      }
+    }
+  }
+}
+
+template <int DT, int SC, int F>
+hipError_t launch_member(const GemmArgs& g, hipStream_t s) {
+  constexpr TileShape t = kTileFamily[F];
+  hipLaunchKernelGGL((gemm_tiles_kernel<DT, SC, t.tm, t.tn, t.wm, t.wn, t.wk, t.nst>), dim3((unsigned)(g.grid_m * g.grid_n)),
+                     dim3(64 * t.wm * t.wn * t.wk), 0, s, g);
+  return hipGetLastError();
+}
+
+template <int DT, int SC>
+hipError_t launch_family(int member, const GemmArgs& g, hipStream_t s) {
+  switch (member) {
+    case 0: return launch_member<DT, SC, 0>(g, s);
+    case 1: return launch_member<DT, SC, 1>(g, s);
+    case 2: return launch_member<DT, SC, 2>(g, s);
+    case 3: return launch_member<DT, SC, 3>(g, s);
+    case 4: return launch_member<DT, SC, 4>(g, s);
+    case 5: return launch_member<DT, SC, 5>(g, s);
+    case 6: return launch_member<DT, SC, 6>(g, s);
+    case 7: return launch_member<DT, SC, 7>(g, s);
+    case 8: return launch_member<DT, SC, 8>(g, s);
+    default: return hipErrorInvalidValue;
+  }
+  static_assert(kTileFamilySize == 9, "one case per member");
+}
+
+}  // namespace tiles
+}  // namespace axe

@@ -56,4 +56,8 @@ void canon_D(std::vector<HIter>& D);
 // Common refinement of two digit systems with equal total extent; false if none exists.
 bool joint_refine(const std::vector<HIter>& s, const std::vector<HIter>& d, std::vector<JointIter>& out);
 
+// The member of the tile family (tile_family.h) that axe_gemm launches for a descriptor it accepts; -1: another kernel
+// (or a descriptor it refuses).
+int gemm_family_member(const axe_gemm_desc_t* g);
+
 }  // namespace axe

@@ -17,6 +17,9 @@ hipError_t launch_relayout_transpose(const TransposePlan& p, int elem_bytes, con
 inline int transpose_tile_edge(int elem_bytes) { return elem_bytes == 8 ? 64 : 128; }
 hipError_t launch_relayout_generic(const GenericRelayoutPlan& p, int unit_bytes, const void* src, void* dst,
                                    hipStream_t s);
+// a member of the tile family (tile_family.h)
+hipError_t launch_gemm_tiles_16bit(int member, const GemmArgs& g, hipStream_t s);
+hipError_t launch_gemm_tiles_fp8(int member, const GemmArgs& g, hipStream_t s);
 hipError_t launch_gemm_small(const GemmArgs& g, bool fp8, hipStream_t s);
 // Large-tile kernels: 256 x tile_n workgroup tile (tile_n = 256, or 224 for bf16); require
 // M % 256 == 0, N % tile_n == 0 and K a multiple of the K step (bf16: 64, fp8: 128).
@@ -71,6 +74,16 @@ inline int cu_count() {
   return cus;
 }
 
+// The burst variant of the 64 x 64 kernel serves 16-bit problems made of whole 64 x 64 tiles with at most 8 K-tiles of 64
+// (K <= 512), C rows aligned for the vector stores, and few enough tiles that they are all on the chip at once (a workgroup
+// holds 16 KiB of LDS per K-tile, so at most one or two fit a compute unit: with many tiles the regular kernel's higher
+// occupancy wins).
+inline bool small_preload_fits(int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, int64_t ldc) {
+  static const bool enabled = [] { const char* v = getenv("AXE_SMALL_BURST"); return !v || atoi(v) != 0; }();
+  if (!enabled || M % 64 || N % 64 || K % 64 || K > 512 || K <= 0) return false;
+  if (ldc % 4 || 64 * lda * 2 >= (int64_t(1) << 31) || 64 * ldb * 2 >= (int64_t(1) << 31)) return false;
+  return (M / 64) * (N / 64) <= cu_count();
+}
 
 // Whether two planned grouped problems (the second reading what the first writes) can run as one launch: both on
 // the chained tile pipeline with the same tile height, and few enough tiles in the worst case that one workgroup per

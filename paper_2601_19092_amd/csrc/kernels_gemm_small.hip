@@ -1,8 +1,9 @@
 // Small-tile GEMM for gfx950: workgroup tile 64 x 64, K step of one LDS row (bf16: 32 elements
 // = 64 B, fp8: 128 elements = 128 B), 4 waves in a 2 x 2 grid, each wave a 32 x 32 sub-tile made
 // of 2 x 2 MFMA 16x16 fragments.  Ragged M / N are handled by zero-filled loads and guarded
-// stores, so this kernel serves every shape the library accepts; the large-tile kernel takes
-// over for big aligned problems.
+// stores, so this kernel serves every shape the library accepts.  It runs when it is asked for (tile_hint), for rows too far
+// apart for the tile family's 32-bit offsets and, as its burst variant, for short K; the tile family (gemm_tiles.h, 2 - 10
+// times as fast) and the large tiles take the rest.
 //
 // Tile movements (all K-contiguous, A row-major and B column-major):
 //   HBM -> VGPR : thread t fetches 16-byte chunk (row = t / CH, chunk = t % CH) of the tile
@@ -316,20 +317,9 @@ __global__ __launch_bounds__(256) void gemm_small_preload_kernel(GemmArgs g) {
     }
 }
 
-// The burst variant serves 16-bit problems made of whole 64 x 64 tiles with at most 8 K-tiles of 64 (K <= 512), C
-// rows aligned for the vector stores, and few enough tiles that they are all on the chip at once (a workgroup holds
-// 16 KiB of LDS per K-tile, so at most one or two fit a compute unit: with many tiles the regular kernel's higher
-// occupancy wins).
-bool small_preload_fits(const GemmArgs& g, bool fp8) {
-  static const bool enabled = [] { const char* v = getenv("AXE_SMALL_BURST"); return !v || atoi(v) != 0; }();
-  if (!enabled || fp8 || g.M % 64 || g.N % 64 || g.K % 64 || g.K > 512 || g.K <= 0) return false;
-  if (g.ldc % 4 || 64 * g.lda * 2 >= (int64_t(1) << 31) || 64 * g.ldb * 2 >= (int64_t(1) << 31)) return false;
-  return (g.M / 64) * (g.N / 64) <= cu_count();
-}
-
 hipError_t launch_gemm_small(const GemmArgs& g, bool fp8, hipStream_t s) {
   dim3 grid((unsigned)((g.N + 63) / 64), (unsigned)((g.M + 63) / 64));
-  if (small_preload_fits(g, fp8)) {
+  if (!fp8 && small_preload_fits(g.M, g.N, g.K, g.lda, g.ldb, g.ldc)) {
     if (g.f16) hipLaunchKernelGGL(gemm_small_preload_kernel<true>, grid, dim3(256), 0, s, g);
     else hipLaunchKernelGGL(gemm_small_preload_kernel<false>, grid, dim3(256), 0, s, g);
     return hipGetLastError();

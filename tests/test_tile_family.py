@@ -1,0 +1,165 @@
+"""The family of small and medium GEMM tiles: the layouts axe_gemm_describe reports for each member against the index
+functions the kernels compute with, which member a problem takes, and each member on the device against the oracle at the
+edges of its tile, of a K-tile and of its ring."""
+import ctypes as C
+import os
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import axe_ref as R
+from paper_2601_19092_amd import binding as B
+from paper_2601_19092_amd import workloads as W
+
+# (tile rows, tile columns, waves of a group, wave columns, groups, stages): tile_family.h
+MEMBERS = [(16, 16, 1, 1, 8, 4), (16, 32, 1, 1, 8, 3), (32, 16, 1, 1, 8, 3), (32, 32, 1, 1, 4, 4), (64, 32, 2, 1, 4, 3),
+           (64, 64, 4, 2, 2, 4), (128, 64, 8, 2, 1, 5), (128, 128, 8, 2, 1, 4), (256, 128, 8, 2, 1, 3)]
+CODE = {"bf16": B.AXE_BF16, "f16": B.AXE_F16, "fp8": B.AXE_FP8_E4M3, "f32": B.AXE_F32}
+TOL = {"bf16": 5e-3, "f16": 2e-3, "f32": 3e-5}              # results in 16 bits: their rounding; in fp32: see exact_tolerance
+
+
+class forced:
+    """The library takes this member for every problem it would give to the family (its own knob for experiments)."""
+
+    def __init__(self, member):
+        self.member = member
+
+    def __enter__(self):
+        os.environ["AXE_TILE_MEMBER"] = str(self.member)
+
+    def __exit__(self, *exc):
+        del os.environ["AXE_TILE_MEMBER"]
+
+
+def descriptor(M, N, K, dt="bf16", out="bf16", scales=None, rows=0, lda=None, ldb=None, ldc=None, off=0):
+    lda, ldb, ldc = lda or K, ldb or K, ldc or N
+    A = W.spec([(M, lda, "m"), (K, 1, "m")], O={"m": off})
+    Bs = W.spec([(K, 1, "m"), (N, ldb, "m")], O={"m": off})
+    Cs = W.spec([(M, ldc, "m"), (N, 1, "m")], O={"m": off})
+    sa, sb = scales if scales else (None, None)
+    return B.GemmDesc(M, N, K, CODE[dt], CODE[out], B.Layout(A), B.Layout(Bs), B.Layout(Cs), M * lda + off, N * ldb + off, M * ldc + off, sa, sb,
+                      scale_dtype=B.AXE_SCALE_E8M0 if scales and sa.dtype == torch.uint8 else B.AXE_SCALE_F32, scale_a_rows=rows)
+
+
+@pytest.mark.parametrize("member", range(len(MEMBERS)))
+@pytest.mark.parametrize("dt", ["bf16", "fp8"])
+def test_described_layouts_are_the_kernels_index_functions(member, dt):
+    hc = C.CDLL(os.environ.get("AXE_TEST_HOST_LIB") or os.path.join(os.path.dirname(B.LIB_PATH), "libaxe_hostcheck.so"))
+    fn = hc.axe_hostcheck_describe_vs_tile_maps
+    fn.restype = C.c_int
+    fn.argtypes = [C.POINTER(B.axe_gemm_desc_t)] + [C.c_int32] * 7 + [C.c_int64, C.c_int32]
+    tm, tn, ng, wn, _, _ = MEMBERS[member]
+    eb = 1 if dt == "fp8" else 2
+    d = descriptor(2 * tm, 2 * tn, 1024, dt)
+    with forced(member):
+        assert B.axe_gemm_describe(d, B.AXE_DESC_C_STORE)[1] == (tm, tn)
+        for which in range(8):
+            assert fn(C.byref(d.c), which, tm, tn, 128 // eb, eb, ng, wn, tm * 128 // eb, 2 if tm <= 64 else 0) == 0, which
+
+
+def taken(M, N, K, dt="bf16"):
+    d = descriptor(M, N, K, dt)
+    assert B.axe_gemm_tile(d) in (B.AXE_TILE_64x64x32, B.AXE_TILE_256x256x64, B.AXE_TILE_256x224x64)
+    return B.axe_gemm_describe(d, B.AXE_DESC_C_STORE)[1]
+
+
+def test_which_tile_a_problem_takes():
+    """The least rows loaded per compute unit over all rounds of tiles (256 compute units assumed where there is no device)."""
+    assert taken(16, 3584, 8192) == (16, 16) and taken(1, 512, 8192) == (16, 16)
+    assert taken(16, 8192, 8192) == (16, 32)                # 512 tiles of 16 x 16 would take two rounds
+    assert taken(64, 3584, 8192) == (32, 32)                # 224 tiles of 64 rows each loaded, against 112 of 96
+    assert taken(512, 3584, 8192) == (128, 64)
+    assert taken(2000, 2000, 2048) == (128, 128) and taken(1024, 3584, 8192, "fp8") == (128, 128)
+    assert taken(2048, 4096, 2048) == (256, 128) and taken(4096, 4096, 2048) == (256, 256)
+    assert taken(1000, 1000, 1000) == (64, 64)
+    assert taken(256, 256, 256) == (64, 64) and taken(256, 256, 512) == (16, 16)      # the burst variant up to four K-tiles
+
+
+def operands(M, N, K, dt, scale, rows, seed):
+    g = W.gemm_fp8(M, N, K, seed, scaled=False) if dt == "fp8" else (W.gemm_f16 if dt == "f16" else W.gemm_bf16)(M, N, K, seed)
+    sa = sb = None
+    if scale:
+        rng = np.random.default_rng(seed)
+        shape_a, shape_b = (M if rows == 1 else -(-M // 128), -(-K // 128)), (-(-N // 128), -(-K // 128))
+        draw = (lambda s: rng.integers(120, 135, s).astype(np.uint8)) if scale == "e8m0" else (lambda s: rng.uniform(0.5, 2.0, s).astype(np.float32))
+        sa, sb = draw(shape_a), draw(shape_b)
+    return g, sa, sb
+
+
+def padded(words, pitch, off, fill):
+    """(rows, K) words at `off` with rows `pitch` apart; what lies between holds `fill`."""
+    out = np.full(off + words.shape[0] * pitch, fill, dtype=words.dtype)
+    out[off:].reshape(words.shape[0], pitch)[:, :words.shape[1]] = words
+    return out
+
+
+def check(member, M, N, K, dt, out, scale=None, rows=0, pad=0):
+    g, sa, sb = operands(M, N, K, dt, scale, rows, 1000 * member + M + N + K)
+    t = [None if s is None else torch.from_numpy(s).cuda() for s in (sa, sb)]
+    vec = 16 if dt == "fp8" else 8
+    off = pad * vec
+    lda, ldb, ldc = K + pad * vec, K + 2 * pad * vec, N + (8 * pad if pad < 2 else 3)
+    nan = 0x7F if dt == "fp8" else (0x7E00 if dt == "f16" else 0x7FC0)   # read by mistake, it shows
+    dA, dB = (torch.from_numpy(padded(w, p, off, nan).view(np.uint8 if dt == "fp8" else np.int16)).cuda() for w, p in ((g.a_mk, lda), (g.b_nk, ldb)))
+    d = descriptor(M, N, K, dt, out, tuple(t) if scale else None, rows, lda, ldb, ldc, off)
+    dC = torch.full((M * ldc + off,), -7, dtype=torch.float32 if out == "f32" else torch.int16, device="cuda")
+    with forced(member):
+        assert B.axe_gemm_describe(d, B.AXE_DESC_C_STORE)[1] == MEMBERS[member][:2]
+        B.axe_gemm(d, dA, dB, dC)
+    torch.cuda.synchronize()
+    c = dC.cpu().numpy()
+    assert (c[:off] == -7).all()
+    c = c[off:].reshape(M, ldc)
+    assert (c[:, N:] == -7).all(), "columns past N written"
+    c = c[:, :N]
+    got = c.astype(np.float64) if out == "f32" else (R.f16_to_f64 if out == "f16" else R.bf16_to_f64)(np.ascontiguousarray(c).view(np.uint16))
+    kw = dict(scale_a=sa, scale_b=sb, block_m_a=1) if rows == 1 else dict(scale_a=sa, scale_b=sb)
+    if scale == "e8m0":
+        kw.update(scale_a=np.exp2(sa.astype(np.float32) - 127).astype(np.float32), scale_b=np.exp2(sb.astype(np.float32) - 127).astype(np.float32))
+    want = R.gemm_ref(g.a_mk, g.b_nk.T, {"bf16": R.AXE_BF16, "f16": R.AXE_F16, "fp8": R.AXE_FP8_E4M3}[dt], **(kw if scale else {}))
+    # fp32 results: 16-bit inputs sum in fp32 (K at most 1100 here: well below 1e-6); fp8's matrix instruction aligns its
+    # products to the largest one, 2^-16 of it (the repository's bound for that case is 3e-5)
+    tol = TOL[out] if out != "f32" or dt == "fp8" else 1e-6
+    assert R.rel_frobenius(got, want) <= tol
+    for r0 in range(0, M, 64):                                     # no tile may hide behind the others
+        for c0 in range(0, N, 64):
+            assert R.rel_frobenius(got[r0:r0 + 64, c0:c0 + 64], want[r0:r0 + 64, c0:c0 + 64]) <= 4 * tol, (r0, c0)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("member", range(len(MEMBERS)))
+@pytest.mark.parametrize("dt,out,scale,rows", [("bf16", "bf16", None, 0), ("f16", "f32", None, 0), ("fp8", "bf16", None, 0), ("fp8", "f32", "f32", 1),
+                                               ("fp8", "bf16", "f32", 0), ("fp8", "bf16", "e8m0", 1), ("fp8", "f32", "e8m0", 0)])
+def test_member_matches_the_oracle(member, dt, out, scale, rows):
+    tm, tn, _, _, wk, nst = MEMBERS[member]
+    kt = 128 if dt == "fp8" else 64
+    vec = 16 if dt == "fp8" else 8
+    # one row and column past whole tiles; K: one chunk past a K-tile, whole trips of the ring plus one, a single chunk
+    check(member, 2 * tm + 1, tn + 3, kt + vec, dt, out, scale, rows)
+    check(member, tm, 2 * tn + 8, (wk * nst + 1) * kt, dt, out, scale, rows, pad=1)
+    check(member, tm - 1, tn - 1, wk * (nst - 1) * kt, dt, out, scale, rows, pad=2)
+    # a single chunk of K (a descriptor per member: the plan of the last one is kept).  fp8 to fp32: of 16 products the largest
+    # is about 3 times the sum's deviation, so an error of 2^-16 of it is 2^-14.4 = 5e-5 of an average sum and more of one that
+    # cancels; the 3e-5 of TOL is a norm over many sums of many products, hence 64 columns there
+    check(member, 1, (64 if dt == "fp8" and out == "f32" else 1) + member, vec, dt, out, scale, rows)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("member", range(len(MEMBERS)))
+def test_fast_build_equals_checking_build(member):
+    """Counted waits and one barrier per K-step against a build that waits for every load: the same bits."""
+    from test_gpu_paranoid_build import PARANOID, library
+    for dt, scale in (("bf16", None), ("fp8", "f32")):
+        M, N, K = 520, 392, 2048 + (16 if dt == "fp8" else 8)
+        g, sa, sb = operands(M, N, K, dt, scale, 1, 5)
+        t = tuple(torch.from_numpy(s).cuda() for s in (sa, sb)) if scale else None
+        dA, dB = (torch.from_numpy(np.ascontiguousarray(w).view(np.uint8 if dt == "fp8" else np.int16)).cuda() for w in (g.a_mk, g.b_nk))
+        d = descriptor(M, N, K, dt, "bf16", t, 1 if scale else 0)
+        out = []
+        for path in (B.LIB_PATH, PARANOID):
+            with library(path), forced(member):
+                out.append(torch.zeros(M * N, dtype=torch.int16, device="cuda"))
+                B.axe_gemm(d, dA, dB, out[-1])
+                torch.cuda.synchronize()
+        assert torch.equal(out[0], out[1])
