@@ -149,6 +149,83 @@ __global__ __launch_bounds__(256) void layout_eval_fast_kernel(EvalDesc d, int64
   }
 }
 
+// Replicas, or more axes than the fast kernel takes (fewer than 2^31 points): the per = E_R n_axes words of an index are
+// consecutive in the output, so one thread per index would scatter 8-byte stores per x 8 bytes apart.  Here a workgroup
+// evaluates D + O of 256 indices once, one per thread (32-bit digits, as above), parks the coordinates in LDS, and writes the
+// 256 per words as 16-byte pairs, consecutive lanes on consecutive pairs: a thread keeps its two (replica, axis) positions for
+// the whole block -- the stride between its pairs is a multiple of per -- so the replica's offset is worked out once and a word
+// costs one LDS read and one addition.  Bound: the 8 per bytes written per index.  2048 x 4096 points of a 4-axis layout with
+// two replicas (537 MB): 300 -> 81 us (6.6 TB/s).
+template <int NAX>
+__global__ __launch_bounds__(256) void layout_eval_block_kernel(EvalDesc d, int64_t n, const int64_t* __restrict__ idx, int64_t* __restrict__ out) {
+  typedef __attribute__((ext_vector_type(2))) int64_t i64x2;
+  __shared__ int64_t coord[256 * NAX];
+  __shared__ uint8_t outside[256];
+  const int tid = threadIdx.x;
+  const int per = (int)d.E_R * NAX;
+  // pairs of words that the workgroup writes at a time: whole indices, an even number of words
+  int words = 512 / per * per;
+  if (words & 1) words -= per;
+  const int step = words / per;                                    // indices between two pairs of a thread
+  const bool writes = 2 * tid < words;
+  int di[2] = {0, 0}, ax[2] = {0, 0};
+  int64_t ro[2] = {0, 0};
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int q = 2 * tid + h;
+    di[h] = q / per;
+    int t = (q - di[h] * per) / NAX;
+    ax[h] = q % NAX;                                               // (per is a multiple of NAX)
+    for (int k = d.n_r - 1; k >= 0; --k) {
+      const int e = (int)d.rext[k], p = t / e;
+      if (d.raxis[k] == ax[h]) ro[h] += (int64_t)(t - p * e) * d.rstr[k];
+      t = p;
+    }
+  }
+  for (int64_t b0 = (int64_t)blockIdx.x * 256; b0 < n; b0 += (int64_t)gridDim.x * 256) {
+    const int count = n - b0 < 256 ? (int)(n - b0) : 256;
+    {
+      const int64_t x = tid < count ? (idx ? idx[b0 + tid] : b0 + tid) : 0;
+      int64_t c[NAX];
+#pragma unroll
+      for (int a = 0; a < NAX; ++a) c[a] = d.off[a];
+      uint32_t rem = (uint32_t)x;
+      for (int k = d.n_d - 1; k >= 0; --k) {
+        const uint32_t e = (uint32_t)d.ext[k];
+        uint32_t dig;
+        if (d.shift[k] >= 0) {
+          dig = rem & (e - 1u);
+          rem >>= d.shift[k];
+        } else {
+          const uint32_t q = rem / e;
+          dig = rem - q * e;
+          rem = q;
+        }
+        const int64_t v = (int64_t)dig * d.str[k];
+#pragma unroll
+        for (int a = 0; a < NAX; ++a) c[a] += a == d.axis[k] ? v : 0;
+      }
+#pragma unroll
+      for (int a = 0; a < NAX; ++a) coord[tid * NAX + a] = c[a];
+      outside[tid] = x < 0 || x >= d.E_D;
+    }
+    __syncthreads();
+    if (writes) {
+      auto word = [&](int i, int h) __attribute__((always_inline)) -> int64_t {
+        int64_t v = coord[(i + di[h]) * NAX + ax[h]] + ro[h];
+        if (ax[h] == d.swz_axis) v = swz_apply(v, d.swz);
+        return outside[i + di[h]] ? INT64_MIN : v;
+      };
+      int64_t* o = out + b0 * per + 2 * tid;
+      for (int i = 0; i < count; i += step, o += words) {
+        if (i + di[1] < count) __builtin_nontemporal_store(i64x2{word(i, 0), word(i, 1)}, (i64x2*)o);
+        else if (i + di[0] < count) *o = word(i, 0);
+      }
+    }
+    __syncthreads();
+  }
+}
+
 hipError_t launch_layout_eval(const EvalDesc& d, int64_t n, const int64_t* idx, int64_t* out, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   if (d.use32 && d.E_R == 1 && d.n_r == 0 && d.n_axes <= 4 && n < (int64_t(1) << 40)) {
@@ -167,6 +244,23 @@ hipError_t launch_layout_eval(const EvalDesc& d, int64_t n, const int64_t* idx, 
   }
   int64_t blocks = (n + 255) / 256;
   if (blocks > 65536 * 4) blocks = 65536 * 4;
+  // a pair of words per thread, whole indices per trip of a workgroup (per <= 256: two thirds of its threads write at least);
+  // pairs start on 16 bytes.  More words per index leave few whole indices to a trip and long runs to a thread: the general
+  // kernel keeps those, and index spaces of 2^31 points and more.
+  if (d.use32 && d.E_R * d.n_axes <= 256 && ((uintptr_t)out & 15) == 0) {
+    const dim3 grid((unsigned)blocks), block(256);
+    switch (d.n_axes) {
+      case 1: hipLaunchKernelGGL(layout_eval_block_kernel<1>, grid, block, 0, s, d, n, idx, out); break;
+      case 2: hipLaunchKernelGGL(layout_eval_block_kernel<2>, grid, block, 0, s, d, n, idx, out); break;
+      case 3: hipLaunchKernelGGL(layout_eval_block_kernel<3>, grid, block, 0, s, d, n, idx, out); break;
+      case 4: hipLaunchKernelGGL(layout_eval_block_kernel<4>, grid, block, 0, s, d, n, idx, out); break;
+      case 5: hipLaunchKernelGGL(layout_eval_block_kernel<5>, grid, block, 0, s, d, n, idx, out); break;
+      case 6: hipLaunchKernelGGL(layout_eval_block_kernel<6>, grid, block, 0, s, d, n, idx, out); break;
+      case 7: hipLaunchKernelGGL(layout_eval_block_kernel<7>, grid, block, 0, s, d, n, idx, out); break;
+      default: hipLaunchKernelGGL(layout_eval_block_kernel<8>, grid, block, 0, s, d, n, idx, out); break;
+    }
+    return hipGetLastError();
+  }
   if (d.use32)
     hipLaunchKernelGGL(layout_eval_kernel<uint32_t>, dim3((unsigned)blocks), dim3(256), 0, s, d, n, idx, out);
   else
