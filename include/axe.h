@@ -230,8 +230,9 @@ typedef struct {
  * epilogue).  Two kernels: the streaming kernel (any scales; groups of more than 64 rows take several passes over
  * their weights), and, with E8M0 scales or none, the tile kernel on the matrix cores' scale path (tiles of 256
  * or 128 rows: kernel_hint AXE_GROUPED_TILES, _256 or _128; gated: N / 2 a multiple of 128; AUTO takes it
- * from 9 rows per group on average, 16 when K <= 1024, with 128-row tiles up to 384 rows per group).  A hint
- * that asks for tiles with fp32 scales is AXE_EUNSUPPORTED. */
+ * from 9 rows per group on average, 16 when K <= 1024, with 128-row tiles up to 384 rows per group).  With fp32 scales
+ * AUTO takes tiles of 128 x 128 that fold the scales on the vector ALU, from 9 rows per group on average (18 when K <= 1024)
+ * and K = 512 on; a hint that asks for tiles with fp32 scales is AXE_EUNSUPPORTED. */
 
 /* Two kernels serve the same family.  AXE_GROUPED_TILES: 256 x 256 tiles of the chained GEMM pipeline, for
  * groups of hundreds of rows (of 128 x 256 unless groups average more than 384 rows: a K-step then takes half
@@ -342,7 +343,7 @@ int axe_gemm_describe(const axe_gemm_desc_t* g, int32_t which, axe_layout_t* out
 /* The same for axe_gemm_grouped (Sec. 4.1, fused MoE layer; host only).  The grouped tile kernels are the dense
  * 256-wide 16-bit kernel at a tile height of 256 or 128 rows and report its layouts at that height; AXE_DESC_ACC is
  * the accumulator layout of one tile (where a tile lies in the problem depends on the group sizes, which only the
- * device knows).  AXE_EUNSUPPORTED: the streaming kernel (no LDS stage; its register maps are stated in its source),
+ * device knows).  fp8 with fp32 scales: the 128 x 128 tile's own layouts.  AXE_EUNSUPPORTED: the streaming kernel (no LDS stage; its register maps are stated in its source),
  * and AXE_DESC_C_STORE with the gated epilogue (a stored element comes from two accumulators).
  * axe_gemm_grouped_kernel returns the kernel axe_gemm_grouped would launch: AXE_GROUPED_STREAM,
  * AXE_GROUPED_TILES_256 or AXE_GROUPED_TILES_128, or the error axe_gemm_grouped would return. */

@@ -827,6 +827,9 @@ int grouped_b(const axe_layout_t* L, int mem_axis, int64_t G, int64_t K, int64_t
   return AXE_OK;
 }
 
+// fp8 groups with fp32 scales: their tile kernel is the tile family's
+bool scales_f32(const GemmArgs& a) { return a.fp8 && a.scale_a && !a.scale_e8m0; }
+
 int plan_gemm_grouped(const axe_gemm_grouped_desc_t* g, const void* dA, const void* dB, void* dC, const int32_t* rows,
                       GemmArgs& a, bool need_ptrs) {
   const char* fn = "axe_gemm_grouped";
@@ -949,7 +952,7 @@ int plan_gemm_grouped(const axe_gemm_grouped_desc_t* g, const void* dA, const vo
   a.groups = g->G;
   a.gated = gated;
   a.tile_m = g->kernel_hint == AXE_GROUPED_TILES_256 ? 256 : (g->kernel_hint == AXE_GROUPED_TILES_128 ? 128 : 0);
-  if (fp8 && !fp8_tiles_ok) a.tile_m = -1;                         // -1: only the streaming kernel serves this problem
+  if (fp8 && !fp8_tiles_ok && !(scales_f32(a) && grouped_tiles_fit(g->N, g->K))) a.tile_m = -1;   // -1: only the streaming kernel serves this problem
   return AXE_OK;
 }
 
@@ -959,18 +962,25 @@ int plan_gemm_grouped(const axe_gemm_grouped_desc_t* g, const void* dA, const vo
 // streaming kernel against tiles, us): fp16 gemm1 at 12 rows per group 148 against 152, at 16 rows 165 against 152;
 // fp16 gemm2 at 16 rows 84 against 88, at 20 rows 92 against 90; fp8 (tiles of 128 rows) gemm1 at 6 rows 78 against 84,
 // at 8 rows 84 against 85, at 10 rows 91 against 85; fp8 gemm2 at 12 rows 44 against 49, at 16 rows 50 against 50, at
-// 20 rows 55 against 50.  Far from the crossover (fp8 layer): 4 rows per group 104 against 151, 256 rows 1373 against 274.
+// 20 rows 55 against 50; with fp32 scales gemm1 at 8 rows 83 against 86, at 16 rows 108 against 87, gemm2 at 8 rows 43 against 55,
+// at 16 rows 55 against 57, at 32 rows 80 against 61.  Far from the crossover (fp8 layer): 4 rows per group 104 against 151, 256 rows 1373 against 274.
 bool grouped_goes_to_stream(const axe_gemm_grouped_desc_t* g, const GemmArgs& a) {
   if (g->kernel_hint == AXE_GROUPED_STREAM) return true;
   if (a.fp8 && a.tile_m < 0) return true;
   if (g->kernel_hint != AXE_GROUPED_AUTO) return false;            // tiles asked for
   const bool short_k = g->K <= 1024;
-  int64_t rows = a.fp8 ? (short_k ? 15 : 8) : (short_k ? 19 : 13);
+  int64_t rows = a.fp8 ? (short_k ? (scales_f32(a) ? 17 : 15) : 8) : (short_k ? 19 : 13);
   if (a.fp8) {
     static const int64_t min_rows = [] { const char* v = getenv("AXE_GROUPED_FP8_TILE_ROWS"); return v ? atoll(v) : int64_t(0); }();
     if (min_rows > 0) rows = min_rows - 1;
   }
   return g->M <= rows * (int64_t)g->G;
+}
+
+hipError_t launch_grouped(const GemmArgs& a, bool streams, hipStream_t st) {
+  if (streams) return launch_gemm_grouped_stream(a, st);
+  if (scales_f32(a)) return launch_gemm_tiles_grouped(a, st);
+  return a.fp8 ? launch_gemm_fp8_e8m0_256_grouped(a, st) : launch_gemm_bf16_256_grouped(a, st);
 }
 
 }  // namespace
@@ -979,9 +989,7 @@ int axe_gemm_grouped(const axe_gemm_grouped_desc_t* g, const void* d_A, const vo
                      const int32_t* d_group_rows, void* stream) {
   GemmArgs a;
   if (int rc = plan_gemm_grouped(g, d_A, d_B, d_C, d_group_rows, a, true)) return rc;
-  hipError_t e = grouped_goes_to_stream(g, a) ? launch_gemm_grouped_stream(a, (hipStream_t)stream)
-                 : a.fp8                      ? launch_gemm_fp8_e8m0_256_grouped(a, (hipStream_t)stream)
-                                              : launch_gemm_bf16_256_grouped(a, (hipStream_t)stream);
+  hipError_t e = launch_grouped(a, grouped_goes_to_stream(g, a), (hipStream_t)stream);
   return e == hipSuccess ? AXE_OK : hip_fail(e, "axe_gemm_grouped");
 }
 
@@ -990,6 +998,7 @@ int axe_gemm_grouped_kernel(const axe_gemm_grouped_desc_t* g) {
   GemmArgs a;
   if (int rc = plan_gemm_grouped(g, nullptr, nullptr, nullptr, nullptr, a, false)) return rc;
   if (grouped_goes_to_stream(g, a)) return AXE_GROUPED_STREAM;
+  if (scales_f32(a)) return AXE_GROUPED_TILES_128;
   if (a.fp8) return grouped_fp8_tile_rows(a.M, a.groups, a.tile_m) == 128 ? AXE_GROUPED_TILES_128 : AXE_GROUPED_TILES_256;
   return grouped_tile_rows(a.M, a.groups, a.tile_m) == 128 ? AXE_GROUPED_TILES_128 : AXE_GROUPED_TILES_256;
 }
@@ -1083,9 +1092,7 @@ int axe_gemm_grouped_pair(const axe_gemm_grouped_desc_t* g1, const axe_gemm_grou
     const axe_gemm_grouped_desc_t* g = i ? g2 : g1;
     const GemmArgs& a = i ? a2 : a1;
     const bool streams = i ? pair_second_goes_to_stream(g1, g2, a1, a2) : grouped_goes_to_stream(g1, a1);
-    hipError_t e = streams ? launch_gemm_grouped_stream(a, st)
-                   : a.fp8 ? launch_gemm_fp8_e8m0_256_grouped(a, st)
-                           : launch_gemm_bf16_256_grouped(a, st);
+    hipError_t e = launch_grouped(a, streams, st);
     if (e != hipSuccess) return hip_fail(e, "axe_gemm_grouped_pair");
   }
   return AXE_OK;

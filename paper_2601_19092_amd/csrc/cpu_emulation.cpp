@@ -207,6 +207,7 @@ hipError_t launch_relayout_generic(const GenericRelayoutPlan& p, int unit, const
 }
 
 hipError_t launch_gemm_tiles_16bit(int, const GemmArgs&, hipStream_t) { return hipErrorNotSupported; }
+hipError_t launch_gemm_tiles_grouped(const GemmArgs&, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_gemm_tiles_fp8(int, const GemmArgs&, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_gemm_small(const GemmArgs&, bool, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_gemm_bf16_256(const GemmArgs&, hipStream_t) { return hipErrorNotSupported; }

@@ -38,6 +38,7 @@
 
 #include "device_types.h"
 #include "gemm_common.h"
+#include "grouped_tiles.h"
 #include "kernels.h"
 #include "tile_family.h"
 #include "tile_maps.h"
@@ -66,7 +67,9 @@ __device__ __forceinline__ void wait_loads() {                     // all but th
 }
 
 // DT: 0 bf16, 1 fp16, 2 fp8 e4m3.  SC (fp8): 0 unscaled, 1 fp32 scales, 2 E8M0 codes.
-template <int DT, int SC, int TM, int TN, int WM, int WN, int WK, int NST>
+// GRP: 0 dense; 1, 2 grouped (A's scales one per row), 2 with the gated epilogue.  A grouped launch finds its workgroup's
+// tiles on the device (grouped_tiles.h) and walks them one after the other.
+template <int DT, int SC, int TM, int TN, int WM, int WN, int WK, int NST, int GRP = 0>
 __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_tiles_kernel(GemmArgs g) {
   constexpr int EB = DT == 2 ? 1 : 2;
   constexpr int kRow = maps::kLargeRowBytes;
@@ -76,6 +79,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_tiles_kernel(GemmArgs 
   constexpr int kLoads = PA + PB;
   constexpr int kGroup = (TM + TN) * kRow, kStage = WK * kGroup;   // bytes of a group's K-tile, of a stage
   constexpr int U = SC ? 4 : 2;                                    // stages per trip of the main loop
+  constexpr int NB = GRP == 2 ? 2 : 1;                             // column blocks of B's scales that a wave needs
   static_assert(TM % (16 * WM) == 0 && TN % (16 * WN) == 0 && (TM / 8) % NG == 0 && (TN / 8) % NG == 0, "whole fragments and pieces");
   static_assert(NST * kStage <= 160 * 1024 && (WK - 1) * TM * TN * 4 <= NST * kStage, "the ring, and then the partial sums, fit LDS");
   static_assert((NST - 1) * kLoads <= 63, "the counted wait");
@@ -87,33 +91,63 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_tiles_kernel(GemmArgs 
   const int kpart = w / NG, wg = w % NG;                           // group, wave inside the group
   const int wm = wg / WN, wn = wg % WN;
 
-  int tm, tn;
-  tile_of_block((int)blockIdx.x, (int)gridDim.x, g.grid_m, g.grid_n, tm, tn);
-  const int64_t m0 = (int64_t)tm * TM, n0 = (int64_t)tn * TN;
-  const int rows = g.M - m0 < TM ? (int)(g.M - m0) : TM, cols = g.N - n0 < TN ? (int)(g.N - n0) : TN;
-
   const int kbytes = (int)(g.K * EB);                              // bytes of K per row
   const int nk = (kbytes + kRow - 1) / kRow;                       // K-tiles
+  // stages, whole trips of them; grouped: a last trip may be half a one (the branch costs a dense launch, whose K loop is its
+  // whole time, 3 %).  Stages past the last K-tile multiply zeros.
+  constexpr bool kHalfTrip = GRP != 0 && U == 4;
+  constexpr int kWhole = kHalfTrip ? 2 : U;
+  const int ns = ((nk + WK - 1) / WK + kWhole - 1) / kWhole * kWhole;
   const int a_pitch = (int)(g.lda * EB), b_pitch = (int)(g.ldb * EB);
-  const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc((void*)((const uint8_t*)g.A + m0 * g.lda * EB), 0,
-                                                                      (rows - 1) * a_pitch + kbytes, 0x00020000);
-  const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc((void*)((const uint8_t*)g.B + n0 * g.ldb * EB), 0,
-                                                                      (cols - 1) * b_pitch + kbytes, 0x00020000);
-
   // ---- HBM -> LDS: this wave's pieces of a K-tile: of A, then of B
   constexpr int kOutside = 0x7fff0000;                             // past the end of every descriptor (the host keeps them below 2^30 bytes)
   const int lr = lane / maps::kLargeChunks, lp = lane % maps::kLargeChunks;
-  int voff[kLoads], kchunk[kLoads];                                // offset of the lane's chunk in the operand, and inside its row
+  int kchunk[kLoads];                                              // offset of the lane's chunk inside its row
 #pragma unroll
-  for (int i = 0; i < kLoads; ++i) {
-    const bool is_a = i < PA;
-    const int row = maps::piece_row(wg, is_a ? i : i - PA, lr, NG);
-    kchunk[i] = maps::lds_chunk_pos(row, lp, maps::kLargeChunks) * maps::kChunkBytes;
-    voff[i] = row < (is_a ? rows : cols) ? row * (is_a ? a_pitch : b_pitch) + kchunk[i] : kOutside;
-  }
-  auto issue = [&](int s, int slot) __attribute__((always_inline)) {
-    const int kt = s * WK + kpart;
-    const int left = kbytes - kt * kRow;                           // bytes of K from this K-tile on
+  for (int i = 0; i < kLoads; ++i)
+    kchunk[i] = maps::lds_chunk_pos(maps::piece_row(wg, i < PA ? i : i - PA, lr, NG), lp, maps::kLargeChunks) * maps::kChunkBytes;
+  int voff[kLoads];                                                // offset of the lane's chunk in the operand
+#pragma unroll
+  for (int i = 0; i < kLoads; ++i) voff[i] = maps::piece_row(wg, i < PA ? i : i - PA, lr, NG) * (i < PA ? a_pitch : b_pitch) + kchunk[i];
+  // The workgroup's tiles.  Dense: one, found from its id.  Grouped: found on the device, one per lane; the loads run on from
+  // a tile's last stage into the next tile's first ones, so the load side, the scales and the matrix side each keep a
+  // place of their own.
+  int t_row0 = 0, t_desc = 0;
+  if constexpr (GRP != 0) group_tiles<TM>(g, lane, t_row0, t_desc);
+  struct Place {
+    int64_t m0, n0;
+    int rows, cols, group;                                         // rows = 0: no such tile
+  };
+  auto place = [&](int t) __attribute__((always_inline)) -> Place {
+    Place o;
+    if constexpr (GRP != 0) {
+      const int d = t < 64 ? __builtin_amdgcn_readlane(t_desc, t) : 0;
+      o.rows = desc_rows(d), o.cols = TN, o.group = desc_group(d);
+      o.m0 = __builtin_amdgcn_readlane(t_row0, t & 63), o.n0 = (int64_t)desc_tn(d) * TN;
+    } else {
+      int tm, tn;
+      tile_of_block((int)blockIdx.x, (int)gridDim.x, g.grid_m, g.grid_n, tm, tn);
+      o.m0 = (int64_t)tm * TM, o.n0 = (int64_t)tn * TN, o.group = 0;
+      o.rows = g.M - o.m0 < TM ? (int)(g.M - o.m0) : TM, o.cols = g.N - o.n0 < TN ? (int)(g.N - o.n0) : TN;
+    }
+    return o;
+  };
+  Place here = place(0);                                           // the tile being multiplied
+  if (here.rows == 0) return;                                      // (the whole workgroup: no barrier is left waiting)
+  __amdgpu_buffer_rsrc_t ra, rb;                                   // the tile being loaded: rows past the end lie outside the descriptors
+  int l_stage = 0, l_tile = 0, l_bytes = 0;
+  auto load_from = [&](const Place& p) __attribute__((always_inline)) {
+    l_stage = 0;
+    l_bytes = p.rows ? kbytes : 0;
+    // (no such tile: an empty descriptor -- (0 - 1) rows would wrap round to one that reaches everything)
+    const int a_bytes = p.rows ? (p.rows - 1) * a_pitch + kbytes : 0;
+    ra = __builtin_amdgcn_make_buffer_rsrc((void*)((const uint8_t*)g.A + p.m0 * g.lda * EB), 0, a_bytes, 0x00020000);
+    rb = __builtin_amdgcn_make_buffer_rsrc((void*)((const uint8_t*)g.B + (p.group * g.ldg + p.n0 * g.ldb) * EB), 0, (p.cols - 1) * b_pitch + kbytes, 0x00020000);
+  };
+  load_from(here);
+  auto issue = [&](int slot) __attribute__((always_inline)) {     // the load side's next stage
+    const int kt = l_stage * WK + kpart;
+    const int left = l_bytes - kt * kRow;                          // bytes of K from this K-tile on
     const lds_u8 base = lds3 + slot * kStage + kpart * kGroup;
     const int soff = left > 0 ? kt * kRow : 0;
 #pragma unroll
@@ -124,6 +158,8 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_tiles_kernel(GemmArgs 
                                                16, off, soff, 0, 0);
       AXE_PARANOID_WAIT();
     }
+    ++l_stage;
+    if (GRP != 0 && l_stage == ns) load_from(place(++l_tile));
   };
 
   // ---- LDS -> VGPR
@@ -134,31 +170,38 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_tiles_kernel(GemmArgs 
   auto read = [&](lds_u8 p) __attribute__((always_inline)) -> i32x4 { return *(__attribute__((address_space(3))) const i32x4*)p; };
 
   f32x4 acc[MF][NF];
-#pragma unroll
-  for (int i = 0; i < MF; ++i)
-#pragma unroll
-    for (int j = 0; j < NF; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   // ---- scales.  Lane (fr, fq) holds, for each of its fragment rows, the product of the row's and the column block's scale in
   //      the K-tile of stage s0 + fq; two swaps between lane groups hand every lane those of all four stages of a trip.
   //      One load per fragment row and one for the column block serve four stages; they are issued a trip ahead.
-  constexpr int kScaleLoads = SC ? MF + 1 : 0;
+  //      With the gated epilogue the wave's gate and up columns lie in one column block each.
+  constexpr int kScaleLoads = SC ? MF + NB : 0;
   constexpr int SB = SC == 2 ? 1 : 4;                              // bytes of a stored scale
-  const bool by_row = g.scale_a_rows == 1;
-  __amdgpu_buffer_rsrc_t rsa, rsb;
-  int sa_off[SC ? MF : 1], sb_off = 0;
-  if constexpr (SC != 0) {
-    const int64_t a0 = by_row ? m0 : m0 / 128, b0 = n0 / 128;
-    rsa = __builtin_amdgcn_make_buffer_rsrc((void*)((const uint8_t*)g.scale_a + a0 * g.nkb * SB), 0, (by_row ? rows : (rows + 127) / 128) * g.nkb * SB, 0x00020000);
-    rsb = __builtin_amdgcn_make_buffer_rsrc((void*)((const uint8_t*)g.scale_b + b0 * g.nkb * SB), 0, g.nkb * SB, 0x00020000);
+  const bool by_row = GRP != 0 || g.scale_a_rows == 1;
+  int sa_off[SC ? MF : 1];
 #pragma unroll
-    for (int i = 0; i < MF; ++i) {
-      const int r = wm * (TM / WM) + i * 16 + fr;                  // (rows past the end: any value, they are never stored)
-      sa_off[i] = (by_row ? r : r / 128) * g.nkb * SB;
-    }
+  for (int i = 0; i < (SC ? MF : 0); ++i) {
+    const int r = wm * (TM / WM) + i * 16 + fr;                    // (rows past the end: any value, they are never stored)
+    sa_off[i] = (by_row ? r : r / 128) * g.nkb * SB;
   }
   static_assert((TM <= 128 || TM % 128 == 0) && TN <= 128, "row blocks of scales start with a tile or inside one, a tile lies in one column block");
-  uint32_t sa_raw[SC ? MF : 1], sb_raw = 0;
+  uint32_t sa_raw[SC ? MF : 1], sb_raw[NB];
+  __amdgpu_buffer_rsrc_t rsa, rsb[NB];
+  auto scales_from = [&](const Place& p) __attribute__((always_inline)) {
+    if constexpr (SC != 0) {
+      const int64_t a0 = by_row ? p.m0 : p.m0 / 128;
+      const int an = p.rows == 0 ? 1 : (by_row ? p.rows : (p.rows + 127) / 128);
+      rsa = __builtin_amdgcn_make_buffer_rsrc((void*)((const uint8_t*)g.scale_a + a0 * g.nkb * SB), 0, an * g.nkb * SB, 0x00020000);
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
+        // gated: image rows n0 + wn TN / WN .. hold the logical gate columns from half of that on, and the up columns N / 2 further
+        const int64_t col = GRP == 2 ? b * (g.N / 2) + (p.n0 + wn * (TN / WN)) / 2 : p.n0;
+        const int64_t b0 = (GRP != 0 ? p.group * (g.N / 128) : 0) + col / 128;
+        rsb[b] = __builtin_amdgcn_make_buffer_rsrc((void*)((const uint8_t*)g.scale_b + b0 * g.nkb * SB), 0, g.nkb * SB, 0x00020000);
+      }
+    }
+  };
+  scales_from(here);
   auto fetch_scales = [&](int s0) __attribute__((always_inline)) {
     if constexpr (SC != 0) {
       asm volatile("" ::: "memory");                               // the waits below count these loads: they stay where they are
@@ -168,7 +211,8 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_tiles_kernel(GemmArgs 
         if constexpr (SC == 2) return __builtin_amdgcn_raw_buffer_load_b8(r, off, 0, 0);
         else return __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0);
       };
-      sb_raw = load(rsb, sb_off + o);
+#pragma unroll
+      for (int b = 0; b < NB; ++b) sb_raw[b] = load(rsb[b], o);
 #pragma unroll
       for (int i = 0; i < MF; ++i) sa_raw[i] = load(rsa, sa_off[i] + o);
       asm volatile("" ::: "memory");
@@ -177,19 +221,21 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_tiles_kernel(GemmArgs 
   auto scale_value = [](uint32_t raw) __attribute__((always_inline)) -> float {
     return __builtin_bit_cast(float, SC == 2 ? raw << 23 : raw);
   };
-  float sc[SC ? MF : 1][4];
+  float sc[NB][SC ? MF : 1][4];
   auto spread_scales = [&](int s0) __attribute__((always_inline)) {
     if constexpr (SC != 0) {
       const bool in = (s0 + fq) * WK + kpart < nk;                 // stages past the last one multiply zeros by zero
 #pragma unroll
-      for (int i = 0; i < MF; ++i) {
-        const uint32_t v = in ? __builtin_bit_cast(uint32_t, scale_value(sa_raw[i]) * scale_value(sb_raw)) : 0u;
-        const auto h = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-        const auto q0 = __builtin_amdgcn_permlane16_swap(h[0], h[0], false, false);
-        const auto q2 = __builtin_amdgcn_permlane16_swap(h[1], h[1], false, false);
-        sc[i][0] = __builtin_bit_cast(float, (uint32_t)q0[0]), sc[i][1] = __builtin_bit_cast(float, (uint32_t)q0[1]);
-        sc[i][2] = __builtin_bit_cast(float, (uint32_t)q2[0]), sc[i][3] = __builtin_bit_cast(float, (uint32_t)q2[1]);
-      }
+      for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int i = 0; i < MF; ++i) {
+          const uint32_t v = in ? __builtin_bit_cast(uint32_t, scale_value(sa_raw[i]) * scale_value(sb_raw[b])) : 0u;
+          const auto h = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+          const auto q0 = __builtin_amdgcn_permlane16_swap(h[0], h[0], false, false);
+          const auto q2 = __builtin_amdgcn_permlane16_swap(h[1], h[1], false, false);
+          sc[b][i][0] = __builtin_bit_cast(float, (uint32_t)q0[0]), sc[b][i][1] = __builtin_bit_cast(float, (uint32_t)q0[1]);
+          sc[b][i][2] = __builtin_bit_cast(float, (uint32_t)q2[0]), sc[b][i][3] = __builtin_bit_cast(float, (uint32_t)q2[1]);
+        }
     }
   };
 
@@ -229,7 +275,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_tiles_kernel(GemmArgs 
 #pragma unroll
           for (int j = 0; j < NF; ++j)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) acc[i][j][e] = __builtin_fmaf(sc[i][u], p[j][e], acc[i][j][e]);
+            for (int e = 0; e < 4; ++e) acc[i][j][e] = __builtin_fmaf(sc[NB == 2 ? j & 1 : 0][i][u], p[j][e], acc[i][j][e]);
         } else {
 #pragma unroll
           for (int j = 0; j < NF; ++j)
@@ -239,31 +285,42 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_tiles_kernel(GemmArgs 
     }
   };
 
-  const int ns = (nk + WK - 1) / WK;                               // stages
+  // ---- prologue: the first tile's first stages
+  Frags f[2];
   fetch_scales(0);
 #pragma unroll
-  for (int s = 0; s < NST; ++s) issue(s, s);
-  Frags f[2];
+  for (int s = 0; s < NST; ++s) issue(s);
   wait_loads<(NST - 1) * kLoads>();
   if constexpr (NG > 1) wg_barrier();
   AXE_PARANOID_SYNC();
   read_frags(f[0], 0);
 
   int cur = 0;                                                     // slot of the stage whose fragments are in f[u & 1]
+  for (int t = 1;; ++t) {
+#pragma unroll
+  for (int i = 0; i < MF; ++i)
+#pragma unroll
+    for (int j = 0; j < NF; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   for (int s0 = 0; s0 < ns; s0 += U) {
     spread_scales(s0);
 #pragma unroll
-    for (int u = 0; u < U; ++u) {                                  // (stages past the last one multiply zeros)
+    for (int u = 0; u < U; ++u) {
+      if (kHalfTrip && u == 2 && s0 + 2 >= ns) break;
       // stage s + 1 has landed, everybody's reads of stage s are done: its slot takes stage s + NST.  (The scales fetched
-      // at the head of the trip are younger than the stages up to s0 + NST - 1.)
+      // at the head of the trip are younger than the stages up to s0 + NST - 1; whatever else is in flight only makes a
+      // counted wait stricter.)
       if (u >= 1 && u <= NST - 2) wait_loads<(NST - 2) * kLoads + kScaleLoads>();
       else wait_loads<(NST - 2) * kLoads>();
       if constexpr (NG > 1) wg_barrier();
       AXE_PARANOID_SYNC();
       const int nxt = cur + 1 == NST ? 0 : cur + 1;
       read_frags(f[(u + 1) & 1], nxt);
-      if (u == 0) fetch_scales(s0 + U);
-      issue(s0 + u + NST, cur);
+      if (u == 0) {
+        const bool last = GRP != 0 && s0 + U >= ns;                // the next trip is the next tile's first
+        if (last) scales_from(place(t));
+        fetch_scales(last ? 0 : s0 + U);
+      }
+      issue(cur);
       multiply(f[u & 1], u);
       cur = nxt;
     }
@@ -298,11 +355,26 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_tiles_kernel(GemmArgs 
   const bool whole = (g.ldc & 3) == 0;
 #pragma unroll
   for (int i = 0; i < MF; ++i) {
-    const int64_t m = m0 + wm * (TM / WM) + i * 16 + fr;
-    if (m >= g.M) continue;
+    const int r = wm * (TM / WM) + i * 16 + fr;
+    if (r >= here.rows) continue;
+    const int64_t m = here.m0 + r;
+    if constexpr (GRP == 2) {                                      // fragments 2 p and 2 p + 1: gate and up of the same 16 outputs
+#pragma unroll
+      for (int p = 0; p < NF / 2; ++p) {
+        float h[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float gate = acc[i][2 * p][e], up = acc[i][2 * p + 1][e];
+          h[e] = gate * __builtin_amdgcn_rcpf(1.0f + __expf(-gate)) * up;
+        }
+        uint16_t* C = (uint16_t*)g.C + m * g.ldc + (here.n0 + wn * (TN / WN)) / 2 + p * 16 + maps::kAccCols * fq;
+        *(u32x2*)C = u32x2{pack2<DT>(h[0], h[1]), pack2<DT>(h[2], h[3])};
+      }
+      continue;
+    }
 #pragma unroll
     for (int j = 0; j < NF; ++j) {
-      const int64_t n = n0 + wn * (TN / WN) + j * 16 + maps::kAccCols * fq;
+      const int64_t n = here.n0 + wn * (TN / WN) + j * 16 + maps::kAccCols * fq;
       if (g.out_bf16) {
         uint16_t* C = (uint16_t*)g.C + m * g.ldc + n;
         const u32x2 d = {pack2<DT>(acc[i][j][0], acc[i][j][1]), pack2<DT>(acc[i][j][2], acc[i][j][3])};
@@ -324,6 +396,10 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_tiles_kernel(GemmArgs 
         }
       }
     }
+  }
+  if constexpr (GRP == 0) return;
+  here = place(t);
+  if (here.rows == 0) return;
   }
 }
 

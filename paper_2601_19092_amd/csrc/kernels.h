@@ -19,6 +19,8 @@ hipError_t launch_relayout_generic(const GenericRelayoutPlan& p, int unit_bytes,
                                    hipStream_t s);
 // a member of the tile family (tile_family.h)
 hipError_t launch_gemm_tiles_16bit(int member, const GemmArgs& g, hipStream_t s);
+// fp8 groups with fp32 scales on the tile family; grouped_tiles_fit(N, K)
+hipError_t launch_gemm_tiles_grouped(const GemmArgs& g, hipStream_t s);
 hipError_t launch_gemm_tiles_fp8(int member, const GemmArgs& g, hipStream_t s);
 hipError_t launch_gemm_small(const GemmArgs& g, bool fp8, hipStream_t s);
 // Large-tile kernels: 256 x tile_n workgroup tile (tile_n = 256, or 224 for bf16); require

@@ -1,0 +1,38 @@
+// Grouped GEMM on the 128 x 128 tile of gemm_tiles.h: fp8 groups with fp32 scales, which the matrix cores' scale path cannot
+// carry and the grouped tile kernel of that path does not take.  One workgroup per compute unit walks its tiles as one
+// pipeline (the loads run on into the next tile's first stages).
+//
+// Bound: HBM, the groups' weights, once tiles replace the streaming kernel's passes of 64 rows over them.  An MoE layer of 128
+// experts (8 per token, N, K = 1536, 2048 gated and 2048, 768), us, streaming -> this: 256 tokens 108 + 55 -> 87 + 57, 1024 tokens 287 + 126
+// -> 109 + 72 (604 MB of weights: 3.3 TB/s), 4096 tokens 990 + 403 -> 193 + 137.  Other tiles, 1024 / 4096 tokens: one tile at a time
+// without running on 112 + 85 / 201 + 172; 64 x 128 in four waves, two workgroups per compute unit 105 + 70 / 217 + 151, in eight waves
+// 127 + 83 / 278 + 177; 32 x 128 122 + 76 / 290 + 195; 128 x 128 with two stages 163 + 103 / 305 + 198.
+#include "gemm_tiles.h"
+
+#include <algorithm>
+
+namespace axe {
+
+namespace {
+constexpr TileShape kShape = kTileFamily[kGroupedMember];
+template <int GRP>
+void launch(const GemmArgs& g, unsigned nwg, hipStream_t s) {
+  hipLaunchKernelGGL((tiles::gemm_tiles_kernel<2, 1, kShape.tm, kShape.tn, kShape.wm, kShape.wn, kShape.wk, kShape.nst, GRP>), dim3(nwg),
+                     dim3(64 * kShape.wm * kShape.wn * kShape.wk), 0, s, g);
+}
+}  // namespace
+
+hipError_t launch_gemm_tiles_grouped(const GemmArgs& g0, hipStream_t s) {
+  GemmArgs g = g0;
+  if (!grouped_tiles_fit(g.N, g.K) || !g.fp8 || !g.scale_a || g.scale_e8m0) return hipErrorInvalidValue;
+  g.grid_n = (int32_t)(g.N / kShape.tn);
+  const int64_t worst = (g.M / kShape.tm + g.groups) * (int64_t)g.grid_n;
+  int64_t nwg = std::max<int64_t>(cu_count(), (worst + 63) / 64);  // a wave keeps the workgroup's tiles one per lane
+  nwg = (std::min(nwg, worst) + 7) / 8 * 8;                        // the tile sequence is cut into 8 parts, one per XCD
+  if (nwg > 0x7fffffff) return hipErrorInvalidValue;
+  if (g.gated) launch<2>(g, (unsigned)nwg, s);
+  else launch<1>(g, (unsigned)nwg, s);
+  return hipGetLastError();
+}
+
+}  // namespace axe

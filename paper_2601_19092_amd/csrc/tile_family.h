@@ -23,4 +23,13 @@ constexpr TileShape kTileFamily[] = {
 };
 constexpr int kTileFamilySize = sizeof kTileFamily / sizeof kTileFamily[0];
 
+// The member that serves grouped problems (one wave group: the pipeline runs on from tile to tile), and the problems it takes:
+// whole tiles along N, counted in 11 bits, and at least as many K-tiles of 128 as its ring has stages.
+constexpr int kGroupedMember = 7;
+static_assert(kTileFamily[kGroupedMember].wk == 1, "no partial sums");
+inline bool grouped_tiles_fit(int64_t N, int64_t K) {
+  const TileShape& t = kTileFamily[kGroupedMember];
+  return N % t.tn == 0 && N / t.tn <= 2048 && K % 128 == 0 && K / 128 >= t.nst;
+}
+
 }  // namespace axe
