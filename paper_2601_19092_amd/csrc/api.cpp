@@ -209,8 +209,25 @@ int axe_relayout(const axe_layout_t* src, const axe_layout_t* dst, int32_t rank,
     if (ok) {
       TransposePlan p;
       memset(&p, 0, sizeof p);
-      p.elementwise = chunks ? 0 : 1;
-      const int64_t T = chunks ? transpose_tile_edge(elem_bytes) : 64;
+      // How the tiles move (TransposePlan::elementwise): in aligned chunks (0); element by element (1) where a swizzle is not
+      // made of such chunks; else in chunks that start at any element (2), or, with the boundaries of the tiles on the
+      // destination's lines, skewed (3).  The skew pays where the destination goes to memory rather than to the
+      // last-level cache (8191 x 8193 bf16 56 us against 83; 7000 x 3001, 84 MB in all, 23 against 19) and not for single
+      // bytes, whose lines are as long as the tile (8191 x 8193 43 against 40).  AXE_TRANSPOSE_VARIANT asks for one.
+      auto lines = [&](int64_t elems) { return elems * elem_bytes % 128 == 0; };
+      const bool swizzled = ms.swz.mask || md.swz.mask;
+      bool on_lines = ((uintptr_t)d_dst & 127) == 0 && lines(md.off), skew_ok = !swizzled && elem_bytes > 1;
+      for (size_t k = 0; k < J.size(); ++k)
+        if ((int)k != kD && J[k].e > 1 && !lines(J[k].ds)) on_lines = false;
+      for (const HIter& it : md.R)
+        if (!lines(it.s)) skew_ok = false;                         // (a row's phase is that of all its replicas)
+      p.elementwise = chunks ? 0 : (swizzled ? 1 : 2);
+      if (skew_ok && !on_lines && 2 * E * (int64_t)elem_bytes >= (int64_t(112) << 20)) p.elementwise = 3;
+      const int asked = env_int("AXE_TRANSPOSE_VARIANT", -1);
+      if (asked == 1 || (asked == 2 && !swizzled) || (asked == 3 && skew_ok)) p.elementwise = asked;
+      const int64_t T = p.elementwise == 1 ? 64 : transpose_tile_edge(elem_bytes);
+      const int64_t TS = p.elementwise == 3 ? skew_tile_s(elem_bytes) : T;
+      const int64_t TD = p.elementwise == 3 ? skew_tile_d(elem_bytes) : T;
       p.s_swz = ms.swz, p.d_swz = md.swz;
       p.n_r = (int)md.R.size();
       for (int k = 0; k < p.n_r; ++k) p.rext[k] = (int32_t)md.R[k].e, p.rstr[k] = md.R[k].s;
@@ -218,7 +235,9 @@ int axe_relayout(const axe_layout_t* src, const axe_layout_t* dst, int32_t rank,
       p.eS = J[kS].e, p.dS = J[kS].ds;
       p.eD = J[kD].e, p.sD = J[kD].ss;
       p.s_off = ms.off, p.d_off = md.off;
-      const uint64_t tiles_s = (uint64_t)((p.eS + T - 1) / T), tiles_d = (uint64_t)((p.eD + T - 1) / T);
+      // (skewed tiles: a row's last one ends up to a line short of its nominal end)
+      const uint64_t tiles_s = (uint64_t)((p.eS + TS - 1) / TS);
+      const uint64_t tiles_d = (uint64_t)((p.eD + (p.elementwise == 3 ? 128 / elem_bytes - 1 : 0) + TD - 1) / TD);
       uint64_t blocks = tiles_s * tiles_d;
       // outer digits, smallest strides first so that neighbouring workgroups stay close in memory
       std::vector<JointIter> outer;

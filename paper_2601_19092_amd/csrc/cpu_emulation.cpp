@@ -107,8 +107,8 @@ hipError_t launch_relayout_transpose(const TransposePlan& p, int eb, const void*
       f(swz_apply(ra, p.d_swz));
     }
   };
-  if (p.elementwise) {                                           // 64 x 64 tiles, element by element
-    ++g_transposes_elem;
+  if (p.elementwise) ++g_transposes_elem;
+  if (p.elementwise == 1) {                                      // 64 x 64 tiles, element by element
     const int64_t T = 64;
     for (uint64_t blk = 0; blk < p.blocks; ++blk) {
       uint64_t b = blk;
@@ -133,6 +133,55 @@ hipError_t launch_relayout_transpose(const TransposePlan& p, int eb, const void*
     }
     return hipSuccess;
   }
+  if (p.elementwise == 3) {                                      // tiles whose boundaries lie on the destination's lines
+    const int64_t TS = skew_tile_s(eb), TD = skew_tile_d(eb), CE = 16 / eb, H = 128 / eb;
+    for (uint64_t blk = 0; blk < p.blocks; ++blk) {
+      uint64_t b = blk;
+      const int64_t ts = (int64_t)(b % p.tiles_s);
+      b /= p.tiles_s;
+      int64_t td = (int64_t)(b % p.tiles_d);
+      b /= p.tiles_d;
+      if (p.diag > 0) td = (td + ts / p.diag) % p.tiles_d;
+      int64_t sb = p.s_off, db = p.d_off;
+      for (int k = 0; k < p.n; ++k) {
+        sb += (int64_t)(b % p.ext[k]) * p.ss[k];
+        db += (int64_t)(b % p.ext[k]) * p.ds[k];
+        b /= p.ext[k];
+      }
+      std::vector<char> tile((size_t)((TD + H) * TS * eb), 0), have((size_t)((TD + H) * TS), 0);
+      for (int64_t r = 0; r < TD + H; ++r)
+        for (int64_t c = 0; c < TS; c += CE) {
+          const int64_t iD = td * TD - H + r, iS = ts * TS + c;
+          const int64_t jD = iD < 0 ? 0 : (iD < p.eD ? iD : p.eD - 1), jS = iS + CE <= p.eS ? iS : p.eS - CE;
+          const int64_t a = (sb + jD * p.sD + jS) * eb;
+          if (a < 0 || a + 16 > g_src_bytes) {
+            ++g_violations;
+            continue;
+          }
+          for (int64_t k = 0; k < CE && jD == iD; ++k)
+            if (iS + k < p.eS) {
+              memcpy(&tile[(size_t)((r * TS + c + k) * eb)], src + a + (k + iS - jS) * eb, (size_t)eb);
+              have[(size_t)(r * TS + c + k)] = 1;
+            }
+        }
+      for (int64_t r = 0; r < TS; ++r)
+        for (int64_t c = 0; c < TD; c += CE) {
+          const int64_t iS = ts * TS + r, delta = (int64_t)((uintptr_t)(dst + (db + iS * p.dS) * eb) & 127) / eb;
+          const int64_t iD = td * TD + c - delta;
+          if (iS >= p.eS) continue;
+          if (iD >= 0 && iD + CE <= p.eD && ((uintptr_t)(dst + (db + iS * p.dS + iD) * eb) & 15)) ++g_violations;   // stored as a whole chunk
+          for (int64_t k = 0; k < CE; ++k)
+            if (iD + k >= 0 && iD + k < p.eD) {
+              if (!have[(size_t)((H + c - delta + k) * TS + r)]) ++g_violations;
+              replicas(db + iS * p.dS + iD + k, [&](int64_t da) {
+                if (da < 0 || (da + 1) * eb > g_dst_bytes) ++g_violations;
+                else memcpy(dst + da * eb, &tile[(size_t)(((H + c - delta + k) * TS + r) * eb)], (size_t)eb);
+              });
+            }
+        }
+    }
+    return hipSuccess;
+  }
   const int64_t T = transpose_tile_edge(eb), CE = 16 / eb, CPR = T / CE;
   for (uint64_t blk = 0; blk < p.blocks; ++blk) {
     uint64_t b = blk;
@@ -151,6 +200,20 @@ hipError_t launch_relayout_transpose(const TransposePlan& p, int eb, const void*
     std::vector<char> have((size_t)(T * T), 0);
     for (int64_t c = 0; c < T * CPR; ++c) {                       // HBM -> LDS
       const int64_t r = c / CPR, cc = c % CPR, iD = td * T + r, iS = ts * T + cc * CE;
+      if (p.elementwise == 2) {                                   // the nearest chunk inside the tensor, shifted where it was moved back
+        const int64_t jD = iD < p.eD ? iD : p.eD - 1, jS = iS + CE <= p.eS ? iS : p.eS - CE;
+        const int64_t a = (sb + jD * p.sD + jS) * eb;
+        if (a < 0 || a + 16 > g_src_bytes) {
+          ++g_violations;
+          continue;
+        }
+        for (int64_t k = 0; k < CE && iD < p.eD; ++k)
+          if (iS + k < p.eS) {
+            memcpy(&tile[(size_t)((r * T + cc * CE + k) * eb)], src + a + (k + iS - jS) * eb, (size_t)eb);
+            have[(size_t)(r * T + cc * CE + k)] = 1;
+          }
+        continue;
+      }
       if (iD >= p.eD || iS >= p.eS) continue;
       const int64_t a = swz_apply(sb + iD * p.sD + iS, p.s_swz) * eb;
       if (a < 0 || a + 16 > g_src_bytes || (a & 15)) {
@@ -164,12 +227,12 @@ hipError_t launch_relayout_transpose(const TransposePlan& p, int eb, const void*
       const int64_t r = c / CPR, cc = c % CPR, iS = ts * T + r, iD = td * T + cc * CE;
       if (iS >= p.eS || iD >= p.eD) continue;
       replicas(db + iS * p.dS + iD, [&](int64_t da) {
-        const int64_t a = da * eb;
-        if (a < 0 || a + 16 > g_dst_bytes || (a & 15)) {
+        const int64_t a = da * eb, m = p.elementwise == 2 && iD + CE > p.eD ? p.eD - iD : CE;   // elements of the chunk that exist
+        if (a < 0 || a + m * eb > g_dst_bytes || (p.elementwise == 0 && (a & 15))) {
           ++g_violations;
           return;
         }
-        for (int64_t k = 0; k < CE; ++k) {
+        for (int64_t k = 0; k < m; ++k) {
           if (!have[(size_t)((cc * CE + k) * T + r)]) ++g_violations;   // would store what was never loaded
           memcpy(dst + a + k * eb, &tile[(size_t)(((cc * CE + k) * T + r) * eb)], (size_t)eb);
         }

@@ -67,7 +67,8 @@ struct TransposePlan {
   int32_t rext[kMaxR];
   int64_t rstr[kMaxR];
   int64_t E_R;
-  int32_t elementwise;             // 1: tiles of 64 x 64 moved element by element (no alignment requirement at all)
+  int32_t elementwise;             // 0: aligned 16-byte chunks; 1: tiles of 64 x 64 moved element by element (any strides, any swizzle);
+                                   // 2: 16-byte chunks that start at any element (no swizzle); 3: the same, tiles skewed onto the destination's lines
 };
 
 // Fallback when the two digit systems have no common refinement: decode each side separately.

@@ -15,6 +15,10 @@ hipError_t launch_relayout_transpose(const TransposePlan& p, int elem_bytes, con
 // (measured on 8192 x 8192: rows of 256 - 512 bytes per tile beat 128-byte rows by 10 - 17 %, except for
 //  single bytes, where the gather of 16 LDS bytes per store makes a 256 x 256 tile slower)
 inline int transpose_tile_edge(int elem_bytes) { return elem_bytes == 8 ? 64 : 128; }
+// tile of its skewed variant, elements along the source and along the destination.  Measured, 8191 x 8193 bf16, us: 64 x 128 56, 64 x 256
+// 58, 128 x 192 63, 64 x 192 65, 128 x 128 66; 5001 x 7001 fp32: 64 x 128 63, 32 x 192 65, 64 x 192 69, 32 x 128 72, 32 x 96 75.
+constexpr int skew_tile_s(int elem_bytes) { return elem_bytes == 8 ? 32 : 64; }
+constexpr int skew_tile_d(int elem_bytes) { return elem_bytes == 8 ? 64 : 128; }
 hipError_t launch_relayout_generic(const GenericRelayoutPlan& p, int unit_bytes, const void* src, void* dst,
                                    hipStream_t s);
 // a member of the tile family (tile_family.h)

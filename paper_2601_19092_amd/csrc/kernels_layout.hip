@@ -279,6 +279,11 @@ template <> struct Word<4> { using T = uint32_t; };
 template <> struct Word<8> { using T = __attribute__((ext_vector_type(2))) uint32_t; };
 template <> struct Word<16> { using T = __attribute__((ext_vector_type(4))) uint32_t; };
 
+template <int EB>
+struct Row {                                                       // a 16-byte chunk as elements
+  typename Word<EB>::T w[16 / EB];
+};
+
 template <int BYTES, int U, bool REPL, bool NT>
 __global__ __launch_bounds__(256) void relayout_joint_kernel(RelayoutPlan p, const void* __restrict__ src_,
                                                              void* __restrict__ dst_) {
@@ -374,7 +379,15 @@ hipError_t launch_relayout_joint(const RelayoutPlan& p, int unit_bytes, const vo
 // LDS rows.  The LDS image is XOR-swizzled, not padded: 16-byte chunk c of row r sits at chunk position
 // c ^ (r / elements per chunk), which keeps the gather on distinct banks for every element size.
 // ------------------------------------------------------------------------------------------
-template <int EB, bool NT>
+//
+// ANY: the same tiles where extents, strides, offsets or buffers are no multiples of a chunk (odd matrix sizes): the 16-byte
+// accesses start at any element (global memory takes them), a chunk that sticks out of the tensor is loaded from the last
+// place inside it and shifted, and stored element by element.  The rows of neighbouring tiles then share lines of the
+// destination: ordinary stores (non-temporal ones do not combine), and the grid is padded to whole rounds of the 8 XCDs
+// along the source, so that the tiles that complete a line meet in one XCD's L2.  us, element by element -> now, rotating over
+// three pairs of buffers: bf16 7000 x 3001 27 -> 19 (4.4 TB/s), 4095 x 4097 20.6 -> 15.5, bytes 8191 x 8193 70 -> 40, bf16 105 -> 83 (a band of
+// tiles along the destination per XCD instead of the padding: 93).
+template <int EB, bool NT, bool ANY>
 __global__ __launch_bounds__(256) void relayout_transpose_kernel(TransposePlan p, const uint8_t* __restrict__ src,
                                                                  uint8_t* __restrict__ dst) {
   constexpr int T = EB == 8 ? 64 : 128;                           // tile edge, elements (transpose_tile_edge)
@@ -382,6 +395,7 @@ __global__ __launch_bounds__(256) void relayout_transpose_kernel(TransposePlan p
   constexpr int CPR = T / CE;                                    // chunks per tile row
   constexpr int ROWB = T * EB;                                   // bytes of a tile row in LDS
   typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+  typedef u32x4 u32x4_any __attribute__((aligned(1)));
   // LDS image of the tile: rows of ROWB bytes, the 16-byte chunk c of row r at chunk position c ^ (r / CE) -- the
   // same kind of XOR stage as the swizzled layouts of the GEMM tiles.  Rows come in whole chunks (one 16-byte
   // write each); on the way out a lane gathers the CE elements of its chunk from CE consecutive rows at one
@@ -396,8 +410,10 @@ __global__ __launch_bounds__(256) void relayout_transpose_kernel(TransposePlan p
 
   // workgroup -> (tile along S, tile along D, outer digits)
   uint64_t b = blockIdx.x;
-  const uint32_t ts = (uint32_t)(b % p.tiles_s);
-  b /= p.tiles_s;
+  const uint32_t grid_s = ANY ? (p.tiles_s + 7) & ~7u : p.tiles_s;
+  const uint32_t ts = (uint32_t)(b % grid_s);
+  if (ANY && ts >= p.tiles_s) return;
+  b /= grid_s;
   uint32_t td = (uint32_t)(b % p.tiles_d);
   b /= p.tiles_d;
   // Row by row (ts fastest, td fixed for tiles_s workgroups in a row) the workgroups running at one time read
@@ -429,10 +445,23 @@ __global__ __launch_bounds__(256) void relayout_transpose_kernel(TransposePlan p
     // extents are multiples of CE: a chunk is in or out as a whole.  A chunk outside the tensor is replaced by the
     // tile's first one (always inside) instead of being skipped: a load under a branch would be waited for at
     // the end of that branch, one by one.
+    if constexpr (ANY) {                                           // the nearest chunk that lies inside the tensor as a whole
+      const int64_t jD = iD < p.eD ? iD : p.eD - 1, jS = iS + CE <= p.eS ? iS : p.eS - CE;
+      held[i] = *(const u32x4_any*)(src + (sb + jD * p.sD + jS) * EB);
+      continue;
+    }
     const bool in = iD < p.eD && iS < p.eS;
     // (a swizzle stage moves whole chunks: the host admits it here only when it leaves the bits inside a chunk alone)
     const u32x4* a = (const u32x4*)(src + swz_apply(sb + (in ? iD * p.sD + iS : d0 * p.sD + s0), p.s_swz) * EB);
     held[i] = NT ? __builtin_nontemporal_load(a) : *a;
+  }
+  if (ANY && s0 + T > p.eS) {                                      // the last tile along the source: chunks that were moved back
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const int64_t over = s0 + (int64_t)((threadIdx.x + 256 * i) % CPR) * CE + CE - p.eS;
+      if (over > 0 && over < CE)
+        held[i] = __builtin_bit_cast(u32x4, __builtin_bit_cast(unsigned __int128, held[i]) >> (int)(over * EB * 8));
+    }
   }
 #pragma unroll
   for (int i = 0; i < NL; ++i) {
@@ -480,9 +509,116 @@ __global__ __launch_bounds__(256) void relayout_transpose_kernel(TransposePlan p
           ra += (tr % p.rext[k]) * p.rstr[k];
           tr /= p.rext[k];
         }
+        if constexpr (ANY) {
+          using W = typename Word<EB>::T;
+          if (iD + CE <= p.eD) {
+            *(u32x4_any*)(dst + ra * EB) = v;
+          } else {
+#pragma unroll
+            for (int k = 0; k < CE; ++k)
+              if (iD + k < p.eD) ((W*)dst)[ra + k] = __builtin_bit_cast(Row<EB>, v).w[k];
+          }
+          continue;
+        }
         u32x4* a = (u32x4*)(dst + swz_apply(ra, p.d_swz) * EB);
         if (NT) __builtin_nontemporal_store(v, a);
         else *a = v;
+      }
+    }
+  }
+}
+
+// SKEW: destination rows that do not start on 128-byte lines (odd or merely 16-byte aligned pitches).  A tile that ends at the
+// same index in every row then ends inside a line in most of them, and a line that two workgroups write in parts costs HBM far
+// more than a whole one: 8184 x 8200 bf16, all of whose chunks are aligned, takes 85 us where 8192 x 8192 takes 51.  Here
+// every row of the destination has its own boundaries, on lines: the tile of destination index d0 writes [d0 - delta, d0 + TD -
+// delta) of a row whose phase in its line is delta, and reads the H = 128 / EB source rows before d0 besides its own TD.  So
+// each line is written whole, by eight lanes of one store instruction; the H rows are read twice (mostly from the last-level
+// cache).  us, rotating over three pairs: bf16 8191 x 8193 105 (element by element) -> 56 (4.8 TB/s), 8184 x 8200 85 (aligned
+// chunks) -> 60, fp32 4095 x 4097 42 -> 30, 8-byte 4095 x 4097 73 -> 51 (5.3 TB/s).
+template <int EB, bool NT>
+__global__ __launch_bounds__(256) void relayout_transpose_skew_kernel(TransposePlan p, const uint8_t* __restrict__ src, uint8_t* __restrict__ dst) {
+  constexpr int TS = skew_tile_s(EB), TD = skew_tile_d(EB);        // elements along the source and along the destination
+  constexpr int CE = 16 / EB, H = 128 / EB;                        // elements per chunk, per line
+  constexpr int CS = TS / CE, CD = TD / CE;                        // chunks of a tile row on either side
+  constexpr int ROWB = TS * EB;
+  typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+  typedef u32x4 u32x4_any __attribute__((aligned(1)));
+  using W = typename Word<EB>::T;
+  __shared__ __attribute__((aligned(16))) uint8_t tile[(TD + H) * ROWB];
+  // (the image of the kernel above: chunk c of row r at chunk position c ^ (r / CE))
+  auto lds_at = [&](int row, int byte_col) -> uint8_t* {
+    return tile + row * ROWB + ((((byte_col >> 4) ^ (row / CE)) & (CS - 1)) << 4) + (byte_col & 15);
+  };
+  uint64_t b = blockIdx.x;
+  const uint32_t ts = (uint32_t)(b % p.tiles_s);
+  b /= p.tiles_s;
+  uint32_t td = (uint32_t)(b % p.tiles_d);
+  b /= p.tiles_d;
+  if (p.diag > 0) td = (td + ts / (uint32_t)p.diag) % p.tiles_d;
+  int64_t sb = p.s_off, db = p.d_off;
+  for (int k = 0; k < p.n; ++k) {
+    const uint64_t q = b / p.ext[k];
+    const int64_t dig = (int64_t)(b - q * p.ext[k]);
+    sb += dig * p.ss[k];
+    db += dig * p.ds[k];
+    b = q;
+  }
+  const int64_t s0 = (int64_t)ts * TS, d0 = (int64_t)td * TD;
+
+  // HBM -> LDS: LDS row r is destination-fast index d0 - H + r
+  constexpr int NL = (TD + H) * CS / 256;
+  static_assert((TD + H) * CS % 256 == 0, "whole trips");
+  u32x4 held[NL];
+#pragma unroll
+  for (int i = 0; i < NL; ++i) {
+    const int c = (int)threadIdx.x + 256 * i;
+    const int64_t iD = d0 - H + c / CS, iS = s0 + (c % CS) * CE;
+    const int64_t jD = iD < 0 ? 0 : (iD < p.eD ? iD : p.eD - 1), jS = iS + CE <= p.eS ? iS : p.eS - CE;   // the nearest place inside the tensor
+    held[i] = *(const u32x4_any*)(src + (sb + jD * p.sD + jS) * EB);
+  }
+  if (s0 + TS > p.eS) {                                            // the last tile along the source: chunks that were moved back
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const int64_t over = s0 + (int64_t)((threadIdx.x + 256 * i) % CS) * CE + CE - p.eS;
+      if (over > 0 && over < CE)
+        held[i] = __builtin_bit_cast(u32x4, __builtin_bit_cast(unsigned __int128, held[i]) >> (int)(over * EB * 8));
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < NL; ++i) {
+    const int c = (int)threadIdx.x + 256 * i;
+    *(u32x4*)lds_at(c / CS, (c % CS) * 16) = held[i];
+  }
+  __syncthreads();
+  // LDS -> HBM: output row r is source-fast index s0 + r
+  for (int c = threadIdx.x; c < TS * CD; c += 256) {
+    const int r = c / CD, cc = c % CD;
+    const int64_t iS = s0 + r;
+    if (iS >= p.eS) continue;
+    uint8_t* row = dst + (db + iS * p.dS) * EB;                    // destination index 0 of this row
+    const int delta = (int)((uintptr_t)row & 127) / EB;
+    const int64_t iD = d0 + cc * CE - delta;
+    if (iD + CE <= 0 || iD >= p.eD) continue;
+    const int l0 = H + cc * CE - delta;                            // LDS row of the chunk's first element
+    W w[CE];
+#pragma unroll
+    for (int k = 0; k < CE; ++k) w[k] = *(const W*)lds_at(l0 + k, r * EB);
+    for (int64_t t = 0; t < p.E_R; ++t) {                          // (replicas lie whole lines apart)
+      int64_t tr = t, ro = 0;
+      for (int k = p.n_r - 1; k >= 0; --k) {
+        ro += (tr % p.rext[k]) * p.rstr[k];
+        tr /= p.rext[k];
+      }
+      uint8_t* at = row + (ro + iD) * EB;
+      if (iD >= 0 && iD + CE <= p.eD) {
+        const u32x4 v = __builtin_bit_cast(u32x4, w);
+        if (NT) __builtin_nontemporal_store(v, (u32x4*)at);
+        else *(u32x4*)at = v;
+      } else {
+#pragma unroll
+        for (int k = 0; k < CE; ++k)
+          if (iD + k >= 0 && iD + k < p.eD) ((W*)at)[k] = w[k];
       }
     }
   }
@@ -548,11 +684,15 @@ __global__ __launch_bounds__(256) void relayout_transpose_elem_kernel(TransposeP
 
 template <int EB>
 static hipError_t launch_transpose_e(const TransposePlan& p, const void* src, void* dst, hipStream_t s) {
-  if (p.streaming)
-    hipLaunchKernelGGL((relayout_transpose_kernel<EB, true>), dim3((unsigned)p.blocks), dim3(256), 0, s, p, (const uint8_t*)src,
+  if (p.elementwise) {
+    const uint64_t blocks = p.blocks / p.tiles_s * ((p.tiles_s + 7) & ~7u);
+    hipLaunchKernelGGL((relayout_transpose_kernel<EB, false, true>), dim3((unsigned)blocks), dim3(256), 0, s, p, (const uint8_t*)src,
+                       (uint8_t*)dst);
+  } else if (p.streaming)
+    hipLaunchKernelGGL((relayout_transpose_kernel<EB, true, false>), dim3((unsigned)p.blocks), dim3(256), 0, s, p, (const uint8_t*)src,
                        (uint8_t*)dst);
   else
-    hipLaunchKernelGGL((relayout_transpose_kernel<EB, false>), dim3((unsigned)p.blocks), dim3(256), 0, s, p, (const uint8_t*)src,
+    hipLaunchKernelGGL((relayout_transpose_kernel<EB, false, false>), dim3((unsigned)p.blocks), dim3(256), 0, s, p, (const uint8_t*)src,
                        (uint8_t*)dst);
   return hipGetLastError();
 }
@@ -560,7 +700,22 @@ static hipError_t launch_transpose_e(const TransposePlan& p, const void* src, vo
 hipError_t launch_relayout_transpose(const TransposePlan& p, int elem_bytes, const void* src, void* dst, hipStream_t s) {
   if (p.blocks == 0) return hipSuccess;
   if (p.blocks > 0x7fffffffull) return hipErrorInvalidValue;
-  if (p.elementwise) {
+  if (p.elementwise == 3) {
+    const dim3 grid((unsigned)p.blocks), block(256);
+    const uint8_t* from = (const uint8_t*)src;
+    uint8_t* to = (uint8_t*)dst;
+    switch (elem_bytes * 2 + (p.streaming ? 1 : 0)) {
+      case 4: hipLaunchKernelGGL((relayout_transpose_skew_kernel<2, false>), grid, block, 0, s, p, from, to); break;
+      case 5: hipLaunchKernelGGL((relayout_transpose_skew_kernel<2, true>), grid, block, 0, s, p, from, to); break;
+      case 8: hipLaunchKernelGGL((relayout_transpose_skew_kernel<4, false>), grid, block, 0, s, p, from, to); break;
+      case 9: hipLaunchKernelGGL((relayout_transpose_skew_kernel<4, true>), grid, block, 0, s, p, from, to); break;
+      case 16: hipLaunchKernelGGL((relayout_transpose_skew_kernel<8, false>), grid, block, 0, s, p, from, to); break;
+      case 17: hipLaunchKernelGGL((relayout_transpose_skew_kernel<8, true>), grid, block, 0, s, p, from, to); break;
+      default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+  }
+  if (p.elementwise == 1) {
     const dim3 grid((unsigned)p.blocks), block(256);
     switch (elem_bytes) {
       case 1: hipLaunchKernelGGL(relayout_transpose_elem_kernel<1>, grid, block, 0, s, p, src, dst); break;
