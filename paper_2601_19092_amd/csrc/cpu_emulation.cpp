@@ -15,6 +15,7 @@ namespace axe {
 static int64_t g_src_bytes = 0, g_dst_bytes = 0;
 static int g_violations = 0;
 static int g_transposes = 0;      // launches of the transposing relayout since the buffers were declared
+static int g_rows = 0;            // relayouts of rows that start anywhere
 static int g_transposes_elem = 0; // ... of which element by element (not in 16-byte chunks)
 
 static int64_t swz_apply(int64_t x, Swz z) { return x ^ (((x >> z.shift) & (int64_t)z.mask) << z.base); }
@@ -85,6 +86,35 @@ hipError_t launch_relayout_joint(const RelayoutPlan& p, int unit, const void* sr
           tr /= p.rext[k];
         }
         move(src, dst, sa, swz_apply(ra, p.d_swz), unit);
+      }
+    }
+  }
+  return hipSuccess;
+}
+
+// The same chunks and addresses as the kernel; every 16 bytes it would load must lie inside the source.
+hipError_t launch_relayout_rows(const RowPlan& p, int eb, const void* src_, void* dst_, hipStream_t) {
+  const char* src = (const char*)src_;
+  char* dst = (char*)dst_;
+  ++g_rows;
+  for (uint64_t t = 0; t < p.slots; ++t) {
+    uint64_t row = t / p.slots_per_row;
+    const int64_t seg = (int64_t)(t - row * p.slots_per_row), bytes = p.run * eb;
+    int64_t s = p.s_off, d = p.d_off;
+    for (int k = 0; k < p.n; ++k) {
+      s += (int64_t)(row % p.ext[k]) * p.ss[k];
+      d += (int64_t)(row % p.ext[k]) * p.ds[k];
+      row /= p.ext[k];
+    }
+    s *= eb, d *= eb;
+    for (int lane = 0; lane < 64; ++lane) {
+      const int64_t o = (seg * 64 + lane) * 16 - (int64_t)((uintptr_t)(dst + d) & 15);
+      if (o >= bytes) continue;
+      const int64_t in = o < 0 ? 0 : (o + 16 <= bytes ? o : bytes - 16);
+      if (s + in < 0 || s + in + 16 > g_src_bytes) ++g_violations;
+      for (int64_t b = o < 0 ? 0 : o; b < o + 16 && b < bytes; ++b) {
+        if (s + b < 0 || s + b >= g_src_bytes || d + b < 0 || d + b >= g_dst_bytes || b < in || b >= in + 16) ++g_violations;
+        else dst[d + b] = src[s + b];
       }
     }
   }
@@ -293,8 +323,10 @@ extern "C" void axe_hostcheck_set_buffers(int64_t src_bytes, int64_t dst_bytes) 
   axe::g_violations = 0;
   axe::g_transposes = 0;
   axe::g_transposes_elem = 0;
+  axe::g_rows = 0;
 }
 extern "C" int axe_hostcheck_violations(void) { return axe::g_violations; }
+extern "C" int axe_hostcheck_rows(void) { return axe::g_rows; }
 extern "C" int axe_hostcheck_transposes(void) { return axe::g_transposes; }
 extern "C" int axe_hostcheck_transposes_elementwise(void) { return axe::g_transposes_elem; }
 

@@ -48,6 +48,18 @@ struct RelayoutPlan {
   int32_t streaming;               // 1: non-temporal loads and stores (data larger than the caches)
 };
 
+// Relayout of rows that are contiguous on both sides and start anywhere: run elements each, the other digits (fastest first) as
+// in RelayoutPlan.  A wave takes four slots, a slot 64 16-byte chunks of one row, cut at 16-byte boundaries of the destination.
+struct RowPlan {
+  int32_t n;
+  uint32_t ext[kMaxJoint];
+  int64_t ss[kMaxJoint], ds[kMaxJoint];
+  int64_t s_off, d_off;
+  int64_t run;
+  uint32_t slots_per_row, rows;
+  uint64_t slots;                  // rows * slots_per_row
+};
+
 // Transposing relayout: the joint loop nest has one digit that is contiguous in the source (extent
 // eS, destination stride dS) and another that is contiguous in the destination (extent eD, source
 // stride sD).  A workgroup moves one T x T tile of those two digits through LDS; the other digits

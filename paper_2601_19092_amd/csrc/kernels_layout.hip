@@ -370,6 +370,93 @@ hipError_t launch_relayout_joint(const RelayoutPlan& p, int unit_bytes, const vo
 }
 
 // ------------------------------------------------------------------------------------------
+// Relayout of contiguous rows whose length, pitch or start is no multiple of 16 bytes (padding an odd matrix, cutting a
+// window out of one).  The loop nest above moves such rows in the largest unit that divides everything, single elements at
+// worst.  Here a lane moves a 16-byte chunk of the destination, aligned there, loaded from wherever it starts in the
+// source (global memory takes any address); the chunk a row begins or ends in is loaded from inside the row, shifted,
+// and stored element by element.  Which row a wave is at is worked out once for four slots of 64 chunks, on uniform
+// values: the divisions would otherwise be most of the work.  Bound: HBM.  us, rotating over three pairs of buffers: bf16
+// 8191 x 8191 to rows on whole lines 190 -> 51 (5.3 TB/s), bytes 8191 x 8190 99 -> 28, fp32 4097 x 4095 58 -> 28, 8-byte 62 -> 53,
+// bf16 4450 x 943 8.5 -> 6.3.
+// ------------------------------------------------------------------------------------------
+template <int EB>
+__global__ __launch_bounds__(256) void relayout_rows_kernel(RowPlan p, const uint8_t* __restrict__ src, uint8_t* __restrict__ dst) {
+  typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+  typedef u32x4 u32x4_any __attribute__((aligned(1)));
+  using W = typename Word<EB>::T;
+  constexpr int CE = 16 / EB, U = 4;
+  const int lane = threadIdx.x & 63;
+  const uint64_t t = ((uint64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * U;
+  if (t >= p.slots) return;
+  uint32_t row = (uint32_t)(t / p.slots_per_row), seg = (uint32_t)(t - (uint64_t)row * p.slots_per_row);
+  const int64_t bytes = p.run * EB;
+  const uint8_t* s = nullptr;
+  uint8_t* d = nullptr;
+  auto locate = [&]() __attribute__((always_inline)) {            // start of the row on either side
+    int64_t so = p.s_off, dof = p.d_off;
+    uint32_t rem = row;
+    for (int k = 0; k < p.n; ++k) {
+      const uint32_t q = rem / p.ext[k], dig = rem - q * p.ext[k];
+      so += (int64_t)dig * p.ss[k];
+      dof += (int64_t)dig * p.ds[k];
+      rem = q;
+    }
+    s = src + so * EB, d = dst + dof * EB;
+  };
+  locate();
+  u32x4 held[U];
+  uint8_t* at[U];
+  int64_t off[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    at[u] = d;
+    off[u] = bytes;                                                // (no such slot: nothing to store)
+    if (row < p.rows) {
+      const int64_t o = ((int64_t)seg * 64 + lane) * 16 - ((uintptr_t)d & 15);   // byte of the row the chunk begins at
+      const int64_t in = o < 0 ? 0 : (o + 16 <= bytes ? o : bytes - 16);         // the nearest chunk inside the row
+      held[u] = *(const u32x4_any*)(s + in);
+      off[u] = o;
+      if (++seg == p.slots_per_row) {
+        seg = 0, ++row;
+        if (u + 1 < U && row < p.rows) locate();
+      }
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int64_t o = off[u];
+    if (o >= bytes) continue;
+    if (o >= 0 && o + 16 <= bytes) {
+      *(u32x4*)(at[u] + o) = held[u];
+    } else {
+      unsigned __int128 x = __builtin_bit_cast(unsigned __int128, held[u]);
+      x = o < 0 ? x << (int)(-o * 8) : x >> (int)((o + 16 - bytes) * 8);
+      const Row<EB> e = __builtin_bit_cast(Row<EB>, x);
+#pragma unroll
+      for (int k = 0; k < CE; ++k)
+        if (o + k * EB >= 0 && o + k * EB < bytes) *(W*)(at[u] + o + k * EB) = e.w[k];
+    }
+  }
+}
+
+hipError_t launch_relayout_rows(const RowPlan& p, int elem_bytes, const void* src, void* dst, hipStream_t s) {
+  if (p.slots == 0) return hipSuccess;
+  const uint64_t blocks = (p.slots + 15) / 16;
+  if (blocks > 0x7fffffffull) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)blocks), block(256);
+  const uint8_t* from = (const uint8_t*)src;
+  uint8_t* to = (uint8_t*)dst;
+  switch (elem_bytes) {
+    case 1: hipLaunchKernelGGL(relayout_rows_kernel<1>, grid, block, 0, s, p, from, to); break;
+    case 2: hipLaunchKernelGGL(relayout_rows_kernel<2>, grid, block, 0, s, p, from, to); break;
+    case 4: hipLaunchKernelGGL(relayout_rows_kernel<4>, grid, block, 0, s, p, from, to); break;
+    case 8: hipLaunchKernelGGL(relayout_rows_kernel<8>, grid, block, 0, s, p, from, to); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+// ------------------------------------------------------------------------------------------
 // Relayout, transposing: source and destination are contiguous along different digits of the joint
 // loop nest (row-major <-> column-major and their batched, strided relatives).  Moving single
 // elements would leave one side with 2-byte accesses scattered over rows; instead a workgroup
