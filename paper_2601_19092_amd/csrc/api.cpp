@@ -90,6 +90,7 @@ int axe_layout_eval(const axe_layout_t* L, int32_t rank, const int64_t* shape, i
     d.str[k] = h.D[k].s;
     d.axis[k] = h.D[k].axis;
     d.shift[k] = is_pow2(h.D[k].e) ? ilog2(h.D[k].e) : -1;
+    if (d.use32) d.div[k] = div31_by(h.D[k].e);
   }
   for (int k = 0; k < d.n_r; ++k) {
     d.rext[k] = h.R[k].e;

@@ -33,8 +33,9 @@ hipError_t launch_layout_eval(const EvalDesc& d, int64_t n, const int64_t* idx, 
     for (int a = 0; a < kMaxAxes; ++a) c[a] = d.off[a];
     uint64_t rem = (uint64_t)x;
     for (int k = d.n_d - 1; k >= 0; --k) {
-      c[d.axis[k]] += (int64_t)(rem % (uint64_t)d.ext[k]) * d.str[k];
-      rem /= (uint64_t)d.ext[k];
+      const uint64_t q = d.use32 && d.shift[k] < 0 ? div31((uint32_t)rem, d.div[k]) : rem / (uint64_t)d.ext[k];
+      c[d.axis[k]] += (int64_t)(rem - q * (uint64_t)d.ext[k]) * d.str[k];
+      rem = q;
     }
     for (int64_t t = 0; t < d.E_R; ++t) {
       int64_t r[kMaxAxes];

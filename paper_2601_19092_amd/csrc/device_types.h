@@ -14,11 +14,30 @@ struct Swz {
   int32_t mask, base, shift;
 };
 
+// Division of 31-bit numbers by a fixed d > 1 as a multiplication: with 2^(s-1) < d <= 2^s and m = floor(2^(31+s) / d) + 1 (below
+// 2^32), floor(n m / 2^(31+s)) = floor(n / d) for every n < 2^31, since m d - 2^(31+s) <= 2^s.  Two instructions, where a
+// division by a run-time number takes some 25 on the vector ALU.
+struct Div31 {
+  uint32_t mul;                // 0: not prepared
+  int32_t shift;               // s - 1
+};
+inline Div31 div31_by(int64_t d) {
+  if (d < 2 || d >= (int64_t(1) << 31)) return Div31{0, 0};
+  int s = 0;
+  while ((int64_t(1) << s) < d) ++s;
+  return Div31{(uint32_t)(((uint64_t(1) << (31 + s)) / (uint64_t)d) + 1), s - 1};
+}
+#if defined(__HIPCC__)
+__host__ __device__
+#endif
+inline uint32_t div31(uint32_t n, Div31 d) { return (uint32_t)(((uint64_t)n * d.mul) >> 32) >> d.shift; }
+
 // Full layout for axe_layout_eval (all axes kept).
 struct EvalDesc {
   int32_t n_d, n_r, n_axes;
   int32_t use32;               // E_D < 2^31: digit arithmetic in 32 bits
   int32_t shift[kMaxD];        // log2(ext) when ext is a power of two, else -1
+  Div31 div[kMaxD];            // otherwise, when use32
   int64_t ext[kMaxD], str[kMaxD];
   int32_t axis[kMaxD];
   int64_t rext[kMaxR], rstr[kMaxR];

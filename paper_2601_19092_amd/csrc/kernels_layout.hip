@@ -66,7 +66,8 @@ __global__ __launch_bounds__(256) void layout_eval_kernel(EvalDesc d, int64_t n,
 
 // The common case -- no replicas, fewer than 2^31 points, at most 4 axes -- without the generic loop's
 // 64-bit divisions and 8-way axis selects: digits in 32 bits (a shift and a mask where the extent is a
-// power of two), one 64-bit multiply-add per digit, the axis loop unrolled to NAX.  A thread evaluates
+// power of two, a multiplication otherwise: 2816 x 5504 points of a tiled layout, 124 MB, 33 us with 32-bit divisions,
+// 23 now), one 64-bit multiply-add per digit, the axis loop unrolled to NAX.  A thread evaluates
 // PTS consecutive indices (4 when there is a single axis: two 16-byte stores), so that an iter's
 // parameters are fetched once for all of them.  Bound: the 8 NAX bytes written per index.
 template <int NAX, int PTS>
@@ -106,7 +107,7 @@ __global__ __launch_bounds__(256) void layout_eval_fast_kernel(EvalDesc d, int64
         dig = rem[p] & (e - 1u);
         rem[p] >>= sh;
       } else {
-        const uint32_t q = rem[p] / e;
+        const uint32_t q = div31(rem[p], d.div[k]);
         dig = rem[p] - q * e;
         rem[p] = q;
       }
@@ -197,7 +198,7 @@ __global__ __launch_bounds__(256) void layout_eval_block_kernel(EvalDesc d, int6
           dig = rem & (e - 1u);
           rem >>= d.shift[k];
         } else {
-          const uint32_t q = rem / e;
+          const uint32_t q = div31(rem, d.div[k]);
           dig = rem - q * e;
           rem = q;
         }

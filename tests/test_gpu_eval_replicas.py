@@ -48,3 +48,21 @@ def test_eval_matches_the_oracle(naxes, replicas, given):
         odd = torch.zeros(n * L.E_R * naxes + 1, dtype=torch.int64, device="cuda")[1:].view(n, L.E_R, naxes)   # 8 bytes off a pair
         B.axe_layout_eval(L, shape, n, d_idx, odd)
         assert torch.equal(odd, out)
+
+
+@pytest.mark.parametrize("extents", [(3, 7, 11, 13), (2147483647,), (46341, 46339), (1073741825, 1), (2, 1073741823), (5, 3, 715827, 199), (65537, 32765)])
+def test_eval_divides_exactly_by_any_extent(extents):
+    """Digits come from multiplications: extents around powers of two, primes, index spaces up to 2^31 - 1, at the indices where
+    a quotient steps."""
+    D, s = [], 1
+    for e in reversed(extents):
+        D.insert(0, (e, s, "m"))
+        s *= e + 1                                             # the digits stay readable in the coordinate
+    L, Lo = B.Layout(W.spec(D)), Layout.from_spec(W.spec(D))
+    E = int(np.prod([int(e) for e in extents], dtype=object))
+    last = int(extents[-1])
+    rng = np.random.default_rng(1)
+    q = rng.integers(0, max(1, E // last), 4000)
+    idx = np.unique(np.clip(np.concatenate([q * last - 1, q * last, q * last + 1, rng.integers(0, E, 4000), [0, E - 1, E - 2, E // 2]]), 0, E - 1))
+    got = B.axe_layout_eval(L, (E,), len(idx), torch.from_numpy(idx).cuda()).cpu().numpy()
+    assert np.array_equal(got, R.evaluate_np(Lo, idx, ["m"]))
