@@ -766,6 +766,10 @@ int plan_gemm(const axe_gemm_desc_t* g, const void* dA, const void* dB, void* dC
       // up to four K-tiles the burst variant of the 64 x 64 kernel is the faster one where it fits (graph replays, us, burst /
       // cheapest member: 256^3 3.4 / 3.6, 512 x 512 x 128 2.7 / 4.0, 1024 x 1024 x 256 3.7 / 4.4; K = 512: 4.8 / 3.6, 5.1 / 5.0)
       if (!fp8 && g->K <= 256 && small_preload_fits(g->M, g->N, g->K, lda, ldb, ldc)) P.member = -1;
+      // and so is the 64 x 64 kernel itself up to five K-tiles of 16-bit inputs, when storing C is most of the work and several
+      // small workgroups per compute unit overlap it (us, 64 x 64 / cheapest member, K = 288: 3840 x 1280 11.6 / 13.2, 1051 x 7888
+      // 16.8 / 20.7, 600 x 1500 5.1 / 5.6; 2040 x 4096 15.1 / 14.0, 4096 x 4088 27.1 / 23.7; K = 512: 3840 x 1280 15.8 / 14.1)
+      if (!fp8 && g->K <= 320 && g->M * g->N < int64_t(8) << 20 && env_int("AXE_TILE_MEMBER", -1) < 0) P.member = -1;
     }
   }
   P.ragged = tile == AXE_TILE_256x256x64 && !big_ok && !blocked && ragged_ok;

@@ -49,6 +49,9 @@ namespace tiles {
 typedef __attribute__((address_space(3))) void* lds_ptr;
 typedef __attribute__((address_space(3))) uint8_t* lds_u8;
 typedef __attribute__((ext_vector_type(2))) unsigned int u32x2;
+// rows of C start at any element (odd N): global memory takes the vector there, four element stores cost four times as much
+typedef u32x2 u32x2_any __attribute__((aligned(2)));
+typedef f32x4 f32x4_any __attribute__((aligned(4)));
 
 template <int DT>
 __device__ __forceinline__ uint32_t pack2(float lo, float hi) {
@@ -352,7 +355,6 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_tiles_kernel(GemmArgs 
   }
 
   // ---- VGPR -> HBM: lane holds C[m][n .. n + 3]
-  const bool whole = (g.ldc & 3) == 0;
 #pragma unroll
   for (int i = 0; i < MF; ++i) {
     const int r = wm * (TM / WM) + i * 16 + fr;
@@ -378,8 +380,8 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_tiles_kernel(GemmArgs 
       if (g.out_bf16) {
         uint16_t* C = (uint16_t*)g.C + m * g.ldc + n;
         const u32x2 d = {pack2<DT>(acc[i][j][0], acc[i][j][1]), pack2<DT>(acc[i][j][2], acc[i][j][3])};
-        if (n + 3 < g.N && whole) {
-          *(u32x2*)C = d;
+        if (n + 3 < g.N) {
+          *(u32x2_any*)C = d;
         } else {
 #pragma unroll
           for (int e = 0; e < 4; ++e)
@@ -387,8 +389,8 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_tiles_kernel(GemmArgs 
         }
       } else {
         float* C = (float*)g.C + m * g.ldc + n;
-        if (n + 3 < g.N && whole) {
-          *(f32x4*)C = acc[i][j];
+        if (n + 3 < g.N) {
+          *(f32x4_any*)C = acc[i][j];
         } else {
 #pragma unroll
           for (int e = 0; e < 4; ++e)

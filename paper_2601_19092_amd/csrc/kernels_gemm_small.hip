@@ -30,6 +30,8 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(8))) int i32x8;
 typedef __attribute__((ext_vector_type(4))) int i32x4;
+typedef __attribute__((ext_vector_type(2), aligned(2))) uint32_t uint2_any;
+typedef f32x4 float4_any __attribute__((aligned(4)));
 
 __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
   __bf16 h = (__bf16)f;                       // v_cvt_pk_bf16_f32: round to nearest even
@@ -184,8 +186,8 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(GemmArgs g) {
         uint16_t h[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) h[e] = F16 ? f32_to_f16_rne(acc[i][j][e]) : f32_to_bf16_rne(acc[i][j][e]);
-        if (n + 3 < g.N && ((g.ldc & 3) == 0)) {
-          *(uint2*)C = uint2{(uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16)};
+        if (n + 3 < g.N) {                                         // (rows of C may start at any element: global memory takes the vector)
+          *(uint2_any*)C = uint2_any{(uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16)};
         } else {
 #pragma unroll
           for (int e = 0; e < 4; ++e)
@@ -193,8 +195,8 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(GemmArgs g) {
         }
       } else {
         float* C = (float*)g.C + m * g.ldc + n;
-        if (n + 3 < g.N && ((g.ldc & 3) == 0)) {
-          *(float4*)C = float4{acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]};
+        if (n + 3 < g.N) {
+          *(float4_any*)C = acc[i][j];
         } else {
 #pragma unroll
           for (int e = 0; e < 4; ++e)

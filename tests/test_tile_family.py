@@ -74,6 +74,9 @@ def test_which_tile_a_problem_takes():
     assert taken(2048, 4096, 2048) == (256, 128) and taken(4096, 4096, 2048) == (256, 256)
     assert taken(1000, 1000, 1000) == (64, 64)
     assert taken(256, 256, 256) == (64, 64) and taken(256, 256, 512) == (16, 16)      # the burst variant up to four K-tiles
+    # 16-bit inputs, five K-tiles: the 64 x 64 kernel below 2^23 elements of C
+    assert taken(2040, 4096, 320) == (64, 64) and taken(2056, 4096, 312) == (256, 128) and taken(1051, 7885, 328) == (256, 128)
+    assert taken(1051, 7885, 320) == (64, 64) and taken(1051, 7885, 320, "fp8") == (256, 128)
 
 
 def operands(M, N, K, dt, scale, rows, seed):
