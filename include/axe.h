@@ -18,8 +18,9 @@
  *   - Return value: AXE_OK (0) or a negative error code; nothing is launched when an error is
  *     returned.  No call aborts or throws.  axe_strerror() names a code, axe_last_error() gives
  *     the detailed message of the calling thread's last failure.
- *   - The library keeps no global mutable state apart from that thread-local message, and
- *     allocates no device memory.
+ *   - The library keeps no mutable state apart from thread-local ones -- that message, and the plan of the
+ *     thread's last axe_gemm, axe_relayout and axe_layout_eval, used again when the next call's descriptor is
+ *     the same word by word -- and allocates no device memory.
  *   - One GPU holds the whole tensor: an axis other than the memory axis may appear only with
  *     total extent 1 (e.g. the extent-1 `gpuid` iter and `gpuid` offset of one shard of a
  *     sharded tensor, Sec. 2.2); such iters are removed by canonicalisation rule D0 (App. A)

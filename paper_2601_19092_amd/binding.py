@@ -8,6 +8,7 @@ for the current HIP stream.
 from __future__ import annotations
 
 import ctypes as C
+import functools
 import os
 from typing import Dict, List, Optional, Sequence, Tuple
 
@@ -188,14 +189,20 @@ def _stream_ptr(stream=None) -> int:
         return stream if isinstance(stream, int) else int(stream.cuda_stream)
     import torch
     if _raw_stream is None:
-        _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", False)
+        _raw_stream = hasattr(torch._C, "_cuda_getDevice") and getattr(torch._C, "_cuda_getCurrentRawStream", False)
     if _raw_stream:
-        return int(_raw_stream(torch.cuda.current_device()))
+        return _raw_stream(torch._C._cuda_getDevice())            # (the call's tensors live on the GPU: torch has initialised it)
     return int(torch.cuda.current_stream().cuda_stream)
 
 
+@functools.lru_cache(maxsize=256)
+def _shape_of(shape: Tuple[int, ...]):
+    return (C.c_int64 * len(shape))(*shape)
+
+
 def _shape_arr(shape: Sequence[int]):
-    return (C.c_int64 * len(shape))(*[int(s) for s in shape])
+    """The shape as a C array (the library only reads it: calls with one shape share it)."""
+    return _shape_of(tuple(map(int, shape)))
 
 
 def axe_layout_eval(layout: Layout, shape: Sequence[int], n: int, flat_idx=None, out=None, stream=None):

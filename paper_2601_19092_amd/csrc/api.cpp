@@ -2,6 +2,7 @@
 #include <hip/hip_runtime.h>
 #include <stdlib.h>
 #include <string.h>
+#include <unistd.h>
 
 #include <algorithm>
 
@@ -31,6 +32,86 @@ int env_int(const char* name, int dflt) {
   return s && *s ? atoi(s) : dflt;
 }
 
+// The contents of a descriptor as a flat run of words: what a plan depends on, device pointers aside (of those
+// only whether they are given and their alignment matter).  False when the descriptor is malformed in a way
+// that makes its arrays unreadable: the planner then reports the error.
+constexpr int kKeyWords = 24 + 3 * (12 + 3 * (AXE_MAX_D + AXE_MAX_R) + AXE_MAX_AXES);
+struct PlanKey {
+  int64_t w[kKeyWords];
+  int n = 0;
+  void put(int64_t v) { w[n++] = v; }
+};
+bool key_of_layout(const axe_layout_t& L, PlanKey& k) {
+  if (L.n_axes < 1 || L.n_axes > AXE_MAX_AXES || L.n_d < 1 || L.n_d > AXE_MAX_D || L.n_r < 0 || L.n_r > AXE_MAX_R || !L.d ||
+      (L.n_r && !L.r))
+    return false;
+  k.put(L.n_axes), k.put(L.n_d), k.put(L.n_r);
+  for (int i = 0; i < L.n_d; ++i) k.put(L.d[i].extent), k.put(L.d[i].stride), k.put(L.d[i].axis);
+  for (int i = 0; i < L.n_r; ++i) k.put(L.r[i].extent), k.put(L.r[i].stride), k.put(L.r[i].axis);
+  for (int a = 0; a < L.n_axes; ++a) k.put(L.offset ? L.offset[a] : 0);
+  k.put(L.swz_axis), k.put(L.swz_bits), k.put(L.swz_base), k.put(L.swz_shift);
+  return true;
+}
+
+// Whether any of the library's knobs is set (they are read whenever a call is planned: no plan is kept then).
+bool knobs_set() {
+  for (char** e = environ; e && *e; ++e)
+    if (!strncmp(*e, "AXE_", 4)) return true;
+  return false;
+}
+
+// The plan of the last call of one kind that this thread made: a caller that moves or evaluates the same layouts again
+// (compared word by word; other buffers of the same alignment are fine) skips the layout analysis, 1 - 1.5 us of a
+// call whose launch takes 2.5.
+template <class Plan>
+struct LastPlan {
+  PlanKey key;
+  Plan plan;
+  bool have = false;
+  bool holds(const PlanKey& k) const { return have && k.n == key.n && memcmp(k.w, key.w, sizeof(int64_t) * k.n) == 0; }
+  void keep(const PlanKey& k, const Plan& p) { key = k, plan = p, have = true; }
+};
+
+// A planned relayout: which kernel, and its plan.
+struct RelayoutCall {
+  enum Kernel { kGeneric, kTranspose, kRows, kJoint } kernel;
+  int unit;                                                        // bytes per unit of the plan's addresses
+  union {
+    GenericRelayoutPlan generic;
+    TransposePlan transpose;
+    RowPlan rows;
+    RelayoutPlan joint;
+  };
+};
+int launch_relayout(const RelayoutCall& c, const void* d_src, void* d_dst, hipStream_t st) {
+  hipError_t e = hipSuccess;
+  switch (c.kernel) {
+    case RelayoutCall::kGeneric: e = launch_relayout_generic(c.generic, c.unit, d_src, d_dst, st); break;
+    case RelayoutCall::kTranspose: e = launch_relayout_transpose(c.transpose, c.unit, d_src, d_dst, st); break;
+    case RelayoutCall::kRows: e = launch_relayout_rows(c.rows, c.unit, d_src, d_dst, st); break;
+    case RelayoutCall::kJoint: e = launch_relayout_joint(c.joint, c.unit, d_src, d_dst, st); break;
+  }
+  return e == hipSuccess ? AXE_OK : hip_fail(e, "axe_relayout");
+}
+
+int check_relayout_pointers(int32_t elem_bytes, const void* d_src, int64_t src_elems, const void* d_dst, int64_t dst_elems) {
+  if (!d_src || !d_dst) {
+    set_error("axe_relayout: NULL device pointer");
+    return AXE_EINVAL;
+  }
+  if (((uintptr_t)d_src | (uintptr_t)d_dst) % (uintptr_t)elem_bytes) {
+    set_error("axe_relayout: buffers are not aligned to the element size");
+    return AXE_EINVAL;
+  }
+  const char* s0 = (const char*)d_src;
+  const char* d0 = (const char*)d_dst;
+  if (s0 < d0 + dst_elems * elem_bytes && d0 < s0 + src_elems * elem_bytes) {
+    set_error("axe_relayout: source and destination buffers overlap");
+    return AXE_EINVAL;
+  }
+  return AXE_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -55,31 +136,10 @@ const char* axe_strerror(int code) {
 const char* axe_last_error(void) { return last_error(); }
 
 // ---------------------------------------------------------------------------------------------
-int axe_layout_eval(const axe_layout_t* L, int32_t rank, const int64_t* shape, int64_t n, const int64_t* d_flat_idx,
-                    int64_t* d_out, void* stream) {
+static int plan_layout_eval(const axe_layout_t* L, int32_t rank, const int64_t* shape, EvalDesc& d) {
   HLayout h;
   if (int rc = load_layout(L, h, "axe_layout_eval")) return rc;
   if (int rc = check_shape(h, rank, shape, "axe_layout_eval")) return rc;
-  if (n < 0) {
-    set_error("axe_layout_eval: n = %lld is negative", (long long)n);
-    return AXE_EINVAL;
-  }
-  if (!d_flat_idx && n > h.E_D) {
-    set_error("axe_layout_eval: n = %lld exceeds E_D = %lld with implicit indices", (long long)n, (long long)h.E_D);
-    return AXE_ERANGE;
-  }
-  if (n > 0 && !d_out) {
-    set_error("axe_layout_eval: d_out is NULL");
-    return AXE_EINVAL;
-  }
-  int64_t per, total;
-  if (__builtin_mul_overflow(h.E_R, (int64_t)h.n_axes, &per) || __builtin_mul_overflow(per, n, &total) ||
-      total > (INT64_MAX >> 4)) {
-    set_error("axe_layout_eval: output size overflows");
-    return AXE_ERANGE;
-  }
-  if (n == 0) return AXE_OK;
-  EvalDesc d;
   memset(&d, 0, sizeof d);
   d.n_d = (int)h.D.size();
   d.n_r = (int)h.R.size();
@@ -102,6 +162,45 @@ int axe_layout_eval(const axe_layout_t* L, int32_t rank, const int64_t* shape, i
   d.swz = Swz{h.swz_axis >= 0 ? (1 << h.swz_bits) - 1 : 0, h.swz_base, h.swz_shift};
   d.E_D = h.E_D;
   d.E_R = h.E_R;
+  return AXE_OK;
+}
+
+int axe_layout_eval(const axe_layout_t* L, int32_t rank, const int64_t* shape, int64_t n, const int64_t* d_flat_idx,
+                    int64_t* d_out, void* stream) {
+  static thread_local LastPlan<EvalDesc> last;
+  PlanKey key;
+  bool keyed = L && shape && rank >= 1 && rank <= AXE_MAX_RANK;
+  if (keyed) {
+    key.put(rank);
+    for (int i = 0; i < rank; ++i) key.put(shape[i]);
+    keyed = key_of_layout(*L, key);
+  }
+  EvalDesc fresh;
+  const bool kept = keyed && last.holds(key);
+  if (!kept) {
+    if (int rc = plan_layout_eval(L, rank, shape, fresh)) return rc;
+    if (keyed) last.keep(key, fresh);
+  }
+  const EvalDesc& d = kept ? last.plan : fresh;
+  if (n < 0) {
+    set_error("axe_layout_eval: n = %lld is negative", (long long)n);
+    return AXE_EINVAL;
+  }
+  if (!d_flat_idx && n > d.E_D) {
+    set_error("axe_layout_eval: n = %lld exceeds E_D = %lld with implicit indices", (long long)n, (long long)d.E_D);
+    return AXE_ERANGE;
+  }
+  if (n > 0 && !d_out) {
+    set_error("axe_layout_eval: d_out is NULL");
+    return AXE_EINVAL;
+  }
+  int64_t per, total;
+  if (__builtin_mul_overflow(d.E_R, (int64_t)d.n_axes, &per) || __builtin_mul_overflow(per, n, &total) ||
+      total > (INT64_MAX >> 4)) {
+    set_error("axe_layout_eval: output size overflows");
+    return AXE_ERANGE;
+  }
+  if (n == 0) return AXE_OK;
   hipError_t e = launch_layout_eval(d, n, d_flat_idx, d_out, (hipStream_t)stream);
   return e == hipSuccess ? AXE_OK : hip_fail(e, "axe_layout_eval");
 }
@@ -111,9 +210,8 @@ int axe_layout_eval(const axe_layout_t* L, int32_t rank, const int64_t* shape, i
 // the innermost unit-stride run common to both sides becomes the access width (up to 16 bytes);
 // the remaining digits are ordered so that neighbouring threads touch neighbouring memory on at
 // least one side, and a per-thread unroll digit is taken along the other side's fastest digit.
-int axe_relayout(const axe_layout_t* src, const axe_layout_t* dst, int32_t rank, const int64_t* shape,
-                 int32_t elem_bytes, int32_t mem_axis, const void* d_src, int64_t src_elems, void* d_dst,
-                 int64_t dst_elems, void* stream) {
+static int plan_relayout(const axe_layout_t* src, const axe_layout_t* dst, int32_t rank, const int64_t* shape, int32_t elem_bytes,
+                         int32_t mem_axis, const void* d_src, int64_t src_elems, const void* d_dst, int64_t dst_elems, RelayoutCall& call) {
   HLayout hs, hd;
   if (int rc = load_layout(src, hs, "axe_relayout(src)")) return rc;
   if (int rc = load_layout(dst, hd, "axe_relayout(dst)")) return rc;
@@ -132,27 +230,11 @@ int axe_relayout(const axe_layout_t* src, const axe_layout_t* dst, int32_t rank,
     set_error("axe_relayout(dst): two logical elements may share an address (strides do not nest)");
     return AXE_EALIAS;
   }
-  if (!d_src || !d_dst) {
-    set_error("axe_relayout: NULL device pointer");
-    return AXE_EINVAL;
-  }
-  if (((uintptr_t)d_src | (uintptr_t)d_dst) % (uintptr_t)elem_bytes) {
-    set_error("axe_relayout: buffers are not aligned to the element size");
-    return AXE_EINVAL;
-  }
-  {
-    const char* s0 = (const char*)d_src;
-    const char* d0 = (const char*)d_dst;
-    if (s0 < d0 + dst_elems * elem_bytes && d0 < s0 + src_elems * elem_bytes) {
-      set_error("axe_relayout: source and destination buffers overlap");
-      return AXE_EINVAL;
-    }
-  }
+  if (int rc = check_relayout_pointers(elem_bytes, d_src, src_elems, d_dst, dst_elems)) return rc;
   if (md.E_R > (int64_t(1) << 20)) {
     set_error("axe_relayout(dst): %lld replicas", (long long)md.E_R);
     return AXE_EUNSUPPORTED;
   }
-  hipStream_t st = (hipStream_t)stream;
   const int64_t E = hs.E_D;
 
   std::vector<JointIter> J;
@@ -172,8 +254,8 @@ int axe_relayout(const axe_layout_t* src, const axe_layout_t* dst, int32_t rank,
     for (int k = 0; k < p.n_r; ++k) p.rext[k] = (int32_t)md.R[k].e, p.rstr[k] = md.R[k].s;
     p.E_R = md.E_R;
     p.total = E;
-    hipError_t e = launch_relayout_generic(p, elem_bytes, d_src, d_dst, st);
-    return e == hipSuccess ? AXE_OK : hip_fail(e, "axe_relayout");
+    call.kernel = RelayoutCall::kGeneric, call.unit = elem_bytes, call.generic = p;
+    return AXE_OK;
   }
 
   // --- transposing case: no digit is contiguous on both sides, but one is contiguous in the source
@@ -264,8 +346,8 @@ int axe_relayout(const axe_layout_t* src, const axe_layout_t* dst, int32_t rank,
         const int nt = env_int("AXE_RELAYOUT_NT", -1);
         p.streaming = nt >= 0 ? nt : (2 * E * (int64_t)elem_bytes >= (int64_t(128) << 20));
         p.diag = env_int("AXE_TRANSPOSE_DIAG", 1);
-        hipError_t e = launch_relayout_transpose(p, elem_bytes, d_src, d_dst, st);
-        return e == hipSuccess ? AXE_OK : hip_fail(e, "axe_relayout");
+        call.kernel = RelayoutCall::kTranspose, call.unit = elem_bytes, call.transpose = p;
+        return AXE_OK;
       }
     }
   }
@@ -317,8 +399,8 @@ int axe_relayout(const axe_layout_t* src, const axe_layout_t* dst, int32_t rank,
     if (fits && rows < (uint64_t(1) << 31) && slots < (uint64_t(1) << 31) && rows * slots < (uint64_t(1) << 34)) {
       p.n = (int)outer.size();
       p.rows = (uint32_t)rows, p.slots_per_row = (uint32_t)slots, p.slots = rows * slots;
-      hipError_t e = launch_relayout_rows(p, elem_bytes, d_src, d_dst, st);
-      return e == hipSuccess ? AXE_OK : hip_fail(e, "axe_relayout");
+      call.kernel = RelayoutCall::kRows, call.unit = elem_bytes, call.rows = p;
+      return AXE_OK;
     }
   }
   if (v > 1) {
@@ -410,8 +492,32 @@ int axe_relayout(const axe_layout_t* src, const axe_layout_t* dst, int32_t rank,
   // non-temporal accesses once the data cannot stay in the 256 MiB last-level cache anyway
   const int nt = env_int("AXE_RELAYOUT_NT", -1);
   p.streaming = nt >= 0 ? nt : (2 * E * (int64_t)elem_bytes >= (int64_t(128) << 20));
-  hipError_t e = launch_relayout_joint(p, unit, d_src, d_dst, st);
-  return e == hipSuccess ? AXE_OK : hip_fail(e, "axe_relayout");
+  call.kernel = RelayoutCall::kJoint, call.unit = unit, call.joint = p;
+  return AXE_OK;
+}
+
+int axe_relayout(const axe_layout_t* src, const axe_layout_t* dst, int32_t rank, const int64_t* shape,
+                 int32_t elem_bytes, int32_t mem_axis, const void* d_src, int64_t src_elems, void* d_dst,
+                 int64_t dst_elems, void* stream) {
+  static thread_local LastPlan<RelayoutCall> last;
+  PlanKey key;
+  bool keyed = src && dst && shape && rank >= 1 && rank <= AXE_MAX_RANK && !knobs_set();
+  if (keyed) {
+    key.put(rank);
+    for (int i = 0; i < rank; ++i) key.put(shape[i]);
+    key.put(elem_bytes), key.put(mem_axis), key.put(src_elems), key.put(dst_elems);
+    // (the plans look at the buffers' place in a chunk, and at the destination's in a 128-byte line)
+    key.put((int64_t)((uintptr_t)d_src & 15)), key.put((int64_t)((uintptr_t)d_dst & 127));
+    keyed = key_of_layout(*src, key) && key_of_layout(*dst, key);
+  }
+  if (keyed && last.holds(key)) {
+    if (int rc = check_relayout_pointers(elem_bytes, d_src, src_elems, d_dst, dst_elems)) return rc;
+    return launch_relayout(last.plan, d_src, d_dst, (hipStream_t)stream);
+  }
+  RelayoutCall call;
+  if (int rc = plan_relayout(src, dst, rank, shape, elem_bytes, mem_axis, d_src, src_elems, d_dst, dst_elems, call)) return rc;
+  if (keyed) last.keep(key, call);
+  return launch_relayout(call, d_src, d_dst, (hipStream_t)stream);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -453,26 +559,6 @@ int bind_gemm_pointers(const axe_gemm_desc_t* g, const void* dA, const void* dB,
   return AXE_OK;
 }
 
-// The contents of a descriptor as a flat run of words: what a plan depends on, device pointers aside (of the scale
-// pointers only whether they are given and their alignment matter).  False when the descriptor is malformed in a way
-// that makes its arrays unreadable: the planner then reports the error.
-constexpr int kKeyWords = 24 + 3 * (12 + 3 * (AXE_MAX_D + AXE_MAX_R) + AXE_MAX_AXES);
-struct PlanKey {
-  int64_t w[kKeyWords];
-  int n = 0;
-  void put(int64_t v) { w[n++] = v; }
-};
-bool key_of_layout(const axe_layout_t& L, PlanKey& k) {
-  if (L.n_axes < 1 || L.n_axes > AXE_MAX_AXES || L.n_d < 1 || L.n_d > AXE_MAX_D || L.n_r < 0 || L.n_r > AXE_MAX_R || !L.d ||
-      (L.n_r && !L.r))
-    return false;
-  k.put(L.n_axes), k.put(L.n_d), k.put(L.n_r);
-  for (int i = 0; i < L.n_d; ++i) k.put(L.d[i].extent), k.put(L.d[i].stride), k.put(L.d[i].axis);
-  for (int i = 0; i < L.n_r; ++i) k.put(L.r[i].extent), k.put(L.r[i].stride), k.put(L.r[i].axis);
-  for (int a = 0; a < L.n_axes; ++a) k.put(L.offset ? L.offset[a] : 0);
-  k.put(L.swz_axis), k.put(L.swz_bits), k.put(L.swz_base), k.put(L.swz_shift);
-  return true;
-}
 bool key_of_gemm(const axe_gemm_desc_t* g, PlanKey& k) {
   k.n = 0;
   k.put(g->M), k.put(g->N), k.put(g->K), k.put(g->in_dtype), k.put(g->out_dtype), k.put(g->mem_axis);
