@@ -1225,7 +1225,9 @@ int axe_gemm_grouped_pair(const axe_gemm_grouped_desc_t* g1, const axe_gemm_grou
                                                      env_int("AXE_GROUPED_PAIR_TEST_NEVER", 0) ? 1 : 0, st);
     return e == hipSuccess ? AXE_OK : hip_fail(e, "axe_gemm_grouped_pair");
   }
-  if (d_sync)                                                      // the status word answers for this call too
+  // the status word answers for this call too: the streaming kernel clears it, or a small kernel
+  if (d_sync && grouped_goes_to_stream(g1, a1)) a1.clear = d_sync + g1->M;
+  else if (d_sync)
     if (hipError_t e = launch_pair_sync_clear(d_sync + g1->M, 1, st); e != hipSuccess) return hip_fail(e, "axe_gemm_grouped_pair");
   for (int i = 0; i < 2; ++i) {                                    // one after the other, on the stream
     const axe_gemm_grouped_desc_t* g = i ? g2 : g1;

@@ -83,6 +83,8 @@ __global__ __launch_bounds__(256) void gemm_grouped_stream_kernel(GemmArgs g) {
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int M = (int)g.M;
+  // (a pair's status word: a launch of its own for one word took 2 of a pair's 20 us at one token)
+  if (g.clear && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *g.clear = 0;
   int e = blockIdx.y;                                              // group
   if (g.compact_groups) {
     // fewer rows than groups (the first tokens of a decode batch): at most M groups have rows, and the launch
