@@ -248,3 +248,55 @@ def test_grouped_fast_build_equals_checking_build_and_every_replay():
                 B.axe_gemm_grouped(d, dA, dB, out[-1], dR)
         torch.cuda.synchronize()
     assert all(torch.equal(out[0], o) for o in out[1:])
+
+
+# ---- what the counted waits rely on, on the ISA hipcc emits
+def kernels_of(source, out):
+    import re
+    import subprocess
+    from paper_2601_19092_amd import build as BLD
+    subprocess.check_call([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), *BLD.FLAGS, "-I", BLD.CSRC, "-S", "--cuda-device-only",
+                           os.path.join(BLD.CSRC, source), "-o", str(out)], stderr=subprocess.DEVNULL)
+    for m in re.finditer(r"^_ZN3axe5tiles17gemm_tiles_kernelI((?:Li\d+E)+)\w*:[^\n]*\n(.*?)\n\ts_endpgm", open(out).read(), re.S | re.M):
+        yield [int(x) for x in re.findall(r"Li(\d+)E", m.group(1))], m.group(2).split("\n")
+
+
+@pytest.mark.parametrize("source", ["kernels_gemm_tiles_16bit.hip", "kernels_gemm_tiles_fp8.hip", "kernels_gemm_tiles_grouped.hip"])
+def test_loads_between_counted_waits(source, tmp_path):
+    """In every K loop: no spills, each stage's loads between its counted wait and the next, the scale loads of a trip after its
+    first wait and before that stage's loads, and no wait of the compiler's own that is stricter than the counted ones."""
+    import re
+    seen = 0
+    for (dt, sc, tm, tn, wm, wn, wk, nst, grp), lines in kernels_of(source, tmp_path / "k.s"):
+        assert not [x for x in lines if "scratch_" in x], (dt, sc, tm, tn, grp)
+        loads = tm // 8 // (wm * wn) + tn // 8 // (wm * wn)
+        scales = (tm // wm // 16 + (2 if grp == 2 else 1)) if sc else 0
+        base = (nst - 2) * loads
+        labels = {x.split(":")[0]: i for i, x in enumerate(lines) if re.match(r"^\.LBB\d+_\d+:", x)}
+        loops = [(labels[m.group(1)], i) for i, x in enumerate(lines) for m in [re.match(r"\ts_cbranch_\w+ (\.LBB\d+_\d+)", x)]
+                 if m and labels.get(m.group(1), i) < i]
+        loops = [a for a in loops if any("v_mfma" in x for x in lines[a[0]:a[1]])]
+        inner = [a for a in loops if not any(b != a and a[0] <= b[0] and b[1] <= a[1] for b in loops)]
+        assert inner
+        for a, b in inner:
+            tokens = []
+            for x in lines[a:b]:
+                if m := re.match(r"\ts_waitcnt vmcnt\((\d+)\) lgkmcnt\(0\)$", x):
+                    tokens.append(int(m.group(1)))
+                elif re.match(r"\tbuffer_load_dwordx4 .* lds$", x):
+                    tokens.append("L")
+                elif re.match(r"\tbuffer_load_(dword|ubyte) ", x):
+                    tokens.append("S")
+                elif m := re.search(r"vmcnt\((\d+)\)", x):
+                    assert int(m.group(1)) >= base, (dt, sc, tm, tn, grp, x)
+            waits = [t for t in tokens if isinstance(t, int)]
+            text = "".join("W" if isinstance(t, int) else t for t in tokens)
+            u = 4 if sc else 2
+            assert waits == [base + (scales if 1 <= k <= nst - 2 else 0) for k in range(u)], (dt, sc, tm, tn, grp, waits)
+            # (grouped loops are rotated by the branch of a half trip: their text may begin inside a stage)
+            if grp == 0:
+                assert text == "W" + "S" * scales + "L" * loads + ("W" + "L" * loads) * (u - 1), (dt, sc, tm, tn, text)
+            else:
+                assert text.count("L") == u * loads and text.count("S") == scales and "LS" not in text, (sc, tm, tn, text)
+            seen += 1
+    assert seen >= (2 if "grouped" in source else 18)
