@@ -304,13 +304,10 @@ static int plan_relayout(const axe_layout_t* src, const axe_layout_t* dst, int32
         if ((int)k != kD && J[k].e > 1 && !lines(J[k].ds)) on_lines = false;
       for (const HIter& it : md.R)
         if (!lines(it.s)) skew_ok = false;                         // (a row's phase is that of all its replicas)
-      p.elementwise = chunks ? 0 : (swizzled ? 1 : 2);
-      if (skew_ok && !on_lines && 2 * E * (int64_t)elem_bytes >= (int64_t(112) << 20)) p.elementwise = 3;
+      int variant = chunks ? 0 : (swizzled ? 1 : 2);
+      if (skew_ok && !on_lines && 2 * E * (int64_t)elem_bytes >= (int64_t(112) << 20)) variant = 3;
       const int asked = env_int("AXE_TRANSPOSE_VARIANT", -1);
-      if (asked == 1 || (asked == 2 && !swizzled) || (asked == 3 && skew_ok)) p.elementwise = asked;
-      const int64_t T = p.elementwise == 1 ? 64 : transpose_tile_edge(elem_bytes);
-      const int64_t TS = p.elementwise == 3 ? skew_tile_s(elem_bytes) : T;
-      const int64_t TD = p.elementwise == 3 ? skew_tile_d(elem_bytes) : T;
+      if (asked == 1 || (asked == 2 && !swizzled) || (asked == 3 && skew_ok)) variant = asked;
       p.s_swz = ms.swz, p.d_swz = md.swz;
       p.n_r = (int)md.R.size();
       for (int k = 0; k < p.n_r; ++k) p.rext[k] = (int32_t)md.R[k].e, p.rstr[k] = md.R[k].s;
@@ -318,10 +315,6 @@ static int plan_relayout(const axe_layout_t* src, const axe_layout_t* dst, int32
       p.eS = J[kS].e, p.dS = J[kS].ds;
       p.eD = J[kD].e, p.sD = J[kD].ss;
       p.s_off = ms.off, p.d_off = md.off;
-      // (skewed tiles: a row's last one ends up to a line short of its nominal end)
-      const uint64_t tiles_s = (uint64_t)((p.eS + TS - 1) / TS);
-      const uint64_t tiles_d = (uint64_t)((p.eD + (p.elementwise == 3 ? 128 / elem_bytes - 1 : 0) + TD - 1) / TD);
-      uint64_t blocks = tiles_s * tiles_d;
       // outer digits, smallest strides first so that neighbouring workgroups stay close in memory
       std::vector<JointIter> outer;
       for (size_t k = 0; k < J.size(); ++k)
@@ -330,19 +323,37 @@ static int plan_relayout(const axe_layout_t* src, const axe_layout_t* dst, int32
       std::stable_sort(outer.begin(), outer.end(), [&](const JointIter& a, const JointIter& b) {
         return std::min(mag(a.ss), mag(a.ds)) < std::min(mag(b.ss), mag(b.ds));
       });
-      bool fits = tiles_s < (uint64_t(1) << 31) && tiles_d < (uint64_t(1) << 31) && outer.size() <= (size_t)kMaxJoint;
+      bool fits = outer.size() <= (size_t)kMaxJoint;
+      uint64_t matrices = 1;
       for (size_t k = 0; k < outer.size() && fits; ++k) {
-        fits = outer[k].e < (int64_t(1) << 31) && blocks < (uint64_t(1) << 31);
+        fits = outer[k].e < (int64_t(1) << 31) && matrices <= kMaxBlocks256;
         p.ext[k] = (uint32_t)outer[k].e;
         p.ss[k] = outer[k].ss;
         p.ds[k] = outer[k].ds;
-        blocks *= (uint64_t)outer[k].e;
+        matrices *= (uint64_t)outer[k].e;
       }
-      if (fits && blocks < (uint64_t(1) << 31)) {
+      // Tiles and workgroups of a variant; false: more than one launch holds.
+      auto tiled = [&](int variant) -> bool {
+        const int64_t T = variant == 1 ? 64 : transpose_tile_edge(elem_bytes);
+        const int64_t TS = variant == 3 ? skew_tile_s(elem_bytes) : T, TD = variant == 3 ? skew_tile_d(elem_bytes) : T;
+        // (skewed tiles: a row's last one ends up to a line short of its nominal end)
+        const uint64_t tiles_s = (uint64_t)((p.eS + TS - 1) / TS);
+        const uint64_t tiles_d = (uint64_t)((p.eD + (variant == 3 ? 128 / elem_bytes - 1 : 0) + TD - 1) / TD);
+        if (tiles_s > kMaxBlocks256 || tiles_d > kMaxBlocks256 || matrices > kMaxBlocks256 || tiles_s * tiles_d > kMaxBlocks256) return false;
+        // chunks that start at any element: the grid padded to whole rounds of the 8 XCDs along the source, so that the tiles that
+        // complete a line meet in one L2, where that adds at most an eighth of workgroups that only return (us, padded / not: 3001 x 7000 bf16
+        // 24.3 / 28.8, bytes 8191 x 8193 42 / 56; but 300 x 500 x 501, 4 tiles padded to 8, 123 / 94, and 60000 x 66 x 66, 1 to 8, 1996 / 270)
+        const uint64_t padded = (tiles_s + 7) & ~uint64_t(7);
+        uint64_t grid_s = tiles_s;
+        if (variant == 2 && (padded - tiles_s) * 8 <= tiles_s && padded * tiles_d * matrices <= kMaxBlocks256) grid_s = padded;
+        if (grid_s * tiles_d * matrices > kMaxBlocks256) return false;
+        p.elementwise = variant;
+        p.tiles_s = (uint32_t)tiles_s, p.tiles_d = (uint32_t)tiles_d, p.grid_s = (uint32_t)grid_s;
+        p.blocks = grid_s * tiles_d * matrices;
+        return true;
+      };
+      if (fits && (tiled(variant) || (variant == 3 && tiled(chunks ? 0 : 2)))) {
         p.n = (int)outer.size();
-        p.tiles_s = (uint32_t)tiles_s;
-        p.tiles_d = (uint32_t)tiles_d;
-        p.blocks = blocks;
         const int nt = env_int("AXE_RELAYOUT_NT", -1);
         p.streaming = nt >= 0 ? nt : (2 * E * (int64_t)elem_bytes >= (int64_t(128) << 20));
         p.diag = env_int("AXE_TRANSPOSE_DIAG", 1);

@@ -17,6 +17,9 @@ static int g_violations = 0;
 static int g_transposes = 0;      // launches of the transposing relayout since the buffers were declared
 static int g_rows = 0;            // relayouts of rows that start anywhere
 static int g_transposes_elem = 0; // ... of which element by element (not in 16-byte chunks)
+static int g_plan_only = 0;       // 1: a relayout is planned but moves nothing (the buffers need not exist)
+static uint64_t g_workgroups = 0; // of the last relayout by tiles or by rows
+static int g_variant = -1;        // TransposePlan::elementwise of the last transposing relayout
 
 static int64_t swz_apply(int64_t x, Swz z) { return x ^ (((x >> z.shift) & (int64_t)z.mask) << z.base); }
 
@@ -61,6 +64,7 @@ static bool move(const char* src, char* dst, int64_t s, int64_t d, int unit) {
 }
 
 hipError_t launch_relayout_joint(const RelayoutPlan& p, int unit, const void* src_, void* dst_, hipStream_t) {
+  if (g_plan_only) return hipSuccess;
   const char* src = (const char*)src_;
   char* dst = (char*)dst_;
   for (uint64_t w0 = 0; w0 < p.threads; ++w0) {
@@ -98,6 +102,9 @@ hipError_t launch_relayout_rows(const RowPlan& p, int eb, const void* src_, void
   const char* src = (const char*)src_;
   char* dst = (char*)dst_;
   ++g_rows;
+  g_workgroups = (p.slots + 15) / 16;
+  if (g_workgroups > kMaxBlocks256) return hipErrorInvalidValue;
+  if (g_plan_only) return hipSuccess;
   for (uint64_t t = 0; t < p.slots; ++t) {
     uint64_t row = t / p.slots_per_row;
     const int64_t seg = (int64_t)(t - row * p.slots_per_row), bytes = p.run * eb;
@@ -139,6 +146,9 @@ hipError_t launch_relayout_transpose(const TransposePlan& p, int eb, const void*
     }
   };
   if (p.elementwise) ++g_transposes_elem;
+  g_workgroups = p.blocks, g_variant = p.elementwise;
+  if (p.blocks > kMaxBlocks256) return hipErrorInvalidValue;
+  if (g_plan_only) return hipSuccess;
   if (p.elementwise == 1) {                                      // 64 x 64 tiles, element by element
     const int64_t T = 64;
     for (uint64_t blk = 0; blk < p.blocks; ++blk) {
@@ -216,8 +226,9 @@ hipError_t launch_relayout_transpose(const TransposePlan& p, int eb, const void*
   const int64_t T = transpose_tile_edge(eb), CE = 16 / eb, CPR = T / CE;
   for (uint64_t blk = 0; blk < p.blocks; ++blk) {
     uint64_t b = blk;
-    const int64_t ts = (int64_t)(b % p.tiles_s);
-    b /= p.tiles_s;
+    const int64_t ts = (int64_t)(b % p.grid_s);
+    b /= p.grid_s;
+    if (ts >= (int64_t)p.tiles_s) continue;                        // (the grid may be padded along the source)
     int64_t td = (int64_t)(b % p.tiles_d);
     b /= p.tiles_d;
     if (p.diag > 0) td = (td + ts / p.diag) % p.tiles_d;
@@ -274,6 +285,7 @@ hipError_t launch_relayout_transpose(const TransposePlan& p, int eb, const void*
 }
 
 hipError_t launch_relayout_generic(const GenericRelayoutPlan& p, int unit, const void* src_, void* dst_, hipStream_t) {
+  if (g_plan_only) return hipSuccess;
   const char* src = (const char*)src_;
   char* dst = (char*)dst_;
   for (int64_t x = 0; x < p.total; ++x) {
@@ -326,6 +338,9 @@ extern "C" void axe_hostcheck_set_buffers(int64_t src_bytes, int64_t dst_bytes) 
   axe::g_transposes_elem = 0;
   axe::g_rows = 0;
 }
+extern "C" void axe_hostcheck_plan_only(int on) { axe::g_plan_only = on; }
+extern "C" int64_t axe_hostcheck_workgroups(void) { return (int64_t)axe::g_workgroups; }
+extern "C" int axe_hostcheck_transpose_variant(void) { return axe::g_variant; }
 extern "C" int axe_hostcheck_violations(void) { return axe::g_violations; }
 extern "C" int axe_hostcheck_rows(void) { return axe::g_rows; }
 extern "C" int axe_hostcheck_transposes(void) { return axe::g_transposes; }

@@ -90,7 +90,8 @@ struct TransposePlan {
   int64_t eS, eD, sD, dS;
   int64_t s_off, d_off;
   uint32_t tiles_s, tiles_d;       // tiles along the source-fast and the destination-fast digit
-  uint64_t blocks;                 // tiles_s * tiles_d * product of ext[]
+  uint32_t grid_s;                 // workgroups along the source: tiles_s, or more of which the last ones only return
+  uint64_t blocks;                 // workgroups launched: grid_s * tiles_d * product of ext[]
   int32_t streaming;               // 1: non-temporal loads and stores
   int32_t diag;                    // g > 0: tiles are walked diagonally, td = (row + ts / g) mod tiles_d; 0: row by row
   Swz s_swz, d_swz;                // swizzle stages of the two sides (mask 0: none), applied to an access's first element

@@ -7,6 +7,9 @@
 
 namespace axe {
 
+// HIP refuses a launch of 2^32 threads or more: workgroups of 256 that one launch holds
+constexpr uint64_t kMaxBlocks256 = (uint64_t(1) << 24) - 1;
+
 hipError_t launch_layout_eval(const EvalDesc& d, int64_t n, const int64_t* idx, int64_t* out, hipStream_t s);
 hipError_t launch_relayout_joint(const RelayoutPlan& p, int unit_bytes, const void* src, void* dst, hipStream_t s);
 // elem_bytes 1, 2, 4 or 8; rows of at least 16 bytes

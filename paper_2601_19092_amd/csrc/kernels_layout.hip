@@ -471,8 +471,8 @@ hipError_t launch_relayout_rows(const RowPlan& p, int elem_bytes, const void* sr
 // ANY: the same tiles where extents, strides, offsets or buffers are no multiples of a chunk (odd matrix sizes): the 16-byte
 // accesses start at any element (global memory takes them), a chunk that sticks out of the tensor is loaded from the last
 // place inside it and shifted, and stored element by element.  The rows of neighbouring tiles then share lines of the
-// destination: ordinary stores (non-temporal ones do not combine), and the grid is padded to whole rounds of the 8 XCDs
-// along the source, so that the tiles that complete a line meet in one XCD's L2.  us, element by element -> now, rotating over
+// destination: ordinary stores (non-temporal ones do not combine), and the grid may be padded to whole rounds of the 8 XCDs
+// along the source (grid_s), so that the tiles that complete a line meet in one XCD's L2.  us, element by element -> now, rotating over
 // three pairs of buffers: bf16 7000 x 3001 27 -> 19 (4.4 TB/s), 4095 x 4097 20.6 -> 15.5, bytes 8191 x 8193 70 -> 40, bf16 105 -> 83 (a band of
 // tiles along the destination per XCD instead of the padding: 93).
 template <int EB, bool NT, bool ANY>
@@ -498,10 +498,9 @@ __global__ __launch_bounds__(256) void relayout_transpose_kernel(TransposePlan p
 
   // workgroup -> (tile along S, tile along D, outer digits)
   uint64_t b = blockIdx.x;
-  const uint32_t grid_s = ANY ? (p.tiles_s + 7) & ~7u : p.tiles_s;
-  const uint32_t ts = (uint32_t)(b % grid_s);
+  const uint32_t ts = (uint32_t)(b % p.grid_s);
   if (ANY && ts >= p.tiles_s) return;
-  b /= grid_s;
+  b /= p.grid_s;
   uint32_t td = (uint32_t)(b % p.tiles_d);
   b /= p.tiles_d;
   // Row by row (ts fastest, td fixed for tiles_s workgroups in a row) the workgroups running at one time read
@@ -773,8 +772,7 @@ __global__ __launch_bounds__(256) void relayout_transpose_elem_kernel(TransposeP
 template <int EB>
 static hipError_t launch_transpose_e(const TransposePlan& p, const void* src, void* dst, hipStream_t s) {
   if (p.elementwise) {
-    const uint64_t blocks = p.blocks / p.tiles_s * ((p.tiles_s + 7) & ~7u);
-    hipLaunchKernelGGL((relayout_transpose_kernel<EB, false, true>), dim3((unsigned)blocks), dim3(256), 0, s, p, (const uint8_t*)src,
+    hipLaunchKernelGGL((relayout_transpose_kernel<EB, false, true>), dim3((unsigned)p.blocks), dim3(256), 0, s, p, (const uint8_t*)src,
                        (uint8_t*)dst);
   } else if (p.streaming)
     hipLaunchKernelGGL((relayout_transpose_kernel<EB, true, false>), dim3((unsigned)p.blocks), dim3(256), 0, s, p, (const uint8_t*)src,
@@ -787,7 +785,7 @@ static hipError_t launch_transpose_e(const TransposePlan& p, const void* src, vo
 
 hipError_t launch_relayout_transpose(const TransposePlan& p, int elem_bytes, const void* src, void* dst, hipStream_t s) {
   if (p.blocks == 0) return hipSuccess;
-  if (p.blocks > 0x7fffffffull) return hipErrorInvalidValue;
+  if (p.blocks > kMaxBlocks256) return hipErrorInvalidValue;
   if (p.elementwise == 3) {
     const dim3 grid((unsigned)p.blocks), block(256);
     const uint8_t* from = (const uint8_t*)src;

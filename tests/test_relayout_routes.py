@@ -1,0 +1,66 @@
+"""Which kernel a relayout goes to, and in how many workgroups, for copies too large to be made on the host: the plan alone is
+made (the stand-ins of libaxe_hostcheck.so move nothing)."""
+import ctypes as C
+
+import pytest
+
+from paper_2601_19092_amd import binding as B
+from paper_2601_19092_amd import workloads as W
+from test_host_plans import hc                                 # noqa: F401
+
+LIMIT = 1 << 32                                                # HIP refuses a launch of that many threads
+
+
+@pytest.fixture
+def plan(hc):                                                  # noqa: F811
+    """(rc, variant of the transposing kernel or None, "rows" / "tiles" / "nest", workgroups) of a relayout."""
+    hc.axe_hostcheck_workgroups.restype = C.c_int64
+
+    def run(shape, s, d, eb, src=1 << 12, dst=1 << 45):
+        ls, ld = B.Layout(s), B.Layout(d)
+        hc.axe_hostcheck_set_buffers(1 << 44, 1 << 44)
+        hc.axe_hostcheck_plan_only(1)
+        try:
+            rc = hc.axe_relayout(C.byref(ls.c), C.byref(ld.c), len(shape), (C.c_int64 * len(shape))(*shape), eb, 0, src, (1 << 44) // eb,
+                                 dst, (1 << 44) // eb, None)
+        finally:
+            hc.axe_hostcheck_plan_only(0)
+        if hc.axe_hostcheck_transposes():
+            return rc, hc.axe_hostcheck_transpose_variant(), "tiles", hc.axe_hostcheck_workgroups()
+        return rc, None, "rows" if hc.axe_hostcheck_rows() else "nest", hc.axe_hostcheck_workgroups()
+    return run
+
+
+def batched(b, r, c, src_pad=0, dst_pad=0):
+    """b matrices of r x c from row-major (rows src_pad apart) to column-major."""
+    return ((b, r, c), W.spec([(b, r * (c + src_pad), "m"), (r, c + src_pad, "m"), (c, 1, "m")]),
+            W.spec([(b, (r + dst_pad) * c, "m"), (r, 1, "m"), (c, r + dst_pad, "m")]))
+
+
+@pytest.mark.parametrize("eb", [1, 2, 4, 8])
+@pytest.mark.parametrize("b", [1 << 18, (1 << 21) - 1, 1 << 21, (1 << 23) + 5, (1 << 24) - 1])
+def test_many_small_matrices_fit_one_launch(plan, b, eb):
+    """Up to 2^24 - 1 matrices of one tile each: no grid padding may take the launch past what HIP accepts."""
+    n = max(64 // eb, 8) + 1
+    for shape, s, d in (batched(b, 64, n, src_pad=1), batched(b, 64, n)):
+        if n > 64:
+            shape, s, d = batched(b // 2, 64, n)               # (two tiles of 64)
+        rc, _, how, wgs = plan(shape, s, d, eb)
+        assert rc == B.AXE_OK and how == "tiles" and wgs * 256 < LIMIT
+
+
+def test_more_than_one_launch_of_tiles_goes_to_the_loop_nest(plan):
+    rc, _, how, _ = plan(*batched(1 << 24, 8, 9), 8)           # 2^24 workgroups of 256
+    assert rc == B.AXE_OK and how == "nest"
+    assert plan(*batched(1 << 24, 33, 33), 2)[0] == B.AXE_EUNSUPPORTED   # ... nor does that hold 2^24 x 1089 elements
+
+
+@pytest.mark.parametrize("c", [100, 129, 500, 1000, 1031, 2047, 7001, 8193])
+def test_padding_adds_at_most_an_eighth(plan, c):
+    """The grid is padded along the source only where the empty workgroups are few."""
+    for b, r in ((1, 4001), (3, 400), (40, 129)):
+        rc, v, how, wgs = plan(*batched(b, r, c), 2)
+        assert rc == B.AXE_OK and how == "tiles"
+        if v == 2:
+            tiles = b * -(-r // 128) * -(-c // 128)
+            assert tiles <= wgs and 8 * wgs <= 9 * tiles
