@@ -407,7 +407,7 @@ static int plan_relayout(const axe_layout_t* src, const axe_layout_t* dst, int32
     }
     // chunks of a row: up to one more than its length when it starts inside one
     const uint64_t per_row = ((uint64_t)p.run * elem_bytes + 15 + 15) / 16, slots = (per_row + 63) / 64;
-    if (fits && rows < (uint64_t(1) << 31) && slots < (uint64_t(1) << 31) && rows * slots < (uint64_t(1) << 34)) {
+    if (fits && rows < (uint64_t(1) << 31) && slots < (uint64_t(1) << 31) && (rows * slots + kRowSlots - 1) / kRowSlots <= kMaxBlocks256) {
       p.n = (int)outer.size();
       p.rows = (uint32_t)rows, p.slots_per_row = (uint32_t)slots, p.slots = rows * slots;
       call.kernel = RelayoutCall::kRows, call.unit = elem_bytes, call.rows = p;

@@ -102,7 +102,7 @@ hipError_t launch_relayout_rows(const RowPlan& p, int eb, const void* src_, void
   const char* src = (const char*)src_;
   char* dst = (char*)dst_;
   ++g_rows;
-  g_workgroups = (p.slots + 15) / 16;
+  g_workgroups = (p.slots + kRowSlots - 1) / kRowSlots;
   if (g_workgroups > kMaxBlocks256) return hipErrorInvalidValue;
   if (g_plan_only) return hipSuccess;
   for (uint64_t t = 0; t < p.slots; ++t) {

@@ -12,7 +12,8 @@ constexpr uint64_t kMaxBlocks256 = (uint64_t(1) << 24) - 1;
 
 hipError_t launch_layout_eval(const EvalDesc& d, int64_t n, const int64_t* idx, int64_t* out, hipStream_t s);
 hipError_t launch_relayout_joint(const RelayoutPlan& p, int unit_bytes, const void* src, void* dst, hipStream_t s);
-// elem_bytes 1, 2, 4 or 8; rows of at least 16 bytes
+// elem_bytes 1, 2, 4 or 8; rows of at least 16 bytes; a workgroup takes kRowSlots slots, and one launch holds kMaxBlocks256 workgroups
+constexpr uint64_t kRowSlots = 16;
 hipError_t launch_relayout_rows(const RowPlan& p, int elem_bytes, const void* src, void* dst, hipStream_t s);
 // elem_bytes 1, 2, 4 or 8; every 16-byte chunk of a tile row must be aligned on both sides
 hipError_t launch_relayout_transpose(const TransposePlan& p, int elem_bytes, const void* src, void* dst, hipStream_t s);

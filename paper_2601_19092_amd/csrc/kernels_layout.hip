@@ -385,7 +385,7 @@ __global__ __launch_bounds__(256) void relayout_rows_kernel(RowPlan p, const uin
   typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
   typedef u32x4 u32x4_any __attribute__((aligned(1)));
   using W = typename Word<EB>::T;
-  constexpr int CE = 16 / EB, U = 4;
+  constexpr int CE = 16 / EB, U = kRowSlots / 4;                   // slots of a wave
   const int lane = threadIdx.x & 63;
   const uint64_t t = ((uint64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * U;
   if (t >= p.slots) return;
@@ -442,8 +442,8 @@ __global__ __launch_bounds__(256) void relayout_rows_kernel(RowPlan p, const uin
 
 hipError_t launch_relayout_rows(const RowPlan& p, int elem_bytes, const void* src, void* dst, hipStream_t s) {
   if (p.slots == 0) return hipSuccess;
-  const uint64_t blocks = (p.slots + 15) / 16;
-  if (blocks > 0x7fffffffull) return hipErrorInvalidValue;
+  const uint64_t blocks = (p.slots + kRowSlots - 1) / kRowSlots;
+  if (blocks > kMaxBlocks256) return hipErrorInvalidValue;
   const dim3 grid((unsigned)blocks), block(256);
   const uint8_t* from = (const uint8_t*)src;
   uint8_t* to = (uint8_t*)dst;
