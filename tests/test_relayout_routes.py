@@ -75,5 +75,5 @@ def test_rows_beyond_one_launch_go_to_the_loop_nest(plan, rows):
     """A slot per row: 2^28 slots are 2^24 workgroups.  What holds more stays with the loop nest, which serves it."""
     rc, _, how, wgs = plan(*padded_rows(rows, 33), 8)          # (264 bytes, in units of 8; a multiple of 4 rows: the nest unrolls them)
     assert rc == B.AXE_OK and (how == "nest" or rows <= 16 * ((1 << 24) - 1) and wgs * 256 < LIMIT)
-    rc, _, how, wgs = plan(*padded_rows(1 << 20, 4095), 1)     # four slots a row
-    assert rc == B.AXE_OK and how == "rows" and wgs == 1 << 18
+    rc, _, how, wgs = plan(*padded_rows(1 << 20, 4095), 1)     # up to 257 chunks, five slots a row
+    assert rc == B.AXE_OK and how == "rows" and wgs == 5 << 16
