@@ -294,9 +294,19 @@ static int plan_relayout(const axe_layout_t* src, const axe_layout_t* dst, int32
       memset(&p, 0, sizeof p);
       // How the tiles move (TransposePlan::elementwise): in aligned chunks (0); element by element (1) where a swizzle is not
       // made of such chunks; else in chunks that start at any element (2), or, with the boundaries of the tiles on the
-      // destination's lines, skewed (3).  The skew pays where the destination goes to memory rather than to the
-      // last-level cache (8191 x 8193 bf16 56 us against 83; 7000 x 3001, 84 MB in all, 23 against 19) and not for single
-      // bytes, whose lines are as long as the tile (8191 x 8193 43 against 40).  AXE_TRANSPOSE_VARIANT asks for one.
+      // destination's lines, skewed (3).  AXE_TRANSPOSE_VARIANT asks for one.
+      //   A tile costs much the same however full it is (variant 1 some 3.7 ns, 2 and 3 some 4 ns for 2-byte elements and 8 and 5 for
+      // 4-byte ones), so of small or narrow matrices the variant with few tiles is the fast one.  us, rotating over 900 MB of buffers:
+      //   2 against 1.  2-byte: 60000 x 66 x 66 270 / 866, 700000 x 33 30 / 37, but 100000 x 33 x 33 399 / 303 and, where memory bounds
+      // both and the tiles of 64 are full, 5000 x 127 x 129 136 / 114.  4-byte, two of whose large tiles fill a compute unit's LDS: 300 x 200 x 65
+      // 11.9 / 14.6, 4785 x 1217 (380 tiles on 256 compute units) 13.3 / 16.5, 8860 x 1380 (770) 28.8 / 30.6, but 4000 x 33 x 1001 392 / 254, 1400 x
+      // 1700 (126) 8.8 / 7.4, 9253 x 1016 (584, just over a round) 23.3 / 20.2, and 9760 x 1406, whose rows start on lines, 29.0 / 25.8.
+      //   3 against 1.  The skew pays where the destination goes to memory rather than to the last-level cache (8191 x 8193 bf16 56 / 105;
+      // 7000 x 3001, 84 MB in all, 28 / 32, and 2 takes 24) and not for single bytes, whose lines are as long as the tile.  2-byte: 2000 x
+      // 200 x 201 98 / 124, but 60000 x 66 x 66 987 / 866; 4-byte: 800 x 200 x 129 41 / 49, but 12000 x 130 x 130 481 / 436; 8-byte: 3001 x 3003
+      // 34 / 41, 20000 x 33 x 65 142 / 222, but 30000 x 50 x 41 350 / 169 (and 2 takes 176).
+      //   3 against aligned chunks (0).  2-byte: 2000 x 200 x 200 93 / 131, but where one tile holds the whole matrix no line is shared: 100000 x 40 x
+      // 40 340 / 280; 4-byte the same 473 / 673, but 20000 x 72 x 72 217 / 189; 8-byte: 100000 x 24 x 24 205 / 281, but 30000 x 56 x 56 394 / 246.
       auto lines = [&](int64_t elems) { return elems * elem_bytes % 128 == 0; };
       const bool swizzled = ms.swz.mask || md.swz.mask;
       bool on_lines = ((uintptr_t)d_dst & 127) == 0 && lines(md.off), skew_ok = !swizzled && elem_bytes > 1;
@@ -304,8 +314,24 @@ static int plan_relayout(const axe_layout_t* src, const axe_layout_t* dst, int32
         if ((int)k != kD && J[k].e > 1 && !lines(J[k].ds)) on_lines = false;
       for (const HIter& it : md.R)
         if (!lines(it.s)) skew_ok = false;                         // (a row's phase is that of all its replicas)
-      int variant = chunks ? 0 : (swizzled ? 1 : 2);
-      if (skew_ok && !on_lines && 2 * E * (int64_t)elem_bytes >= (int64_t(112) << 20)) variant = 3;
+      const int64_t eS = J[kS].e, eD = J[kD].e, bytes = 2 * E * (int64_t)elem_bytes;
+      auto tiles = [](int64_t extent, int64_t edge) { return (extent + edge - 1) / edge; };
+      const int64_t edge = transpose_tile_edge(elem_bytes);
+      const int64_t n1 = tiles(eS, 64) * tiles(eD, 64), n2 = tiles(eS, edge) * tiles(eD, edge);
+      const int64_t n3 = skew_ok ? tiles(eS, skew_tile_s(elem_bytes)) * tiles(eD + 128 / elem_bytes - 1, skew_tile_d(elem_bytes)) : 0;
+      bool any_start = !swizzled, skew = skew_ok && !on_lines && bytes >= (int64_t(112) << 20);
+      if (elem_bytes == 2) {
+        any_start = any_start && 2 * n2 <= n1 && (bytes < (int64_t(64) << 20) || 10 * n2 <= 3 * n1 || 20 * eS * eD <= 13 * 4096 * n1);
+        skew = skew && (chunks ? n2 > 1 && n3 <= 3 * n2 : 4 * n3 <= 3 * n1);
+      } else if (elem_bytes == 4) {
+        const int64_t wgs = E / (eS * eD) * n2, cus = cu_count();
+        any_start = any_start && !on_lines && 7 * n2 <= 2 * n1 && (n2 <= 2 || (4 * wgs >= 5 * cus && (wgs <= 2 * cus || 2 * wgs >= 5 * cus)));
+        skew = skew && (chunks ? n3 <= (n2 > 1 ? 3 * n2 : 1) : 5 * n3 <= 3 * n1);
+      } else if (elem_bytes == 8) {
+        any_start = any_start && (n1 > 2 || bytes < (int64_t(112) << 20));
+        skew = skew && (n1 > 2 ? 2 * n3 <= 5 * n1 : 2 * n3 <= 3 * n1);
+      }
+      int variant = skew ? 3 : (chunks ? 0 : (any_start ? 2 : 1));
       const int asked = env_int("AXE_TRANSPOSE_VARIANT", -1);
       if (asked == 1 || (asked == 2 && !swizzled) || (asked == 3 && skew_ok)) variant = asked;
       p.s_swz = ms.swz, p.d_swz = md.swz;
@@ -352,7 +378,7 @@ static int plan_relayout(const axe_layout_t* src, const axe_layout_t* dst, int32
         p.blocks = grid_s * tiles_d * matrices;
         return true;
       };
-      if (fits && (tiled(variant) || (variant == 3 && tiled(chunks ? 0 : 2)))) {
+      if (fits && (tiled(variant) || (variant == 3 && tiled(chunks ? 0 : (any_start ? 2 : 1))))) {
         p.n = (int)outer.size();
         const int nt = env_int("AXE_RELAYOUT_NT", -1);
         p.streaming = nt >= 0 ? nt : (2 * E * (int64_t)elem_bytes >= (int64_t(128) << 20));

@@ -77,3 +77,26 @@ def test_rows_beyond_one_launch_go_to_the_loop_nest(plan, rows):
     assert rc == B.AXE_OK and (how == "nest" or rows <= 16 * ((1 << 24) - 1) and wgs * 256 < LIMIT)
     rc, _, how, wgs = plan(*padded_rows(1 << 20, 4095), 1)     # up to 257 chunks, five slots a row
     assert rc == B.AXE_OK and how == "rows" and wgs == 5 << 16
+
+
+CHUNKS, ELEMENTS, ANY_START, SKEWED = 0, 1, 2, 3
+
+
+@pytest.mark.parametrize("eb,b,r,c,variant", [
+    # single bytes: chunks from any element at every size
+    (1, 100000, 65, 65, ANY_START), (1, 1000, 65, 65, ANY_START), (1, 1, 8191, 8193, ANY_START),
+    # matrices inside one tile of 64: element by element
+    (2, 1000, 33, 33, ELEMENTS), (2, 100000, 33, 33, ELEMENTS), (2, 20000, 64, 33, ELEMENTS), (4, 1000, 33, 33, ELEMENTS), (4, 200000, 16, 17, ELEMENTS),
+    # more than one: the tiles of 128 are fewer
+    (2, 60000, 66, 66, ANY_START), (2, 1000, 257, 100, ANY_START), (2, 1, 700000, 33, ANY_START), (2, 16, 4097, 77, ANY_START), (2, 5000, 127, 129, ELEMENTS),
+    (4, 1, 100000, 33, ELEMENTS), (4, 300, 200, 65, ANY_START), (4, 2, 531, 700, ELEMENTS), (4, 1, 4785, 1217, ANY_START), (4, 1, 9253, 1016, ELEMENTS),
+    # out to memory: skewed where that does not take many more tiles
+    (2, 1, 8191, 8193, SKEWED), (2, 2000, 200, 201, SKEWED), (2, 4000, 33, 1001, ANY_START), (4, 4000, 1001, 33, SKEWED), (4, 4000, 33, 1001, ELEMENTS),
+    (4, 1, 17, 3000001, ELEMENTS), (4, 1, 3000001, 17, SKEWED), (4, 12000, 130, 130, ELEMENTS), (8, 200000, 9, 8, SKEWED), (8, 30000, 50, 41, ELEMENTS),
+    # aligned chunks, rows off the lines: a matrix inside one tile shares none
+    (2, 1, 8184, 8200, SKEWED), (2, 2000, 200, 200, SKEWED), (2, 30000, 72, 72, CHUNKS), (2, 100000, 40, 40, CHUNKS), (4, 100000, 40, 40, SKEWED),
+    (4, 20000, 72, 72, CHUNKS), (8, 100000, 24, 24, SKEWED), (8, 30000, 56, 56, CHUNKS)])
+def test_variant_of_a_transpose(plan, eb, b, r, c, variant):
+    """The variant that was the fastest, or level with it, when all that serve the copy were timed."""
+    rc, got, how, _ = plan(*batched(b, r, c), eb)
+    assert rc == B.AXE_OK and how == "tiles" and got == variant
