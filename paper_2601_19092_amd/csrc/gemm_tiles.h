@@ -32,9 +32,16 @@
 // 1024 x 3584 x 8192 76 -> 36, bf16 2048 x 4096 x 2048 40 -> 34.
 //
 // Scales (fp8).  A K-tile is one 128-deep scale block: its product is formed alone and folded into the sum on the vector
-// ALU with the row's scale times the column block's (fp32, or E8M0 codes decoded as 2^(code - 127)).
+// ALU with the row's scale times the column block's (fp32, or E8M0 codes built as 2^(their sum - 254)).  Two codes may
+// add up to a power of two that no float holds, where the product is zero or small, so they are scale operands of the matrix
+// instruction.  The same bits as factors give, and as fast in most tiles (us, factors / codes: 512 x 3584 x 8192 25.1 / 25.1, 64 x 3584 x 8192
+// 8.8 / 8.8, but 300 x 1024 x 1024 6.0 / 6.2, 2048 x 4096 x 8192 65.6 / 67.3); the 128 x 128 tile, where they are not (1024 x 3584 x 8192 35.8 / 37.9),
+// multiplies by factors up to the first trip whose codes have none, and runs a second K loop from there (35.1; the largest tile has no
+// registers for two loops, in the others they cost 2 - 9 %).  Adding in place too, 34.2 here, gives sums that are less exact.
 #pragma once
 #include <hip/hip_runtime.h>
+
+#include <type_traits>
 
 #include "device_types.h"
 #include "gemm_common.h"
@@ -221,24 +228,58 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_tiles_kernel(GemmArgs 
       asm volatile("" ::: "memory");
     }
   };
-  auto scale_value = [](uint32_t raw) __attribute__((always_inline)) -> float {
-    return __builtin_bit_cast(float, SC == 2 ? raw << 23 : raw);
-  };
   float sc[NB][SC ? MF : 1][4];
-  auto spread_scales = [&](int s0) __attribute__((always_inline)) {
+  // the scales of a trip as factors; true: E8M0 codes among them whose power of two is no normal number
+  auto spread_scales = [&](int s0) __attribute__((always_inline)) -> bool {
+    bool far = false;
     if constexpr (SC != 0) {
       const bool in = (s0 + fq) * WK + kpart < nk;                 // stages past the last one multiply zeros by zero
 #pragma unroll
       for (int b = 0; b < NB; ++b)
 #pragma unroll
         for (int i = 0; i < MF; ++i) {
-          const uint32_t v = in ? __builtin_bit_cast(uint32_t, scale_value(sa_raw[i]) * scale_value(sb_raw[b])) : 0u;
+          uint32_t v;
+          if constexpr (SC == 2) {
+            v = (sa_raw[i] + sb_raw[b] - 127u) << 23;
+            far = far || (in && sa_raw[i] + sb_raw[b] - 128u >= 254u);
+          } else {
+            v = __builtin_bit_cast(uint32_t, __builtin_bit_cast(float, sa_raw[i]) * __builtin_bit_cast(float, sb_raw[b]));
+          }
+          v = in ? v : 0u;
           const auto h = __builtin_amdgcn_permlane32_swap(v, v, false, false);
           const auto q0 = __builtin_amdgcn_permlane16_swap(h[0], h[0], false, false);
           const auto q2 = __builtin_amdgcn_permlane16_swap(h[1], h[1], false, false);
           sc[b][i][0] = __builtin_bit_cast(float, (uint32_t)q0[0]), sc[b][i][1] = __builtin_bit_cast(float, (uint32_t)q0[1]);
           sc[b][i][2] = __builtin_bit_cast(float, (uint32_t)q2[0]), sc[b][i][3] = __builtin_bit_cast(float, (uint32_t)q2[1]);
         }
+    }
+    return __ballot(far) != 0;
+  };
+  // the same as codes, a byte per stage of the trip (stages past the last one multiply zeros by one)
+  uint32_t sa_codes[SC == 2 ? MF : 1], sb_codes = 0;
+  auto spread_codes = [&](int s0) __attribute__((always_inline)) {
+    if constexpr (SC == 2) {
+      const bool in = (s0 + fq) * WK + kpart < nk;
+      auto codes = [&](uint32_t raw) __attribute__((always_inline)) -> uint32_t {
+        const uint32_t v = (in ? raw : 127u) << (8 * fq);
+        const auto h = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+        const uint32_t w = h[0] | h[1];
+        const auto q = __builtin_amdgcn_permlane16_swap(w, w, false, false);
+        return q[0] | q[1];
+      };
+#pragma unroll
+      for (int i = 0; i < MF; ++i) sa_codes[i] = codes(sa_raw[i]);
+      sb_codes = codes(sb_raw[0]);
+    }
+  };
+  // product of two fragments' K-tile times 2^(code - 127) of either, stage u of the trip
+  auto scaled_product = [&](const i32x8& b, const i32x8& a, uint32_t a_codes, int u) __attribute__((always_inline)) -> f32x4 {
+    const f32x4 z = {0.f, 0.f, 0.f, 0.f};
+    switch (u) {                                                   // (the byte is an immediate of the instruction)
+      case 0: return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(b, a, z, 0, 0, 0, (int)sb_codes, 0, (int)a_codes);
+      case 1: return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(b, a, z, 0, 0, 1, (int)sb_codes, 1, (int)a_codes);
+      case 2: return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(b, a, z, 0, 0, 2, (int)sb_codes, 2, (int)a_codes);
+      default: return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(b, a, z, 0, 0, 3, (int)sb_codes, 3, (int)a_codes);
     }
   };
 
@@ -252,7 +293,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_tiles_kernel(GemmArgs 
 #pragma unroll
     for (int i = 0; i < MF; ++i) f.a[i][0] = read(base + fa_off + i * 16 * kRow + pos0), f.a[i][1] = read(base + fa_off + i * 16 * kRow + pos1);
   };
-  auto multiply = [&](const Frags& f, int u) __attribute__((always_inline)) {
+  auto multiply = [&](const Frags& f, int u, auto far) __attribute__((always_inline)) {
     if constexpr (DT != 2) {
 #pragma unroll
       for (int h = 0; h < 2; ++h)
@@ -270,7 +311,16 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_tiles_kernel(GemmArgs 
       auto wide = [](const i32x4* p) { return i32x8{p[0][0], p[0][1], p[0][2], p[0][3], p[1][0], p[1][1], p[1][2], p[1][3]}; };
 #pragma unroll
       for (int i = 0; i < MF; ++i) {
-        if constexpr (SC != 0) {
+        if constexpr (far) {
+          f32x4 p[NF];
+#pragma unroll
+          for (int j = 0; j < NF; ++j) p[j] = scaled_product(wide(f.b[j]), wide(f.a[i]), sa_codes[i], u);
+#pragma unroll
+          for (int j = 0; j < NF; ++j) {
+            acc[i][j] += p[j];
+            asm volatile("" : "+v"(acc[i][j]));                    // (one after the other: products waiting for their sums would spill)
+          }
+        } else if constexpr (SC != 0) {
           f32x4 p[NF];
 #pragma unroll
           for (int j = 0; j < NF; ++j)
@@ -299,13 +349,8 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_tiles_kernel(GemmArgs 
   read_frags(f[0], 0);
 
   int cur = 0;                                                     // slot of the stage whose fragments are in f[u & 1]
-  for (int t = 1;; ++t) {
-#pragma unroll
-  for (int i = 0; i < MF; ++i)
-#pragma unroll
-    for (int j = 0; j < NF; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  for (int s0 = 0; s0 < ns; s0 += U) {
-    spread_scales(s0);
+  // the stages of a trip; far: E8M0 scales as codes
+  auto stages = [&](int s0, int t, auto far) __attribute__((always_inline)) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if (kHalfTrip && u == 2 && s0 + 2 >= ns) break;
@@ -324,10 +369,27 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_tiles_kernel(GemmArgs 
         fetch_scales(last ? 0 : s0 + U);
       }
       issue(cur);
-      multiply(f[u & 1], u);
+      multiply(f[u & 1], u, far);
       cur = nxt;
     }
-  }
+  };
+  for (int t = 1;; ++t) {
+#pragma unroll
+  for (int i = 0; i < MF; ++i)
+#pragma unroll
+    for (int j = 0; j < NF; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  constexpr bool kCodesOnly = SC == 2 && MF * NF != 8;
+  int s0 = 0;
+  if constexpr (!kCodesOnly)
+    for (; s0 < ns; s0 += U) {
+      if (spread_scales(s0)) break;
+      stages(s0, t, std::false_type{});
+    }
+  if constexpr (SC == 2)
+    for (; s0 < ns; s0 += U) {
+      spread_codes(s0);
+      stages(s0, t, std::true_type{});
+    }
 
   // ---- the groups' sums meet in LDS: group 0 adds them in the order of the groups
   if constexpr (WK > 1) {
