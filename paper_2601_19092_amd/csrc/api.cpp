@@ -411,12 +411,13 @@ static int plan_relayout(const axe_layout_t* src, const axe_layout_t* dst, int32
     };
     while (v > 1 && !fits(v)) v >>= 1;
   }
-  // --- rows that start anywhere: contiguous on both sides, at least 256 bytes (a slot of 64 lanes takes one
-  //     row: 8192 rows of 129 bytes 7.3 us against 6.7, of 258 bytes 6.3 against 6.7), but no 16-byte unit divides everything.
-  //     Replicas and swizzles stay with the loop nest.
-  if (vec_k >= 0 && unit * v < 16 && J[vec_k].e * elem_bytes >= 256 && !ms.swz.mask && !md.swz.mask && md.R.empty() &&
-      env_int("AXE_RELAYOUT_ROWS", 1) != 0) {
-    RowPlan p;
+  // --- rows that start anywhere: contiguous on both sides, at least 256 bytes (a slot of 64 lanes takes one row), but no 16-byte unit
+  //     divides everything.  Replicas and swizzles stay with the loop nest, and so does what it moves in larger pieces (below).
+  RowPlan row_plan;
+  int64_t row_bytes = 0;                                           // 0: not such rows
+  const int rows_knob = env_int("AXE_RELAYOUT_ROWS", -1);          // 0: never, 1: always
+  if (vec_k >= 0 && unit * v < 16 && J[vec_k].e * elem_bytes >= 256 && !ms.swz.mask && !md.swz.mask && md.R.empty() && rows_knob != 0) {
+    RowPlan& p = row_plan;
     memset(&p, 0, sizeof p);
     p.run = J[vec_k].e, p.s_off = ms.off, p.d_off = md.off;
     std::vector<JointIter> outer;
@@ -436,8 +437,7 @@ static int plan_relayout(const axe_layout_t* src, const axe_layout_t* dst, int32
     if (fits && rows < (uint64_t(1) << 31) && slots < (uint64_t(1) << 31) && (rows * slots + kRowSlots - 1) / kRowSlots <= kMaxBlocks256) {
       p.n = (int)outer.size();
       p.rows = (uint32_t)rows, p.slots_per_row = (uint32_t)slots, p.slots = rows * slots;
-      call.kernel = RelayoutCall::kRows, call.unit = elem_bytes, call.rows = p;
-      return AXE_OK;
+      row_bytes = p.run * elem_bytes;
     }
   }
   if (v > 1) {
@@ -500,18 +500,35 @@ static int plan_relayout(const axe_layout_t* src, const axe_layout_t* dst, int32
   memset(&p, 0, sizeof p);
   p.n = (int)J.size();
   uint64_t threads = 1;
+  bool too_many = false;                                           // for one launch of the nest
   for (int k = 0; k < p.n; ++k) {
-    if (J[k].e >= (int64_t(1) << 31)) {
+    if (J[k].e >= (int64_t(1) << 31) && !row_bytes) {
       set_error("axe_relayout: digit extent %lld too large", (long long)J[k].e);
       return AXE_EUNSUPPORTED;
     }
+    too_many = too_many || J[k].e >= (int64_t(1) << 31) || threads >= (uint64_t(1) << 32);
     p.ext[k] = (uint32_t)J[k].e;
     p.shift[k] = is_pow2(J[k].e) ? ilog2(J[k].e) : -1;
     p.ss[k] = J[k].ss;
     p.ds[k] = J[k].ds;
     threads *= (uint64_t)J[k].e;
   }
-  if (threads >= (uint64_t(1) << 32) || (threads + 255) / 256 >= (uint64_t(1) << 31)) {
+  too_many = too_many || threads >= (uint64_t(1) << 32);
+  // The rows kernel costs a row much the same however short it is, and moves 16 bytes per lane; a lane of the nest moves U units.  us, rows /
+  // nest, 200000 (odd: 200001) rows, rotating over 900 MB: 32 bytes per lane 512 B 52 / 39, 3000 B 255 / 229; 16 bytes 264 B 49 / 29, 1032 B 91 / 88,
+  // 4100 B 323 / 332, 8 x 1024 B 88 / 72; 8 bytes 520 B 60 / 58, 700 B 71 / 78, 1602 B 128 / 168; 4 bytes 390 B 52 / 67, 520 B 73 / 101 (20000: 264 B 8.6 / 6.5, 450 B
+  // 8.9 / 8.9); 2 bytes 258 B 50 / 77, of single bytes 257 B 65 / 81 (60000: 22.4 / 21.9); 1 byte 257 B 65 / 134.  Single bytes at the ends of the
+  // rows cost a small copy more than it saves: 3001 rows of 520 B 6.7 / 6.1 whatever U.  A handful of rows is a launch either way.
+  if (row_bytes) {
+    const int per_lane = unit * U;
+    const int64_t from = per_lane >= 16 ? INT64_MAX : (per_lane == 8 ? 704 : (per_lane == 4 ? 448 : (per_lane == 2 && unit == 1 ? 320 : 256)));
+    const bool small = unit == 1 && E * elem_bytes < (int64_t(per_lane == 1 ? 2 : 4) << 20);
+    if (rows_knob == 1 || too_many || row_plan.slots <= 64 || (row_bytes >= from && !small)) {
+      call.kernel = RelayoutCall::kRows, call.unit = elem_bytes, call.rows = row_plan;
+      return AXE_OK;
+    }
+  }
+  if (too_many) {
     set_error("axe_relayout: %llu work items exceed one launch", (unsigned long long)threads);
     return AXE_EUNSUPPORTED;
   }

@@ -100,3 +100,27 @@ def test_variant_of_a_transpose(plan, eb, b, r, c, variant):
     """The variant that was the fastest, or level with it, when all that serve the copy were timed."""
     rc, got, how, _ = plan(*batched(b, r, c), eb)
     assert rc == B.AXE_OK and how == "tiles" and got == variant
+
+
+@pytest.mark.parametrize("rows,n,eb,pad,how", [
+    # (row bytes, unit, rows the nest unrolls by) 16 bytes per lane and more: the nest
+    (60000, 33, 8, 1, "nest"), (60000, 66, 4, 1, "nest"), (400000, 66, 4, 2, "nest"), (60000, 375, 8, 1, "nest"), (60002, 375, 8, 1, "nest"),
+    # 8 bytes: from 704 on
+    (60001, 65, 8, 1, "nest"), (60001, 97, 8, 1, "rows"), (60002, 129, 4, 1, "nest"), (60002, 193, 4, 1, "rows"), (60000, 260, 2, 1, "nest"),
+    (60000, 385, 2, 1, "rows"),
+    # 4 bytes: from 448 on
+    (60001, 65, 4, 1, "nest"), (60001, 129, 4, 1, "rows"), (20002, 161, 2, 1, "nest"), (20002, 225, 2, 1, "rows"), (60000, 257, 1, 1, "nest"),
+    (60000, 515, 1, 1, "rows"),
+    # 2 bytes and single ones
+    (20001, 129, 2, 1, "rows"), (60002, 257, 1, 1, "nest"), (60002, 321, 1, 1, "rows"), (20001, 257, 1, 1, "rows"), (3001, 515, 1, 1, "nest"),
+    (8191, 8191, 2, 1, "rows"), (4097, 4095, 4, 1, "rows"), (9, 257, 1, 1, "rows")])
+def test_rows_or_loop_nest(plan, rows, n, eb, pad, how):
+    """The kernel that was the faster one, or level with the other, when both were timed."""
+    rc, _, got, _ = plan(*padded_rows(rows, n, pad), eb)
+    assert rc == B.AXE_OK and got == how
+
+
+def test_permuted_rows_of_a_few_hundred_bytes_stay_with_the_nest(plan):
+    b, h, n = 4000, 16, 132                                    # (token, head, d) -> (head, token, d)
+    s, d = W.spec([(b, h * n, "m"), (h, n, "m"), (n, 1, "m")]), W.spec([(b, n, "m"), (h, b * n, "m"), (n, 1, "m")])
+    assert plan((b, h, n), s, d, 2)[0::2] == (B.AXE_OK, "nest")
