@@ -1149,20 +1149,39 @@ int plan_gemm_grouped(const axe_gemm_grouped_desc_t* g, const void* dA, const vo
   return AXE_OK;
 }
 
+// fp8 groups with fp32 scales: rows per group on average up to which the streaming kernel is the faster one, from measurements of both
+// (us, streaming / tiles; every group as large as the others, and with sizes drawn from 0.2 + an exponential distribution, where a group of
+// more rows than a pass takes costs the streaming kernel another).  A tile's own costs weigh more the less a group's weights are
+// (16 rows: 128 groups x 1536 x 2048 94 / 88 and 111 / 88, 512 x 512 x 2048 125 / 150 and 148 / 151, 128 x 512 x 1152 22 / 31 and 31 / 31; 40 rows there
+// 28 / 32 and 63 / 39), and still more with a pipeline of four or five steps (8 x 4096 x 512, 20 rows 7 / 9 and 9 / 9); fewer tiles than compute units
+// leave the chip idle where the streaming kernel splits K (8 x 1536 x 2048, 16 rows 11 / 15 and 19 / 16); and every workgroup walks the table of
+// groups (4096 x 256 x 1152, 64 rows 512 / 763 and 746 / 784).  Up to 16 tiles in all the lines of the larger problems stand (1 x 1536 x 2048 at
+// 9 rows 9 / 15, at 64 rows 19 / 15).
+int64_t f32_scales_stream_rows(int64_t G, int64_t N, int64_t K) {
+  const int64_t tiles = G * N / kTileFamily[kGroupedMember].tn, cus = cu_count();
+  if (tiles <= 16) return 0;
+  int64_t rows = 4 + (int64_t(15) << 20) / (N * K);
+  if (K <= 640) rows += 10;
+  if (tiles < cus) rows += 24 * (cus - tiles) / cus;
+  if (G > 1024) rows += (G - 1024) / 100;
+  return rows;
+}
+
 // Which kernel a planned grouped problem goes to: the streaming kernel while the groups average few rows, then the
 // tile kernels.  The crossover depends on K -- a tile's fixed costs (tile table, prologue, stores) weigh more when its
 // K loop is short -- and was measured on the two GEMMs of an MoE layer (128 groups; gemm1: K = 2048, gemm2: K = 768;
 // streaming kernel against tiles, us): fp16 gemm1 at 12 rows per group 148 against 152, at 16 rows 165 against 152;
 // fp16 gemm2 at 16 rows 84 against 88, at 20 rows 92 against 90; fp8 (tiles of 128 rows) gemm1 at 6 rows 78 against 84,
 // at 8 rows 84 against 85, at 10 rows 91 against 85; fp8 gemm2 at 12 rows 44 against 49, at 16 rows 50 against 50, at
-// 20 rows 55 against 50; with fp32 scales gemm1 at 8 rows 83 against 86, at 16 rows 108 against 87, gemm2 at 8 rows 43 against 55,
-// at 16 rows 55 against 57, at 32 rows 80 against 61.  Far from the crossover (fp8 layer): 4 rows per group 104 against 151, 256 rows 1373 against 274.
+// 20 rows 55 against 50; with fp32 scales (more above) gemm1 at 8 rows 83 against 86, at 16 rows 108 against 87, gemm2 at 8 rows 43 against
+// 55, at 16 rows 55 against 57, at 32 rows 80 against 61.  Far from the crossover (fp8 layer): 4 rows per group 104 against 151, 256 rows 1373 against 274.
 bool grouped_goes_to_stream(const axe_gemm_grouped_desc_t* g, const GemmArgs& a) {
   if (g->kernel_hint == AXE_GROUPED_STREAM) return true;
   if (a.fp8 && a.tile_m < 0) return true;
   if (g->kernel_hint != AXE_GROUPED_AUTO) return false;            // tiles asked for
   const bool short_k = g->K <= 1024;
   int64_t rows = a.fp8 ? (short_k ? (scales_f32(a) ? 17 : 15) : 8) : (short_k ? 19 : 13);
+  if (scales_f32(a)) rows = std::max(rows, f32_scales_stream_rows(g->G, g->N, g->K));
   if (a.fp8) {
     static const int64_t min_rows = [] { const char* v = getenv("AXE_GROUPED_FP8_TILE_ROWS"); return v ? atoll(v) : int64_t(0); }();
     if (min_rows > 0) rows = min_rows - 1;
