@@ -56,7 +56,7 @@ bool key_of_layout(const axe_layout_t& L, PlanKey& k) {
 // Whether any of the library's knobs is set (they are read whenever a call is planned: no plan is kept then).
 bool knobs_set() {
   for (char** e = environ; e && *e; ++e)
-    if (!strncmp(*e, "AXE_", 4)) return true;
+    if ((*e)[0] == 'A' && (*e)[1] == 'X' && (*e)[2] == 'E' && (*e)[3] == '_') return true;
   return false;
 }
 
@@ -905,11 +905,12 @@ int plan_gemm(const axe_gemm_desc_t* g, const void* dA, const void* dB, void* dC
       tile = AXE_TILE_64x64x32;
       // up to four K-tiles the burst variant of the 64 x 64 kernel is the faster one where it fits (graph replays, us, burst /
       // cheapest member: 256^3 3.4 / 3.6, 512 x 512 x 128 2.7 / 4.0, 1024 x 1024 x 256 3.7 / 4.4; K = 512: 4.8 / 3.6, 5.1 / 5.0)
-      if (!fp8 && g->K <= 256 && small_preload_fits(g->M, g->N, g->K, lda, ldb, ldc)) P.member = -1;
+      const bool forced = env_int("AXE_TILE_MEMBER", -1) >= 0;
+      if (!fp8 && !forced && g->K <= 256 && small_preload_fits(g->M, g->N, g->K, lda, ldb, ldc)) P.member = -1;
       // and so is the 64 x 64 kernel itself up to five K-tiles of 16-bit inputs, when storing C is most of the work and several
       // small workgroups per compute unit overlap it (us, 64 x 64 / cheapest member, K = 288: 3840 x 1280 11.6 / 13.2, 1051 x 7888
       // 16.8 / 20.7, 600 x 1500 5.1 / 5.6; 2040 x 4096 15.1 / 14.0, 4096 x 4088 27.1 / 23.7; K = 512: 3840 x 1280 15.8 / 14.1)
-      if (!fp8 && g->K <= 320 && g->M * g->N < int64_t(8) << 20 && env_int("AXE_TILE_MEMBER", -1) < 0) P.member = -1;
+      if (!fp8 && !forced && g->K <= 320 && g->M * g->N < int64_t(8) << 20) P.member = -1;
     }
   }
   P.ragged = tile == AXE_TILE_256x256x64 && !big_ok && !blocked && ragged_ok;
@@ -1360,7 +1361,7 @@ int axe_gemm(const axe_gemm_desc_t* g, const void* d_A, const void* d_B, void* d
   static thread_local bool have_last = false;
   GemmPlan P;
   PlanKey key;
-  const bool keyed = g && key_of_gemm(g, key);
+  const bool keyed = g && key_of_gemm(g, key) && !knobs_set();
   if (keyed && have_last && key.n == last_key.n && memcmp(key.w, last_key.w, sizeof(int64_t) * key.n) == 0) {
     P = last_plan;
     P.args.scale_a = (const float*)g->d_scale_a;

@@ -312,10 +312,11 @@ hipError_t launch_relayout_generic(const GenericRelayoutPlan& p, int unit, const
   return hipSuccess;
 }
 
-hipError_t launch_gemm_tiles_16bit(int, const GemmArgs&, hipStream_t) { return hipErrorNotSupported; }
+static int g_member = -2;         // of the tile family in the last dense GEMM; -1: the 64 x 64 kernel, -2: none yet
+hipError_t launch_gemm_tiles_16bit(int m, const GemmArgs&, hipStream_t) { return g_member = m, hipErrorNotSupported; }
 hipError_t launch_gemm_tiles_grouped(const GemmArgs&, hipStream_t) { return hipErrorNotSupported; }
-hipError_t launch_gemm_tiles_fp8(int, const GemmArgs&, hipStream_t) { return hipErrorNotSupported; }
-hipError_t launch_gemm_small(const GemmArgs&, bool, hipStream_t) { return hipErrorNotSupported; }
+hipError_t launch_gemm_tiles_fp8(int m, const GemmArgs&, hipStream_t) { return g_member = m, hipErrorNotSupported; }
+hipError_t launch_gemm_small(const GemmArgs&, bool, hipStream_t) { return g_member = -1, hipErrorNotSupported; }
 hipError_t launch_gemm_bf16_256(const GemmArgs&, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_gemm_bf16_256_grouped(const GemmArgs&, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_gemm_bf16_256_ragged(const GemmArgs&, hipStream_t) { return hipErrorNotSupported; }
@@ -338,6 +339,7 @@ extern "C" void axe_hostcheck_set_buffers(int64_t src_bytes, int64_t dst_bytes) 
   axe::g_transposes_elem = 0;
   axe::g_rows = 0;
 }
+extern "C" int axe_hostcheck_gemm_member(void) { return axe::g_member; }
 extern "C" void axe_hostcheck_plan_only(int on) { axe::g_plan_only = on; }
 extern "C" int64_t axe_hostcheck_workgroups(void) { return (int64_t)axe::g_workgroups; }
 extern "C" int axe_hostcheck_transpose_variant(void) { return axe::g_variant; }
