@@ -903,14 +903,27 @@ int plan_gemm(const axe_gemm_desc_t* g, const void* dA, const void* dB, void* dC
       P.member = -1;
     } else {
       tile = AXE_TILE_64x64x32;
-      // up to four K-tiles the burst variant of the 64 x 64 kernel is the faster one where it fits (graph replays, us, burst /
-      // cheapest member: 256^3 3.4 / 3.6, 512 x 512 x 128 2.7 / 4.0, 1024 x 1024 x 256 3.7 / 4.4; K = 512: 4.8 / 3.6, 5.1 / 5.0)
-      const bool forced = env_int("AXE_TILE_MEMBER", -1) >= 0;
-      if (!fp8 && !forced && g->K <= 256 && small_preload_fits(g->M, g->N, g->K, lda, ldb, ldc)) P.member = -1;
-      // and so is the 64 x 64 kernel itself up to five K-tiles of 16-bit inputs, when storing C is most of the work and several
-      // small workgroups per compute unit overlap it (us, 64 x 64 / cheapest member, K = 288: 3840 x 1280 11.6 / 13.2, 1051 x 7888
-      // 16.8 / 20.7, 600 x 1500 5.1 / 5.6; 2040 x 4096 15.1 / 14.0, 4096 x 4088 27.1 / 23.7; K = 512: 3840 x 1280 15.8 / 14.1)
-      if (!fp8 && !forced && g->K <= 320 && g->M * g->N < int64_t(8) << 20) P.member = -1;
+      // Short K, where a member's ring is mostly prologue (AXE_TILE_MEMBER asks for a member all the same).  us, 64 x 64 / cheapest member:
+      //   - fp8, a single K-tile, tiles of 64 x 64 that fit one round: scaled 128 x 4096 4.5 / 6.1, 1024 x 1024 5.0 / 5.4, 1 x 8192 4.1 / 5.4, unscaled 128 x
+      //     4096 4.3 / 5.1 (but 256 x 256 4.0 / 3.7); two rounds 1000 x 1100 6.3 / 5.5; K = 144: 128 x 4096 6.6 / 6.1.
+      //   - 16-bit inputs, the burst variant: K = 256 level; K = 320 1024 x 768 4.0 / 5.4, 512 x 512 3.8 / 4.2; K = 384 64 x 2048 (32 tiles) 4.2 / 4.6, 256 x 256
+      //     (16) 4.1 / 3.7; K = 512 512 x 768 (96) 4.9 / 5.1, 512 x 512 (64) 4.9 / 4.2.
+      //   - 16-bit inputs up to five K-tiles otherwise, when storing C is most of the work and several small workgroups per compute unit overlap
+      //     it: K = 288 3840 x 1280 10.5 / 12.3, 1051 x 7888 16.3 / 20.2, 500 x 1500 5.0 / 5.4.  Not where the largest member fills most of its one round: K = 256
+      //     2500 x 2504 (200 tiles on 256 compute units) 12.6 / 10.0, 20000 x 384 17.1 / 11.1, 60000 x 96 16.1 / 9.9; K = 192 11.1 / 10.0, 14.9 / 11.0, 13.6 / 9.5;
+      //     K = 288, half a K-tile less to do here, 2500 x 2504 13.4 / 11.7, but 3072 x 2048 (192) 11.5 / 12.5.  Whole rounds and few rows
+      //     stay although the member is ahead (K = 320: 2040 x 4096 14.8 / 12.3, 16 x 4096 4.7 / 4.0).
+      const int64_t tiles64 = ((g->M + 63) / 64) * ((g->N + 63) / 64), cus = cu_count();
+      if (P.member < 0 || env_int("AXE_TILE_MEMBER", -1) >= 0) {
+      } else if (fp8) {
+        if (g->K <= bk && tiles64 <= cus) P.member = -1;
+      } else if (small_preload_fits(g->M, g->N, g->K, lda, ldb, ldc)) {
+        if (g->K <= 320 || tiles64 >= (g->K <= 384 ? 32 : 96)) P.member = -1;
+      } else if (g->K <= 320 && g->M * g->N < int64_t(8) << 20) {
+        const TileShape& t = kTileFamily[P.member];
+        const int64_t tiles = ((g->M + t.tm - 1) / t.tm) * ((g->N + t.tn - 1) / t.tn);
+        if (g->K <= 2 * bk || t.tm * t.tn < 256 * 128 || 100 * tiles < (g->K % bk ? 77 : 70) * cus || tiles >= cus) P.member = -1;
+      }
     }
   }
   P.ragged = tile == AXE_TILE_256x256x64 && !big_ok && !blocked && ragged_ok;
