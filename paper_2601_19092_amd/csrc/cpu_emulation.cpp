@@ -17,6 +17,7 @@ static int g_violations = 0;
 static int g_transposes = 0;      // launches of the transposing relayout since the buffers were declared
 static int g_rows = 0;            // relayouts of rows that start anywhere
 static int g_transposes_elem = 0; // ... of which element by element (not in 16-byte chunks)
+static int g_blocks = -1;         // 1: the last evaluation would go by blocks of indices if the fast kernel does not take it
 static int g_plan_only = 0;       // 1: a relayout is planned but moves nothing (the buffers need not exist)
 static uint64_t g_workgroups = 0; // of the last relayout by tiles or by rows
 static int g_variant = -1;        // TransposePlan::elementwise of the last transposing relayout
@@ -24,6 +25,7 @@ static int g_variant = -1;        // TransposePlan::elementwise of the last tran
 static int64_t swz_apply(int64_t x, Swz z) { return x ^ (((x >> z.shift) & (int64_t)z.mask) << z.base); }
 
 hipError_t launch_layout_eval(const EvalDesc& d, int64_t n, const int64_t* idx, int64_t* out, hipStream_t) {
+  g_blocks = layout_eval_by_blocks(d, n, out);
   const int64_t per = d.E_R * d.n_axes;
   for (int64_t i = 0; i < n; ++i) {
     int64_t x = idx ? idx[i] : i;
@@ -339,6 +341,7 @@ extern "C" void axe_hostcheck_set_buffers(int64_t src_bytes, int64_t dst_bytes) 
   axe::g_transposes_elem = 0;
   axe::g_rows = 0;
 }
+extern "C" int axe_hostcheck_eval_by_blocks(void) { return axe::g_blocks; }
 extern "C" int axe_hostcheck_gemm_member(void) { return axe::g_member; }
 extern "C" void axe_hostcheck_plan_only(int on) { axe::g_plan_only = on; }
 extern "C" int64_t axe_hostcheck_workgroups(void) { return (int64_t)axe::g_workgroups; }

@@ -11,6 +11,17 @@ namespace axe {
 constexpr uint64_t kMaxBlocks256 = (uint64_t(1) << 24) - 1;
 
 hipError_t launch_layout_eval(const EvalDesc& d, int64_t n, const int64_t* idx, int64_t* out, hipStream_t s);
+// Whether an evaluation that the fast kernel does not take goes by blocks of indices.  A thread of the block kernel writes a pair of words
+// per trip, a trip whole indices and an even number of words: per <= 256, so more than half of the threads write (an odd per of
+// 129 .. 169 leaves two of the three indices that fit; 52 % at 133).  Pairs start on 16 bytes.  More words per index leave few whole
+// indices to a trip and long runs to a thread: the general kernel keeps those, and index spaces of 2^31 points and more -- and a
+// few indices with such an odd per, whose half trips a handful of workgroups would make one after the other (1536 indices, 43 replicas on 3
+// axes: 20.6 us on the general kernel, 25.8 by blocks; 10000: 21.8 and 27.4; 90300: 74 and 35; 1536, 129 replicas on one axis: 46 and 25).
+inline bool layout_eval_by_blocks(const EvalDesc& d, int64_t n, const int64_t* out) {
+  const int64_t per = d.E_R * d.n_axes;
+  const bool half_trips = (per & 1) && 512 / per == 3;
+  return d.use32 && per <= 256 && ((uintptr_t)out & 15) == 0 && !(half_trips && n < 16384 && d.E_R <= 64);
+}
 hipError_t launch_relayout_joint(const RelayoutPlan& p, int unit_bytes, const void* src, void* dst, hipStream_t s);
 // elem_bytes 1, 2, 4 or 8; rows of at least 16 bytes; a workgroup takes kRowSlots slots, and one launch holds kMaxBlocks256 workgroups
 constexpr uint64_t kRowSlots = 16;

@@ -100,6 +100,7 @@ __global__ __launch_bounds__(256) void layout_eval_fast_kernel(EvalDesc d, int64
     const uint32_t e = (uint32_t)d.ext[k];
     const int64_t st = d.str[k];
     const int ax = d.axis[k];
+    const Div31 by = d.div[k];                                     // (fetched with the others: on demand it is waited for by itself)
 #pragma unroll
     for (int p = 0; p < PTS; ++p) {
       uint32_t dig;
@@ -107,7 +108,7 @@ __global__ __launch_bounds__(256) void layout_eval_fast_kernel(EvalDesc d, int64
         dig = rem[p] & (e - 1u);
         rem[p] >>= sh;
       } else {
-        const uint32_t q = div31(rem[p], d.div[k]);
+        const uint32_t q = div31(rem[p], by);
         dig = rem[p] - q * e;
         rem[p] = q;
       }
@@ -193,12 +194,13 @@ __global__ __launch_bounds__(256) void layout_eval_block_kernel(EvalDesc d, int6
       uint32_t rem = (uint32_t)x;
       for (int k = d.n_d - 1; k >= 0; --k) {
         const uint32_t e = (uint32_t)d.ext[k];
+        const Div31 by = d.div[k];
         uint32_t dig;
         if (d.shift[k] >= 0) {
           dig = rem & (e - 1u);
           rem >>= d.shift[k];
         } else {
-          const uint32_t q = div31(rem, d.div[k]);
+          const uint32_t q = div31(rem, by);
           dig = rem - q * e;
           rem = q;
         }
@@ -245,10 +247,7 @@ hipError_t launch_layout_eval(const EvalDesc& d, int64_t n, const int64_t* idx, 
   }
   int64_t blocks = (n + 255) / 256;
   if (blocks > 65536 * 4) blocks = 65536 * 4;
-  // a pair of words per thread, whole indices per trip of a workgroup (per <= 256: two thirds of its threads write at least);
-  // pairs start on 16 bytes.  More words per index leave few whole indices to a trip and long runs to a thread: the general
-  // kernel keeps those, and index spaces of 2^31 points and more.
-  if (d.use32 && d.E_R * d.n_axes <= 256 && ((uintptr_t)out & 15) == 0) {
+  if (layout_eval_by_blocks(d, n, out)) {
     const dim3 grid((unsigned)blocks), block(256);
     switch (d.n_axes) {
       case 1: hipLaunchKernelGGL(layout_eval_block_kernel<1>, grid, block, 0, s, d, n, idx, out); break;
