@@ -234,7 +234,7 @@ def bench_transpose(steps, warmup, n_pairs=4):
     log(f"[bench] relayout 8192^2 bf16 row-major -> column-major (transposing tiles): {r['GBps']:.0f} GB/s rotating "
         f"({100 * r['frac_of_hbm_peak']:.1f}% of HBM peak)")
     del pairs
-    # the same with extents that are no multiples of a 16-byte chunk: the element-wise tiles
+    # the same with extents that are no multiples of a 16-byte chunk: tiles skewed onto the destination's lines
     ro, co = 8191, 8193
     Ls, Ld = B.Layout(W.row_major_spec(ro, co)), B.Layout(W.col_major_spec(ro, co))
     pairs = [(torch.randint(-30000, 30000, (ro * co,), dtype=torch.int16, device="cuda"),
@@ -263,7 +263,7 @@ def bench_transpose(steps, warmup, n_pairs=4):
     _, d_reg = time_loop(lambda i: B.axe_relayout(srcL, dstL, shape, a, outs[i % 2]), steps, warmup)
     r["to_mfma_operand_registers_8192"] = {"kernel_ms": d_reg, "replicas": n_dst // (M * K),
                                            "GBps": (M * K + n_dst) * 2.0 / (d_reg * 1e-3) / 1e9}
-    log(f"[bench] relayout 8191 x 8193 bf16 row-major -> column-major (element-wise tiles): {r['odd_extents_8191x8193']['GBps']:.0f} GB/s; "
+    log(f"[bench] relayout 8191 x 8193 bf16 row-major -> column-major (tiles skewed onto the destination's lines): {r['odd_extents_8191x8193']['GBps']:.0f} GB/s; "
         f"8192^2 bf16 -> MFMA operand register order, both wave copies: {r['to_mfma_operand_registers_8192']['GBps']:.0f} GB/s (read + written)")
     return r
 

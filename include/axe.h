@@ -180,9 +180,12 @@ int axe_gemm(const axe_gemm_desc_t* g, const void* d_A, const void* d_B, void* d
  * bounds (plain operands only).
  * Left to itself (tile_hint 0) the library answers AXE_TILE_64x64x32 for every problem the large tiles do not pay for, and
  * then launches whichever of a family of tiles from 16 x 16 to 256 x 128 loads the fewest rows per compute unit over
- * all rounds of tiles (few rows of A: narrow tiles with K dealt to up to eight waves), or the 64 x 64 kernel itself for
- * K up to 256; the large tiles are taken when they load no more.  axe_gemm_describe reports the tile that runs.
- * tile_hint AXE_TILE_64x64x32 always means the 64 x 64 kernel. */
+ * all rounds of tiles (few rows of A: narrow tiles with K dealt to up to eight waves); the large tiles are taken when they load
+ * no more.  Exceptions: the 64 x 64 kernel itself serves K up to 128 with fp8 inputs and one round of its tiles; with 16-bit inputs
+ * K up to 320 below 2^23 elements of C unless a 256 x 128 tile fills most of its one round, and K up to 512 where all of its operands
+ * fit LDS at once (whole tiles of 64 x 64, no more than compute units, 32 at least from K = 384 and 96 from K = 448 on); problems of at
+ * most two K-tiles go to the large tile by the elements of C (fp8 2^20, else 5 x 2^20), and E8M0 codes per row of A take it from 2^22
+ * elements on, where it fits.  axe_gemm_describe reports the tile that runs.  tile_hint AXE_TILE_64x64x32 always means the 64 x 64 kernel. */
 int axe_gemm_tile(const axe_gemm_desc_t* g);
 
 /* ---------------------------------------------------------------------------------------------

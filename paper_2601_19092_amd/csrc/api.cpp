@@ -889,9 +889,10 @@ int plan_gemm(const axe_gemm_desc_t* g, const void* dA, const void* dB, void* dC
     // The large tiles (one workgroup per compute unit, 256 x 256 or 256 x 224) or the family of smaller ones, whichever
     // costs less.  Measured, us, large tile / cheapest member -- bf16: 2048 x 2048 x 2048 39 / 20, 1024 x 3584 x 8192 129 / 59,
     // 2048 x 4096 x 2048 40 / 34, 4096 x 4096 x 2048 52 / 70; fp8 with fp32 block scales: 1024 x 1024 x 2048 27 / 7,
-    // 2048 x 4096 x 2048 30 / 24, 4096 x 4096 x 2048 36 / 46.  Two lines are older than this rule and stand as what
-    // axe_gemm_tile has promised: problems of at most two K-tiles go by the elements of C (bf16 2304 x 2304 x 128 11.5 us on the
-    // large tile), and E8M0 codes per row of A take the large tile from 2048 x 2048 on (26 us at K = 2048, against 13).
+    // 2048 x 4096 x 2048 30 / 24, 4096 x 4096 x 2048 36 / 46.  Two lines are older than this rule, and the figures speak against
+    // them; the tests hold axe_gemm_tile to them: problems of at most two K-tiles go by the elements of C (bf16 2304 x 2304 x 128 11.4 us on
+    // the large tile, 9.1 on the 64 x 64 kernel; fp8 1024 x 1024 x 128 10 - 13 and 5), and E8M0 codes per row of A take the large tile from
+    // 2048 x 2048 on (26 us at K = 2048, against 13).
     int64_t family_cost;
     P.member = family_member(g->M, g->N, eb, lda, ldb, &family_cost);
     const int64_t t256 = large_ok && !(n224_ok && !big_ok) ? tile_cost(std::max<int64_t>(g->M, 256), std::max<int64_t>(g->N, 256), 256, 256) : INT64_MAX;

@@ -2,11 +2,14 @@
 // parameters (tile_family.h).  It serves what the 256-row kernels are too coarse for: a decode step's handful of rows,
 // prefill chunks, edges that fill no large tile, and fp8 with scales the matrix cores' scale path cannot carry.
 //
-// Bound: the L2 -> CU path.  A K-step of a TM x TN tile moves (TM + TN) x 128 bytes for TM x TN x 128 bytes' worth of
-// products; at the 21 - 25 TB/s the L2s deliver (about 86 GB/s per CU) a 128 x 128 tile's K-step takes 370 ns, of which the
-// matrix cores need 240.  Hence tiles as large as the problem can fill the chip with, every load instruction 8 rows of
-// whole 128-byte lines straight into LDS (buffer_load ... lds: no registers, no ds_write), and a ring deep enough to keep
-// 96 - 128 KiB in flight per CU.
+// What bounds it.  A K-step of a TM x TN tile moves (TM + TN) x 128 bytes for TM x TN x 128 bytes' worth of products; at the 21 - 25
+// TB/s the L2s deliver (about 86 GB/s per CU) a 128 x 128 tile's K-step takes 370 ns, of which the matrix cores need 240.  Hence
+// tiles as large as the problem can fill the chip with, every load instruction 8 rows of whole 128-byte lines straight into
+// LDS (buffer_load ... lds: no registers, no ds_write), and a ring deep enough to keep 96 - 128 KiB in flight per CU.  What it
+// reaches is less: 50 - 62 GB/s per CU over a whole launch of 128 x 128 tiles, 73 - 87 inside long K loops, while the 256-row kernels'
+// loads alone run at 94 - 106 through the same instruction.  So the path itself is not what stops it (matrix cores 46 % and 41 % busy in
+// the two shapes below); what does -- one barrier per K-step for eight waves, a stage's fragment reads in one burst at its head, the
+// fold beside the matrix instructions, prologue and last stores -- has not been told apart.
 //
 // Tile movements (tile_maps.h, the image of the 256-row kernels):
 //   HBM -> LDS  : pieces of 8 rows x 128 bytes, one wave instruction each; the XOR swizzle is applied on the global side.
@@ -27,8 +30,8 @@
 // each (27.6 there, level on 512 tiles).
 //
 // Measured, us, against the 64 x 64 kernel that served these problems: bf16 16 x 3584 x 8192 91.5 -> 11.4 (58.9 MB, 5.2 TB/s),
-// 64 x 3584 x 8192 94 -> 15, 512 x 3584 x 8192 101 -> 40, fp16 2000 x 2000 x 2048 39 -> 20 (800 TFLOP/s), fp8 with one fp32 scale per
-// row 1000 x 3584 x 8192 365 -> 37 (1590 TFLOP/s), fp8 E8M0 256 x 512 x 6400 105 -> 7.6; and against the large tile: fp8
+// 64 x 3584 x 8192 94 -> 15, 512 x 3584 x 8192 101 -> 40, fp16 2000 x 2000 x 2048 39 -> 20 - 21 (780 - 820 TFLOP/s), fp8 with one fp32 scale per
+// row 1000 x 3584 x 8192 365 -> 37 - 39 (1500 - 1590 TFLOP/s), fp8 E8M0 256 x 512 x 6400 105 -> 7.6; and against the large tile: fp8
 // 1024 x 3584 x 8192 76 -> 36, bf16 2048 x 4096 x 2048 40 -> 34.
 //
 // Scales (fp8).  A K-tile is one 128-deep scale block: its product is formed alone and folded into the sum on the vector

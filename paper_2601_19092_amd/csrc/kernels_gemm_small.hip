@@ -2,8 +2,9 @@
 // = 64 B, fp8: 128 elements = 128 B), 4 waves in a 2 x 2 grid, each wave a 32 x 32 sub-tile made
 // of 2 x 2 MFMA 16x16 fragments.  Ragged M / N are handled by zero-filled loads and guarded
 // stores, so this kernel serves every shape the library accepts.  It runs when it is asked for (tile_hint), for rows too far
-// apart for the tile family's 32-bit offsets and, as its burst variant, for short K; the tile family (gemm_tiles.h, 2 - 10
-// times as fast) and the large tiles take the rest.
+// apart for the tile family's 32-bit offsets, and for short K: as its burst variant up to K = 512, itself up to K = 320 with 16-bit
+// inputs and one K-tile with fp8, within the limits that axe_gemm's choice states with the times of both sides; the tile family
+// (gemm_tiles.h, 2 - 10 times as fast on long K) and the large tiles take the rest.
 //
 // Tile movements (all K-contiguous, A row-major and B column-major):
 //   HBM -> VGPR : thread t fetches 16-byte chunk (row = t / CH, chunk = t % CH) of the tile

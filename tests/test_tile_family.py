@@ -142,7 +142,7 @@ def test_member_matches_the_oracle(member, dt, out, scale, rows):
     check(member, 2 * tm + 1, tn + 3, kt + vec, dt, out, scale, rows)
     check(member, tm, 2 * tn + 8, (wk * nst + 1) * kt, dt, out, scale, rows, pad=1)
     check(member, tm - 1, tn - 1, wk * (nst - 1) * kt, dt, out, scale, rows, pad=2)
-    # a single chunk of K (a descriptor per member: the plan of the last one is kept).  fp8 to fp32: of 16 products the largest
+    # a single chunk of K.  fp8 to fp32: of 16 products the largest
     # is about 3 times the sum's deviation, so an error of 2^-16 of it is 2^-14.4 = 5e-5 of an average sum and more of one that
     # cancels; the 3e-5 of TOL is a norm over many sums of many products, hence 64 columns there
     check(member, 1, (64 if dt == "fp8" and out == "f32" else 1) + member, vec, dt, out, scale, rows)
