@@ -37,8 +37,8 @@
 // Scales (fp8).  A K-tile is one 128-deep scale block: its product is formed alone and folded into the sum on the vector
 // ALU with the row's scale times the column block's (fp32, or E8M0 codes built as 2^(their sum - 254)).  Two codes may
 // add up to a power of two that no float holds, where the product is zero or small, so they are scale operands of the matrix
-// instruction.  The same bits as factors give, and as fast in most tiles (us, factors / codes: 512 x 3584 x 8192 25.1 / 25.1, 64 x 3584 x 8192
-// 8.8 / 8.8, but 300 x 1024 x 1024 6.0 / 6.2, 2048 x 4096 x 8192 65.6 / 67.3); the 128 x 128 tile, where they are not (1024 x 3584 x 8192 35.8 / 37.9),
+// instruction.  The same bits as factors give, and as fast in most tiles (us, factors / codes: 512 x 3584 x 8192 25.1 / 25.1, 300 x 1024 x 1024
+// 6.0 / 6.0, but 2048 x 4096 x 8192 65.4 / 68.7); the 128 x 128 tile, where they are not (1024 x 3584 x 8192 35.8 / 37.9),
 // multiplies by factors up to the first trip whose codes have none, and runs a second K loop from there (35.1; the largest tile has no
 // registers for two loops, in the others they cost 2 - 9 %).  Adding in place too, 34.2 here, gives sums that are less exact.
 #pragma once
@@ -322,7 +322,9 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_tiles_kernel(GemmArgs 
 #pragma unroll
           for (int j = 0; j < NF; ++j) {
             acc[i][j] += p[j];
-            asm volatile("" : "+v"(acc[i][j]));                    // (one after the other: products waiting for their sums would spill)
+            // (in order where a group has K to itself: products waiting for their sums would spill in the largest tile and cost the
+            //  128 x 64 one 2 - 4 %; the small ones are 2 % faster as the compiler likes it: 300 x 1024 x 1024 6.0 us, 6.2 in order)
+            if constexpr (WK == 1) asm volatile("" : "+v"(acc[i][j]));
           }
         } else if constexpr (SC != 0) {
           f32x4 p[NF];
