@@ -303,7 +303,7 @@ static int plan_relayout(const axe_layout_t* src, const axe_layout_t* dst, int32
       // 1700 (126) 8.8 / 7.4, 9253 x 1016 (584, just over a round) 23.3 / 20.2, and 9760 x 1406, whose rows start on lines, 29.0 / 25.8.
       //   3 against 1.  The skew pays where the destination goes to memory rather than to the last-level cache (8191 x 8193 bf16 56 / 105;
       // 7000 x 3001, 84 MB in all, 28 / 32, and 2 takes 24) and not for single bytes, whose lines are as long as the tile.  2-byte: 2000 x
-      // 200 x 201 98 / 124, but 60000 x 66 x 66 987 / 866; 4-byte: 800 x 200 x 129 41 / 49, but 12000 x 130 x 130 481 / 436; 8-byte: 3001 x 3003
+      // 200 x 201 98 / 124, but 60000 x 66 x 66 987 / 866; 4-byte: 800 x 200 x 129 41 / 49, 2671 x 161 x 177 142 / 178, but 12000 x 130 x 130, whose tiles of 64 are half empty, 481 / 436; 8-byte: 3001 x 3003
       // 34 / 41, 20000 x 33 x 65 142 / 222, but 30000 x 50 x 41 350 / 169 (and 2 takes 176).
       //   3 against aligned chunks (0).  2-byte: 2000 x 200 x 200 93 / 131, but where one tile holds the whole matrix no line is shared: 100000 x 40 x
       // 40 340 / 280; 4-byte the same 473 / 673, but 20000 x 72 x 72 217 / 189; 8-byte: 100000 x 24 x 24 205 / 281, but 30000 x 56 x 56 394 / 246.
@@ -321,12 +321,12 @@ static int plan_relayout(const axe_layout_t* src, const axe_layout_t* dst, int32
       const int64_t n3 = skew_ok ? tiles(eS, skew_tile_s(elem_bytes)) * tiles(eD + 128 / elem_bytes - 1, skew_tile_d(elem_bytes)) : 0;
       bool any_start = !swizzled, skew = skew_ok && !on_lines && bytes >= (int64_t(112) << 20);
       if (elem_bytes == 2) {
-        any_start = any_start && 2 * n2 <= n1 && (bytes < (int64_t(64) << 20) || 10 * n2 <= 3 * n1 || 20 * eS * eD <= 13 * 4096 * n1);
+        any_start = any_start && 19 * n2 <= 10 * n1 && (bytes < (int64_t(64) << 20) || 10 * n2 <= 3 * n1 || 20 * eS * eD <= 13 * 4096 * n1);
         skew = skew && (chunks ? n2 > 1 && n3 <= 3 * n2 : 4 * n3 <= 3 * n1);
       } else if (elem_bytes == 4) {
         const int64_t wgs = E / (eS * eD) * n2, cus = cu_count();
         any_start = any_start && !on_lines && 7 * n2 <= 2 * n1 && (n2 <= 2 || (4 * wgs >= 5 * cus && (wgs <= 2 * cus || 2 * wgs >= 5 * cus)));
-        skew = skew && (chunks ? n3 <= (n2 > 1 ? 3 * n2 : 1) : 5 * n3 <= 3 * n1);
+        skew = skew && (chunks ? n3 <= (n2 > 1 ? 3 * n2 : 1) : 5 * n3 <= 3 * n1 || (3 * n3 <= 2 * n1 && 20 * eS * eD >= 13 * 4096 * n1));
       } else if (elem_bytes == 8) {
         any_start = any_start && (n1 > 2 || bytes < (int64_t(112) << 20));
         skew = skew && (n1 > 2 ? 2 * n3 <= 5 * n1 : 2 * n3 <= 3 * n1);
@@ -367,11 +367,13 @@ static int plan_relayout(const axe_layout_t* src, const axe_layout_t* dst, int32
         const uint64_t tiles_d = (uint64_t)((p.eD + (variant == 3 ? 128 / elem_bytes - 1 : 0) + TD - 1) / TD);
         if (tiles_s > kMaxBlocks256 || tiles_d > kMaxBlocks256 || matrices > kMaxBlocks256 || tiles_s * tiles_d > kMaxBlocks256) return false;
         // chunks that start at any element: the grid padded to whole rounds of the 8 XCDs along the source, so that the tiles that
-        // complete a line meet in one L2, where that adds at most an eighth of workgroups that only return (us, padded / not: 3001 x 7000 bf16
-        // 24.3 / 28.8, bytes 8191 x 8193 42 / 56; but 300 x 500 x 501, 4 tiles padded to 8, 123 / 94, and 60000 x 66 x 66, 1 to 8, 1996 / 270)
+        // complete a line meet in one L2, where that adds at most an eighth of workgroups that only return, or a quarter in a large matrix (us,
+        // padded / not: 3001 x 7000 bf16 24.3 / 28.8, bytes 8191 x 8193 42 / 56, 7954 x 3298 (26 tiles to 32) 29 / 35; but 4 x 1001 x 1627 (13 to 16)
+        // 8 % behind, 300 x 500 x 501 (4 to 8) 123 / 94, and 60000 x 66 x 66 (1 to 8) 1996 / 270)
         const uint64_t padded = (tiles_s + 7) & ~uint64_t(7);
         uint64_t grid_s = tiles_s;
-        if (variant == 2 && (padded - tiles_s) * 8 <= tiles_s && padded * tiles_d * matrices <= kMaxBlocks256) grid_s = padded;
+        const bool pads = (padded - tiles_s) * 8 <= tiles_s || ((padded - tiles_s) * 4 <= tiles_s && tiles_d >= 8 && bytes >= (int64_t(48) << 20));
+        if (variant == 2 && pads && padded * tiles_d * matrices <= kMaxBlocks256) grid_s = padded;
         if (grid_s * tiles_d * matrices > kMaxBlocks256) return false;
         p.elementwise = variant;
         p.tiles_s = (uint32_t)tiles_s, p.tiles_d = (uint32_t)tiles_d, p.grid_s = (uint32_t)grid_s;
@@ -912,7 +914,7 @@ int plan_gemm(const axe_gemm_desc_t* g, const void* dA, const void* dB, void* dC
       //   - 16-bit inputs up to five K-tiles otherwise, when storing C is most of the work and several small workgroups per compute unit overlap
       //     it: K = 288 3840 x 1280 10.5 / 12.3, 1051 x 7888 16.3 / 20.2, 500 x 1500 5.0 / 5.4.  Not where the largest member fills most of its one round: K = 256
       //     2500 x 2504 (200 tiles on 256 compute units) 12.6 / 10.0, 20000 x 384 17.1 / 11.1, 60000 x 96 16.1 / 9.9; K = 192 11.1 / 10.0, 14.9 / 11.0, 13.6 / 9.5;
-      //     K = 288, half a K-tile less to do here, 2500 x 2504 13.4 / 11.7, but 3072 x 2048 (192) 11.5 / 12.5.  Whole rounds and few rows
+      //     K = 288, half a K-tile less to do here, 2500 x 2504 13.4 / 11.7, but 3072 x 2048 (192 tiles) 11.5 / 12.5, and K = 192 there 9.8 / 11.0.  Whole rounds and few rows
       //     stay although the member is ahead (K = 320: 2040 x 4096 14.8 / 12.3, 16 x 4096 4.7 / 4.0).
       const int64_t tiles64 = ((g->M + 63) / 64) * ((g->N + 63) / 64), cus = cu_count();
       if (P.member < 0 || env_int("AXE_TILE_MEMBER", -1) >= 0) {
@@ -923,7 +925,7 @@ int plan_gemm(const axe_gemm_desc_t* g, const void* dA, const void* dB, void* dC
       } else if (g->K <= 320 && g->M * g->N < int64_t(8) << 20) {
         const TileShape& t = kTileFamily[P.member];
         const int64_t tiles = ((g->M + t.tm - 1) / t.tm) * ((g->N + t.tn - 1) / t.tn);
-        if (g->K <= 2 * bk || t.tm * t.tn < 256 * 128 || 100 * tiles < (g->K % bk ? 77 : 70) * cus || tiles >= cus) P.member = -1;
+        if (g->K <= 2 * bk || t.tm * t.tn < 256 * 128 || 100 * tiles < (g->K % bk || g->K <= 3 * bk ? 77 : 70) * cus || tiles >= cus) P.member = -1;
       }
     }
   }
@@ -1169,7 +1171,8 @@ int plan_gemm_grouped(const axe_gemm_grouped_desc_t* g, const void* dA, const vo
 // more rows than a pass takes costs the streaming kernel another).  A tile's own costs weigh more the less a group's weights are
 // (16 rows: 128 groups x 1536 x 2048 94 / 88 and 111 / 88, 512 x 512 x 2048 125 / 150 and 148 / 151, 128 x 512 x 1152 22 / 31 and 31 / 31; 40 rows there
 // 28 / 32 and 63 / 39), and still more with a pipeline of four or five steps (8 x 4096 x 512, 20 rows 7 / 9 and 9 / 9); fewer tiles than compute units
-// leave the chip idle where the streaming kernel splits K (8 x 1536 x 2048, 16 rows 11 / 15 and 19 / 16); and every workgroup walks the table of
+// leave the chip idle where the streaming kernel splits K (8 x 1536 x 2048, 16 rows 11 / 15 and 19 / 16; less so where K is long: 16 x 256 x 8192,
+// 20 rows 49 / 45 and 101 / 45); and every workgroup walks the table of
 // groups (4096 x 256 x 1152, 64 rows 512 / 763 and 746 / 784).  Up to 16 tiles in all the lines of the larger problems stand (1 x 1536 x 2048 at
 // 9 rows 9 / 15, at 64 rows 19 / 15).
 int64_t f32_scales_stream_rows(int64_t G, int64_t N, int64_t K) {
@@ -1177,7 +1180,7 @@ int64_t f32_scales_stream_rows(int64_t G, int64_t N, int64_t K) {
   if (tiles <= 16) return 0;
   int64_t rows = 4 + (int64_t(15) << 20) / (N * K);
   if (K <= 640) rows += 10;
-  if (tiles < cus) rows += 24 * (cus - tiles) / cus;
+  if (tiles < cus) rows += 24 * (cus - tiles) * 4096 / (cus * std::max<int64_t>(K, 4096));
   if (G > 1024) rows += (G - 1024) / 100;
   return rows;
 }

@@ -24,7 +24,7 @@ def kernel(G, N, K, rows, hint=B.AXE_GROUPED_AUTO, dtype=B.AXE_SCALE_F32):
     (128, 1536, 2048, 8, 12), (128, 2048, 768, 16, 24), (128, 4096, 4096, 5, 9),       # an MoE layer's two products, a larger one
     (128, 512, 1152, 24, 48), (512, 512, 2048, 16, 24), (1024, 512, 1152, 24, 64),     # little weight per group
     (8, 4096, 512, 20, 48), (128, 2048, 512, 16, 32),                                  # a short pipeline
-    (8, 1536, 2048, 16, 32), (16, 256, 8192, 9, 40), (32, 512, 640, 48, 96),           # fewer tiles than compute units
+    (8, 1536, 2048, 16, 32), (16, 256, 8192, 9, 24), (32, 512, 640, 48, 96),           # fewer tiles than compute units
     (4096, 256, 1152, 64, 128), (4096, 512, 1024, 48, 96), (2048, 256, 2048, 40, 64)])  # many groups
 def test_choice_by_rows_per_group(G, N, K, stream, tiles):
     assert kernel(G, N, K, stream) == S and kernel(G, N, K, tiles) == T

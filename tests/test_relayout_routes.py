@@ -55,15 +55,18 @@ def test_more_than_one_launch_of_tiles_goes_to_the_loop_nest(plan):
     assert plan(*batched(1 << 24, 33, 33), 2)[0] == B.AXE_EUNSUPPORTED   # ... nor does that hold 2^24 x 1089 elements
 
 
-@pytest.mark.parametrize("c", [100, 129, 500, 1000, 1031, 2047, 7001, 8193])
-def test_padding_adds_at_most_an_eighth(plan, c):
-    """The grid is padded along the source only where the empty workgroups are few."""
-    for b, r in ((1, 4001), (3, 400), (40, 129)):
+@pytest.mark.parametrize("c", [100, 129, 500, 1000, 1031, 2047, 3298, 7001, 8193])
+def test_padding_adds_few_workgroups(plan, c):
+    """The grid is padded along the source only where the empty workgroups are few: an eighth, in a large matrix a quarter."""
+    for b, r in ((1, 4001), (3, 400), (40, 129), (1, 7955)):
         rc, v, how, wgs = plan(*batched(b, r, c), 2)
         assert rc == B.AXE_OK and how == "tiles"
         if v == 2:
             tiles = b * -(-r // 128) * -(-c // 128)
-            assert tiles <= wgs and 8 * wgs <= 9 * tiles
+            large = r >= 1000 and 4 * b * r * c >= 48 << 20
+            assert tiles <= wgs and (4 * wgs <= 5 * tiles if large else 8 * wgs <= 9 * tiles)
+            if (r, c) == (7955, 3298):
+                assert wgs == 63 * 32
 
 
 def padded_rows(rows, n, pad=1):
@@ -92,7 +95,7 @@ CHUNKS, ELEMENTS, ANY_START, SKEWED = 0, 1, 2, 3
     (4, 1, 100000, 33, ELEMENTS), (4, 300, 200, 65, ANY_START), (4, 2, 531, 700, ELEMENTS), (4, 1, 4785, 1217, ANY_START), (4, 1, 9253, 1016, ELEMENTS),
     # out to memory: skewed where that does not take many more tiles
     (2, 1, 8191, 8193, SKEWED), (2, 2000, 200, 201, SKEWED), (2, 4000, 33, 1001, ANY_START), (4, 4000, 1001, 33, SKEWED), (4, 4000, 33, 1001, ELEMENTS),
-    (4, 1, 17, 3000001, ELEMENTS), (4, 1, 3000001, 17, SKEWED), (4, 12000, 130, 130, ELEMENTS), (8, 200000, 9, 8, SKEWED), (8, 30000, 50, 41, ELEMENTS),
+    (4, 1, 17, 3000001, ELEMENTS), (4, 1, 3000001, 17, SKEWED), (4, 12000, 130, 130, ELEMENTS), (4, 2671, 161, 177, SKEWED), (8, 200000, 9, 8, SKEWED), (8, 30000, 50, 41, ELEMENTS),
     # aligned chunks, rows off the lines: a matrix inside one tile shares none
     (2, 1, 8184, 8200, SKEWED), (2, 2000, 200, 200, SKEWED), (2, 30000, 72, 72, CHUNKS), (2, 100000, 40, 40, CHUNKS), (4, 100000, 40, 40, SKEWED),
     (4, 20000, 72, 72, CHUNKS), (8, 100000, 24, 24, SKEWED), (8, 30000, 56, 56, CHUNKS)])

@@ -16,7 +16,7 @@ SMALL = -1                                                     # the 64 x 64 ker
     ("bf16", 256, 256, 384, False), ("bf16", 256, 256, 320, True), ("f16", 64, 2048, 384, True), ("f16", 64, 2048, 448, False), ("bf16", 1024, 1024, 576, False),
     # up to five K-tiles: large members where they nearly fill one round
     ("bf16", 60000, 90, 192, False), ("bf16", 20000, 380, 256, False), ("bf16", 2500, 2501, 320, False), ("f16", 2500, 2501, 288, False),
-    ("f16", 3072, 2048, 288, True), ("bf16", 1024, 6144, 288, True), ("f16", 768, 4096, 256, True),
+    ("f16", 3072, 2048, 288, True), ("bf16", 3072, 2048, 192, True), ("bf16", 1024, 6144, 288, True), ("f16", 768, 4096, 256, True),
     ("bf16", 3840, 1279, 288, True), ("bf16", 1051, 7885, 288, True), ("bf16", 500, 1500, 320, True), ("bf16", 2040, 4090, 320, True)])
 def test_small_kernel_or_family(hc, dt, M, N, K, small):       # noqa: F811
     d = descriptor(M, N, K, dt, "f16" if dt == "f16" else "bf16")
