@@ -30,7 +30,7 @@
 // each (27.6 there, level on 512 tiles).
 //
 // Measured, us, against the 64 x 64 kernel that served these problems: bf16 16 x 3584 x 8192 91.5 -> 11.4 (58.9 MB, 5.2 TB/s),
-// 64 x 3584 x 8192 94 -> 15, 512 x 3584 x 8192 101 -> 40, fp16 2000 x 2000 x 2048 39 -> 20 - 21 (780 - 820 TFLOP/s), fp8 with one fp32 scale per
+// 64 x 3584 x 8192 94 -> 15, 512 x 3584 x 8192 101 -> 40, fp16 2000 x 2000 x 2048 39 -> 19 - 21 (770 - 860 TFLOP/s), fp8 with one fp32 scale per
 // row 1000 x 3584 x 8192 365 -> 37 - 39 (1500 - 1590 TFLOP/s), fp8 E8M0 256 x 512 x 6400 105 -> 7.6; and against the large tile: fp8
 // 1024 x 3584 x 8192 76 -> 36, bf16 2048 x 4096 x 2048 40 -> 34.
 //
