@@ -81,8 +81,8 @@ __device__ __forceinline__ void wait_loads() {                     // all but th
 
 // DT: 0 bf16, 1 fp16, 2 fp8 e4m3.  SC (fp8): 0 unscaled, 1 fp32 scales, 2 E8M0 codes.
 // GRP: 0 dense; 1, 2 grouped (A's scales one per row), 2 with the gated epilogue.  A grouped launch finds its workgroup's
-// tiles on the device (grouped_tiles.h) and walks them one after the other.
-template <int DT, int SC, int TM, int TN, int WM, int WN, int WK, int NST, int GRP = 0>
+// tiles on the device (grouped_tiles.h) and walks them one after the other.  ONCE: B is loaded past the caches.
+template <int DT, int SC, int TM, int TN, int WM, int WN, int WK, int NST, int GRP = 0, bool ONCE = false>
 __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_tiles_kernel(GemmArgs g) {
   constexpr int EB = DT == 2 ? 1 : 2;
   constexpr int kRow = maps::kLargeRowBytes;
@@ -167,8 +167,9 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_tiles_kernel(GemmArgs 
     for (int i = 0; i < kLoads; ++i) {
       const bool is_a = i < PA;
       const int off = kchunk[i] < left ? voff[i] : kOutside;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(is_a ? ra : rb, (lds_ptr)(base + (is_a ? 0 : TM * kRow) + maps::piece_row(wg, is_a ? i : i - PA, 0, NG) * kRow),
-                                               16, off, soff, 0, 0);
+      const lds_ptr to = (lds_ptr)(base + (is_a ? 0 : TM * kRow) + maps::piece_row(wg, is_a ? i : i - PA, 0, NG) * kRow);
+      if (is_a) __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, to, 16, off, soff, 0, 0);
+      else __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, to, 16, off, soff, 0, ONCE ? kOnce : 0);
       AXE_PARANOID_WAIT();
     }
     ++l_stage;

@@ -28,12 +28,17 @@ __device__ __forceinline__ int wave_prefix_sum(int x) {
   x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);   // row_bcast:31 into rows 2 and 3
   return x;
 }
+// Returns whether the weights are best loaded past the caches (kOnce): the host says so by their size, and at least three quarters
+// of the tiles are the only row block of their group, so that no other tile reads their rows of B.  MoE layer of 128 experts, us, through the
+// caches -> past them: fp16 256 / 512 / 1024 tokens 221 -> 199 / 232 -> 211 / 273 -> 254, E8M0 120 -> 107 / 128 -> 114 / 157 -> 143; with half of the
+// rows in one group 259 -> 250 (fp16, 512 tokens).  Everywhere instead: 2048 / 4096 tokens 323 -> 371 / 444 -> 547 (40 % and more of the groups have a
+// second row block, whose tile then reads the weights from memory again).
 // What bounds the table: latency, before a workgroup's first load can be issued.  So: the offsets of the first 128 groups are
 // fetched once, both halves at the same time, and every lane finds its tile's group by bisecting the prefix sums across lanes (six
 // permutes), not by looking at the groups one after the other.  128 groups: about 10 us per launch less (an MoE layer of two products, us, before ->
 // now: fp16 512 / 4096 tokens 252 -> 231 / 441 -> 423, fp8 with fp32 scales 1024 tokens 184 -> 159, E8M0 codes 256 tokens 146 -> 120).
 template <int TM, bool ONE = false>                               // rows of a tile; ONE: a single group of all M rows, no offsets array
-__device__ __forceinline__ void group_tiles(const GemmArgs& g, int lane, int& t_row0, int& t_desc) {
+__device__ __forceinline__ bool group_tiles(const GemmArgs& g, int lane, int& t_row0, int& t_desc) {
   const int G = g.groups, M = (int)g.M, gn = g.grid_n;
   const int* __restrict__ off = g.group_rows;
   struct Chunk {
@@ -63,10 +68,14 @@ __device__ __forceinline__ void group_tiles(const GemmArgs& g, int lane, int& t_
   if (!ONE && G > 64) fetch(64, a1, b1);
   const Chunk c0 = chunk(a0, b0), c1 = chunk(a1, b1);
   int total = __builtin_amdgcn_readlane(c0.incl, 63) + __builtin_amdgcn_readlane(c1.incl, 63);
+  auto single = [&](const Chunk& c) __attribute__((always_inline)) -> int { return __popcll(__ballot(c.rows > 0 && c.rows <= TM)); };
+  int singles = single(c0) + single(c1);                           // groups of one row block
   for (int g0 = 128; g0 < G; g0 += 64) {
     fetch(g0, a0, b0);
-    total += __builtin_amdgcn_readlane(chunk(a0, b0).incl, 63);
+    const Chunk c = chunk(a0, b0);
+    total += __builtin_amdgcn_readlane(c.incl, 63), singles += single(c);
   }
+  const bool once = g.stream_b && 4 * (int64_t)singles * gn >= 3 * (int64_t)total;
   const int per = (total + 7) >> 3;                                // tiles per XCD
   const int s = (int)(blockIdx.x >> 3) + lane * (int)(gridDim.x >> 3);
   const int u = (int)(blockIdx.x & 7) * per + s;                   // position of this lane's tile in the sequence
@@ -97,6 +106,7 @@ __device__ __forceinline__ void group_tiles(const GemmArgs& g, int lane, int& t_
   t_row0 = f_r0 + tm * TM;
   const int left = f_rows - tm * TM;
   t_desc = (left < TM ? left : TM) | (tn << 9) | (f_group << 20);
+  return once;
 }
 
 }  // namespace axe

@@ -155,9 +155,11 @@ __device__ __forceinline__ lds_u8 tile_lds() {
 // second, all workgroups are resident at once (the host launches no more than there are compute units), and tiles
 // of the first GEMM wait for nothing: every wait ends.  Should one not (the limit on polls is reached), the wait
 // is counted in done[M] and the tile is computed from what is there: wrong rows, but every wave leaves the kernel.
+//
+// Grouped: lane t of (tb_row0, tb_desc) describes the workgroup's t-th tile (group_tiles).  ONCE: B is loaded past the caches.
 template <int NB, bool GROUPED, bool BLOCKED, bool GATED = false, bool F16 = false, int MR = 8, bool RAGGED = false, bool OUT32 = false,
-          int PAIR = 0>
-__device__ __forceinline__ void gemm_bf16_256_body(const GemmArgs& g, const PairSync ps = PairSync{}) {
+          int PAIR = 0, bool ONCE = false>
+__device__ __forceinline__ void gemm_bf16_256_body(const GemmArgs& g, int tb_row0 = 0, int tb_desc = 0, const PairSync ps = PairSync{}) {
   static_assert(PAIR == 0 || (GROUPED && !RAGGED && !OUT32), "a fused pair is made of two grouped kernels");
   static_assert(!OUT32 || ((!GROUPED || RAGGED) && NB == 256), "the fp32 output exists for the dense 256-wide kernels");
   static_assert(!RAGGED || (GROUPED && !GATED && NB == 256), "ragged edges are handled by the grouped 256-wide kernel");
@@ -200,8 +202,6 @@ __device__ __forceinline__ void gemm_bf16_256_body(const GemmArgs& g, const Pair
   struct Tile {
     __amdgpu_buffer_rsrc_t ra, rb;
   };
-  int tb_row0 = 0, tb_desc = 0;                                    // grouped: lane t = the workgroup's t-th tile
-  if constexpr (GROUPED) group_tiles<TM, RAGGED>(g, lane, tb_row0, tb_desc);
   auto table_rows = [&](int t) __attribute__((always_inline)) -> int { return t < 64 ? desc_rows(__builtin_amdgcn_readlane(tb_desc, t)) : 0; };
   // dense: v = tile id; grouped: v = index into the workgroup's table
   auto describe = [&](int v) __attribute__((always_inline)) -> Tile {
@@ -290,7 +290,7 @@ __device__ __forceinline__ void gemm_bf16_256_body(const GemmArgs& g, const Pair
   auto b_load = [&](int T, int i, int slot_off, bool cross) __attribute__((always_inline)) {
     const bool nx = cross && T >= nk;
     __builtin_amdgcn_raw_ptr_buffer_load_lds(nx ? nxt.rb : cur.rb, (lds_ptr)(lds3 + slot_off + maps::piece_row(w, i, 0, 4) * kRow), 16,
-                                             b_voff_p[i], (nx ? T - nk : T) * b_kstep, 0, 0);
+                                             b_voff_p[i], (nx ? T - nk : T) * b_kstep, 0, ONCE ? kOnce : 0);
     AXE_PARANOID_WAIT();
   };
 
@@ -610,36 +610,51 @@ __device__ __forceinline__ void gemm_bf16_256_body(const GemmArgs& g, const Pair
   }
 }
 
+// A grouped kernel's tiles, worked out on the device, and its body on them.  128-row tiles come in both cache policies for B: the
+// table says which (larger tiles go with groups of several row blocks).
+template <bool GATED, bool F16, int MR, bool RAGGED = false, bool OUT32 = false, int PAIR = 0>
+__device__ __forceinline__ void gemm_bf16_256_grouped_body(const GemmArgs& g, const PairSync ps = PairSync{}) {
+  int row0, desc;
+  const bool once = group_tiles<32 * MR, RAGGED>(g, threadIdx.x & 63, row0, desc);
+  if constexpr (MR == 4) {
+    if (once) {
+      gemm_bf16_256_body<256, true, true, GATED, F16, MR, RAGGED, OUT32, PAIR, true>(g, row0, desc, ps);
+      return;
+    }
+  }
+  gemm_bf16_256_body<256, true, true, GATED, F16, MR, RAGGED, OUT32, PAIR>(g, row0, desc, ps);
+}
+
 // (plain kernels around the template: a __global__ template would be instantiated by the host pass
 //  too, which cannot parse the register constraints of the asm statements)
 __global__ __launch_bounds__(256, 1) void gemm_bf16_256_kernel(GemmArgs g) { gemm_bf16_256_body<256, false, false>(g); }
 __global__ __launch_bounds__(256, 1) void gemm_bf16_256x224_kernel(GemmArgs g) { gemm_bf16_256_body<224, false, false>(g); }
 __global__ __launch_bounds__(256, 1) void gemm_bf16_256_blocked_kernel(GemmArgs g) { gemm_bf16_256_body<256, false, true>(g); }
-__global__ __launch_bounds__(256, 1) void gemm_bf16_256_grouped_kernel(GemmArgs g) { gemm_bf16_256_body<256, true, true>(g); }
-__global__ __launch_bounds__(256, 1) void gemm_bf16_256_grouped_gated_kernel(GemmArgs g) { gemm_bf16_256_body<256, true, true, true>(g); }
+__global__ __launch_bounds__(256, 1) void gemm_bf16_256_grouped_kernel(GemmArgs g) { gemm_bf16_256_grouped_body<false, false, 8>(g); }
+__global__ __launch_bounds__(256, 1) void gemm_bf16_256_grouped_gated_kernel(GemmArgs g) { gemm_bf16_256_grouped_body<true, false, 8>(g); }
 // IEEE binary16 inputs and output: the dense kernel (plain or blocked operands) and the grouped ones
 __global__ __launch_bounds__(256, 1) void gemm_f16_256_kernel(GemmArgs g) { gemm_bf16_256_body<256, false, true, false, true>(g); }
-__global__ __launch_bounds__(256, 1) void gemm_f16_256_grouped_kernel(GemmArgs g) { gemm_bf16_256_body<256, true, true, false, true>(g); }
-__global__ __launch_bounds__(256, 1) void gemm_f16_256_grouped_gated_kernel(GemmArgs g) { gemm_bf16_256_body<256, true, true, true, true>(g); }
+__global__ __launch_bounds__(256, 1) void gemm_f16_256_grouped_kernel(GemmArgs g) { gemm_bf16_256_grouped_body<false, true, 8>(g); }
+__global__ __launch_bounds__(256, 1) void gemm_f16_256_grouped_gated_kernel(GemmArgs g) { gemm_bf16_256_grouped_body<true, true, 8>(g); }
 // grouped, tiles of 128 rows (small groups)
 // fp32 output (plain or blocked operands)
 __global__ __launch_bounds__(256, 1) void gemm_bf16_256_f32out_kernel(GemmArgs g) { gemm_bf16_256_body<256, false, true, false, false, 8, false, true>(g); }
 __global__ __launch_bounds__(256, 1) void gemm_f16_256_f32out_kernel(GemmArgs g) { gemm_bf16_256_body<256, false, true, false, true, 8, false, true>(g); }
 // dense with ragged edges and an fp32 output (any M, N a multiple of 4)
-__global__ __launch_bounds__(256, 1) void gemm_bf16_256_ragged_f32out_kernel(GemmArgs g) { gemm_bf16_256_body<256, true, true, false, false, 8, true, true>(g); }
-__global__ __launch_bounds__(256, 1) void gemm_f16_256_ragged_f32out_kernel(GemmArgs g) { gemm_bf16_256_body<256, true, true, false, true, 8, true, true>(g); }
+__global__ __launch_bounds__(256, 1) void gemm_bf16_256_ragged_f32out_kernel(GemmArgs g) { gemm_bf16_256_grouped_body<false, false, 8, true, true>(g); }
+__global__ __launch_bounds__(256, 1) void gemm_f16_256_ragged_f32out_kernel(GemmArgs g) { gemm_bf16_256_grouped_body<false, true, 8, true, true>(g); }
 // dense with ragged edges (any M, N a multiple of 8)
-__global__ __launch_bounds__(256, 1) void gemm_bf16_256_ragged_kernel(GemmArgs g) { gemm_bf16_256_body<256, true, true, false, false, 8, true>(g); }
-__global__ __launch_bounds__(256, 1) void gemm_f16_256_ragged_kernel(GemmArgs g) { gemm_bf16_256_body<256, true, true, false, true, 8, true>(g); }
-__global__ __launch_bounds__(256, 1) void gemm_bf16_128_grouped_kernel(GemmArgs g) { gemm_bf16_256_body<256, true, true, false, false, 4>(g); }
-__global__ __launch_bounds__(256, 1) void gemm_bf16_128_grouped_gated_kernel(GemmArgs g) { gemm_bf16_256_body<256, true, true, true, false, 4>(g); }
-__global__ __launch_bounds__(256, 1) void gemm_f16_128_grouped_kernel(GemmArgs g) { gemm_bf16_256_body<256, true, true, false, true, 4>(g); }
-__global__ __launch_bounds__(256, 1) void gemm_f16_128_grouped_gated_kernel(GemmArgs g) { gemm_bf16_256_body<256, true, true, true, true, 4>(g); }
+__global__ __launch_bounds__(256, 1) void gemm_bf16_256_ragged_kernel(GemmArgs g) { gemm_bf16_256_grouped_body<false, false, 8, true>(g); }
+__global__ __launch_bounds__(256, 1) void gemm_f16_256_ragged_kernel(GemmArgs g) { gemm_bf16_256_grouped_body<false, true, 8, true>(g); }
+__global__ __launch_bounds__(256, 1) void gemm_bf16_128_grouped_kernel(GemmArgs g) { gemm_bf16_256_grouped_body<false, false, 4>(g); }
+__global__ __launch_bounds__(256, 1) void gemm_bf16_128_grouped_gated_kernel(GemmArgs g) { gemm_bf16_256_grouped_body<true, false, 4>(g); }
+__global__ __launch_bounds__(256, 1) void gemm_f16_128_grouped_kernel(GemmArgs g) { gemm_bf16_256_grouped_body<false, true, 4>(g); }
+__global__ __launch_bounds__(256, 1) void gemm_f16_128_grouped_gated_kernel(GemmArgs g) { gemm_bf16_256_grouped_body<true, true, 4>(g); }
 // the fused pair: both GEMMs of an MoE layer's expert computation in one launch (gated first GEMM, plain second)
 template <bool F16, int MR>
 __device__ __forceinline__ void grouped_pair_body(const GemmArgs& g1, const GemmArgs& g2, const PairSync& ps) {
-  gemm_bf16_256_body<256, true, true, true, F16, MR, false, false, 1>(g1, ps);
-  gemm_bf16_256_body<256, true, true, false, F16, MR, false, false, 2>(g2, ps);
+  gemm_bf16_256_grouped_body<true, F16, MR, false, false, 1>(g1, ps);
+  gemm_bf16_256_grouped_body<false, F16, MR, false, false, 2>(g2, ps);
 }
 __global__ __launch_bounds__(256, 1) void gemm_bf16_256_grouped_pair_kernel(GemmArgs g1, GemmArgs g2, PairSync ps) { grouped_pair_body<false, 8>(g1, g2, ps); }
 __global__ __launch_bounds__(256, 1) void gemm_f16_256_grouped_pair_kernel(GemmArgs g1, GemmArgs g2, PairSync ps) { grouped_pair_body<true, 8>(g1, g2, ps); }

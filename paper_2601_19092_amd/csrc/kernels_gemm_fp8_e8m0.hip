@@ -60,6 +60,11 @@ __device__ __forceinline__ void mfma_scaled(f32x4& acc, i32x8 first, i32x8 secon
                : "+a"(acc)
                : "v"(first), "v"(second), "v"(s_first), "v"(s_second));
 }
+// The workgroup's LDS, one array for every body of a kernel
+__device__ __forceinline__ lds_u8 tile_lds() {
+  __shared__ __attribute__((aligned(1024))) uint8_t lds_mem[kLds];
+  return (lds_u8)lds_mem;
+}
 }  // namespace
 
 // ROWS: one E8M0 code per row of A and k block (scale_a is (M, K / 128)) instead of one per 128 x 128 block; B's
@@ -74,14 +79,14 @@ __device__ __forceinline__ void mfma_scaled(f32x4& acc, i32x8 first, i32x8 secon
 // MR = fragment rows per wave: 8 (tiles of 256 rows), or 4 for the grouped kernel when groups are small (tiles of 128
 // rows, a wave owns 64 x 128: a K-step is 2 x 16 MFMAs per wave and moves half as much of A; as in the 16-bit kernel
 // the A blocks in LDS keep their places, half of each is used).
-template <bool ROWS, bool GROUPED = false, bool GATED = false, int MR = 8>
-__device__ __forceinline__ void gemm_fp8_e8m0_256_body(const GemmArgs& g) {
+// Grouped: lane t of (tb_row0, tb_desc) describes the workgroup's t-th tile (group_tiles).  ONCE: B is loaded past the caches.
+template <bool ROWS, bool GROUPED = false, bool GATED = false, int MR = 8, bool ONCE = false>
+__device__ __forceinline__ void gemm_fp8_e8m0_256_body(const GemmArgs& g, int tb_row0 = 0, int tb_desc = 0) {
   static_assert(!GROUPED || ROWS, "the grouped kernel scales A per row");
   static_assert(!GATED || GROUPED, "the gated epilogue exists for the grouped kernel");
   static_assert(MR == 8 || (MR == 4 && GROUPED), "128-row tiles exist for the grouped kernel");
   constexpr int TM = 32 * MR, WR = 16 * MR;                        // rows of a tile, of a wave's part of it
-  __shared__ __attribute__((aligned(1024))) uint8_t lds_mem[kLds];
-  const lds_u8 lds3 = (lds_u8)lds_mem;                             // 32-bit LDS addresses
+  const lds_u8 lds3 = tile_lds();                                  // 32-bit LDS addresses
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -99,8 +104,6 @@ __device__ __forceinline__ void gemm_fp8_e8m0_256_body(const GemmArgs& g) {
     const uint8_t *sa, *sb, *sb2;                                  // E8M0 codes of this wave's row block (not ROWS) and column block(s), one per K-tile
     int sa_row;                                                    // ROWS: the lane's row of fragment row 0 (fragment row i: 16 i further)
   };
-  int tb_row0 = 0, tb_desc = 0;
-  if constexpr (GROUPED) group_tiles<TM, false>(g, lane, tb_row0, tb_desc);
   auto table_rows = [&](int t) __attribute__((always_inline)) -> int { return t < 64 ? desc_rows(__builtin_amdgcn_readlane(tb_desc, t)) : 0; };
   auto describe = [&](int v) __attribute__((always_inline)) -> Tile {
     Tile t;
@@ -236,7 +239,7 @@ __device__ __forceinline__ void gemm_fp8_e8m0_256_body(const GemmArgs& g) {
   auto b_load = [&](int T, int i, int slot_off, bool cross) __attribute__((always_inline)) {
     const bool nx = cross && T >= nk;
     __builtin_amdgcn_raw_ptr_buffer_load_lds(nx ? nxt.rb : cur.rb, (lds_ptr)(lds3 + slot_off + maps::piece_row(w, i, 0, 4) * kRow), 16, b_voff_p[i],
-                                             (nx ? T - nk : T) * kRow, 0, 0);
+                                             (nx ? T - nk : T) * kRow, 0, ONCE ? kOnce : 0);
     AXE_PARANOID_WAIT();
   };
 
@@ -513,13 +516,27 @@ __device__ __forceinline__ void gemm_fp8_e8m0_256_body(const GemmArgs& g) {
   }
 }
 
+// A grouped kernel's tiles, worked out on the device, and its body on them (both cache policies for B, as in the 16-bit kernels)
+template <bool GATED, int MR>
+__device__ __forceinline__ void gemm_fp8_e8m0_grouped_body(const GemmArgs& g) {
+  int row0, desc;
+  const bool once = group_tiles<32 * MR>(g, threadIdx.x & 63, row0, desc);
+  if constexpr (MR == 4) {
+    if (once) {
+      gemm_fp8_e8m0_256_body<true, true, GATED, MR, true>(g, row0, desc);
+      return;
+    }
+  }
+  gemm_fp8_e8m0_256_body<true, true, GATED, MR>(g, row0, desc);
+}
+
 __global__ __launch_bounds__(256, 1) void gemm_fp8_e8m0_256_kernel(GemmArgs g) { gemm_fp8_e8m0_256_body<false>(g); }
 __global__ __launch_bounds__(256, 1) void gemm_fp8_e8m0_256_rows_kernel(GemmArgs g) { gemm_fp8_e8m0_256_body<true>(g); }
-__global__ __launch_bounds__(256, 1) void gemm_fp8_e8m0_256_grouped_kernel(GemmArgs g) { gemm_fp8_e8m0_256_body<true, true>(g); }
-__global__ __launch_bounds__(256, 1) void gemm_fp8_e8m0_256_grouped_gated_kernel(GemmArgs g) { gemm_fp8_e8m0_256_body<true, true, true>(g); }
+__global__ __launch_bounds__(256, 1) void gemm_fp8_e8m0_256_grouped_kernel(GemmArgs g) { gemm_fp8_e8m0_grouped_body<false, 8>(g); }
+__global__ __launch_bounds__(256, 1) void gemm_fp8_e8m0_256_grouped_gated_kernel(GemmArgs g) { gemm_fp8_e8m0_grouped_body<true, 8>(g); }
 // grouped, tiles of 128 rows (small groups)
-__global__ __launch_bounds__(256, 1) void gemm_fp8_e8m0_128_grouped_kernel(GemmArgs g) { gemm_fp8_e8m0_256_body<true, true, false, 4>(g); }
-__global__ __launch_bounds__(256, 1) void gemm_fp8_e8m0_128_grouped_gated_kernel(GemmArgs g) { gemm_fp8_e8m0_256_body<true, true, true, 4>(g); }
+__global__ __launch_bounds__(256, 1) void gemm_fp8_e8m0_128_grouped_kernel(GemmArgs g) { gemm_fp8_e8m0_grouped_body<false, 4>(g); }
+__global__ __launch_bounds__(256, 1) void gemm_fp8_e8m0_128_grouped_gated_kernel(GemmArgs g) { gemm_fp8_e8m0_grouped_body<true, 4>(g); }
 
 hipError_t launch_gemm_fp8_e8m0_256(const GemmArgs& g, hipStream_t s) {
   const int ntiles = g.grid_m * g.grid_n;

@@ -7,7 +7,7 @@
 // are 18 - 23 % busy: a K-step takes 1.1 us where the same body takes 0.5 there.  On what has not been found out (candidates: the rows
 // missing from half-empty tiles' A, a tile's epilogue between two K loops, the table, the last tiles).  An MoE layer of 128
 // experts (8 per token, N, K = 1536, 2048 gated and 2048, 768), us, streaming -> this: 256 tokens 108 + 55 -> 87 + 57, 1024 tokens 287 + 126
-// -> 109 + 72 (604 MB of weights: 3.3 TB/s), 4096 tokens 990 + 403 -> 193 + 137.  Other tiles, 1024 / 4096 tokens: one tile at a time
+// -> 109 + 72 (604 MB of weights: 3.3 TB/s), 4096 tokens 990 + 403 -> 193 + 137 (all with a tile table that took 10 us longer per launch than now).  Other tiles, 1024 / 4096 tokens: one tile at a time
 // without running on 112 + 85 / 201 + 172; 64 x 128 in four waves, two workgroups per compute unit 105 + 70 / 217 + 151, in eight waves
 // 127 + 83 / 278 + 177; 32 x 128 122 + 76 / 290 + 195; 128 x 128 with two stages 163 + 103 / 305 + 198.
 #include "gemm_tiles.h"
@@ -18,9 +18,9 @@ namespace axe {
 
 namespace {
 constexpr TileShape kShape = kTileFamily[kGroupedMember];
-template <int GRP>
+template <int GRP, bool ONCE>
 void launch(const GemmArgs& g, unsigned nwg, hipStream_t s) {
-  hipLaunchKernelGGL((tiles::gemm_tiles_kernel<2, 1, kShape.tm, kShape.tn, kShape.wm, kShape.wn, kShape.wk, kShape.nst, GRP>), dim3(nwg),
+  hipLaunchKernelGGL((tiles::gemm_tiles_kernel<2, 1, kShape.tm, kShape.tn, kShape.wm, kShape.wn, kShape.wk, kShape.nst, GRP, ONCE>), dim3(nwg),
                      dim3(64 * kShape.wm * kShape.wn * kShape.wk), 0, s, g);
 }
 }  // namespace
@@ -33,8 +33,11 @@ hipError_t launch_gemm_tiles_grouped(const GemmArgs& g0, hipStream_t s) {
   int64_t nwg = std::max<int64_t>(cu_count(), (worst + 63) / 64);  // a wave keeps the workgroup's tiles one per lane
   nwg = (std::min(nwg, worst) + 7) / 8 * 8;                        // the tile sequence is cut into 8 parts, one per XCD
   if (nwg > 0x7fffffff) return hipErrorInvalidValue;
-  if (g.gated) launch<2>(g, (unsigned)nwg, s);
-  else launch<1>(g, (unsigned)nwg, s);
+  // Weights past the caches where most groups should have one row block: the host's guess from the average, since a second body in this kernel
+  // spills.  us: 256 / 512 / 1024 tokens 130 -> 127 / 130 -> 122 / 158 -> 151; guessed wrong, all rows in one group 46.6 -> 47.4, in four 44.7 -> 46.1.
+  const bool once = g.stream_b && 2 * g.M <= kShape.tm * (int64_t)g.groups;
+  if (g.gated) once ? launch<2, true>(g, (unsigned)nwg, s) : launch<2, false>(g, (unsigned)nwg, s);
+  else once ? launch<1, true>(g, (unsigned)nwg, s) : launch<1, false>(g, (unsigned)nwg, s);
   return hipGetLastError();
 }
 
