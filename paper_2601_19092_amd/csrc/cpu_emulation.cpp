@@ -325,7 +325,8 @@ hipError_t launch_gemm_bf16_256_ragged(const GemmArgs&, hipStream_t) { return hi
 hipError_t launch_pair_sync_clear(int32_t*, int64_t, hipStream_t) { return hipErrorNotSupported; }
 hipError_t pair_static_workspace(int32_t**) { return hipErrorNotSupported; }
 hipError_t launch_gemm_bf16_256_grouped_pair(const GemmArgs&, const GemmArgs&, int32_t*, int, int, hipStream_t) { return hipErrorNotSupported; }
-hipError_t launch_gemm_grouped_stream(const GemmArgs&, hipStream_t) { return hipErrorNotSupported; }
+static int g_narrow = -1;         // whether the last grouped GEMM of few rows per group would have gone to the narrow tiles; -1: none yet
+hipError_t launch_gemm_grouped_stream(const GemmArgs& g, hipStream_t) { return g_narrow = narrow_fits(g), hipErrorNotSupported; }
 hipError_t launch_gemm_fp8_256(const GemmArgs&, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_gemm_fp8_e8m0_256(const GemmArgs&, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_gemm_fp8_e8m0_256_grouped(const GemmArgs&, hipStream_t) { return hipErrorNotSupported; }
@@ -343,6 +344,7 @@ extern "C" void axe_hostcheck_set_buffers(int64_t src_bytes, int64_t dst_bytes) 
 }
 extern "C" int axe_hostcheck_eval_by_blocks(void) { return axe::g_blocks; }
 extern "C" int axe_hostcheck_gemm_member(void) { return axe::g_member; }
+extern "C" int axe_hostcheck_grouped_narrow(void) { return axe::g_narrow; }
 extern "C" void axe_hostcheck_plan_only(int on) { axe::g_plan_only = on; }
 extern "C" int64_t axe_hostcheck_workgroups(void) { return (int64_t)axe::g_workgroups; }
 extern "C" int axe_hostcheck_transpose_variant(void) { return axe::g_variant; }

@@ -147,7 +147,7 @@ struct GemmArgs {
   int32_t gated;                   // 1: store silu(gate) * up (B's rows interleave gate and up in runs of 16), C is N / 2 wide
   int64_t ldg;
   int32_t stream_b;                // 1: the groups' weights are too many to stay in the last-level cache from one call to the next
-  int32_t* clear;                  // streaming kernel: a word it sets to zero (a pair's status), or null
+  int32_t* clear;                  // streaming kernel, narrow tiles: a word they set to zero (a pair's status), or null
 };
 
 // Hand-over between the two grouped GEMMs of a fused pair (the first GEMM's output is the second GEMM's A).  A row

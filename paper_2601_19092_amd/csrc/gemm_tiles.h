@@ -92,7 +92,7 @@ __device__ __forceinline__ void wait_loads() {                     // all but th
   asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N) : "memory");
 }
 
-// DT: 0 bf16, 1 fp16, 2 fp8 e4m3.  SC (fp8): 0 unscaled, 1 fp32 scales, 2 E8M0 codes.
+// DT: 0 bf16, 1 fp16, 2 fp8 e4m3.  SC (fp8): 0 unscaled, 1 fp32 scales, 2 E8M0 codes, 3 E8M0 codes multiplied as floats.
 // GRP: 0 dense; 1, 2 grouped (A's scales one per row), 2 with the gated epilogue.  A grouped launch finds its workgroup's
 // tiles on the device (grouped_tiles.h) and walks them one after the other.  ONCE: B is loaded past the caches.
 template <int DT, int SC, int TM, int TN, int WM, int WN, int WK, int NST, int GRP = 0, bool ONCE = false>
@@ -113,6 +113,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_tiles_kernel(GemmArgs 
   const lds_u8 lds3 = (lds_u8)lds_mem;
 
   const int lane = threadIdx.x & 63;
+  if (GRP != 0 && g.clear && blockIdx.x == 0 && threadIdx.x == 0) *g.clear = 0;
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int kpart = w / NG, wg = w % NG;                           // group, wave inside the group
   const int wm = wg / WN, wn = wg % WN;
@@ -123,6 +124,9 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_tiles_kernel(GemmArgs 
   // whole time, 3 %).  Stages past the last K-tile multiply zeros.
   constexpr bool kHalfTrip = GRP != 0 && U == 4;
   constexpr int kWhole = kHalfTrip ? 2 : U;
+  // A trip's scales are worked out at the end of the trip before, in either of its ends: at a common place the compiler's own wait for them
+  // would allow no more loads in flight than follow them in half a trip.  (The 128-row tile has no registers for that, and a ring no longer.)
+  constexpr bool kSpreadAhead = kHalfTrip && NST > 4;
   const int ns = ((nk + WK - 1) / WK + kWhole - 1) / kWhole * kWhole;
   const int a_pitch = (int)(g.lda * EB), b_pitch = (int)(g.ldb * EB);
   // ---- HBM -> LDS: this wave's pieces of a K-tile: of A, then of B
@@ -203,7 +207,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_tiles_kernel(GemmArgs 
   //      One load per fragment row and one for the column block serve four stages; they are issued a trip ahead.
   //      With the gated epilogue the wave's gate and up columns lie in one column block each.
   constexpr int kScaleLoads = SC ? MF + NB : 0;
-  constexpr int SB = SC == 2 ? 1 : 4;                              // bytes of a stored scale
+  constexpr int SB = SC >= 2 ? 1 : 4;                              // bytes of a stored scale
   const bool by_row = GRP != 0 || g.scale_a_rows == 1;
   int sa_off[SC ? MF : 1];
 #pragma unroll
@@ -235,7 +239,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_tiles_kernel(GemmArgs 
       const int kt = (s0 + fq) * WK + kpart;
       const int o = (kt < nk ? kt : nk - 1) * SB;
       auto load = [&](__amdgpu_buffer_rsrc_t r, int off) -> uint32_t {
-        if constexpr (SC == 2) return __builtin_amdgcn_raw_buffer_load_b8(r, off, 0, 0);
+        if constexpr (SC >= 2) return __builtin_amdgcn_raw_buffer_load_b8(r, off, 0, 0);
         else return __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0);
       };
 #pragma unroll
@@ -250,6 +254,12 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_tiles_kernel(GemmArgs 
   auto spread_scales = [&](int s0) __attribute__((always_inline)) -> bool {
     bool far = false;
     if constexpr (SC != 0) {
+      if constexpr (GRP != 0) {                                    // not before: the compiler's own wait for them would be stricter than the counted ones
+#pragma unroll
+        for (int b = 0; b < NB; ++b) asm volatile("" : "+v"(sb_raw[b]));
+#pragma unroll
+        for (int i = 0; i < MF; ++i) asm volatile("" : "+v"(sa_raw[i]));
+      }
       const bool in = (s0 + fq) * WK + kpart < nk;                 // stages past the last one multiply zeros by zero
 #pragma unroll
       for (int b = 0; b < NB; ++b)
@@ -260,7 +270,8 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_tiles_kernel(GemmArgs 
             v = (sa_raw[i] + sb_raw[b] - 127u) << 23;
             far = far || (in && sa_raw[i] + sb_raw[b] - 128u >= 254u);
           } else {
-            v = __builtin_bit_cast(uint32_t, __builtin_bit_cast(float, sa_raw[i]) * __builtin_bit_cast(float, sb_raw[b]));
+            const int up = SC == 3 ? 23 : 0;                       // a code as the exponent of a float
+            v = __builtin_bit_cast(uint32_t, __builtin_bit_cast(float, sa_raw[i] << up) * __builtin_bit_cast(float, sb_raw[b] << up));
           }
           v = in ? v : 0u;
           const auto h = __builtin_amdgcn_permlane32_swap(v, v, false, false);
@@ -368,6 +379,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_tiles_kernel(GemmArgs 
   AXE_PARANOID_SYNC();
   read_frags(f[0], 0);
 
+  if constexpr (kSpreadAhead) spread_scales(0);
   int cur = 0;                                                     // slot of the stage whose fragments are in f[u & 1]
   for (int t = 1;; ++t) {
 #pragma unroll
@@ -397,7 +409,17 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_tiles_kernel(GemmArgs 
     multiply(f[u & 1], u, far);
     cur = nxt;
   };
-  if constexpr (!kCodesOnly)
+  if constexpr (kSpreadAhead) {
+    for (; s0 < ns; s0 += U) {
+      stage(0, std::false_type{}), stage(1, std::false_type{});
+      if (s0 + 2 >= ns) {
+        spread_scales(0);
+        break;
+      }
+      stage(2, std::false_type{}), stage(3, std::false_type{});
+      spread_scales(s0 + U >= ns ? 0 : s0 + U);
+    }
+  } else if constexpr (!kCodesOnly) {
     for (; s0 < ns; s0 += U) {
       if (spread_scales(s0)) break;
 #pragma unroll
@@ -406,6 +428,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_tiles_kernel(GemmArgs 
         stage(u, std::false_type{});
       }
     }
+  }
   if constexpr (SC == 2)
     for (; s0 < ns; s0 += U) {
       spread_codes(s0);

@@ -80,6 +80,8 @@ inline int grouped_fp8_tile_rows(int64_t M, int groups, int tile_m) {
 }
 // grouped, few rows per group: one workgroup per (group, 128 rows of B), weights streamed once, no LDS
 hipError_t launch_gemm_grouped_stream(const GemmArgs& g, hipStream_t s);
+// the same on narrow tiles whose weights pass through LDS; narrow_fits(g)
+hipError_t launch_gemm_grouped_narrow(const GemmArgs& g, hipStream_t s);
 hipError_t launch_gemm_fp8_256(const GemmArgs& g, hipStream_t s);
 // fp8 with E8M0 block scales (or none) on the matrix cores' scale path; same shape requirements
 hipError_t launch_gemm_fp8_e8m0_256(const GemmArgs& g, hipStream_t s);
@@ -106,6 +108,24 @@ inline bool small_preload_fits(int64_t M, int64_t N, int64_t K, int64_t lda, int
   if (!enabled || M % 64 || N % 64 || K % 64 || K > 512 || K <= 0) return false;
   if (ldc % 4 || 64 * lda * 2 >= (int64_t(1) << 31) || 64 * ldb * 2 >= (int64_t(1) << 31)) return false;
   return (M / 64) * (N / 64) <= cu_count();
+}
+
+// Whether the narrow tiles take a grouped problem of few rows per group from the streaming kernel: plain weights, at least as many K-tiles as their ring
+// has stages, tile columns that fit the table's 11 bits; and where they are the faster ones.  us, streaming / narrow (16-bit: 32-row, fp8: 16-row tiles):
+//   - the table costs every workgroup a pass over the groups: 4096 x 256 x 1152 (groups x N x K) fp16 4 rows per group 398 / 403, 1 row 243 / 267, fp8 135 / 160;
+//     512 x 1024 x 1024 fp16 177 / 162, fp8 96 / 84;
+//   - few tiles: the streaming kernel splits K over waves, in fp8 by two only.  fp16 8 x 1024 x 2048 (128 tiles) 4 rows 8.3 / 9.9, 12 rows 12.6 / 10.0,
+//     16 x 512 x 1024 8 rows 6.5 / 6.9, 12 rows 7.9 / 7.0, 4 x 512 x 1024 (32 tiles) 16 rows 5.9 / 6.8, 24 rows 7.9 / 6.9, 128 x 1024 x 1024 (512) 1 row in four groups
+//     12.3 / 13.4, 64 x 2816 x 2048 (704) 33.6 / 29.2; fp8 8 x 1024 x 2048 1 row 9.6 / 7.6, 1 x 4096 x 4096 (64) 17.5 / 11.2, 16 x 512 x 1024 2 rows 5.2 / 5.7, 4 rows
+//     6.2 / 5.7, 4 x 512 x 1024 8 rows 5.6 / 5.7, 12 rows 6.9 / 5.7, 64 x 512 x 768 (512) 1 row 7.2 / 7.0.
+constexpr int kNarrowStages = 6;
+inline bool narrow_fits(const GemmArgs& g) {
+  const int eb = g.fp8 ? 1 : 2;
+  if (g.b_kstep != 128 || g.b_tpb_shift || g.b_blk_stride != 256 * g.ldb || g.K * eb % 128 || g.K * eb / 128 < kNarrowStages || g.N % 64 || g.N / 64 > 2048) return false;
+  const int64_t active = g.M < g.groups ? g.M : g.groups, tiles = active * (g.N / 64), cus = cu_count();
+  if (g.groups > 1024) return false;
+  if (g.fp8) return g.K >= 2048 || 2 * tiles > cus || g.M > 8 * (int64_t)g.groups || (2 * tiles == cus && g.M >= 4 * (int64_t)g.groups);
+  return tiles > 2 * cus || (g.M > 64 && g.M > 8 * (int64_t)g.groups);
 }
 
 // Whether two planned grouped problems (the second reading what the first writes) can run as one launch: both on

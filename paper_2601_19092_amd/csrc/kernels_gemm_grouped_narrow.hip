@@ -1,0 +1,67 @@
+// Grouped GEMM for few rows per group on narrow tiles (gemm_tiles.h): 16, 32 or 64 rows of a group times 64 rows of its B image, all of
+// K, two workgroups per compute unit, each walking its tiles as one pipeline.  Any of the library's inputs with plain weights; blocked
+// weights, short K, many groups and launches of few tiles stay with the streaming kernel (narrow_fits).
+//
+// What bounds it: HBM, reading the active groups' weights once.  A bare stream of loads into LDS carries 6.75 - 7.0 TB/s through panels of 64 rows
+// x 128 bytes with the non-temporal policy (6.2 - 6.3 without, 6.1 - 6.5 through panels of 256 and 128 rows of 4096 bytes), where loads into
+// registers in the operand layout -- the streaming kernel -- ask for half lines and lose 10 % with that policy.  Hence weights through
+// LDS, whole 128-byte lines, 64 of them per K-step, and rings of 60 - 80 KiB in two workgroups: one's table, first loads and stores lie
+// behind the other's stream.
+//
+// Measured, us, streaming kernel -> this (an MoE layer of 128 experts, 8 per token, both products): fp16 4 / 16 / 64 tokens 51 -> 49 / 125 -> 118 /
+// 192 -> 174 (1.15 GB: 6.6 TB/s), 128 tokens 205 -> 183; fp8 (either scales) 1 / 16 / 64 / 128 tokens 17 -> 14 / 73 -> 61 / 108 -> 89 / 128 -> 96.
+#include "gemm_tiles.h"
+
+#include <algorithm>
+
+namespace axe {
+
+namespace {
+struct NarrowTile {
+  int tm, tn, wm, wn, nst;
+};
+constexpr NarrowTile kNarrow[] = {{16, 64, 1, 2, kNarrowStages}, {32, 64, 2, 2, kNarrowStages}, {64, 64, 2, 2, kNarrowStages - 1}};
+
+template <int DT, int SC, int V, bool ONCE>
+void launch_as(const GemmArgs& g, unsigned nwg, hipStream_t s) {
+  constexpr NarrowTile t = kNarrow[V];
+  static_assert(2 * t.nst * (t.tm + t.tn) * maps::kLargeRowBytes <= 160 * 1024, "two workgroups per compute unit");
+  if (g.gated)
+    hipLaunchKernelGGL((tiles::gemm_tiles_kernel<DT, SC, t.tm, t.tn, t.wm, t.wn, 1, t.nst, 2, ONCE>), dim3(nwg), dim3(64 * t.wm * t.wn), 0, s, g);
+  else
+    hipLaunchKernelGGL((tiles::gemm_tiles_kernel<DT, SC, t.tm, t.tn, t.wm, t.wn, 1, t.nst, 1, ONCE>), dim3(nwg), dim3(64 * t.wm * t.wn), 0, s, g);
+}
+
+template <int V>
+hipError_t launch(const GemmArgs& g0, hipStream_t s) {
+  constexpr NarrowTile t = kNarrow[V];
+  GemmArgs g = g0;
+  g.grid_n = (int32_t)(g.N / t.tn);
+  const int64_t worst = (g.M / t.tm + std::min<int64_t>(g.M, g.groups)) * (int64_t)g.grid_n;
+  int64_t nwg = std::max<int64_t>(2 * cu_count(), (worst + 63) / 64);   // a wave keeps the workgroup's tiles one per lane
+  nwg = (std::min(nwg, worst) + 7) / 8 * 8;                        // the tile sequence is cut into 8 parts, one per XCD
+  if (nwg > 0x7fffffff) return hipErrorInvalidValue;
+  const unsigned n = (unsigned)nwg;
+  auto go = [&](auto dt, auto sc) {
+    if (g.stream_b) launch_as<decltype(dt)::value, decltype(sc)::value, V, true>(g, n, s);
+    else launch_as<decltype(dt)::value, decltype(sc)::value, V, false>(g, n, s);
+  };
+  using std::integral_constant;
+  if (!g.fp8 && g.f16) go(integral_constant<int, 1>{}, integral_constant<int, 0>{});
+  else if (!g.fp8) go(integral_constant<int, 0>{}, integral_constant<int, 0>{});
+  else if (!g.scale_a) go(integral_constant<int, 2>{}, integral_constant<int, 0>{});
+  else if (!g.scale_e8m0) go(integral_constant<int, 2>{}, integral_constant<int, 1>{});
+  else go(integral_constant<int, 2>{}, integral_constant<int, 3>{});
+  return hipGetLastError();
+}
+}  // namespace
+
+// Rows of a tile by the rows per group on average.  us, 16 / 32 / 64 rows: fp16 64 x 2816 x 2048 (groups x N x K) at 1 row 71 / 65 / 67, at 12 134 / 123 / 118,
+// at 16 151 / 129 / 131, at 24 181 / 148 / 144; fp8 at 4 rows 53 / 54 / 57, at 8 59 / 57 / 58, at 16 70 / 64 / 61.
+hipError_t launch_gemm_grouped_narrow(const GemmArgs& g, hipStream_t s) {
+  if (!narrow_fits(g)) return hipErrorInvalidValue;
+  if (g.fp8 && g.M <= 4 * (int64_t)g.groups) return launch<0>(g, s);
+  return g.M <= (g.fp8 ? 12 : 16) * (int64_t)g.groups ? launch<1>(g, s) : launch<2>(g, s);
+}
+
+}  // namespace axe

@@ -22,6 +22,8 @@
 // Groups with more than 64 rows are handled in passes of 64 (the weights are then read again: the
 // host chooses this kernel only when the average group is small).  For a handful of rows per group a
 // second variant splits K over the four waves of a workgroup (see the template below).
+// Plain weights in problems of some size go to the narrow tiles (kernels_gemm_grouped_narrow.hip); this kernel keeps blocked
+// weights, short K, very many groups and launches of few tiles, where its split of K counts.
 #include <hip/hip_runtime.h>
 #include <stdlib.h>
 
@@ -337,6 +339,7 @@ hipError_t launch_gemm_grouped_stream(const GemmArgs& g0, hipStream_t s) {
   static const int force = [] { const char* v = getenv("AXE_GROUPED_STREAM_VARIANT"); return v ? atoi(v) : 0; }();
   const int avg = avg_env > 0 ? avg_env : (g.fp8 ? 8 : 4);
   int variant = force;
+  if (!force && !avg_env && narrow_fits(g)) return launch_gemm_grouped_narrow(g0, s);
   if (variant < 1 || variant > 4) {
     if (g.M <= avg * (int64_t)g.groups) variant = 1;
     else if (g.M <= (g.K <= 1024 ? 24 : 16) * (int64_t)g.groups) variant = 2;
