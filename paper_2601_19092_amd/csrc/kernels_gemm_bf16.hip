@@ -199,13 +199,26 @@ __device__ __forceinline__ void gemm_bf16_256_body(const GemmArgs& g, int tb_row
     if (!BLOCKED) return (int64_t)tn * NB * g.ldb;
     return (int64_t)(tn >> g.b_tpb_shift) * g.b_blk_stride + (int64_t)(tn & ((1 << g.b_tpb_shift) - 1)) * NB * g.ldb;
   };
+  // Rows of B that lie a multiple of 4 KiB apart put one K-tile of all of them on a few of the memory's channels, and the workgroups walk K
+  // side by side.  So every group starts at a K-tile of its own and comes round (tiles of a group together: they share rows of A and of B).  A bare
+  // stream of loads through panels of 256 rows: pitch 4096 5.66 -> 6.1 - 6.25 TB/s, past the caches 6.2 -> 6.9 - 7.0; pitches 1536 and 2048 are level.
+  // MoE layer in fp16 (first product 4096, second 1536), us: 256 / 512 / 1024 / 4096 tokens 199 -> 189 / 212 -> 200 / 253 -> 244 / 427 -> 422; by group and
+  // column, 4096 tokens 426 (rows of A are then read at several places at once).
+  constexpr bool ROT = GROUPED && !RAGGED;
+  const bool rotate = ROT && b_pitch % 4096 == 0 && b_kstep == kRow;
+  auto at = [&](int T, int kstep, int k0) __attribute__((always_inline)) -> int {   // byte offset of a tile's T-th K-tile
+    const int o = T * kstep + k0;
+    return ROT && o >= nk * kstep ? o - nk * kstep : o;
+  };
   struct Tile {
     __amdgpu_buffer_rsrc_t ra, rb;
+    int k0;                                                        // grouped: bytes of a row before the K-tile the tile starts with
   };
   auto table_rows = [&](int t) __attribute__((always_inline)) -> int { return t < 64 ? desc_rows(__builtin_amdgcn_readlane(tb_desc, t)) : 0; };
   // dense: v = tile id; grouped: v = index into the workgroup's table
   auto describe = [&](int v) __attribute__((always_inline)) -> Tile {
     Tile t;
+    t.k0 = 0;
     if constexpr (GROUPED) {
       const int rows = table_rows(v);
       if (rows > 0) {
@@ -217,6 +230,8 @@ __device__ __forceinline__ void gemm_bf16_256_body(const GemmArgs& g, int tb_row
         if constexpr (RAGGED) nb = (int)g.N - tn * NB < NB ? (int)g.N - tn * NB : NB;
         t.rb = __builtin_amdgcn_make_buffer_rsrc((void*)((const uint8_t*)g.B + ((int64_t)grp * g.ldg + b_tile_off(tn)) * 2), 0,
                                                  (nb - 1) * b_pitch + b_span, 0x00020000);
+        if constexpr (ROT)
+          if (rotate) t.k0 = (int)((((uint32_t)grp * 0x9E3779B1u) >> 16) * (uint32_t)nk >> 16) * kRow;
         return t;
       }
     }
@@ -282,7 +297,7 @@ __device__ __forceinline__ void gemm_bf16_256_body(const GemmArgs& g, int tb_row
   auto a_dload = [&](int T, int i, bool cross) __attribute__((always_inline)) {   // piece i of step T into the A block of its parity
     const bool nx = cross && T >= nk;
     __builtin_amdgcn_raw_ptr_buffer_load_lds(nx ? nxt.ra : cur.ra, (lds_ptr)(lds3 + (T & 1) * kBlk + maps::piece_row(w, i, 0, 4) * kRow), 16,
-                                             a_voff_p[i], (nx ? T - nk : T) * a_kstep, 0, 0);   // (K-step T >= nk: step T - nk of the next tile)
+                                             a_voff_p[i], at(nx ? T - nk : T, a_kstep, nx ? nxt.k0 : cur.k0), 0, 0);   // (K-step T >= nk: step T - nk of the next tile)
     AXE_PARANOID_WAIT();
   };
   // B ring: byte offsets of the blocks that hold K-steps kt, kt+1, kt+2 (step kt+3 reuses the first)
@@ -290,7 +305,7 @@ __device__ __forceinline__ void gemm_bf16_256_body(const GemmArgs& g, int tb_row
   auto b_load = [&](int T, int i, int slot_off, bool cross) __attribute__((always_inline)) {
     const bool nx = cross && T >= nk;
     __builtin_amdgcn_raw_ptr_buffer_load_lds(nx ? nxt.rb : cur.rb, (lds_ptr)(lds3 + slot_off + maps::piece_row(w, i, 0, 4) * kRow), 16,
-                                             b_voff_p[i], (nx ? T - nk : T) * b_kstep, 0, ONCE ? kOnce : 0);
+                                             b_voff_p[i], at(nx ? T - nk : T, b_kstep, nx ? nxt.k0 : cur.k0), 0, ONCE ? kOnce : 0);
     AXE_PARANOID_WAIT();
   };
 
