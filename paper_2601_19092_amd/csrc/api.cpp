@@ -375,6 +375,10 @@ static int plan_relayout(const axe_layout_t* src, const axe_layout_t* dst, int32
         const bool pads = (padded - tiles_s) * 8 <= tiles_s || ((padded - tiles_s) * 4 <= tiles_s && tiles_d >= 8 && bytes >= (int64_t(48) << 20));
         if (variant == 2 && pads && padded * tiles_d * matrices <= kMaxBlocks256) grid_s = padded;
         if (grid_s * tiles_d * matrices > kMaxBlocks256) return false;
+        // neighbours along the source on one XCD, where there is a window's worth of tiles (tile_in_runs; figures at the kernels)
+        p.run = 0;
+        if (variant >= 2)
+          while (p.run < (variant == 3 ? 3 : 2) && grid_s >= (uint64_t)(8u << (p.run + 1))) ++p.run;
         p.elementwise = variant;
         p.tiles_s = (uint32_t)tiles_s, p.tiles_d = (uint32_t)tiles_d, p.grid_s = (uint32_t)grid_s;
         p.blocks = grid_s * tiles_d * matrices;

@@ -159,7 +159,7 @@ hipError_t launch_relayout_transpose(const TransposePlan& p, int eb, const void*
       b /= p.tiles_s;
       int64_t td = (int64_t)(b % p.tiles_d);
       b /= p.tiles_d;
-      if (p.diag > 0) td = (td + ts / p.diag) % p.tiles_d;
+      if (p.diag > 0) td = (td + (ts >> p.run) / p.diag) % p.tiles_d;
       int64_t sb = p.s_off, db = p.d_off;
       for (int k = 0; k < p.n; ++k) {
         sb += (int64_t)(b % p.ext[k]) * p.ss[k];
@@ -180,11 +180,11 @@ hipError_t launch_relayout_transpose(const TransposePlan& p, int eb, const void*
     const int64_t TS = skew_tile_s(eb), TD = skew_tile_d(eb), CE = 16 / eb, H = 128 / eb;
     for (uint64_t blk = 0; blk < p.blocks; ++blk) {
       uint64_t b = blk;
-      const int64_t ts = (int64_t)(b % p.tiles_s);
+      const int64_t ts = tile_in_runs((uint32_t)(b % p.tiles_s), p.tiles_s, p.run);
       b /= p.tiles_s;
       int64_t td = (int64_t)(b % p.tiles_d);
       b /= p.tiles_d;
-      if (p.diag > 0) td = (td + ts / p.diag) % p.tiles_d;
+      if (p.diag > 0) td = (td + (ts >> p.run) / p.diag) % p.tiles_d;
       int64_t sb = p.s_off, db = p.d_off;
       for (int k = 0; k < p.n; ++k) {
         sb += (int64_t)(b % p.ext[k]) * p.ss[k];
@@ -228,12 +228,12 @@ hipError_t launch_relayout_transpose(const TransposePlan& p, int eb, const void*
   const int64_t T = transpose_tile_edge(eb), CE = 16 / eb, CPR = T / CE;
   for (uint64_t blk = 0; blk < p.blocks; ++blk) {
     uint64_t b = blk;
-    const int64_t ts = (int64_t)(b % p.grid_s);
+    const int64_t ts = tile_in_runs((uint32_t)(b % p.grid_s), p.grid_s, p.run);
     b /= p.grid_s;
     if (ts >= (int64_t)p.tiles_s) continue;                        // (the grid may be padded along the source)
     int64_t td = (int64_t)(b % p.tiles_d);
     b /= p.tiles_d;
-    if (p.diag > 0) td = (td + ts / p.diag) % p.tiles_d;
+    if (p.diag > 0) td = (td + (ts >> p.run) / p.diag) % p.tiles_d;
     int64_t sb = p.s_off, db = p.d_off;
     for (int k = 0; k < p.n; ++k) {
       sb += (int64_t)(b % p.ext[k]) * p.ss[k];

@@ -79,6 +79,21 @@ struct RowPlan {
   uint64_t slots;                  // rows * slots_per_row
 };
 
+// Neighbours along the source on one XCD.  Source rows that start anywhere are cut by tiles inside a line (a tile's 128 bytes of a row lie on two), and
+// workgroups go round the 8 XCDs one by one, so the two tiles that need such a line used to fetch it into two L2s.  Here runs of 2^run tiles
+// fall to one XCD, side by side and at one step of the diagonal: the tile index along the source is permuted inside windows of 8 x 2^run workgroups,
+// where there is a window's worth of tiles (TransposePlan::run).  us, one by one -> runs of 4: bf16 5000 x 5001 25.6 -> 23.6, 1959 x 1889 7.2 -> 6.9, bytes 8191 x 8193 38 -> 34,
+// 6001 x 4001 14.2 -> 11.6; the skewed kernel, runs of 8: bf16 6001 x 9001 65 -> 51, 8193 x 7999 75 -> 65, 8184 x 8200 61 -> 56, fp32 5001 x 7001 63 -> 59, 8191 x 8193 56
+// either way.  Longer runs of the chunk kernel are level or behind (bytes 6001 x 4001 13.9); with 9 tiles along the source 8193 x 1025 is 9.6, and 10.4 when
+// the diagonal is made coarser all the same.
+#if defined(__HIPCC__)
+__host__ __device__
+#endif
+inline uint32_t tile_in_runs(uint32_t ts, uint32_t n, int run) {
+  const uint32_t window = 8u << run;
+  return ts < (n & ~(window - 1)) ? (ts & ~(window - 1)) | ((ts & 7) << run) | ((ts >> 3) & ((1u << run) - 1)) : ts;
+}
+
 // Transposing relayout: the joint loop nest has one digit that is contiguous in the source (extent
 // eS, destination stride dS) and another that is contiguous in the destination (extent eD, source
 // stride sD).  A workgroup moves one T x T tile of those two digits through LDS; the other digits
@@ -93,7 +108,8 @@ struct TransposePlan {
   uint32_t grid_s;                 // workgroups along the source: tiles_s, or more of which the last ones only return
   uint64_t blocks;                 // workgroups launched: grid_s * tiles_d * product of ext[]
   int32_t streaming;               // 1: non-temporal loads and stores
-  int32_t diag;                    // g > 0: tiles are walked diagonally, td = (row + ts / g) mod tiles_d; 0: row by row
+  int32_t diag;                    // g > 0: tiles are walked diagonally, td = (row + (ts >> run) / g) mod tiles_d; 0: row by row
+  int32_t run;                     // runs of 2^run tiles along S fall to one XCD (tile_in_runs); variants 2 and 3
   Swz s_swz, d_swz;                // swizzle stages of the two sides (mask 0: none), applied to an access's first element
   int32_t n_r;                     // destination replicas: every replica address is written
   int32_t rext[kMaxR];

@@ -497,7 +497,8 @@ __global__ __launch_bounds__(256) void relayout_transpose_kernel(TransposePlan p
 
   // workgroup -> (tile along S, tile along D, outer digits)
   uint64_t b = blockIdx.x;
-  const uint32_t ts = (uint32_t)(b % p.grid_s);
+  uint32_t ts = (uint32_t)(b % p.grid_s);
+  if (ANY && p.run) ts = tile_in_runs(ts, p.grid_s, p.run);
   if (ANY && ts >= p.tiles_s) return;
   b /= p.grid_s;
   uint32_t td = (uint32_t)(b % p.tiles_d);
@@ -506,7 +507,7 @@ __global__ __launch_bounds__(256) void relayout_transpose_kernel(TransposePlan p
   // whole rows of the source between them, but write one narrow column of the destination: short segments a row
   // pitch apart, which with power-of-two pitches fall on a fraction of the memory channels.  Walking the tiles
   // diagonally gives every window of workgroups many different td as well as many different ts.
-  if (p.diag > 0) td = (td + ts / (uint32_t)p.diag) % p.tiles_d;
+  if (p.diag > 0) td = (td + (ts >> p.run) / (uint32_t)p.diag) % p.tiles_d;
   int64_t sb = p.s_off, db = p.d_off;
   for (int k = 0; k < p.n; ++k) {
     const uint64_t q = b / p.ext[k];
@@ -637,11 +638,12 @@ __global__ __launch_bounds__(256) void relayout_transpose_skew_kernel(TransposeP
     return tile + row * ROWB + ((((byte_col >> 4) ^ (row / CE)) & (CS - 1)) << 4) + (byte_col & 15);
   };
   uint64_t b = blockIdx.x;
-  const uint32_t ts = (uint32_t)(b % p.tiles_s);
+  uint32_t ts = (uint32_t)(b % p.tiles_s);
+  if (p.run) ts = tile_in_runs(ts, p.tiles_s, p.run);
   b /= p.tiles_s;
   uint32_t td = (uint32_t)(b % p.tiles_d);
   b /= p.tiles_d;
-  if (p.diag > 0) td = (td + ts / (uint32_t)p.diag) % p.tiles_d;
+  if (p.diag > 0) td = (td + (ts >> p.run) / (uint32_t)p.diag) % p.tiles_d;
   int64_t sb = p.s_off, db = p.d_off;
   for (int k = 0; k < p.n; ++k) {
     const uint64_t q = b / p.ext[k];
