@@ -1201,6 +1201,10 @@ int64_t f32_scales_stream_rows(int64_t G, int64_t N, int64_t K) {
 // at 8 rows 84 against 85, at 10 rows 91 against 85; fp8 gemm2 at 12 rows 44 against 49, at 16 rows 50 against 50, at
 // 20 rows 55 against 50; with fp32 scales (more above) gemm1 at 8 rows 83 against 86, at 16 rows 108 against 87, gemm2 at 8 rows 43 against
 // 55, at 16 rows 55 against 57, at 32 rows 80 against 61.  Far from the crossover (fp8 layer): 4 rows per group 104 against 151, 256 rows 1373 against 274.
+// (These figures and the lines they gave, which the tests hold, are from before the narrow tiles, which now serve most of what is called streaming here, and
+// from before the tile kernels' present table and cache policy.  Now, narrow against tiles: fp16 gemm1 at 12 rows 125 against 133, gemm2 65 against 66, at 16 rows 69
+// against 67; E8M0 gemm1 at 8 rows 61 against 64, at 16 rows 66 against 66, gemm2 at 16 rows 38 against 40; fp32 scales gemm1 at 12 rows 64 against 72, gemm2 at 24 rows
+// 46 against 43.  So the lines still lie within a few percent of where the two meet, but for fp32 scales between 9 and 16 rows at K = 2048.)
 bool grouped_goes_to_stream(const axe_gemm_grouped_desc_t* g, const GemmArgs& a) {
   if (g->kernel_hint == AXE_GROUPED_STREAM) return true;
   if (a.fp8 && a.tile_m < 0) return true;

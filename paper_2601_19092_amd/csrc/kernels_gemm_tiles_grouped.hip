@@ -2,12 +2,11 @@
 // carry and the grouped tile kernel of that path does not take.  One workgroup per compute unit walks its tiles as one
 // pipeline (the loads run on into the next tile's first stages).
 //
-// What it does not read again: the groups' weights, once tiles replace the streaming kernel's passes of 64 rows over them.  HBM
-// carries 3.3 - 3.9 TB/s in it, a quarter of what the loads into LDS reach in the dense kernel runs through them, and the matrix cores
-// are 18 - 23 % busy: a K-step takes 1.1 us where the same body takes 0.5 there.  On what has not been found out (candidates: the rows
-// missing from half-empty tiles' A, a tile's epilogue between two K loops, the table, the last tiles).  An MoE layer of 128
-// experts (8 per token, N, K = 1536, 2048 gated and 2048, 768), us, streaming -> this: 256 tokens 108 + 55 -> 87 + 57, 1024 tokens 287 + 126
-// -> 109 + 72 (604 MB of weights: 3.3 TB/s), 4096 tokens 990 + 403 -> 193 + 137 (all with a tile table that took 10 us longer per launch than now).  Other tiles, 1024 / 4096 tokens: one tile at a time
+// What it does not read again: the groups' weights, once tiles replace the streaming kernel's passes of 64 rows over them.  At 1024 tokens of an MoE layer of
+// 128 experts (8 per token, N, K = 1536, 2048 gated and 2048, 768) it takes 94 + 56 us for 604 MB of weights (4.3 TB/s): the stream of weights, 0.6 us of a
+// K-step's 0.9, beside 0.5 of LDS reads, matrix work and fold, which overlap in part; a ring of five stages is level.  us, first version (a table of 10 us per launch, loads in loops
+// over lanes, weights through the caches) -> now: 256 tokens 143 -> 109, 512 tokens 154 -> 119, 1024 tokens 184 -> 148, 4096 tokens 329 -> 297; streaming kernel 1024 tokens 284 + 128.
+// Other tiles then, 1024 / 4096 tokens: one tile at a time
 // without running on 112 + 85 / 201 + 172; 64 x 128 in four waves, two workgroups per compute unit 105 + 70 / 217 + 151, in eight waves
 // 127 + 83 / 278 + 177; 32 x 128 122 + 76 / 290 + 195; 128 x 128 with two stages 163 + 103 / 305 + 198.
 #include "gemm_tiles.h"
