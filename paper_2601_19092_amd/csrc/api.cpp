@@ -1174,22 +1174,27 @@ int plan_gemm_grouped(const axe_gemm_grouped_desc_t* g, const void* dA, const vo
   return AXE_OK;
 }
 
-// fp8 groups with fp32 scales: rows per group on average up to which the streaming kernel is the faster one, from measurements of both
-// (us, streaming / tiles; every group as large as the others, and with sizes drawn from 0.2 + an exponential distribution, where a group of
-// more rows than a pass takes costs the streaming kernel another).  A tile's own costs weigh more the less a group's weights are
-// (16 rows: 128 groups x 1536 x 2048 94 / 88 and 111 / 88, 512 x 512 x 2048 125 / 150 and 148 / 151, 128 x 512 x 1152 22 / 31 and 31 / 31; 40 rows there
-// 28 / 32 and 63 / 39), and still more with a pipeline of four or five steps (8 x 4096 x 512, 20 rows 7 / 9 and 9 / 9); fewer tiles than compute units
-// leave the chip idle where the streaming kernel splits K (8 x 1536 x 2048, 16 rows 11 / 15 and 19 / 16; less so where K is long: 16 x 256 x 8192,
-// 20 rows 49 / 45 and 101 / 45); and every workgroup walks the table of
-// groups (4096 x 256 x 1152, 64 rows 512 / 763 and 746 / 784).  Up to 16 tiles in all the lines of the larger problems stand (1 x 1536 x 2048 at
-// 9 rows 9 / 15, at 64 rows 19 / 15).
-int64_t f32_scales_stream_rows(int64_t G, int64_t N, int64_t K) {
+// fp8 groups with fp32 scales: rows per group on average up to which what streams is the faster one, from measurements of both (us,
+// streaming / tiles, group sizes drawn around the average with weights exp(N(0, 1/2))).  A tile's own costs weigh more the less a group's
+// weights are.  Where the narrow tiles serve (plain weights, K from 768, up to 1024 groups) and K is long, the line lies two rows higher than the streaming
+// kernel's own: 128 groups x 1536 x 2048 10 / 11 rows 64 / 70 and 65 / 72, 64 x 2816 x 2048 9 - 11 rows 57 - 60 / 67, 16 x 4096 x 4096 47 - 49 / 59; with
+// shorter K both are level for some rows about it (64 x 2048 x 768 17 - 24 rows 24 / 24 to 25 / 26, 512 x 1024 x 1024 16 - 22 rows, 128 x 512 x 1152
+// 24 / 30 rows 18 / 18 and 19 / 19).  Elsewhere the streaming kernel itself
+// does: with five or fewer K-tiles (128 x 2048 x 512 20 / 24 rows 45 / 31 and 49 / 32, 64 x 8192 x 512 14 / 18 rows 71 / 54 and 77 / 56)
+// the line adds nothing for the shorter pipeline unless there is at most a tile for each compute unit (8 x 4096 x 512 12 / 16 rows 7.1 / 7.6 and
+// 8.2 / 7.7).  Fewer tiles than compute units
+// leave the chip idle where both of them split finer (16 x 256 x 8192, 20 rows 22 / 37; less so where K is long), and with many groups a tile of
+// the table costs the tiles more than a pass of few rows, by less than it did (4096 x 256 x 1152, 76 / 88 rows 789 / 417 and 882 / 424).
+// Below these lines the tiles are ahead already at some of the sizes of short K or many groups (4096 x 256 x 1152, 64 rows 684 / 400): the
+// lines lie as low as the kernels' choice that is pinned there allows.  Up to 16 tiles in all the lines of the larger problems stand
+// (1 x 1536 x 2048 at 9 rows 9 / 15, at 64 rows 19 / 15).
+int64_t f32_scales_stream_rows(int64_t G, int64_t N, int64_t K, bool narrow) {
   const int64_t tiles = G * N / kTileFamily[kGroupedMember].tn, cus = cu_count();
   if (tiles <= 16) return 0;
-  int64_t rows = 4 + (int64_t(15) << 20) / (N * K);
-  if (K <= 640) rows += 10;
+  int64_t rows = (narrow && K >= 2048 ? 6 : 4) + (int64_t(15) << 20) / (N * K);
+  if (K <= 640 && tiles <= cus) rows += 10;
   if (tiles < cus) rows += 24 * (cus - tiles) * 4096 / (cus * std::max<int64_t>(K, 4096));
-  if (G > 1024) rows += (G - 1024) / 100;
+  if (G > 1024) rows += (G - 1024) / 160;
   return rows;
 }
 
@@ -1204,14 +1209,14 @@ int64_t f32_scales_stream_rows(int64_t G, int64_t N, int64_t K) {
 // (These figures and the lines they gave, which the tests hold, are from before the narrow tiles, which now serve most of what is called streaming here, and
 // from before the tile kernels' present table and cache policy.  Now, narrow against tiles: fp16 gemm1 at 12 rows 125 against 133, gemm2 65 against 66, at 16 rows 69
 // against 67; E8M0 gemm1 at 8 rows 61 against 64, at 16 rows 66 against 66, gemm2 at 16 rows 38 against 40; fp32 scales gemm1 at 12 rows 64 against 72, gemm2 at 24 rows
-// 46 against 43.  So the lines still lie within a few percent of where the two meet, but for fp32 scales between 9 and 16 rows at K = 2048.)
+// 46 against 43.  So the lines still lie within a few percent of where the two meet, but for fp32 scales between 12 and 16 rows at K = 2048.)
 bool grouped_goes_to_stream(const axe_gemm_grouped_desc_t* g, const GemmArgs& a) {
   if (g->kernel_hint == AXE_GROUPED_STREAM) return true;
   if (a.fp8 && a.tile_m < 0) return true;
   if (g->kernel_hint != AXE_GROUPED_AUTO) return false;            // tiles asked for
   const bool short_k = g->K <= 1024;
   int64_t rows = a.fp8 ? (short_k ? (scales_f32(a) ? 17 : 15) : 8) : (short_k ? 19 : 13);
-  if (scales_f32(a)) rows = std::max(rows, f32_scales_stream_rows(g->G, g->N, g->K));
+  if (scales_f32(a)) rows = std::max(rows, f32_scales_stream_rows(g->G, g->N, g->K, narrow_fits(a)));
   if (a.fp8) {
     static const int64_t min_rows = [] { const char* v = getenv("AXE_GROUPED_FP8_TILE_ROWS"); return v ? atoll(v) : int64_t(0); }();
     if (min_rows > 0) rows = min_rows - 1;
