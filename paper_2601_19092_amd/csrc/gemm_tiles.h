@@ -95,8 +95,14 @@ __device__ __forceinline__ void wait_loads() {                     // all but th
 // DT: 0 bf16, 1 fp16, 2 fp8 e4m3.  SC (fp8): 0 unscaled, 1 fp32 scales, 2 E8M0 codes, 3 E8M0 codes multiplied as floats.
 // GRP: 0 dense; 1, 2 grouped (A's scales one per row), 2 with the gated epilogue.  A grouped launch finds its workgroup's
 // tiles on the device (grouped_tiles.h) and walks them one after the other.  ONCE: B is loaded past the caches.
+// Where AXE_TILES_BODY is defined this is a function, for kernels with more than one body (which hand it the workgroup's LDS and the table).  Not
+// everywhere: as a function inside a kernel it compiles to other code (a decode step of 16 rows 11.41 -> 11.46 us).
 template <int DT, int SC, int TM, int TN, int WM, int WN, int WK, int NST, int GRP = 0, bool ONCE = false>
+#ifdef AXE_TILES_BODY
+__device__ __forceinline__ void gemm_tiles_body(GemmArgs g, lds_u8 lds3, int t_row0, int t_desc) {
+#else
 __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_tiles_kernel(GemmArgs g) {
+#endif
   constexpr int EB = DT == 2 ? 1 : 2;
   constexpr int kRow = maps::kLargeRowBytes;
   constexpr int NG = WM * WN;                                      // waves of a group
@@ -109,11 +115,12 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_tiles_kernel(GemmArgs 
   static_assert(TM % (16 * WM) == 0 && TN % (16 * WN) == 0 && (TM / 8) % NG == 0 && (TN / 8) % NG == 0, "whole fragments and pieces");
   static_assert(NST * kStage <= 160 * 1024 && (WK - 1) * TM * TN * 4 <= NST * kStage, "the ring, and then the partial sums, fit LDS");
   static_assert((NST - 1) * kLoads <= 63, "the counted wait");
+#ifndef AXE_TILES_BODY
   __shared__ __attribute__((aligned(1024))) uint8_t lds_mem[NST * kStage];
   const lds_u8 lds3 = (lds_u8)lds_mem;
-
-  const int lane = threadIdx.x & 63;
   if (GRP != 0 && g.clear && blockIdx.x == 0 && threadIdx.x == 0) *g.clear = 0;
+#endif
+  const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int kpart = w / NG, wg = w % NG;                           // group, wave inside the group
   const int wm = wg / WN, wn = wg % WN;
@@ -142,8 +149,10 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_tiles_kernel(GemmArgs 
   // The workgroup's tiles.  Dense: one, found from its id.  Grouped: found on the device, one per lane; the loads run on from
   // a tile's last stage into the next tile's first ones, so the load side, the scales and the matrix side each keep a
   // place of their own.
+#ifndef AXE_TILES_BODY
   int t_row0 = 0, t_desc = 0;
   if constexpr (GRP != 0) group_tiles<TM>(g, lane, t_row0, t_desc);
+#endif
   struct Place {
     int64_t m0, n0;
     int rows, cols, group;                                         // rows = 0: no such tile
@@ -512,6 +521,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_tiles_kernel(GemmArgs 
   }
 }
 
+#ifndef AXE_TILES_BODY
 template <int DT, int SC, int F>
 hipError_t launch_member(const GemmArgs& g, hipStream_t s) {
   constexpr TileShape t = kTileFamily[F];
@@ -536,6 +546,7 @@ hipError_t launch_family(int member, const GemmArgs& g, hipStream_t s) {
   }
   static_assert(kTileFamilySize == 9, "one case per member");
 }
+#endif
 
 }  // namespace tiles
 }  // namespace axe

@@ -10,11 +10,39 @@
 //
 // Measured, us, streaming kernel -> this (an MoE layer of 128 experts, 8 per token, both products): fp16 4 / 16 / 64 tokens 51 -> 49 / 125 -> 118 /
 // 192 -> 174 (1.15 GB: 6.6 TB/s), 128 tokens 205 -> 183; fp8 (either scales) 1 / 16 / 64 / 128 tokens 17 -> 14 / 73 -> 61 / 108 -> 89 / 128 -> 96.
+//
+// Weights past the caches where the host says that they don't stay there (stream_b) and the table that most groups have one row block: the second row block
+// of a group would read them from memory again.  Two bodies, for a choice at every load costs scaled fp8 7 - 10 % at 8 - 64 tokens.  us, past the caches
+// whatever the table says / by the table / through the caches, 128 x 1536 x 2048 (groups x N x K), fp16: 512 rows in sizes drawn around the average 119 / 119 / 134,
+// half of them in one group 116 / 115 / 128, in 16 groups 28.3 / 26.2 / 26.2, in four 17.6 / 12.6 / 12.4; 1536 rows in 16 groups 48.4 / 42.2 / 42.1, in one 36.4 / 26.8 / 26.5;
+// fp8 512 rows drawn 57.9 / 58.0 / 67.1, in 16 groups 16.8 / 14.4 / 14.3, 1536 rows in four 20.9 / 17.2 / 17.0.
+#define AXE_TILES_BODY
 #include "gemm_tiles.h"
 
 #include <algorithm>
 
 namespace axe {
+
+namespace tiles {
+template <int DT, int SC, int TM, int TN, int WM, int WN, int NST, int GRP>
+__global__ __launch_bounds__(64 * WM * WN) void gemm_narrow_kernel(GemmArgs g) {
+  __shared__ __attribute__((aligned(1024))) uint8_t lds_mem[NST * (TM + TN) * maps::kLargeRowBytes];
+  int t_row0, t_desc;
+  if (g.clear && blockIdx.x == 0 && threadIdx.x == 0) *g.clear = 0;
+  group_tiles<TM>(g, threadIdx.x & 63, t_row0, t_desc);
+  gemm_tiles_body<DT, SC, TM, TN, WM, WN, 1, NST, GRP>(g, (lds_u8)lds_mem, t_row0, t_desc);
+}
+template <int DT, int SC, int TM, int TN, int WM, int WN, int NST, int GRP>
+__global__ __launch_bounds__(64 * WM * WN) void gemm_narrow_by_table_kernel(GemmArgs g) {
+  __shared__ __attribute__((aligned(1024))) uint8_t lds_mem[NST * (TM + TN) * maps::kLargeRowBytes];
+  int t_row0, t_desc;
+  if (g.clear && blockIdx.x == 0 && threadIdx.x == 0) *g.clear = 0;
+  if (group_tiles<TM>(g, threadIdx.x & 63, t_row0, t_desc))
+    gemm_tiles_body<DT, SC, TM, TN, WM, WN, 1, NST, GRP, true>(g, (lds_u8)lds_mem, t_row0, t_desc);
+  else
+    gemm_tiles_body<DT, SC, TM, TN, WM, WN, 1, NST, GRP>(g, (lds_u8)lds_mem, t_row0, t_desc);
+}
+}  // namespace tiles
 
 namespace {
 struct NarrowTile {
@@ -22,14 +50,13 @@ struct NarrowTile {
 };
 constexpr NarrowTile kNarrow[] = {{16, 64, 1, 2, kNarrowStages}, {32, 64, 2, 2, kNarrowStages}, {64, 64, 2, 2, kNarrowStages - 1}};
 
-template <int DT, int SC, int V, bool ONCE>
+template <int DT, int SC, int V, int GRP>
 void launch_as(const GemmArgs& g, unsigned nwg, hipStream_t s) {
   constexpr NarrowTile t = kNarrow[V];
   static_assert(2 * t.nst * (t.tm + t.tn) * maps::kLargeRowBytes <= 160 * 1024, "two workgroups per compute unit");
-  if (g.gated)
-    hipLaunchKernelGGL((tiles::gemm_tiles_kernel<DT, SC, t.tm, t.tn, t.wm, t.wn, 1, t.nst, 2, ONCE>), dim3(nwg), dim3(64 * t.wm * t.wn), 0, s, g);
-  else
-    hipLaunchKernelGGL((tiles::gemm_tiles_kernel<DT, SC, t.tm, t.tn, t.wm, t.wn, 1, t.nst, 1, ONCE>), dim3(nwg), dim3(64 * t.wm * t.wn), 0, s, g);
+  const dim3 block(64 * t.wm * t.wn);
+  if (g.stream_b) hipLaunchKernelGGL((tiles::gemm_narrow_by_table_kernel<DT, SC, t.tm, t.tn, t.wm, t.wn, t.nst, GRP>), dim3(nwg), block, 0, s, g);
+  else hipLaunchKernelGGL((tiles::gemm_narrow_kernel<DT, SC, t.tm, t.tn, t.wm, t.wn, t.nst, GRP>), dim3(nwg), block, 0, s, g);
 }
 
 template <int V>
@@ -43,8 +70,8 @@ hipError_t launch(const GemmArgs& g0, hipStream_t s) {
   if (nwg > 0x7fffffff) return hipErrorInvalidValue;
   const unsigned n = (unsigned)nwg;
   auto go = [&](auto dt, auto sc) {
-    if (g.stream_b) launch_as<decltype(dt)::value, decltype(sc)::value, V, true>(g, n, s);
-    else launch_as<decltype(dt)::value, decltype(sc)::value, V, false>(g, n, s);
+    if (g.gated) launch_as<decltype(dt)::value, decltype(sc)::value, V, 2>(g, n, s);
+    else launch_as<decltype(dt)::value, decltype(sc)::value, V, 1>(g, n, s);
   };
   using std::integral_constant;
   if (!g.fp8 && g.f16) go(integral_constant<int, 1>{}, integral_constant<int, 0>{});

@@ -1,6 +1,7 @@
 """Grouped GEMM of few rows per group on narrow tiles: which problems take them, what their counted waits rely on, and every input type, epilogue and
 tile height against the oracle at the edges of a tile, of a K-tile and of the ring."""
 import ctypes as C
+import os
 
 import numpy as np
 import pytest
@@ -10,7 +11,6 @@ from oracle import axe_ref as R
 from paper_2601_19092_amd import binding as B
 from paper_2601_19092_amd import workloads as W
 from test_host_plans import hc                                 # noqa: F401
-from test_tile_family import kernels_of
 
 
 def described(dt, G, M, N, K, gated=False, lda=None, ldb=None, ldc=None, sa=None, sb=None, blocked=False, hint=B.AXE_GROUPED_STREAM):
@@ -42,12 +42,40 @@ def test_which_problems_take_them(hc, dt, G, N, K, rows, narrow):   # noqa: F811
         assert hc.axe_hostcheck_grouped_narrow() == 0
 
 
-def test_loads_between_counted_waits(tmp_path):
-    """As for the tile family: no spills, a stage's loads between its counted wait and the next, a trip's scale loads before its first loads."""
+def bodies_of(source, out):
+    """The kernels of the narrow tiles, each body by itself: (parameters, whether all its loads of B pass by the caches, lines).  A kernel that goes by its
+    table has two bodies, one for either policy, behind each other."""
     import re
-    seen = 0
-    for (dt, sc, tm, tn, wm, wn, wk, nst, grp), lines in kernels_of("kernels_gemm_grouped_narrow.hip", tmp_path / "k.s"):
-        where = (dt, sc, tm, grp)
+    import subprocess
+    from paper_2601_19092_amd import build as BLD
+    subprocess.check_call([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), *BLD.FLAGS, "-I", BLD.CSRC, "-S", "--cuda-device-only",
+                           os.path.join(BLD.CSRC, source), "-o", str(out)], stderr=subprocess.DEVNULL)
+    for m in re.finditer(r"^_ZN3axe5tiles\d+gemm_narrow_(by_table_)?kernelI((?:Li\d+E)+)\w*:[^\n]*\n(.*?)\n\.Lfunc_end", open(out).read(), re.S | re.M):
+        lines, pars = m.group(3).split("\n"), [int(x) for x in re.findall(r"Li(\d+)E", m.group(2))]
+        tm, tn, wm, wn, nst = pars[2:7]
+        ring = nst * (tm + tn) // 8 // (wm * wn)                   # loads of a body before its first counted wait: all stages of the ring
+        begins, n = [], 0
+        for i, x in enumerate(lines):
+            n += bool(re.match(r"\tbuffer_load_dwordx4 .* lds$", x))
+            if re.match(r"\ts_waitcnt vmcnt\(\d+\) lgkmcnt\(0\)$", x):
+                begins, n = begins + [i] * (n >= ring), 0
+        assert len(begins) == (2 if m.group(1) else 1), pars
+        ahead = ring + ((tm // wm // 16 + (2 if pars[7] == 2 else 1)) if pars[1] else 0)      # and its first scales
+        cuts = [0] + [[i for i, x in enumerate(lines[:b]) if x.startswith("\tbuffer_load_")][-ahead] for b in begins[1:]] + [len(lines)]
+        for a, b in zip(cuts, cuts[1:]):
+            loads = [x for x in lines[a:b] if re.match(r"\tbuffer_load_dwordx4 .* lds$", x.replace(" nt lds", " lds"))]
+            past = sum(" nt lds" in x for x in loads)
+            assert past in (0, len(loads) * tn // (tm + tn)), (pars, past)
+            yield bool(m.group(1)), pars, past > 0, [x.replace(" nt lds", " lds") for x in lines[a:b]]
+
+
+def test_loads_between_counted_waits(tmp_path):
+    """As for the tile family: no spills, a stage's loads between its counted wait and the next, a trip's scale loads before its first loads; and
+    where the table decides, a body for either answer."""
+    import re
+    seen = []
+    for by_table, (dt, sc, tm, tn, wm, wn, nst, grp), past, lines in bodies_of("kernels_gemm_grouped_narrow.hip", tmp_path / "k.s"):
+        where = (dt, sc, tm, grp, by_table, past)
         assert not [x for x in lines if "scratch_" in x], where
         # (a descriptor held in vector registers would be read lane by lane, in a loop around every load)
         assert not [i for i, x in enumerate(lines) if "s_cbranch_execnz" in x and any(" lds" in y for y in lines[max(0, i - 12):i])], where
@@ -63,8 +91,10 @@ def test_loads_between_counted_waits(tmp_path):
         assert all(n >= 2 * loads for n in others) and (sc or not others), (where, others)
         assert len([x for x in lines if re.match(r"\tbuffer_load_dwordx4 .* lds$", x)]) == (u + nst) * loads, where
         assert len([x for x in lines if re.match(r"\tbuffer_load_(dword|ubyte) ", x)]) == 2 * scales, where
-        seen += 1
-    assert seen >= 60
+        seen.append(where)
+    plain = [w for w in seen if not w[4]]
+    assert len(plain) == 30 and not any(w[5] for w in plain)
+    assert len({w for w in seen if w[4]}) == 60
 
 
 @pytest.mark.gpu
