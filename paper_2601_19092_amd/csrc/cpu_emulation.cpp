@@ -326,7 +326,8 @@ hipError_t launch_pair_sync_clear(int32_t*, int64_t, hipStream_t) { return hipEr
 hipError_t pair_static_workspace(int32_t**) { return hipErrorNotSupported; }
 hipError_t launch_gemm_bf16_256_grouped_pair(const GemmArgs&, const GemmArgs&, int32_t*, int, int, hipStream_t) { return hipErrorNotSupported; }
 static int g_narrow = -1;         // whether the last grouped GEMM of few rows per group would have gone to the narrow tiles; -1: none yet
-hipError_t launch_gemm_grouped_stream(const GemmArgs& g, hipStream_t) { return g_narrow = narrow_fits(g), hipErrorNotSupported; }
+static int g_narrow_rows = 0;     // and the rows of their tile, or 0
+hipError_t launch_gemm_grouped_stream(const GemmArgs& g, hipStream_t) { return g_narrow = narrow_fits(g), g_narrow_rows = g_narrow ? narrow_rows(g) : 0, hipErrorNotSupported; }
 hipError_t launch_gemm_fp8_256(const GemmArgs&, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_gemm_fp8_e8m0_256(const GemmArgs&, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_gemm_fp8_e8m0_256_grouped(const GemmArgs&, hipStream_t) { return hipErrorNotSupported; }
@@ -345,6 +346,7 @@ extern "C" void axe_hostcheck_set_buffers(int64_t src_bytes, int64_t dst_bytes) 
 extern "C" int axe_hostcheck_eval_by_blocks(void) { return axe::g_blocks; }
 extern "C" int axe_hostcheck_gemm_member(void) { return axe::g_member; }
 extern "C" int axe_hostcheck_grouped_narrow(void) { return axe::g_narrow; }
+extern "C" int axe_hostcheck_narrow_rows(void) { return axe::g_narrow_rows; }
 extern "C" void axe_hostcheck_plan_only(int on) { axe::g_plan_only = on; }
 extern "C" int64_t axe_hostcheck_workgroups(void) { return (int64_t)axe::g_workgroups; }
 extern "C" int axe_hostcheck_transpose_variant(void) { return axe::g_variant; }

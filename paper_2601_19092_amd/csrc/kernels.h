@@ -119,6 +119,7 @@ inline bool small_preload_fits(int64_t M, int64_t N, int64_t K, int64_t lda, int
 //     12.3 / 13.4, 64 x 2816 x 2048 (704) 33.6 / 29.2; fp8 8 x 1024 x 2048 1 row 9.6 / 7.6, 1 x 4096 x 4096 (64) 17.5 / 11.2, 16 x 512 x 1024 2 rows 5.2 / 5.7, 4 rows
 //     6.2 / 5.7, 4 x 512 x 1024 8 rows 5.6 / 5.7, 12 rows 6.9 / 5.7, 64 x 512 x 768 (512) 1 row 7.2 / 7.0.
 constexpr int kNarrowStages = 6;
+inline int64_t narrow_tiles(const GemmArgs& g) { return (g.M < g.groups ? g.M : g.groups) * (g.N / 64); }   // columns of tiles in all groups that can have rows
 inline bool narrow_fits(const GemmArgs& g) {
   const int eb = g.fp8 ? 1 : 2;
   if (g.b_kstep != 128 || g.b_tpb_shift || g.b_blk_stride != 256 * g.ldb || g.K * eb % 128 || g.K * eb / 128 < kNarrowStages || g.N % 64 || g.N / 64 > 2048) return false;
@@ -126,6 +127,18 @@ inline bool narrow_fits(const GemmArgs& g) {
   if (g.groups > 1024) return false;
   if (g.fp8) return g.K >= 2048 || 2 * tiles > cus || g.M > 8 * (int64_t)g.groups || (2 * tiles == cus && g.M >= 4 * (int64_t)g.groups);
   return tiles > 2 * cus || (g.M > 64 && g.M > 8 * (int64_t)g.groups);
+}
+
+// Rows of a narrow tile, by the rows per group on average.  us, 16 / 32 / 64 rows: fp16 64 x 2816 x 2048 at 1 row 71 / 65 / 67, at 12 134 / 123 / 118,
+// at 16 151 / 129 / 131, at 24 181 / 148 / 144; fp8 at 4 rows 53 / 54 / 57, at 8 59 / 57 / 58, at 16 70 / 64 / 61.  With rows of B a multiple of 4 KiB apart (one K-tile of
+// all of them lies on a few of the memory's channels) and a chip full of tiles the two waves of a 16-row tile fall behind: fp8 16 x 2048 x 4096 at 4 rows
+// 30.3 / 25.9, 64 x 1024 x 4096 54.6 / 46.0 (streaming kernel 50.6), 32 x 1024 x 8192 54.5 / 46.6; with fewer tiles they do not: 12 x 2048 x 4096 22.2 / 23.4, 2 x 2048 x 8192
+// 17.1 / 17.7, and with one row per group on average, drawn, a third of the groups have none: 16 x 2048 x 4096 17.6 / 18.7, 64 x 1024 x 4096 38.4 / 32.7.
+inline int narrow_rows(const GemmArgs& g) {
+  const int64_t G = g.groups;
+  const bool behind = g.ldb % 4096 == 0 && narrow_tiles(g) >= (g.M >= 2 * G ? 2 : 4) * cu_count();
+  if (g.fp8 && g.M <= 4 * G && !behind) return 16;
+  return g.M <= (g.fp8 ? 12 : 16) * G ? 32 : 64;
 }
 
 // Whether two planned grouped problems (the second reading what the first writes) can run as one launch: both on

@@ -83,12 +83,10 @@ hipError_t launch(const GemmArgs& g0, hipStream_t s) {
 }
 }  // namespace
 
-// Rows of a tile by the rows per group on average.  us, 16 / 32 / 64 rows: fp16 64 x 2816 x 2048 (groups x N x K) at 1 row 71 / 65 / 67, at 12 134 / 123 / 118,
-// at 16 151 / 129 / 131, at 24 181 / 148 / 144; fp8 at 4 rows 53 / 54 / 57, at 8 59 / 57 / 58, at 16 70 / 64 / 61.
 hipError_t launch_gemm_grouped_narrow(const GemmArgs& g, hipStream_t s) {
   if (!narrow_fits(g)) return hipErrorInvalidValue;
-  if (g.fp8 && g.M <= 4 * (int64_t)g.groups) return launch<0>(g, s);
-  return g.M <= (g.fp8 ? 12 : 16) * (int64_t)g.groups ? launch<1>(g, s) : launch<2>(g, s);
+  const int rows = narrow_rows(g);
+  return rows == 16 ? launch<0>(g, s) : (rows == 32 ? launch<1>(g, s) : launch<2>(g, s));
 }
 
 }  // namespace axe

@@ -42,6 +42,21 @@ def test_which_problems_take_them(hc, dt, G, N, K, rows, narrow):   # noqa: F811
         assert hc.axe_hostcheck_grouped_narrow() == 0
 
 
+@pytest.mark.parametrize("dt,G,N,K,ldb,rows,height", [            # (rows of all groups together)
+    ("fp8", 128, 1536, 2048, 2048, 512, 16), ("fp8", 128, 1536, 2048, 2048, 513, 32), ("fp8", 128, 1536, 2048, 2048, 12 * 128, 32), ("fp8", 128, 1536, 2048, 2048, 12 * 128 + 1, 64),
+    ("f16", 128, 1536, 2048, 2048, 1, 32), ("f16", 128, 1536, 2048, 2048, 16 * 128, 32), ("f16", 128, 1536, 2048, 2048, 16 * 128 + 1, 64),
+    # rows of B a multiple of 4 KiB apart: from two tiles per compute unit on, with one row per group on average four
+    ("fp8", 16, 2048, 4096, 4096, 64, 32), ("fp8", 16, 2048, 4096, 4112, 64, 16), ("fp8", 16, 2048, 2304, 8192, 64, 32), ("fp8", 16, 2048, 6144, 6144, 64, 16),
+    ("fp8", 15, 2048, 4096, 4096, 60, 16), ("fp8", 16, 2048, 4096, 4096, 31, 16), ("fp8", 16, 2048, 4096, 4096, 32, 32), ("fp8", 64, 2048, 4096, 4096, 31, 16),
+    ("fp8", 64, 2048, 4096, 4096, 32, 32)])
+def test_rows_of_a_tile(hc, dt, G, N, K, ldb, rows, height):   # noqa: F811
+    hc.axe_gemm_grouped.argtypes = [C.POINTER(B.axe_gemm_grouped_desc_t)] + [C.c_void_p] * 5
+    d = described(dt, G, rows, N, K, ldb=ldb)
+    assert hc.axe_gemm_grouped(C.byref(d.c), 1 << 20, 1 << 36, 1 << 44, 1 << 46, None) < 0
+    assert hc.axe_hostcheck_narrow_rows() == (height if hc.axe_hostcheck_grouped_narrow() else 0)
+    assert hc.axe_hostcheck_grouped_narrow() == (0 if dt == "f16" and rows == 1 else 1)
+
+
 def bodies_of(source, out):
     """The kernels of the narrow tiles, each body by itself: (parameters, whether all its loads of B pass by the caches, lines).  A kernel that goes by its
     table has two bodies, one for either policy, behind each other."""
