@@ -111,24 +111,31 @@ inline bool small_preload_fits(int64_t M, int64_t N, int64_t K, int64_t lda, int
 }
 
 // Whether the narrow tiles take a grouped problem of few rows per group from the streaming kernel: plain weights, at least as many K-tiles as their ring
-// has stages, tile columns that fit the table's 11 bits; and where they are the faster ones.  us, streaming / narrow (16-bit: 32-row, fp8: 16-row tiles):
-//   - the table costs every workgroup a pass over the groups: 4096 x 256 x 1152 (groups x N x K) fp16 4 rows per group 398 / 403, 1 row 243 / 267, fp8 135 / 160;
-//     512 x 1024 x 1024 fp16 177 / 162, fp8 96 / 84;
-//   - few tiles: the streaming kernel splits K over waves, in fp8 by two only.  fp16 8 x 1024 x 2048 (128 tiles) 4 rows 8.3 / 9.9, 12 rows 12.6 / 10.0,
-//     16 x 512 x 1024 8 rows 6.5 / 6.9, 12 rows 7.9 / 7.0, 4 x 512 x 1024 (32 tiles) 16 rows 5.9 / 6.8, 24 rows 7.9 / 6.9, 128 x 1024 x 1024 (512) 1 row in four groups
-//     12.3 / 13.4, 64 x 2816 x 2048 (704) 33.6 / 29.2; fp8 8 x 1024 x 2048 1 row 9.6 / 7.6, 1 x 4096 x 4096 (64) 17.5 / 11.2, 16 x 512 x 1024 2 rows 5.2 / 5.7, 4 rows
-//     6.2 / 5.7, 4 x 512 x 1024 8 rows 5.6 / 5.7, 12 rows 6.9 / 5.7, 64 x 512 x 768 (512) 1 row 7.2 / 7.0.
+// has stages, tile columns that fit the table's 11 bits; and where they are the faster ones.  us, streaming / narrow, weights out of the caches (and the same
+// weights again and again), every group as large as the others or drawn around the average with weights exp(N(0, 1/2)):
+//   - the table costs every workgroup a pass over the groups: 4096 x 256 x 1152 (groups x N x K) fp16 4 rows per group 398 / 403, 1 row 243 / 267, fp8
+//     135 / 160; 512 x 1024 x 1024 fp16 177 / 162, fp8 96 / 84.
+//   - fp8: the streaming kernel splits K by two only.  Scaled, 8 x 1024 x 1024 (128 tiles) 2 rows 7.9 / 5.9 (4.9 / 5.0), 4 x 1024 x 1024 (64) 7.4 / 5.5 (4.9 / 5.0),
+//     1 x 256 x 1024 (4) 5.9 / 5.1 (4.8 / 4.9), x 2048 9.7 / 6.7 (7.4 / 6.5), x 4096 17 / 9.9 (12 / 9.8).  With 768 of K the same weights again are 0.3 us faster there:
+//     128 x 2048 x 768, 8 of the groups with a row, 7.4 / 5.8 (4.9 / 5.2), 4 x 1024 x 768 (64) 6.0 / 5.1 (4.4 / 4.7); a gain from 64 tiles on,
+//     below none (1 x 1024 x 768 5.2 / 4.9 (4.3 / 4.6)); from 9 rows on also below (12 rows 5.9 / 5.1 (5.0 / 4.8)).
+//   - 16-bit: it splits K by four, and a chip full of tiles is what the narrow ones need, with loads past the caches (stream_b) or K beyond 512: 128 x 2048 x 768,
+//     32 of the groups with a row (1024 tiles), 20.9 / 18.0, 16 (512) 12.2 / 11.0 and 8.0 / 7.8, 128 x 1536 x 2048 16 with a row (384) 21.7 / 22.1; weights that stay, and those
+//     of three layers in turn: 16 x 2560 x 384 2 rows 8.0 / 9.4 and 7.7 / 8.4, 32 x 2048 x 512 4 rows 13.6 / 15.8 and 12.5 / 12.3, 32 x 1536 x 768 15.6 / 15.9 and 14.1 / 13.2, x 1024
+//     20.3 / 19.5 and 19.0 / 17.0.
+//     From 9 rows on its passes of 16 or 32 rows read the weights of uneven groups again: 16 x 1536 x 1024 12 rows 13.5 / 13.3 and 12.5 / 10.8, 8 x 1024 x 2048 (128)
+//     11.4 / 11.1 and 10.1 / 8.6; with short K or few tiles from 13 on: 8 x 1024 x 768 12 rows 6.0 / 6.5 and 5.6 / 5.7, 4 x 1024 x 1024 (64) 12 rows 1.01 - 1.06 of its time, 20 rows
+//     8.4 / 7.7 and 9.2 / 6.9, 64 x 2048 x 384 12 rows 21.5 / 22.2.
 constexpr int kNarrowStages = 6;
 inline int64_t narrow_tiles(const GemmArgs& g) { return (g.M < g.groups ? g.M : g.groups) * (g.N / 64); }   // columns of tiles in all groups that can have rows
 inline bool narrow_fits(const GemmArgs& g) {
   const int eb = g.fp8 ? 1 : 2;
   if (g.b_kstep != 128 || g.b_tpb_shift || g.b_blk_stride != 256 * g.ldb || g.K * eb % 128 || g.K * eb / 128 < kNarrowStages || g.N % 64 || g.N / 64 > 2048) return false;
-  const int64_t active = g.M < g.groups ? g.M : g.groups, tiles = active * (g.N / 64), cus = cu_count();
   if (g.groups > 1024) return false;
-  if (g.fp8) return g.K >= 2048 || 2 * tiles > cus || g.M > 8 * (int64_t)g.groups || (2 * tiles == cus && g.M >= 4 * (int64_t)g.groups);
-  return tiles > 2 * cus || (g.M > 64 && g.M > 8 * (int64_t)g.groups);
+  if (g.fp8) return g.K >= 1024 || 4 * narrow_tiles(g) >= cu_count() || g.M > 8 * (int64_t)g.groups;
+  if (narrow_tiles(g) > 2 * cu_count() && (g.stream_b || g.K > 512)) return true;
+  return g.M > 64 && g.M > (g.K > 768 && 2 * narrow_tiles(g) >= cu_count() ? 8 : 12) * (int64_t)g.groups;
 }
-
 // Rows of a narrow tile, by the rows per group on average.  us, 16 / 32 / 64 rows: fp16 64 x 2816 x 2048 at 1 row 71 / 65 / 67, at 12 134 / 123 / 118,
 // at 16 151 / 129 / 131, at 24 181 / 148 / 144; fp8 at 4 rows 53 / 54 / 57, at 8 59 / 57 / 58, at 16 70 / 64 / 61.  With rows of B a multiple of 4 KiB apart (one K-tile of
 // all of them lies on a few of the memory's channels) and a chip full of tiles the two waves of a 16-row tile fall behind: fp8 16 x 2048 x 4096 at 4 rows

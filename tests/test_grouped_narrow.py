@@ -25,19 +25,25 @@ def described(dt, G, M, N, K, gated=False, lda=None, ldb=None, ldc=None, sa=None
                              scale_a=sa, scale_b=sb, scale_dtype=B.AXE_SCALE_E8M0 if dt == "fp8 e8m0" else B.AXE_SCALE_F32)
 
 
-@pytest.mark.parametrize("dt,G,N,K,rows,narrow", [              # (256 compute units assumed where there is no device)
-    ("f16", 128, 1536, 2048, 4, 1), ("f16", 64, 2816, 2048, 1, 1), ("f16", 128, 1024, 1024, 4, 1), ("f16", 16, 4096, 4096, 1, 1),
-    ("f16", 8, 1024, 2048, 4, 0), ("f16", 8, 1024, 2048, 12, 1), ("f16", 4, 512, 1024, 16, 0), ("f16", 4, 512, 1024, 24, 1), ("f16", 1, 4096, 4096, 16, 0),
-    ("f16", 4096, 256, 1152, 4, 0), ("f16", 1024, 256, 1152, 4, 1), ("f16", 128, 1536, 320, 4, 0), ("f16", 128, 1536, 384, 4, 1),
-    ("fp8", 1, 4096, 4096, 1, 1), ("fp8", 8, 1024, 2048, 1, 1), ("fp8", 16, 512, 1024, 2, 0), ("fp8", 16, 512, 1024, 4, 1), ("fp8", 4, 512, 1024, 8, 0),
-    ("fp8", 4, 512, 1024, 12, 1), ("fp8", 4096, 256, 1152, 4, 0), ("fp8", 128, 2048, 640, 4, 0), ("fp8", 128, 2048, 768, 4, 1)])
-def test_which_problems_take_them(hc, dt, G, N, K, rows, narrow):   # noqa: F811
+@pytest.mark.parametrize("dt,G,N,K,M,narrow", [                 # (256 compute units assumed where there is no device; M: rows of all groups)
+    # 16-bit: more than two tiles per compute unit, and weights that don't stay in the caches or K beyond 512
+    ("f16", 128, 1536, 2048, 512, 1), ("f16", 64, 2816, 2048, 64, 1), ("f16", 16, 4096, 4096, 16, 1), ("f16", 128, 1536, 384, 512, 1), ("f16", 128, 1536, 320, 512, 0),
+    ("f16", 128, 2048, 768, 16, 0), ("f16", 128, 2048, 768, 17, 1), ("f16", 64, 1536, 512, 512, 0), ("f16", 64, 1536, 576, 512, 1), ("f16", 1, 4096, 4096, 16, 0),
+    ("f16", 1024, 256, 1152, 4096, 1), ("f16", 1025, 256, 1152, 4100, 0), ("f16", 4096, 256, 1152, 16384, 0),
+    # ... or from nine rows per group on, with short K or few tiles from 13
+    ("f16", 8, 1024, 2048, 64, 0), ("f16", 8, 1024, 2048, 65, 1), ("f16", 8, 1024, 768, 96, 0), ("f16", 8, 1024, 768, 97, 1), ("f16", 7, 1024, 1024, 84, 0),
+    ("f16", 7, 1024, 1024, 85, 1), ("f16", 4, 512, 1024, 64, 0), ("f16", 4, 512, 1024, 65, 1), ("f16", 64, 1536, 512, 768, 0), ("f16", 64, 1536, 512, 769, 1),
+    # fp8: K from 1024, or a tile for a quarter of the compute units, or nine rows per group
+    ("fp8", 1, 4096, 4096, 1, 1), ("fp8", 1, 256, 1024, 1, 1), ("fp8", 8, 1024, 2048, 8, 1), ("fp8", 16, 512, 1024, 32, 1), ("fp8", 4, 1024, 768, 4, 1), ("fp8", 4, 768, 768, 4, 0),
+    ("fp8", 128, 1024, 896, 3, 0), ("fp8", 128, 1024, 896, 4, 1), ("fp8", 4, 768, 768, 32, 0), ("fp8", 4, 768, 768, 33, 1), ("fp8", 128, 2048, 640, 512, 0),
+    ("fp8", 128, 2048, 768, 512, 1), ("fp8", 1024, 256, 1152, 4096, 1), ("fp8", 1025, 256, 1152, 4100, 0)])
+def test_which_problems_take_them(hc, dt, G, N, K, M, narrow):   # noqa: F811
     hc.axe_gemm_grouped.argtypes = [C.POINTER(B.axe_gemm_grouped_desc_t)] + [C.c_void_p] * 5
-    d = described(dt, G, G * rows, N, K)
+    d = described(dt, G, M, N, K)
     assert hc.axe_gemm_grouped(C.byref(d.c), 1 << 20, 1 << 36, 1 << 44, 1 << 46, None) < 0
     assert hc.axe_hostcheck_grouped_narrow() == narrow
     if dt == "f16" and narrow:                                     # blocked weights stay with the streaming kernel
-        d = described(dt, G, G * rows, N, K, blocked=True)
+        d = described(dt, G, M, N, K, blocked=True)
         assert hc.axe_gemm_grouped(C.byref(d.c), 1 << 20, 1 << 36, 1 << 44, 1 << 46, None) < 0
         assert hc.axe_hostcheck_grouped_narrow() == 0
 
@@ -112,15 +118,30 @@ def test_loads_between_counted_waits(tmp_path):
     assert len({w for w in seen if w[4]}) == 60
 
 
+# sizes of the groups, N, K-tiles, pitches, rows of a tile
+FP8 = [([1, 0, 2, 16, 17, 0, 1, 3] * 2, 2304, 6, 0, 32), ([1, 0, 2, 5, 17, 0, 1, 3] * 2, 2304, 6, 0, 16),   # as many K-tiles as stages
+       ([0, 15, 16, 1, 33, 2, 0, 9] * 2, 2304, 7, 1, 32),                   # an odd number of K-tiles, pitches
+       ([31, 0, 32, 33, 5, 1, 64, 2], 1024, 16, 0, 64),                     # more rows than the average says
+       ([63, 64, 65, 0, 17, 1], 512, 10, 2, 64), ([3, 0] * 70 + [40, 1], 256, 8, 0, 16)]                    # more than 64 groups
+F16 = [([16, 0, 33, 1, 32, 17, 2, 15], 2304, 6, 0, 32), ([0, 15, 31, 1, 33, 20, 0, 16], 2304, 7, 1, 32), ([31, 0, 32, 33, 5, 1, 64, 2], 1024, 16, 0, 64),
+       ([63, 64, 65, 0, 17, 1], 512, 10, 2, 64), ([30, 0] * 66 + [40, 1], 256, 8, 0, 32)]
+SHAPES = [(dt, *s) for dt in ("bf16", "f16") for s in F16] + [(dt, *s) for dt in ("fp8", "fp8 f32", "fp8 e8m0") for s in FP8]
+
+
+@pytest.mark.parametrize("dt,sizes,N,kt,pads,height", SHAPES)
+def test_the_problems_below_take_them(hc, dt, sizes, N, kt, pads, height):   # noqa: F811
+    hc.axe_gemm_grouped.argtypes = [C.POINTER(B.axe_gemm_grouped_desc_t)] + [C.c_void_p] * 5
+    K, vec = kt * (128 if dt.startswith("fp8") else 64), 16 if dt.startswith("fp8") else 8
+    for gated in (False, True):
+        d = described(dt, len(sizes), sum(sizes) + 5, N, K, gated, K + vec * pads, K + 2 * vec * pads, (N // 2 if gated else N) + 8 * pads)
+        assert hc.axe_gemm_grouped(C.byref(d.c), 1 << 20, 1 << 36, 1 << 44, 1 << 46, None) < 0
+        assert (hc.axe_hostcheck_grouped_narrow(), hc.axe_hostcheck_narrow_rows()) == (1, height)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("gated", [False, True])
-@pytest.mark.parametrize("dt", ["bf16", "f16", "fp8", "fp8 f32", "fp8 e8m0"])
-@pytest.mark.parametrize("sizes,N,kt,pads", [([1, 0, 2, 16, 17, 0, 1, 3] * 2, 2304, 6, 0),            # 16 rows (fp8) or 32; as many K-tiles as stages
-                                             ([0, 15, 16, 1, 33, 2, 0, 9] * 2, 2304, 7, 1),           # an odd number of K-tiles, pitches
-                                             ([31, 0, 32, 33, 5, 1, 64, 2], 1024, 16, 0),             # more rows than the average says
-                                             ([63, 64, 65, 0, 17, 1], 512, 10, 2),                    # 64 rows
-                                             ([3, 0] * 70 + [40, 1], 256, 8, 0)])                     # more than 64 groups
-def test_every_row_of_every_group(sizes, N, kt, pads, dt, gated):
+@pytest.mark.parametrize("dt,sizes,N,kt,pads,height", SHAPES)
+def test_every_row_of_every_group(sizes, N, kt, pads, height, dt, gated):
     fp8 = dt.startswith("fp8")
     K = kt * (128 if fp8 else 64)
     off = np.concatenate([[3], 3 + np.cumsum(sizes)]).astype(np.int32)     # rows 0 .. 2 and the last two belong to no group
