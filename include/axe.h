@@ -235,9 +235,9 @@ typedef struct {
  * their weights), and, with E8M0 scales or none, the tile kernel on the matrix cores' scale path (tiles of 256
  * or 128 rows: kernel_hint AXE_GROUPED_TILES, _256 or _128; gated: N / 2 a multiple of 128; AUTO takes it
  * from 9 rows per group on average, 16 when K <= 1024, with 128-row tiles up to 384 rows per group).  With fp32 scales
- * AUTO takes tiles of 128 x 128 that fold the scales on the vector ALU, from K = 512 and 9 rows per group on average on (18 when
- * K <= 1024), and from more rows where a group has little weight, the tiles are fewer than the compute units or the groups
- * more than a thousand; a hint that asks for tiles with fp32 scales is AXE_EUNSUPPORTED. */
+ * AUTO takes tiles of 128 x 128 that fold the scales on the vector ALU, K from 512, from 17 rows per group on average on (5 with K
+ * up to 640 or more than 1024 groups), and from more rows where the tiles are fewer than three for every compute unit, or where, with K up to
+ * 640 or more than 1024 groups, a group has little weight; a hint that asks for tiles with fp32 scales is AXE_EUNSUPPORTED. */
 
 /* Two kernels serve the same family.  AXE_GROUPED_TILES: 256 x 256 tiles of the chained GEMM pipeline, for
  * groups of hundreds of rows (of 128 x 256 unless groups average more than 384 rows: a K-step then takes half

@@ -1174,49 +1174,46 @@ int plan_gemm_grouped(const axe_gemm_grouped_desc_t* g, const void* dA, const vo
   return AXE_OK;
 }
 
-// fp8 groups with fp32 scales: rows per group on average up to which what streams is the faster one, from measurements of both (us,
-// streaming / tiles, group sizes drawn around the average with weights exp(N(0, 1/2))).  A tile's own costs weigh more the less a group's
-// weights are.  Where the narrow tiles serve (plain weights, K from 768, up to 1024 groups) and K is long, the line lies two rows higher than the streaming
-// kernel's own: 128 groups x 1536 x 2048 10 / 11 rows 64 / 70 and 65 / 72, 64 x 2816 x 2048 9 - 11 rows 57 - 60 / 67, 16 x 4096 x 4096 47 - 49 / 59; with
-// shorter K both are level for some rows about it (64 x 2048 x 768 17 - 24 rows 24 / 24 to 25 / 26, 512 x 1024 x 1024 16 - 22 rows, 128 x 512 x 1152
-// 24 / 30 rows 18 / 18 and 19 / 19).  Elsewhere the streaming kernel itself
-// does: with five or fewer K-tiles (128 x 2048 x 512 20 / 24 rows 45 / 31 and 49 / 32, 64 x 8192 x 512 14 / 18 rows 71 / 54 and 77 / 56)
-// the line adds nothing for the shorter pipeline unless there is at most a tile for each compute unit (8 x 4096 x 512 12 / 16 rows 7.1 / 7.6 and
-// 8.2 / 7.7).  Fewer tiles than compute units
-// leave the chip idle where both of them split finer (16 x 256 x 8192, 20 rows 22 / 37; less so where K is long), and with many groups a tile of
-// the table costs the tiles more than a pass of few rows, by less than it did (4096 x 256 x 1152, 76 / 88 rows 789 / 417 and 882 / 424).
-// Below these lines the tiles are ahead already at some of the sizes of short K or many groups (4096 x 256 x 1152, 64 rows 684 / 400): the
-// lines lie as low as the kernels' choice that is pinned there allows.  Up to 16 tiles in all the lines of the larger problems stand
-// (1 x 1536 x 2048 at 9 rows 9 / 15, at 64 rows 19 / 15).
+// fp8 groups with fp32 scales: rows per group on average up to which what streams is launched, from measurements of both (us, streaming / tiles,
+// group sizes drawn around the average with weights exp(N(0, 1/2)), weights out of the caches).
+// Narrow tiles (narrow_fits) read the weights once as the 128 x 128 tiles do, and are level with them about 16 rows if there are three of those for every
+// compute unit: 128 groups x 1536 x 2048 (N x K) 12 / 16 / 20 / 40 rows 67 / 68, 68 / 71, 76 / 73 and 97 / 86, 64 x 2816 x 2048 61 / 64, 61 / 65, 63 / 66 and 89 / 79,
+// 1024 x 256 x 1024 16 / 40 / 64 rows 65 / 64, 79 / 75 and 103 / 80.  Fewer large tiles leave part of the chip idle that the narrow ones, four for each, fill:
+// 80 x 512 x 1152 (320) at 48 / 80 / 112 rows 0.92, 0.99 and 1.13 of their time, 32 x 512 x 2048 (128) at 32 / 96 / 112 rows 15 / 16, 18 / 18 and 1.13, 8 x 1536 x 2048 (96) at
+// 96 / 160 rows 0.96 and 1.15, 16 x 256 x 8192 (32) at 24 / 192 rows 22 / 36 and 0.55.
+// The streaming kernel (K up to 640, more than 1024 groups) reads them again for every 16 to 64 rows, so the line lies lower, and the lower the more a
+// group's weights are: 128 x 2048 x 512 3 / 6 rows 0.98 / 1.07, 2048 x 256 x 2048 4 / 8 rows 178 / 190 and 215 / 204, 2048 x 256 x 1024 6 / 9 rows
+// 106 / 115 and 128 / 120, 4096 x 256 x 1152 8 / 12 / 64 rows 247 / 272, 294 / 289 and 684 / 400, 512 x 256 x 512 14 / 18 rows 25 / 26 and 28 / 27; higher with fewer than two tiles
+// for every compute unit, by the part of the chip that the last of them leave idle: 9 x 4096 x 512 (288) 14 / 20 / 24 rows 0.91, 0.98 and 1.07, 12 x 4096 x 512 (384) 12 / 16 0.91
+// and 1.02, 8 x 2048 x 512 (128) 14 / 18 0.93 and 1.08, 1 x 8192 x 640 (64) 20 / 28 0.94 and 1.01, 8 x 4096 x 512 (256) 4 / 8 / 12 0.93, 0.99 and 1.03.
+// Beyond 64 tiles for every compute unit a launch has more workgroups than run at once (a wave keeps 64 tiles), the last of them on a mostly idle chip:
+// 4096 x 512 x 1024 (16384) 24 / 28 rows 666 / 731 and 737 / 726, x 768 (24576) 12 / 20 rows 1.00 and 1.15, narrow 1024 x 2048 x 1024 (16384) 32 / 40 rows 0.81 / 1.02.
+// Up to 16 tiles in all the lines of the larger problems stand (1 x 1536 x 2048 at 9 rows 9 / 15, at 64 rows 10 / 14).
 int64_t f32_scales_stream_rows(int64_t G, int64_t N, int64_t K, bool narrow) {
-  const int64_t tiles = G * N / kTileFamily[kGroupedMember].tn, cus = cu_count();
-  if (tiles <= 16) return 0;
-  int64_t rows = (narrow && K >= 2048 ? 6 : 4) + (int64_t(15) << 20) / (N * K);
-  if (K <= 640 && tiles <= cus) rows += 10;
-  if (tiles < cus) rows += 24 * (cus - tiles) * 4096 / (cus * std::max<int64_t>(K, 4096));
-  if (G > 1024) rows += (G - 1024) / 160;
+  const int64_t tiles = G * N / kTileFamily[kGroupedMember].tn, cus = cu_count(), most = 64 * cus;
+  if (tiles <= 16) return K <= 1024 ? 17 : 8;
+  int64_t rows = narrow ? std::min<int64_t>(192, std::max<int64_t>(16, 16 * 3 * cus / tiles)) : 3 + (int64_t(3) << 19) / (N * K);
+  auto idle = [&](int64_t n, int64_t round, int64_t scale) {       // share of the rounds of n things that is empty, times scale
+    const int64_t rounds = (n + round - 1) / round;
+    return scale * (rounds * round - n) / (rounds * round);
+  };
+  if (!narrow && tiles < 2 * cus) rows += std::max<int64_t>(5, idle(tiles, cus, tiles < cus ? 24 : 40));
+  if (tiles >= most) rows += idle(tiles + 1, most, 40);
   return rows;
 }
 
-// Which kernel a planned grouped problem goes to: the streaming kernel while the groups average few rows, then the
-// tile kernels.  The crossover depends on K -- a tile's fixed costs (tile table, prologue, stores) weigh more when its
-// K loop is short -- and was measured on the two GEMMs of an MoE layer (128 groups; gemm1: K = 2048, gemm2: K = 768;
-// streaming kernel against tiles, us): fp16 gemm1 at 12 rows per group 148 against 152, at 16 rows 165 against 152;
-// fp16 gemm2 at 16 rows 84 against 88, at 20 rows 92 against 90; fp8 (tiles of 128 rows) gemm1 at 6 rows 78 against 84,
-// at 8 rows 84 against 85, at 10 rows 91 against 85; fp8 gemm2 at 12 rows 44 against 49, at 16 rows 50 against 50, at
-// 20 rows 55 against 50; with fp32 scales (more above) gemm1 at 8 rows 83 against 86, at 16 rows 108 against 87, gemm2 at 8 rows 43 against
-// 55, at 16 rows 55 against 57, at 32 rows 80 against 61.  Far from the crossover (fp8 layer): 4 rows per group 104 against 151, 256 rows 1373 against 274.
-// (These figures and the lines they gave, which the tests hold, are from before the narrow tiles, which now serve most of what is called streaming here, and
-// from before the tile kernels' present table and cache policy.  Now, narrow against tiles: fp16 gemm1 at 12 rows 125 against 133, gemm2 65 against 66, at 16 rows 69
-// against 67; E8M0 gemm1 at 8 rows 61 against 64, at 16 rows 66 against 66, gemm2 at 16 rows 38 against 40; fp32 scales gemm1 at 12 rows 64 against 72, gemm2 at 24 rows
-// 46 against 43.  So the lines still lie within a few percent of where the two meet, but for fp32 scales between 12 and 16 rows at K = 2048.)
+// Which kernel a planned grouped problem goes to: what streams (the narrow tiles or the streaming kernel: narrow_fits) while the groups average few rows,
+// then the tile kernels.  The crossover depends on K -- a tile's fixed costs (tile table, prologue, stores) weigh more when its K loop is short.  On the
+// two GEMMs of an MoE layer (128 groups; gemm1: N, K = 1536, 2048; gemm2: 2048, 768), us, narrow against tiles: fp16 gemm1 at 12 rows per group 125
+// against 133, gemm2 65 against 66, at 16 rows 69 against 67; E8M0 gemm1 at 8 rows 61 against 64, at 16 rows 66 against 66, gemm2 at 16 rows 38
+// against 40; fp32 scales above.
 bool grouped_goes_to_stream(const axe_gemm_grouped_desc_t* g, const GemmArgs& a) {
   if (g->kernel_hint == AXE_GROUPED_STREAM) return true;
   if (a.fp8 && a.tile_m < 0) return true;
   if (g->kernel_hint != AXE_GROUPED_AUTO) return false;            // tiles asked for
   const bool short_k = g->K <= 1024;
-  int64_t rows = a.fp8 ? (short_k ? (scales_f32(a) ? 17 : 15) : 8) : (short_k ? 19 : 13);
-  if (scales_f32(a)) rows = std::max(rows, f32_scales_stream_rows(g->G, g->N, g->K, narrow_fits(a)));
+  const int64_t line = a.fp8 ? (short_k ? 15 : 8) : (short_k ? 19 : 13);
+  int64_t rows = scales_f32(a) ? f32_scales_stream_rows(g->G, g->N, g->K, narrow_fits(a)) : line;
   if (a.fp8) {
     static const int64_t min_rows = [] { const char* v = getenv("AXE_GROUPED_FP8_TILE_ROWS"); return v ? atoll(v) : int64_t(0); }();
     if (min_rows > 0) rows = min_rows - 1;

@@ -20,12 +20,27 @@ def kernel(G, N, K, rows, hint=B.AXE_GROUPED_AUTO, dtype=B.AXE_SCALE_F32):
     return B.axe_gemm_grouped_kernel(d)
 
 
-@pytest.mark.parametrize("G,N,K,stream,tiles", [                # rows per group that still stream, and that take tiles
-    (128, 1536, 2048, 8, 12), (128, 2048, 768, 16, 24), (128, 4096, 4096, 5, 9),       # an MoE layer's two products, a larger one
-    (128, 512, 1152, 24, 48), (512, 512, 2048, 16, 24), (1024, 512, 1152, 24, 64),     # little weight per group
-    (8, 4096, 512, 20, 48), (128, 2048, 512, 16, 32),                                  # a short pipeline
-    (8, 1536, 2048, 16, 32), (16, 256, 8192, 9, 24), (32, 512, 640, 48, 96),           # fewer tiles than compute units
-    (4096, 256, 1152, 64, 128), (4096, 512, 1024, 48, 96), (2048, 256, 2048, 40, 64)])  # many groups
+# Rows per group that still stream, and that take tiles; both timed, with weights out of the caches: streaming over tiles at either (us where they tell more)
+@pytest.mark.parametrize("G,N,K,stream,tiles", [
+    (128, 1536, 2048, 16, 20),        # 0.98, 1.04: an MoE layer's two products, a larger one
+    (128, 2048, 768, 16, 24),         # 0.98, 1.05
+    (128, 4096, 4096, 16, 20),        # 1.01, 1.05
+    (64, 2816, 2048, 16, 24),         # 0.98, 1.06
+    (128, 512, 1152, 24, 112),        # 1.05 (level from 16 to 96 rows), 1.14: little weight per group
+    (512, 512, 2048, 16, 24),         # 1.01, 1.06
+    (1024, 512, 1152, 16, 24),        # 1.02, 1.04
+    (1024, 256, 1024, 16, 40),        # 1.02, 1.07; at 64 rows 103 / 80 us
+    (8, 4096, 512, 8, 12),            # 0.99, 1.03: a short pipeline (the streaming kernel itself)
+    (128, 2048, 512, 4, 8),           # 1.04, 1.11; at 24 rows 49 / 32 us
+    (512, 256, 512, 14, 18),          # 0.96, 1.05
+    (9, 4096, 512, 20, 24),           # 0.98, 1.07: fewer than two tiles per compute unit
+    (32, 512, 640, 10, 20),           # 1.00, 1.29
+    (8, 1536, 2048, 96, 160),         # 0.96, 1.15: fewer tiles than compute units
+    (32, 512, 2048, 96, 112),         # 0.98, 1.13
+    (4096, 256, 1152, 8, 16),         # 0.92, 1.08: many groups; at 64 rows 684 / 400 us
+    (2048, 256, 2048, 6, 9),          # 1.01, 1.15; at 40 rows twice
+    (4096, 512, 1024, 24, 28),        # 0.92, 1.02: more workgroups of tiles than run at once
+    (4096, 768, 1024, 12, 20)])       # 1.00, 1.15
 def test_choice_by_rows_per_group(G, N, K, stream, tiles):
     assert kernel(G, N, K, stream) == S and kernel(G, N, K, tiles) == T
     assert kernel(G, N, K, tiles, B.AXE_GROUPED_STREAM) == S
