@@ -6,6 +6,7 @@ import pytest
 import torch
 
 from paper_2601_19092_amd import binding as B
+from test_gpu_paranoid_build import PARANOID, library
 from test_grouped_narrow import described
 from test_host_plans import hc                                 # noqa: F401
 
@@ -68,6 +69,8 @@ def test_bits_of_slices_and_the_product(dt, which, gated):
         return out
 
     out = run(0, M, 0, G)
+    with library(PARANOID):                                        # the same arithmetic in the same order with a full wait after every load
+        assert torch.equal(out.view(torch.int16), run(0, M, 0, G).view(torch.int16))
     if fp8:                                                        # (16-bit slices of few rows may go to the streaming kernel, whose sums have another order)
         for e in range(0, G, part):
             i, j = int(rows[e]), int(rows[e + part])

@@ -18,6 +18,7 @@ from oracle.axe_layout import Iter, Layout, Swizzle
 from paper_2601_19092_amd import binding as B
 from paper_2601_19092_amd import workloads as W
 from packing import pack_blocked, pack_gate_up
+from routes import narrow_rows
 
 pytestmark = pytest.mark.gpu
 
@@ -1163,8 +1164,8 @@ def test_gemm_grouped_f16_plain_and_gated():
 @pytest.mark.parametrize("sizes", [[1, 0, 16, 17, 33, 64, 65, 70, 3, 48],                  # 64 rows per pass
                                    [1, 0, 16, 17, 33, 9, 40, 0, 3, 20, 2, 12]])            # a dozen per group: 32 per pass, K split
 def test_gemm_grouped_stream_kernel_variants(dtype, gated, blocked, sizes):
-    """The streaming kernel on ragged small groups (1 .. 70 rows: up to two passes of 64 rows, or of 32, every number
-    of row fragments), plain and gated, plain and blocked weights, bf16 and fp16."""
+    """What streams, on ragged small groups (1 .. 70 rows), plain and gated, bf16 and fp16: the streaming kernel with blocked weights (up to two passes of 64
+    rows, or of 32, every number of row fragments), the narrow tiles with plain ones (six K-tiles: as many as their ring has stages)."""
     off = np.concatenate([[0], np.cumsum(sizes)])
     N, K = 512, 320
     g = W.gemm_grouped_bf16(off, N, K, 101, M=int(off[-1]) + 2, std_b=2.0 * K ** -0.5, dtype=dtype)
@@ -1186,6 +1187,7 @@ def test_gemm_grouped_stream_kernel_variants(dtype, gated, blocked, sizes):
     desc = B.GroupedGemmDesc(g.M, N, Kp, g.G, B.Layout(W.row_major_spec(g.M, Kp)), B.Layout(Bs), B.Layout(W.row_major_spec(g.M, NC)),
                              a_words.size, img.size, g.M * NC, in_dtype=IN_DT[dtype], out_dtype=OUT_DT[dtype],
                              epilogue=B.AXE_EPI_SWIGLU if gated else B.AXE_EPI_NONE, kernel_hint=B.AXE_GROUPED_STREAM)
+    assert narrow_rows(desc) == (0 if blocked else (64 if g.M > 16 * g.G else 32))
     B.axe_gemm_grouped(desc, dA, dB, dC, dR)
     torch.cuda.synchronize()
     raw = dC.cpu().numpy().view(np.uint16).reshape(g.M, NC)
@@ -1204,19 +1206,24 @@ def test_gemm_grouped_stream_kernel_variants(dtype, gated, blocked, sizes):
 
 @pytest.mark.parametrize("tokens", [1, 8, 64])
 def test_gemm_grouped_moe_layer_at_decode_sizes(tokens):
-    """Both grouped GEMMs of the layer at decode batch sizes through the kernel the library picks itself (streaming),
-    blocked weights, gated first GEMM: the whole result against the oracle."""
+    """Both grouped GEMMs of the layer at decode batch sizes through the kernel the library picks itself (the streaming kernel with
+    blocked weights, the narrow tiles past the caches with plain ones), gated first GEMM: the whole result against the oracle."""
     g1, g2 = W.moe_gemm1(tokens), W.moe_gemm2(tokens)
     I = g1.N // 2
-    for g, gated in ((g1, True), (g2, False)):
-        img = pack_blocked(pack_gate_up(g.b_gnk) if gated else g.b_gnk)
+    for g, gated, blocked in ((g1, True, True), (g2, False, True), (g1, True, False), (g2, False, False)):
+        img = pack_gate_up(g.b_gnk) if gated else g.b_gnk
+        img = pack_blocked(img) if blocked else img
         NC = I if gated else g.N
-        Bs = W.gated_b_spec(g.K, g.N, g.G, True) if gated else W.blocked_b_spec(g.K, g.N, G=g.G)
+        if gated:
+            Bs = W.gated_b_spec(g.K, g.N, g.G, blocked)
+        else:
+            Bs = W.blocked_b_spec(g.K, g.N, G=g.G) if blocked else W.grouped_gemm_specs(g)[1]
         dA, dB = dev(g.a_mk.reshape(-1)), dev(img.reshape(-1))
         dC = torch.full((g.M * NC,), SENTINEL, dtype=torch.int16, device="cuda")
         dR = torch.from_numpy(g.group_rows).cuda()
         desc = B.GroupedGemmDesc(g.M, g.N, g.K, g.G, B.Layout(W.row_major_spec(g.M, g.K)), B.Layout(Bs), B.Layout(W.row_major_spec(g.M, NC)),
                                  g.M * g.K, img.size, g.M * NC, epilogue=B.AXE_EPI_SWIGLU if gated else B.AXE_EPI_NONE)
+        assert narrow_rows(desc) == (0 if blocked or tokens == 1 else 32)
         B.axe_gemm_grouped(desc, dA, dB, dC, dR)
         torch.cuda.synchronize()
         c = R.bf16_to_f64(dC.cpu().numpy().view(np.uint16).reshape(g.M, NC))
@@ -1452,7 +1459,7 @@ def test_gemm_grouped_fp8_tile_kernel(sizes, N, K, gated, scale_dtype, tiles):
                                           (B.AXE_GROUPED_STREAM, False)])
 def test_gemm_grouped_is_bitwise_repeatable(kernel, gated):
     """As for the dense kernels: 40 launches of the layer's first GEMM at 512 tokens give the same bits (the 128-row
-    tile has its own schedule of asm-issued loads and counted waits; the streaming kernel adds partial sums in a fixed order)."""
+    tile has its own schedule of asm-issued loads and counted waits; what streams here are the narrow tiles, past the caches)."""
     g = W.moe_gemm1(512)
     NC = g.N // 2 if gated else g.N
     img = pack_gate_up(g.b_gnk) if gated else g.b_gnk
@@ -1529,7 +1536,7 @@ def test_gemm_grouped_stream_kernel_choice_by_launch_size(G, N, lo, hi):
     off = np.concatenate([[0], np.cumsum(sizes)])
     g = W.gemm_grouped_bf16(off, N, 320 if G < 300 else 64, 108)
     assert g.M > 8 * g.G
-    Kp = 384 if G < 300 else 64
+    Kp = 320 if G < 300 else 64                              # five K-tiles at most: no narrow tiles
     a = np.zeros((g.M, Kp), dtype=np.uint16); a[:, :g.K] = g.a_mk
     b = np.zeros((g.G, N, Kp), dtype=np.uint16); b[:, :, :g.K] = g.b_gnk
     gp = W.GroupedGemmInputs(g.M, N, Kp, g.G, a, b, g.group_rows)

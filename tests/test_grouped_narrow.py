@@ -10,6 +10,7 @@ import torch
 from oracle import axe_ref as R
 from paper_2601_19092_amd import binding as B
 from paper_2601_19092_amd import workloads as W
+from test_gpu_paranoid_build import PARANOID, library
 from test_host_plans import hc                                 # noqa: F401
 
 
@@ -168,6 +169,11 @@ def test_every_row_of_every_group(sizes, N, kt, pads, height, dt, gated):
     torch.cuda.synchronize()
     raw = dC.cpu().numpy().reshape(M, ldc)
     assert (raw[:, NC:] == -7).all() and (raw[:3] == -7).all() and (raw[-2:] == -7).all(), "written outside the groups"
+    with library(PARANOID):                                        # the same arithmetic in the same order with a full wait after every load
+        dC.fill_(-7)
+        B.axe_gemm_grouped(described(dt, g.G, M, N, K, gated, lda, ldb, ldc, sa, sb), dA, dB, dC, dR)
+        torch.cuda.synchronize()
+    assert np.array_equal(raw, dC.cpu().numpy().reshape(M, ldc))
     code = R.AXE_FP8_E4M3 if fp8 else (R.AXE_BF16 if dt == "bf16" else R.AXE_F16)
     ref = R.gemm_grouped_ref(g.a_mk, g.b_gnk.transpose(0, 2, 1), off, code, **({"scale_a": so[0], "scale_b": so[1]} if so else {}))
     want = R.swiglu_ref(ref) if gated and (not fp8 or so) else (None if gated else ref)
