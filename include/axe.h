@@ -231,20 +231,22 @@ typedef struct {
  * (G, N/128, ceil(K/128)): one per 128 x 128 block of each B[e]; fp32, or E8M0 codes (one byte, 2^(code - 127);
  * such arrays are read in aligned 4-byte words: 4-byte aligned, allocation padded to a multiple of 4 bytes).
  * Both NULL: unscaled.  K a multiple of 128; B[e] column-major (plain, or gate/up interleaved for the gated
- * epilogue).  Two kernels: the streaming kernel (any scales; groups of more than 64 rows take several passes over
- * their weights), and, with E8M0 scales or none, the tile kernel on the matrix cores' scale path (tiles of 256
+ * epilogue).  AXE_GROUPED_STREAM takes any scales (groups of more rows than a pass or a tile has read their weights again), and,
+ * with E8M0 scales or none, the tile kernel runs on the matrix cores' scale path (tiles of 256
  * or 128 rows: kernel_hint AXE_GROUPED_TILES, _256 or _128; gated: N / 2 a multiple of 128; AUTO takes it
  * from 9 rows per group on average, 16 when K <= 1024, with 128-row tiles up to 384 rows per group).  With fp32 scales
- * AUTO takes tiles of 128 x 128 that fold the scales on the vector ALU, K from 512, from 17 rows per group on average on (5 with K
+ * AUTO takes tiles of 128 x 128 that fold the scales on the vector ALU, K from 512, from 17 rows per group on average on (4 with K
  * up to 640 or more than 1024 groups), and from more rows where the tiles are fewer than three for every compute unit, or where, with K up to
  * 640 or more than 1024 groups, a group has little weight; a hint that asks for tiles with fp32 scales is AXE_EUNSUPPORTED. */
 
-/* Two kernels serve the same family.  AXE_GROUPED_TILES: 256 x 256 tiles of the chained GEMM pipeline, for
+/* Two kinds of kernel serve the same family.  AXE_GROUPED_TILES: 256 x 256 tiles of the chained GEMM pipeline, for
  * groups of hundreds of rows (of 128 x 256 unless groups average more than 384 rows: a K-step then takes half
- * the matrix-core time and the weights stream past faster).  AXE_GROUPED_STREAM: one workgroup per (group, 128 rows of B), the group's
- * rows (16, 32 or 64 at a time) held in registers while its weights stream by once -- for the few rows per group of
- * an MoE layer at decode batch sizes, where the time is that of reading the weights.  AUTO takes the
- * streaming kernel when M <= 13 G, or M <= 19 G when K <= 1024 (the host knows M, not the group sizes; measured
+ * the matrix-core time and the weights stream past faster).  AXE_GROUPED_STREAM: for the few rows per group of an MoE layer at
+ * decode batch sizes, where the time is that of reading the weights.  It is one of two kernels, chosen by what both measure: narrow tiles
+ * (16, 32 or 64 rows of a group times 64 rows of its B image, weights through LDS, all of K in one sum; plain weights, at least six
+ * K-tiles of 128 bytes, up to 1024 groups, N up to 131072), or the streaming kernel (one workgroup per group and 32 to 128 rows of its B image, weights straight into
+ * registers, 16, 32 or 64 rows of the group a pass, K split over two or four waves where rows are few): blocked weights, short K, more groups, and in 16 bits
+ * launches that don't fill the chip.  AUTO takes AXE_GROUPED_STREAM when M <= 13 G, or M <= 19 G when K <= 1024 (the host knows M, not the group sizes; measured
  * crossovers on the two GEMMs of the benchmark's MoE layer).  In a pair the second GEMM follows the first. */
 enum { AXE_GROUPED_AUTO = 0, AXE_GROUPED_TILES = 1, AXE_GROUPED_STREAM = 2,
        /* the tile kernel with tiles of 256 or 128 rows (AXE_GROUPED_TILES takes 128 while M <= 384 G) */
@@ -348,9 +350,9 @@ int axe_gemm_describe(const axe_gemm_desc_t* g, int32_t which, axe_layout_t* out
 /* The same for axe_gemm_grouped (Sec. 4.1, fused MoE layer; host only).  The grouped tile kernels are the dense
  * 256-wide 16-bit kernel at a tile height of 256 or 128 rows and report its layouts at that height; AXE_DESC_ACC is
  * the accumulator layout of one tile (where a tile lies in the problem depends on the group sizes, which only the
- * device knows).  fp8 with fp32 scales: the 128 x 128 tile's own layouts.  AXE_EUNSUPPORTED: the streaming kernel (no LDS stage; its register maps are stated in its source),
+ * device knows).  fp8 with fp32 scales: the 128 x 128 tile's own layouts.  AXE_EUNSUPPORTED: AXE_GROUPED_STREAM (the maps of its kernels are stated in their sources),
  * and AXE_DESC_C_STORE with the gated epilogue (a stored element comes from two accumulators).
- * axe_gemm_grouped_kernel returns the kernel axe_gemm_grouped would launch: AXE_GROUPED_STREAM,
+ * axe_gemm_grouped_kernel returns the kernel axe_gemm_grouped would launch: AXE_GROUPED_STREAM (either of its kernels),
  * AXE_GROUPED_TILES_256 or AXE_GROUPED_TILES_128, or the error axe_gemm_grouped would return. */
 int axe_gemm_grouped_kernel(const axe_gemm_grouped_desc_t* g);
 int axe_gemm_grouped_describe(const axe_gemm_grouped_desc_t* g, int32_t which, axe_layout_t* out,

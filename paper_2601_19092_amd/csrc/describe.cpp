@@ -344,8 +344,8 @@ extern "C" int axe_gemm_grouped_describe(const axe_gemm_grouped_desc_t* g, int32
   const int kernel = axe_gemm_grouped_kernel(g);
   if (kernel < 0) return kernel;
   if (kernel == AXE_GROUPED_STREAM) {
-    axe::set_error("axe_gemm_grouped_describe: the streaming kernel keeps no tile in LDS and its maps are not reported "
-                   "(lane l holds row l %% 16 and the 16-byte chunks l / 16 and l / 16 + 4 of a 64-wide K-tile of either operand)");
+    axe::set_error("axe_gemm_grouped_describe: the maps of the kernels that stream are not reported (streaming kernel: no tile in LDS, lane l holds "
+                   "row l %% 16 and the 16-byte chunks l / 16 and l / 16 + 4 of a 64-wide K-tile of either operand; narrow tiles: a tile of the family, 64 columns wide)");
     return AXE_EUNSUPPORTED;
   }
   if (which < AXE_DESC_A_G2L_THREADS || which > AXE_DESC_C_STORE) {
