@@ -6,10 +6,10 @@
 // TB/s the L2s deliver (about 86 GB/s per CU) a 128 x 128 tile's K-step takes 370 ns, of which the matrix cores need 240.  Hence
 // tiles as large as the problem can fill the chip with, every load instruction 8 rows of whole 128-byte lines straight into
 // LDS (buffer_load ... lds: no registers, no ds_write), and a ring deep enough to keep 96 - 128 KiB in flight per CU.  What it
-// reaches is less: 50 - 62 GB/s per CU over a whole launch of 128 x 128 tiles, 73 - 87 inside long K loops, while the 256-row kernels'
-// loads alone run at 94 - 106 through the same instruction.  So the path itself is not what stops it (matrix cores 46 % and 41 % busy in
-// the two shapes below); what does -- one barrier per K-step for eight waves, a stage's fragment reads in one burst at its head, the
-// fold beside the matrix instructions, prologue and last stores -- has not been told apart.
+// reaches is less: 50 - 62 GB/s per CU over a whole launch of 128 x 128 tiles, 73 - 87 inside long K loops (matrix cores 46 % and 41 % busy in
+// the two shapes below).  Builds with parts taken out, clocks of a K-step at 2.4 GHz, fp16 2000 x 2000 x 2048 / fp8 with row scales 1000 x 3584 x 8192 / bf16 1024 x
+// 3584 x 8192: all of it 1380 / 1380 / 1120, loads and barriers alone 940 / 900 / 800, LDS reads alone (96 KiB in eight waves of 32 x 64) 680 / 590 / 620, matrix work with the
+// fold alone 710 / 1060 / 660.  So no part is the whole of it; they overlap to about two thirds.
 //
 // Tile movements (tile_maps.h, the image of the 256-row kernels):
 //   HBM -> LDS  : pieces of 8 rows x 128 bytes, one wave instruction each; the XOR swizzle is applied on the global side.

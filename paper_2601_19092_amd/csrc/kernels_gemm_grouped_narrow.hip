@@ -1,6 +1,6 @@
 // Grouped GEMM for few rows per group on narrow tiles (gemm_tiles.h): 16, 32 or 64 rows of a group times 64 rows of its B image, all of
 // K, two workgroups per compute unit, each walking its tiles as one pipeline.  Any of the library's inputs with plain weights; blocked
-// weights, short K, many groups and launches of few tiles stay with the streaming kernel (narrow_fits).
+// weights, short K, many groups and, in 16 bits, launches of few tiles stay with the streaming kernel (narrow_fits).
 //
 // What bounds it: HBM, reading the active groups' weights once.  A bare stream of loads into LDS carries 6.75 - 7.0 TB/s through panels of 64 rows
 // x 128 bytes with the non-temporal policy (6.2 - 6.3 without, 6.1 - 6.5 through panels of 256 and 128 rows of 4096 bytes), where loads into

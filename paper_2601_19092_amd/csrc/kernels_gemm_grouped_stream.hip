@@ -22,8 +22,8 @@
 // Groups with more than 64 rows are handled in passes of 64 (the weights are then read again: the
 // host chooses this kernel only when the average group is small).  For a handful of rows per group a
 // second variant splits K over the four waves of a workgroup (see the template below).
-// Plain weights in problems of some size go to the narrow tiles (kernels_gemm_grouped_narrow.hip); this kernel keeps blocked
-// weights, short K, very many groups and launches of few tiles, where its split of K counts.
+// Plain weights mostly go to the narrow tiles (kernels_gemm_grouped_narrow.hip, narrow_fits); this kernel keeps blocked
+// weights, short K, very many groups and, in 16 bits, launches of few tiles, where its split of K counts.
 #include <hip/hip_runtime.h>
 #include <stdlib.h>
 
