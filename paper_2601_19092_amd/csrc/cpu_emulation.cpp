@@ -9,6 +9,7 @@
 
 #include "device_types.h"
 #include "kernels.h"
+#include "tile_family.h"
 
 namespace axe {
 
@@ -347,6 +348,11 @@ extern "C" int axe_hostcheck_eval_by_blocks(void) { return axe::g_blocks; }
 extern "C" int axe_hostcheck_gemm_member(void) { return axe::g_member; }
 extern "C" int axe_hostcheck_grouped_narrow(void) { return axe::g_narrow; }
 extern "C" int axe_hostcheck_narrow_rows(void) { return axe::g_narrow_rows; }
+extern "C" void axe_hostcheck_family_tile(int32_t bid, int32_t grid_m, int32_t grid_n, int32_t* tm, int32_t* tn) {
+  const uint64_t tiles = (uint64_t)grid_m * (uint64_t)grid_n;
+  const axe::TileAt t = axe::family_tile((uint32_t)bid, grid_m, grid_n, axe::div_factor(8 * (uint64_t)grid_n, tiles), axe::div_factor((uint64_t)(grid_m & 7), 8 * (uint64_t)grid_n));
+  *tm = t.tm, *tn = t.tn;
+}
 extern "C" void axe_hostcheck_plan_only(int on) { axe::g_plan_only = on; }
 extern "C" int64_t axe_hostcheck_workgroups(void) { return (int64_t)axe::g_workgroups; }
 extern "C" int axe_hostcheck_transpose_variant(void) { return axe::g_variant; }

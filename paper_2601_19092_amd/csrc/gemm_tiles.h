@@ -59,6 +59,7 @@ namespace tiles {
 typedef __attribute__((address_space(3))) void* lds_ptr;
 typedef __attribute__((address_space(3))) uint8_t* lds_u8;
 typedef __attribute__((ext_vector_type(2))) unsigned int u32x2;
+typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 // rows of C start at any element (odd N): global memory takes the vector there, four element stores cost four times as much
 typedef u32x2 u32x2_any __attribute__((aligned(2)));
 typedef f32x4 f32x4_any __attribute__((aligned(4)));
@@ -120,6 +121,12 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_tiles_kernel(GemmArgs 
   const lds_u8 lds3 = (lds_u8)lds_mem;
   if (GRP != 0 && g.clear && blockIdx.x == 0 && threadIdx.x == 0) *g.clear = 0;
 #endif
+  // the arguments in one fetch: left alone they come one by one, where each is first used, and every fetch is waited for
+  if constexpr (GRP == 0) {
+    asm volatile("" ::"s"(g.A), "s"(g.B), "s"(g.C), "s"(g.M), "s"(g.N), "s"(g.K), "s"(g.lda), "s"(g.ldb), "s"(g.ldc));
+    asm volatile("" ::"s"(g.grid_m), "s"(g.grid_n), "s"(g.div_group), "s"(g.div_last), "s"(g.c_vec), "s"(g.out_bf16));
+    if constexpr (SC != 0) asm volatile("" ::"s"(g.scale_a), "s"(g.scale_b), "s"(g.scale_a_rows), "s"(g.nkb));
+  }
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int kpart = w / NG, wg = w % NG;                           // group, wave inside the group
@@ -164,8 +171,8 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_tiles_kernel(GemmArgs 
       o.rows = desc_rows(d), o.cols = TN, o.group = desc_group(d);
       o.m0 = __builtin_amdgcn_readlane(t_row0, t & 63), o.n0 = (int64_t)desc_tn(d) * TN;
     } else {
-      int tm, tn;
-      tile_of_block((int)blockIdx.x, (int)gridDim.x, g.grid_m, g.grid_n, tm, tn);
+      const TileAt at = family_tile(blockIdx.x, g.grid_m, g.grid_n, g.div_group, g.div_last);
+      const int tm = at.tm, tn = at.tn;
       o.m0 = (int64_t)tm * TM, o.n0 = (int64_t)tn * TN, o.group = 0;
       o.rows = g.M - o.m0 < TM ? (int)(g.M - o.m0) : TM, o.cols = g.N - o.n0 < TN ? (int)(g.N - o.n0) : TN;
     }
@@ -471,6 +478,30 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_tiles_kernel(GemmArgs 
   }
 
   // ---- VGPR -> HBM: lane holds C[m][n .. n + 3]
+  // Through a descriptor of the tile's part of C where the host says so (c_vec): rows past the end lie outside it, columns past the end get an
+  // offset that does, and a fragment's place is one scalar and an immediate.
+  if constexpr (GRP == 0) {
+    if (g.c_vec) {
+      const int cb = g.out_bf16 ? 2 : 4, c_pitch = (int)g.ldc * cb;
+      const __amdgpu_buffer_rsrc_t rc =
+          __builtin_amdgcn_make_buffer_rsrc((uint8_t*)g.C + (here.m0 * g.ldc + here.n0) * cb, 0, (here.rows - 1) * c_pitch + here.cols * cb, 0x00020000);
+      const int col = wn * (TN / WN) + maps::kAccCols * fq, at = (wm * (TM / WM) + fr) * c_pitch + col * cb;
+#pragma unroll
+      for (int j = 0; j < NF; ++j) {
+        const int off = col + j * 16 < here.cols ? at : kOutside;
+#pragma unroll
+        for (int i = 0; i < MF; ++i) {
+          if (g.out_bf16) {
+            const u32x2 d = {pack2<DT>(acc[i][j][0], acc[i][j][1]), pack2<DT>(acc[i][j][2], acc[i][j][3])};
+            __builtin_amdgcn_raw_buffer_store_b64(d, rc, off + j * 32, i * 16 * c_pitch, 0);
+          } else {
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[i][j]), rc, off + j * 64, i * 16 * c_pitch, 0);
+          }
+        }
+      }
+      return;
+    }
+  }
 #pragma unroll
   for (int i = 0; i < MF; ++i) {
     const int r = wm * (TM / WM) + i * 16 + fr;
