@@ -112,6 +112,11 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_tiles_kernel(GemmArgs 
   constexpr int kLoads = PA + PB;
   constexpr int kGroup = (TM + TN) * kRow, kStage = WK * kGroup;   // bytes of a group's K-tile, of a stage
   constexpr int U = SC ? 4 : 2;                                    // stages per trip of the main loop
+  // The 256 x 128 tile's sixteen fragments a wave: left to the compiler, a stage's reads gather behind its products and the next barrier waits for
+  // them.  Said to alternate, us: bf16 2048 x 4096 x 2048 36.8 -> 34.9, fp16 to fp32 2299 x 2950 x 4040 72.1 -> 68.5, fp8 2048 x 4096 x 4096 36.5 -> 34.3 (E8M0
+  // 42.1 -> 40.5).  Smaller tiles are level either way (128 x 128 at 2000 x 2000 x 2048 18.8 / 18.7, 1024 x 3584 x 8192 57.9 / 58.7), and so is this one with
+  // fp32 scales, whose fold stands between the products (1000 x 3584 x 8192 63.0 / 66.4).
+  constexpr bool kInterleave = GRP == 0 && TM * TN >= 256 * 128 && SC != 1;
   constexpr int NB = GRP == 2 ? 2 : 1;                             // column blocks of B's scales that a wave needs
   static_assert(TM % (16 * WM) == 0 && TN % (16 * WN) == 0 && (TM / 8) % NG == 0 && (TN / 8) % NG == 0, "whole fragments and pieces");
   static_assert(NST * kStage <= 160 * 1024 && (WK - 1) * TM * TN * 4 <= NST * kStage, "the ring, and then the partial sums, fit LDS");
@@ -414,6 +419,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_tiles_kernel(GemmArgs 
     else wait_loads<(NST - 2) * kLoads>();
     if constexpr (NG > 1) wg_barrier();
     AXE_PARANOID_SYNC();
+    if constexpr (kInterleave) __builtin_amdgcn_sched_barrier(0);
     const int nxt = cur + 1 == NST ? 0 : cur + 1;
     read_frags(f[(u + 1) & 1], nxt);
     if (u == 0) {
@@ -423,6 +429,18 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_tiles_kernel(GemmArgs 
     }
     issue(cur);
     multiply(f[u & 1], u, far);
+    if constexpr (kInterleave) {                                   // one matrix instruction, then its share of the reads and, after them, of the loads
+      constexpr int kReads = (MF + NF) * 2, kProducts = MF * NF * (DT == 2 ? 1 : 2), kOthers = kReads + kLoads;
+#pragma unroll
+      for (int m = 0; m < kProducts; ++m) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+#pragma unroll
+        for (int k = m * kOthers / kProducts; k < (m + 1) * kOthers / kProducts; ++k)
+          if (k < kReads) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+          else __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
     cur = nxt;
   };
   if constexpr (kSpreadAhead) {
