@@ -151,6 +151,22 @@ inline int narrow_rows(const GemmArgs& g) {
 // Whether two planned grouped problems (the second reading what the first writes) can run as one launch: both on
 // the chained tile pipeline with the same tile height, and few enough tiles in the worst case that one workgroup per
 // compute unit holds them all (a wave keeps 64 per GEMM) -- the workgroups must all be resident for the waits to end.
+// Rows of a tile of the fused pair, 128, 192 or 256, where the caller asks for none: by the rows per group on average.  Measured, us, 128 / 192 / 256 rows,
+// fp16, groups drawn around the average (experts x hidden x intermediate).
+//   - With three tiles of 128 x 256 and more for every compute unit the height with the least weights loaded per compute unit wins: 128 x 2048 x 768 at 112 rows
+//     287 / 288 / 315, 144 306 / 296 / 324, 162 330 / 310 / 332, 219 385 / 362 / 367, 256 433 / 419 / 425, 300 480 / 461 / 449, 350 528 / 508 / 511; 256 x 2048 x 512 at
+//     100 377 / 387 / 411, 140 421 / 406 / 433, 256 581 / 577 / 563.
+//   - Fewer tiles are a round or two, and what counts is how many blocks most groups have: 16 x 4096 x 2048 at 180 204 / 237 / 266, 220 267 / 238 / 280, 256 277 / 249 / 290,
+//     300 286 / 288 / 295; 32 x 2048 x 1024 at 180 116 / 128 / 153, 256 153 / 135 / 165, 300 156 / 177 / 162; 8 x 4096 x 4096 at 180 197 / 238 / 243, 256 287 / 239 / 285;
+//     64 x 1024 x 512 at 180 70 / 79 / 97, 220 94 / 80 / 96, 300 98 / 103 / 102.
+inline int pair_tile_rows(const GemmArgs& g1) {
+  const int rows = grouped_tile_rows(g1.M, g1.groups, g1.tile_m);
+  if (g1.tile_m || rows != 128) return rows;
+  const int64_t G = g1.groups;
+  const bool many = G * g1.grid_n >= 3 * (int64_t)cu_count();
+  if (g1.M > 288 * G) return many ? 256 : 128;
+  return g1.M > (many ? 136 : 208) * G ? 192 : 128;
+}
 inline bool grouped_pair_fusable(const GemmArgs& g1, const GemmArgs& g2) {
   const int cus = cu_count();
   const int tm = grouped_tile_rows(g1.M, g1.groups, g1.tile_m);

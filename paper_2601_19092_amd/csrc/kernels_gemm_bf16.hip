@@ -136,6 +136,10 @@ __device__ __forceinline__ lds_u8 tile_lds() {
 // 2 x 64 and moves half as much of A (4 pieces per wave and K-step), so that the weights stream past twice as
 // fast -- with few rows per group the time is that of reading B from HBM.  The A blocks in LDS keep their
 // places (half of each is used); loads per K-step 12 instead of 16 (the wait count at the barrier is the same).
+// 6 (192 rows) in the fused pair: with some 250 rows per group a compute unit's time is that of its loads -- 256 lines in flight, each for a
+// trip to HBM, whether a neighbour asks for the same line or not -- and a group's 1.8 row blocks read its weights into LDS 1.8 times
+// instead of 2.5, for a tenth more matrix work (256 rows: 1.5 times, a fifth more).  us, 128 / 192 / 256 rows, the layer of 128 groups: 4096 tokens fp16
+// 433 / 419 / 425, bf16 422 / 407 / 411, 2600 tokens 330 / 310 / 332.  Which: pair_tile_rows.
 //
 // RAGGED: a dense GEMM whose M is no multiple of the tile height and whose N is no multiple of 256 (but of 8:
 // a lane stores 8 columns at once), run as a grouped one with a single group of all rows.  What M leaves over
@@ -164,7 +168,7 @@ __device__ __forceinline__ void gemm_bf16_256_body(const GemmArgs& g, int tb_row
   static_assert(!OUT32 || ((!GROUPED || RAGGED) && NB == 256), "the fp32 output exists for the dense 256-wide kernels");
   static_assert(!RAGGED || (GROUPED && !GATED && NB == 256), "ragged edges are handled by the grouped 256-wide kernel");
   static_assert(!GATED || (GROUPED && NB == 256), "the gated epilogue exists for the grouped 256-wide kernel");
-  static_assert(MR == 8 || (MR == 4 && GROUPED), "128-row tiles exist for the grouped kernel");
+  static_assert(MR == 8 || ((MR == 4 || MR == 6) && GROUPED), "tiles of 128 and 192 rows exist for the grouped kernel");
   constexpr int TM = 32 * MR;                                      // rows of a tile
   constexpr int NA = MR;                                           // A pieces (8 rows x 128 bytes) per wave and K-step
   // loads issued after the last load of the next K-step's operands, at the barrier: the last A piece of step
@@ -470,12 +474,12 @@ __device__ __forceinline__ void gemm_bf16_256_body(const GemmArgs& g, int tb_row
     // block step kt has just left.
     const int bT = S == 0 ? kt + 2 : kt + 3;
     const int bslot = S == 0 ? bo2 : bo0;
-    // With 256-row tiles the barrier of a K-step does not stand between the two sub-steps but two rows of MFMAs
+    // With 256- and 192-row tiles the barrier of a K-step does not stand between the two sub-steps but two rows of MFMAs
     // (16 of them, 256 cycles) into sub-step 1: the wave reaches it with the last LDS read of sub-step 0 long
     // complete and a little more time for its loads to land, instead of draining the matrix pipe while it waits
     // for that read.  Everything that needs the barrier -- reads of step kt + 1, loads into what step kt
     // occupied -- is scheduled into rows 2..7 of sub-step 1; rows 0 and 1 only multiply what is in registers.
-    constexpr bool LATE = MR == 8;
+    constexpr bool LATE = MR != 4;
     auto step_barrier = [&]() __attribute__((always_inline)) {
       // Own reads of step kt are complete, and so are own loads of step kt+1 (the 8 younger loads may still
       // be in flight).  After the barrier step kt+1 is readable by every wave and nobody reads step kt any more.
@@ -507,11 +511,12 @@ __device__ __forceinline__ void gemm_bf16_256_body(const GemmArgs& g, int tb_row
           if (i == 3 && j == 4) fa[1] = lds_read(pa + 16 * kRow);
           if (mi >= 2 && (mr >> 1) == NJ - 1) fa[mi] = lds_read(pa + mi * 16 * kRow);
           // the 8 A pieces of step kt + 2 first (they have one K-step to land), then four B loads
-          if (i >= 2 && i < 6 && (j == 2 || j == 6)) a_dload(kt + 2, 2 * (i - 2) + (j == 6), CROSS);
-          if (i >= 6 && (j == 2 || j == 6)) b_load(bT, 2 * (i - 6) + (j == 6), bslot, CROSS);
+          if (i >= 2 && i < 6 && (j == 2 || j == 6) && 2 * (i - 2) + (j == 6) < NA) a_dload(kt + 2, 2 * (i - 2) + (j == 6), CROSS);
+          if (MR == 8 && i >= 6 && (j == 2 || j == 6)) b_load(bT, 2 * (i - 6) + (j == 6), bslot, CROSS);
+          if (MR == 6 && i == 5 && (j & 1) == 0) b_load(bT, j >> 1, bslot, CROSS);   // (behind the 6 A pieces of rows 2 to 4)
         } else {
           // (with 4 rows the reads sit earlier in the row: the last fragment is needed 9 MFMAs after row 3 ends)
-          constexpr int jb0 = MR == 8 ? 1 : 0, jb1 = MR == 8 ? 5 : 3;
+          constexpr int jb0 = MR == 4 ? 0 : 1, jb1 = MR == 4 ? 3 : 5;
           if (i < 4 && (j == jb0 || j == jb1) && 2 * i + (j == jb1) < NJ)
             fb[NXT][2 * i + (j == jb1)] = lds_read(pb + (2 * i + (j == jb1)) * 16 * kRow);
           if ((mr >> 1) == NJ - 1) fa[mi] = lds_read(pa + mi * 16 * kRow);
@@ -521,7 +526,7 @@ __device__ __forceinline__ void gemm_bf16_256_body(const GemmArgs& g, int tb_row
             if (i >= 2 && (j == 2 || j == 6)) b_load(bT, 2 * (i - 2) + (j == 6), bslot, CROSS);
           } else
           // four B loads per sub-step: after MFMA j = 2 of the even rows (8 rows), or of every row (4 rows)
-          if (MR == 8 ? ((i & 1) == 0 && j == 2) : j == 2) b_load(bT, (S == 0 ? 4 : 0) + (MR == 8 ? i >> 1 : i), bslot, CROSS);
+          if (MR == 8 ? ((i & 1) == 0 && j == 2) : (i < 4 && j == 2)) b_load(bT, (S == 0 ? 4 : 0) + (MR == 8 ? i >> 1 : i), bslot, CROSS);
         }
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -673,6 +678,8 @@ __device__ __forceinline__ void grouped_pair_body(const GemmArgs& g1, const Gemm
 }
 __global__ __launch_bounds__(256, 1) void gemm_bf16_256_grouped_pair_kernel(GemmArgs g1, GemmArgs g2, PairSync ps) { grouped_pair_body<false, 8>(g1, g2, ps); }
 __global__ __launch_bounds__(256, 1) void gemm_f16_256_grouped_pair_kernel(GemmArgs g1, GemmArgs g2, PairSync ps) { grouped_pair_body<true, 8>(g1, g2, ps); }
+__global__ __launch_bounds__(256, 1) void gemm_bf16_192_grouped_pair_kernel(GemmArgs g1, GemmArgs g2, PairSync ps) { grouped_pair_body<false, 6>(g1, g2, ps); }
+__global__ __launch_bounds__(256, 1) void gemm_f16_192_grouped_pair_kernel(GemmArgs g1, GemmArgs g2, PairSync ps) { grouped_pair_body<true, 6>(g1, g2, ps); }
 __global__ __launch_bounds__(256, 1) void gemm_bf16_128_grouped_pair_kernel(GemmArgs g1, GemmArgs g2, PairSync ps) { grouped_pair_body<false, 4>(g1, g2, ps); }
 __global__ __launch_bounds__(256, 1) void gemm_f16_128_grouped_pair_kernel(GemmArgs g1, GemmArgs g2, PairSync ps) { grouped_pair_body<true, 4>(g1, g2, ps); }
 
@@ -768,7 +775,7 @@ hipError_t pair_static_workspace(int32_t** out) {
 hipError_t launch_gemm_bf16_256_grouped_pair(const GemmArgs& g1, const GemmArgs& g2, int32_t* sync, int spin_limit, int need_extra,
                                              hipStream_t s) {
   if (!grouped_pair_fusable(g1, g2) || !sync) return hipErrorInvalidValue;
-  const bool t128 = grouped_tile_rows(g1.M, g1.groups, g1.tile_m) == 128;
+  const int rows = pair_tile_rows(g1);
   if (hipError_t e = launch_pair_sync_clear(sync, g1.M + 1, s); e != hipSuccess) return e;
   PairSync ps;
   ps.done = sync;
@@ -776,10 +783,12 @@ hipError_t launch_gemm_bf16_256_grouped_pair(const GemmArgs& g1, const GemmArgs&
   ps.spin_limit = spin_limit;
   ps.M = g1.M;
   const dim3 grid((unsigned)cu_count()), block(256);
-  switch ((t128 ? 2 : 0) + (g1.f16 ? 1 : 0)) {
+  switch ((rows == 256 ? 0 : (rows == 128 ? 2 : 4)) + (g1.f16 ? 1 : 0)) {
     case 0: hipLaunchKernelGGL(gemm_bf16_256_grouped_pair_kernel, grid, block, 0, s, g1, g2, ps); break;
     case 1: hipLaunchKernelGGL(gemm_f16_256_grouped_pair_kernel, grid, block, 0, s, g1, g2, ps); break;
     case 2: hipLaunchKernelGGL(gemm_bf16_128_grouped_pair_kernel, grid, block, 0, s, g1, g2, ps); break;
+    case 4: hipLaunchKernelGGL(gemm_bf16_192_grouped_pair_kernel, grid, block, 0, s, g1, g2, ps); break;
+    case 5: hipLaunchKernelGGL(gemm_f16_192_grouped_pair_kernel, grid, block, 0, s, g1, g2, ps); break;
     default: hipLaunchKernelGGL(gemm_f16_128_grouped_pair_kernel, grid, block, 0, s, g1, g2, ps); break;
   }
   return hipGetLastError();
