@@ -152,7 +152,7 @@ struct GemmArgs {
   int32_t tile_n;                  // columns of C per workgroup tile (64, 224 or 256)
   // tile family, dense (tile_family.h): the divisors of its tile map as factors, and how a lane may store C
   uint32_t div_group, div_last;    // div_factor() of 8 tile columns' worth of tiles, and of the last group's tile rows
-  int32_t c_vec;                   // columns a lane may store as one buffer store: 8, 4, or 0 = none (any N, any pitch)
+  int32_t c_vec;                   // columns a lane may store as one buffer store: 4, or 0 = none (any N, any pitch)
   // 256-tile bf16 kernel: operands pre-tiled along K / blocked along rows (plain matrix: kstep 128, shift 0,
   // blk_stride = tile rows x pitch)
   int32_t a_kstep, b_kstep;        // bytes between consecutive 64-wide K-tiles of one row

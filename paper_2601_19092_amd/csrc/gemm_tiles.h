@@ -497,7 +497,8 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_tiles_kernel(GemmArgs 
 
   // ---- VGPR -> HBM: lane holds C[m][n .. n + 3]
   // Through a descriptor of the tile's part of C where the host says so (c_vec): rows past the end lie outside it, columns past the end get an
-  // offset that does, and a fragment's place is one scalar and an immediate.
+  // offset that does, and a fragment's place is one addition and an immediate.  The rows go into the offset that is checked against the
+  // descriptor's end, not into the scalar one, which is documented as left out of that check.
   if constexpr (GRP == 0) {
     if (g.c_vec) {
       const int cb = g.out_bf16 ? 2 : 4, c_pitch = (int)g.ldc * cb;
@@ -505,15 +506,16 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_tiles_kernel(GemmArgs 
           __builtin_amdgcn_make_buffer_rsrc((uint8_t*)g.C + (here.m0 * g.ldc + here.n0) * cb, 0, (here.rows - 1) * c_pitch + here.cols * cb, 0x00020000);
       const int col = wn * (TN / WN) + maps::kAccCols * fq, at = (wm * (TM / WM) + fr) * c_pitch + col * cb;
 #pragma unroll
-      for (int j = 0; j < NF; ++j) {
-        const int off = col + j * 16 < here.cols ? at : kOutside;
+      for (int i = 0; i < MF; ++i) {
+        const int row_at = at + i * 16 * c_pitch;
 #pragma unroll
-        for (int i = 0; i < MF; ++i) {
+        for (int j = 0; j < NF; ++j) {
+          const int off = col + j * 16 < here.cols ? row_at : kOutside;
           if (g.out_bf16) {
             const u32x2 d = {pack2<DT>(acc[i][j][0], acc[i][j][1]), pack2<DT>(acc[i][j][2], acc[i][j][3])};
-            __builtin_amdgcn_raw_buffer_store_b64(d, rc, off + j * 32, i * 16 * c_pitch, 0);
+            __builtin_amdgcn_raw_buffer_store_b64(d, rc, off + j * 32, 0, 0);
           } else {
-            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[i][j]), rc, off + j * 64, i * 16 * c_pitch, 0);
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[i][j]), rc, off + j * 64, 0, 0);
           }
         }
       }

@@ -3,9 +3,10 @@ import ctypes as C
 import os
 
 import pytest
+import torch
 
 from paper_2601_19092_amd import binding as B
-from test_tile_family import MEMBERS, check
+from test_tile_family import MEMBERS, check, descriptor, forced
 
 
 def tile_map(grid_m, grid_n, ids):
@@ -52,3 +53,20 @@ def test_c_through_a_descriptor(member, dt, out, scale, rows):
     kt = 128 if dt == "fp8" else 64
     check(member, tm + 3, tn + 12, 3 * kt, dt, out, scale, rows, pad=1)
     check(member, 8 * tm + 1, 4, 2 * kt, dt, out, scale, rows, pad=1)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("member", range(len(MEMBERS)))
+@pytest.mark.parametrize("dt,out", [("bf16", "bf16"), ("f16", "f32")])
+def test_nothing_past_the_last_row_is_written(member, dt, out):
+    """One row, and one row past a whole tile: the rows that the last tile has no more of, up to two tiles of them, keep what they held."""
+    tm, tn = MEMBERS[member][:2]
+    tt = torch.bfloat16 if dt == "bf16" else torch.float16
+    for M, N in ((1, 4), (1, tn + 12), (tm + 1, tn)):
+        K, ldc = 192, N + 4
+        a, b = (torch.ones((n, K), dtype=tt, device="cuda") for n in (M, N))
+        held = torch.full(((M + 2 * tm) * ldc,), -7, dtype=torch.float32 if out == "f32" else tt, device="cuda")
+        with forced(member):
+            B.axe_gemm(descriptor(M, N, K, dt, out, ldc=ldc), a, b, held[:M * ldc])
+        c = held.view(-1, ldc)
+        assert (c[:M, :N] == K).all() and (c[:M, N:] == -7).all() and (c[M:] == -7).all(), (M, N)
