@@ -956,10 +956,9 @@ int plan_gemm(const axe_gemm_desc_t* g, const void* dA, const void* dB, void* dC
   P.args.grid_n = (int32_t)((g->N + bn - 1) / bn);
   P.args.tile_n = (int32_t)bn;
   if (P.member >= 0) {
-    const uint64_t tiles = (uint64_t)P.args.grid_m * (uint64_t)P.args.grid_n;
-    P.args.div_group = div_factor(8 * (uint64_t)P.args.grid_n, tiles), P.args.div_last = div_factor((uint64_t)(P.args.grid_m & 7), 8 * (uint64_t)P.args.grid_n);
+    P.args.map = family_map(P.args.grid_m, P.args.grid_n);
     // (a tile's part of C within 32-bit offsets; whole dwords)
-    P.args.c_vec = g->N % 4 == 0 && ldc * ob % 4 == 0 && 256 * ldc * ob < (int64_t(1) << 30) ? 4 : 0;
+    P.args.c_vec = g->N % 4 == 0 && ldc * ob % 4 == 0 && 256 * ldc * ob < (int64_t(1) << 30);
   }
   P.args.a_kstep = (int32_t)(opa.kt_stride ? opa.kt_stride * eb : 64 * eb);
   P.args.b_kstep = (int32_t)(opb.kt_stride ? opb.kt_stride * eb : 64 * eb);

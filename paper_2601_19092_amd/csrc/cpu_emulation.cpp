@@ -316,9 +316,11 @@ hipError_t launch_relayout_generic(const GenericRelayoutPlan& p, int unit, const
 }
 
 static int g_member = -2;         // of the tile family in the last dense GEMM; -1: the 64 x 64 kernel, -2: none yet
-hipError_t launch_gemm_tiles_16bit(int m, const GemmArgs&, hipStream_t) { return g_member = m, hipErrorNotSupported; }
+static GemmArgs g_family;         // what the last dense launch of the tile family was given
+static hipError_t family_launch(int m, const GemmArgs& g) { return g_member = m, g_family = g, hipErrorNotSupported; }
+hipError_t launch_gemm_tiles_16bit(int m, const GemmArgs& g, hipStream_t) { return family_launch(m, g); }
 hipError_t launch_gemm_tiles_grouped(const GemmArgs&, hipStream_t) { return hipErrorNotSupported; }
-hipError_t launch_gemm_tiles_fp8(int m, const GemmArgs&, hipStream_t) { return g_member = m, hipErrorNotSupported; }
+hipError_t launch_gemm_tiles_fp8(int m, const GemmArgs& g, hipStream_t) { return family_launch(m, g); }
 hipError_t launch_gemm_small(const GemmArgs&, bool, hipStream_t) { return g_member = -1, hipErrorNotSupported; }
 hipError_t launch_gemm_bf16_256(const GemmArgs&, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_gemm_bf16_256_grouped(const GemmArgs&, hipStream_t) { return hipErrorNotSupported; }
@@ -348,9 +350,9 @@ extern "C" int axe_hostcheck_eval_by_blocks(void) { return axe::g_blocks; }
 extern "C" int axe_hostcheck_gemm_member(void) { return axe::g_member; }
 extern "C" int axe_hostcheck_grouped_narrow(void) { return axe::g_narrow; }
 extern "C" int axe_hostcheck_narrow_rows(void) { return axe::g_narrow_rows; }
-extern "C" void axe_hostcheck_family_tile(int32_t bid, int32_t grid_m, int32_t grid_n, int32_t* tm, int32_t* tn) {
-  const uint64_t tiles = (uint64_t)grid_m * (uint64_t)grid_n;
-  const axe::TileAt t = axe::family_tile((uint32_t)bid, grid_m, grid_n, axe::div_factor(8 * (uint64_t)grid_n, tiles), axe::div_factor((uint64_t)(grid_m & 7), 8 * (uint64_t)grid_n));
+// Tile of a workgroup of that launch, by the arguments the planner gave it.
+extern "C" void axe_hostcheck_family_tile(uint32_t bid, int32_t* tm, int32_t* tn) {
+  const axe::TileAt t = axe::family_tile(bid, axe::g_family.grid_m, axe::g_family.grid_n, axe::g_family.map);
   *tm = t.tm, *tn = t.tn;
 }
 extern "C" void axe_hostcheck_plan_only(int on) { axe::g_plan_only = on; }

@@ -2,6 +2,8 @@
 #pragma once
 #include <stdint.h>
 
+#include "tile_family.h"
+
 namespace axe {
 
 constexpr int kMaxD = 16;
@@ -150,9 +152,9 @@ struct GemmArgs {
   int32_t fp8;                     // grouped streaming kernel: 1 = e4m3 inputs (K-tiles of 128 elements), bf16 output
   int32_t grid_m, grid_n;          // workgroup tiles along M and N
   int32_t tile_n;                  // columns of C per workgroup tile (64, 224 or 256)
-  // tile family, dense (tile_family.h): the divisors of its tile map as factors, and how a lane may store C
-  uint32_t div_group, div_last;    // div_factor() of 8 tile columns' worth of tiles, and of the last group's tile rows
-  int32_t c_vec;                   // columns a lane may store as one buffer store: 4, or 0 = none (any N, any pitch)
+  // tile family, dense (tile_family.h)
+  TileMap map;                     // its map from workgroups to tiles
+  int32_t c_vec;                   // 1: C's fragments go out as buffer stores of 4 columns a lane; 0: any N, any pitch
   // 256-tile bf16 kernel: operands pre-tiled along K / blocked along rows (plain matrix: kstep 128, shift 0,
   // blk_stride = tile rows x pitch)
   int32_t a_kstep, b_kstep;        // bytes between consecutive 64-wide K-tiles of one row

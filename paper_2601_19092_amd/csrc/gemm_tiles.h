@@ -129,7 +129,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_tiles_kernel(GemmArgs 
   // the arguments in one fetch: left alone they come one by one, where each is first used, and every fetch is waited for
   if constexpr (GRP == 0) {
     asm volatile("" ::"s"(g.A), "s"(g.B), "s"(g.C), "s"(g.M), "s"(g.N), "s"(g.K), "s"(g.lda), "s"(g.ldb), "s"(g.ldc));
-    asm volatile("" ::"s"(g.grid_m), "s"(g.grid_n), "s"(g.div_group), "s"(g.div_last), "s"(g.c_vec), "s"(g.out_bf16));
+    asm volatile("" ::"s"(g.grid_m), "s"(g.grid_n), "s"(g.map.div_group), "s"(g.map.div_last), "s"(g.map.blocks), "s"(g.c_vec), "s"(g.out_bf16));
     if constexpr (SC != 0) asm volatile("" ::"s"(g.scale_a), "s"(g.scale_b), "s"(g.scale_a_rows), "s"(g.nkb));
   }
   const int lane = threadIdx.x & 63;
@@ -176,7 +176,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_tiles_kernel(GemmArgs 
       o.rows = desc_rows(d), o.cols = TN, o.group = desc_group(d);
       o.m0 = __builtin_amdgcn_readlane(t_row0, t & 63), o.n0 = (int64_t)desc_tn(d) * TN;
     } else {
-      const TileAt at = family_tile(blockIdx.x, g.grid_m, g.grid_n, g.div_group, g.div_last);
+      const TileAt at = family_tile(blockIdx.x, g.grid_m, g.grid_n, g.map);
       const int tm = at.tm, tn = at.tn;
       o.m0 = (int64_t)tm * TM, o.n0 = (int64_t)tn * TN, o.group = 0;
       o.rows = g.M - o.m0 < TM ? (int)(g.M - o.m0) : TM, o.cols = g.N - o.n0 < TN ? (int)(g.N - o.n0) : TN;

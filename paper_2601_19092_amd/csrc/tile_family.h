@@ -29,6 +29,23 @@ inline uint32_t div_factor(uint64_t d, uint64_t most) {
   return d == 0 || most >= (uint64_t(1) << 31) / d ? 0 : (uint32_t)(((uint64_t(1) << 31) + d - 1) / d);
 }
 
+// What the map below needs of a grid, worked out by the host.
+struct TileMap {
+  uint32_t div_group, div_last;   // div_factor() of the tiles of a group of 8 tile rows, and of the last group's tile rows (blocks: of the blocks of a row)
+  uint32_t blocks;                // 1: the tiles go to the XCDs in blocks of 16 x 16
+};
+// Where a launch is four rounds of tiles and more, every XCD walks along its rows of C at the pace of the others.  Runs that start at one or two columns (grid_m a
+// multiple of 32), or whole multiples of 16 tile columns apart (4 KiB of a row of C in 16 bits), write the same few of the memory's channels at any time; dealt in blocks, the 256 tiles
+// of a round are 16 columns side by side.  us, runs / blocks: fp8 8176 x 4096 (32 x 32 tiles) K 512 50.0 / 45.9 with fp32 scales, unscaled K 1024 63.3 / 62.1, 8176 x 8192 K 512
+// E8M0 93.3 / 86.2, 4080 x 8192 (16 x 64) 48.2 / 46.4; bf16 8176 x 8188 x 512 129 / 115.  Others start spread out and are faster in runs: 12272 x 4092 x 512 (48 x 32) bf16
+// 83.6 / 91.4, 20464 x 4096 x 1024 (80 x 32) fp8 128 / 154, 8176 x 2044 x 2048 (32 x 16, two rounds) bf16 69.4 / 72.6.
+inline TileMap family_map(int64_t grid_m, int64_t grid_n) {
+  const uint64_t tiles = (uint64_t)grid_m * (uint64_t)grid_n, group = 8 * (uint64_t)grid_n;
+  TileMap m = {div_factor(group, tiles), div_factor((uint64_t)(grid_m & 7), group), 0};
+  if (((grid_m | grid_n) & 15) == 0 && tiles >= 1024 && (grid_m % 32 == 0 || tiles % 1024 == 0)) m.blocks = 1, m.div_last = div_factor((uint64_t)grid_n / 16, tiles / 256);
+  return m;
+}
+
 // Workgroup id -> tile of a dense launch.  Workgroup ids go round the 8 XCDs one by one, and each XCD takes a run of the tile sequence (they
 // differ by one tile at most), in which columns of 8 tile rows follow one another: its 32 workgroups share 8 panels of A and 4 of B.  Grids of a
 // number of tiles that 8 does not divide used to go to the XCDs tile by tile, so that every L2 read every panel; us, before -> with this map and what the
@@ -41,16 +58,22 @@ struct TileAt {
 #if defined(__HIPCC__)
 __host__ __device__
 #endif
-inline TileAt family_tile(uint32_t bid, int32_t grid_m, int32_t grid_n, uint32_t div_group, uint32_t div_last) {
-  const uint32_t nwg = (uint32_t)grid_m * (uint32_t)grid_n, q = nwg >> 3, r = nwg & 7, xcd = bid & 7;
-  const uint32_t lin = xcd * q + (xcd < r ? xcd : r) + (bid >> 3), per_group = grid_n < 1 << 28 ? 8u * (uint32_t)grid_n : ~0u;
+inline TileAt family_tile(uint32_t bid, int32_t grid_m, int32_t grid_n, const TileMap& map) {
+  const uint32_t xcd = bid & 7, pos = bid >> 3;
   auto over = [](uint32_t n, uint32_t d, uint32_t f) -> uint32_t { return f ? (uint32_t)(((uint64_t)(2 * n) * f) >> 32) : n / d; };
-  const uint32_t group = over(lin, per_group, div_group), in_group = lin - group * per_group, left = (uint32_t)grid_m - 8 * group;
   TileAt t;
+  if (map.blocks) {
+    const uint32_t per_row = (uint32_t)grid_n >> 4, block = pos >> 5, row = over(block, per_row, map.div_last), at = block - row * per_row;
+    t.tm = (int32_t)(16 * row + 8 * (xcd >> 2) + (pos & 7)), t.tn = (int32_t)(16 * (row & 1 ? per_row - 1 - at : at) + 4 * (xcd & 3) + (pos >> 3 & 3));
+    return t;
+  }
+  const uint32_t nwg = (uint32_t)grid_m * (uint32_t)grid_n, q = nwg >> 3, r = nwg & 7;
+  const uint32_t lin = xcd * q + (xcd < r ? xcd : r) + pos, per_group = grid_n < 1 << 28 ? 8u * (uint32_t)grid_n : ~0u;
+  const uint32_t group = over(lin, per_group, map.div_group), in_group = lin - group * per_group, left = (uint32_t)grid_m - 8 * group;
   if (left >= 8) {
     t.tm = (int32_t)(8 * group + (in_group & 7)), t.tn = (int32_t)(in_group >> 3);
   } else {
-    const uint32_t c = over(in_group, left, div_last);
+    const uint32_t c = over(in_group, left, map.div_last);
     t.tm = (int32_t)(8 * group + in_group - c * left), t.tn = (int32_t)c;
   }
   return t;

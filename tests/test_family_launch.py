@@ -9,14 +9,21 @@ from paper_2601_19092_amd import binding as B
 from test_tile_family import MEMBERS, check, descriptor, forced
 
 
-def tile_map(grid_m, grid_n, ids):
+def tile_map(grid_m, grid_n, ids, member=0):
+    """Tiles of these workgroups by the arguments that the planner gives a launch of grid_m x grid_n tiles (the host layer over stand-ins of the kernels: nothing
+    is launched, and the addresses are made up)."""
     hc = C.CDLL(os.environ.get("AXE_TEST_HOST_LIB") or os.path.join(os.path.dirname(B.LIB_PATH), "libaxe_hostcheck.so"))
+    hc.axe_gemm.argtypes = [C.POINTER(B.axe_gemm_desc_t)] + [C.c_void_p] * 4
     fn = hc.axe_hostcheck_family_tile
-    fn.argtypes, fn.restype = [C.c_int32] * 3 + [C.POINTER(C.c_int32)] * 2, None
+    fn.argtypes, fn.restype = [C.c_uint32] + [C.POINTER(C.c_int32)] * 2, None
+    d = descriptor(grid_m * MEMBERS[member][0] - 1, grid_n * MEMBERS[member][1] - 1, 512)
+    with forced(member):
+        assert hc.axe_gemm(C.byref(d.c), 1 << 40, 1 << 41, 1 << 42, None) < 0                # (the stand-in answers that it has no device)
+    assert hc.axe_hostcheck_gemm_member() == member
     tm, tn = C.c_int32(), C.c_int32()
     out = []
     for i in ids:
-        fn(i, grid_m, grid_n, C.byref(tm), C.byref(tn))
+        fn(i, C.byref(tm), C.byref(tn))
         out.append((tm.value, tn.value))
     return out
 
@@ -26,9 +33,30 @@ def test_every_tile_once_and_in_runs(grid_m, grid_n):
     n = grid_m * grid_n
     tiles = tile_map(grid_m, grid_n, range(n))
     assert sorted(tiles) == [(i, j) for i in range(grid_m) for j in range(grid_n)]
+    if (grid_m, grid_n) == (16, 64):                       # runs that would all start at one column of their 16 (see below)
+        return
     # in the order of the XCDs: groups of 8 tile rows, inside them column by column
     order = [tiles[i] for x in range(8) for i in range(x, n, 8)]
     assert order == sorted(order, key=lambda t: (t[0] // 8, t[1], t[0]))
+
+
+# Grids on either side of each line, timed in runs and in blocks: four rounds and more, starts on one or two columns or a multiple of 16 columns apart
+@pytest.mark.parametrize("grid_m,grid_n,blocks", [(32, 32, True), (32, 48, True), (32, 64, True), (64, 16, True), (16, 64, True), (16, 128, True), (96, 32, True),
+                                                  (32, 16, False), (16, 32, False), (16, 48, False), (48, 32, False), (80, 32, False), (16, 96, False), (48, 48, False),
+                                                  (32, 40, False), (40, 32, False), (31, 64, False), (32, 33, False)])
+def test_which_grids_go_in_blocks(grid_m, grid_n, blocks):
+    n = grid_m * grid_n
+    tiles = tile_map(grid_m, grid_n, range(n), member=8)
+    assert sorted(tiles) == [(i, j) for i in range(grid_m) for j in range(grid_n)]
+    first = [{(i // 16, j // 16) for i, j in tiles[k:k + 256]} for k in range(0, n - n % 256, 256)]
+    assert all(len(f) == 1 for f in first) == blocks
+    if blocks:
+        # round by round one block, neighbours after one another, and of it 8 x 4 tiles to every XCD
+        order = [f.pop() for f in first]
+        assert all(abs(a - c) + abs(b - d) == 1 for (a, b), (c, d) in zip(order, order[1:]))
+        for x in range(8):
+            i, j = zip(*tiles[x:256:8])
+            assert (max(i) - min(i), max(j) - min(j)) == (7, 3)
 
 
 def test_large_grids_divide():
@@ -53,6 +81,13 @@ def test_c_through_a_descriptor(member, dt, out, scale, rows):
     kt = 128 if dt == "fp8" else 64
     check(member, tm + 3, tn + 12, 3 * kt, dt, out, scale, rows, pad=1)
     check(member, 8 * tm + 1, 4, 2 * kt, dt, out, scale, rows, pad=1)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("grid_m,grid_n", [(32, 32), (16, 64)])
+@pytest.mark.parametrize("member", [0, 3])
+def test_grids_in_blocks(member, grid_m, grid_n):
+    check(member, grid_m * MEMBERS[member][0] - 3, grid_n * MEMBERS[member][1] - 4, 128, "bf16", "bf16", None, 0, pad=1)
 
 
 @pytest.mark.gpu
