@@ -33,16 +33,26 @@ inline uint32_t div_factor(uint64_t d, uint64_t most) {
 struct TileMap {
   uint32_t div_group, div_last;   // div_factor() of the tiles of a group of 8 tile rows, and of the last group's tile rows (blocks: of the blocks of a row)
   uint32_t blocks;                // 1: the tiles go to the XCDs in blocks of 16 x 16
+  uint32_t turns;                 // 4 bits for each XCD: the tile columns by which its run is turned
 };
 // Where a launch is four rounds of tiles and more, every XCD walks along its rows of C at the pace of the others.  Runs that start at one or two columns (grid_m a
 // multiple of 32), or whole multiples of 16 tile columns apart (4 KiB of a row of C in 16 bits), write the same few of the memory's channels at any time; dealt in blocks, the 256 tiles
 // of a round are 16 columns side by side.  us, runs / blocks: fp8 8176 x 4096 (32 x 32 tiles) K 512 50.0 / 45.9 with fp32 scales, unscaled K 1024 63.3 / 62.1, 8176 x 8192 K 512
 // E8M0 93.3 / 86.2, 4080 x 8192 (16 x 64) 48.2 / 46.4; bf16 8176 x 8188 x 512 129 / 115.  Others start spread out and are faster in runs: 12272 x 4092 x 512 (48 x 32) bf16
 // 83.6 / 91.4, 20464 x 4096 x 1024 (80 x 32) fp8 128 / 154, 8176 x 2044 x 2048 (32 x 16, two rounds) bf16 69.4 / 72.6.
+//
+// Turns, for the same reason, where 8 does not divide the tiles, three rounds and more (to 64: the largest timed has 10): XCD x begins its run 4 x columns past a multiple of 16 (its share of a round is 4
+// columns) and ends with what it skipped.  Round robin / runs / turned, us: fp8 31 x 31 tiles 7842 x 3908 x 512 with fp32 scales 40.7 / 44.4 / 42.0, unscaled 7776 x 3968 x 768 52.3 /
+// 50.9 / 48.4, bf16 31 x 33 7840 x 4220 x 512 67.7 / 58.8 / 54.3; over 107 products of 18 such grids 1 / 0.934 / 0.925 of the time, the slowest turned 29 x 29 with scales
+// (7286 x 3652 x 512 36.7 / 38.2 / 38.0), the slowest run 1.09.  (Where 8 divides them the runs start as they always have.)
 inline TileMap family_map(int64_t grid_m, int64_t grid_n) {
-  const uint64_t tiles = (uint64_t)grid_m * (uint64_t)grid_n, group = 8 * (uint64_t)grid_n;
-  TileMap m = {div_factor(group, tiles), div_factor((uint64_t)(grid_m & 7), group), 0};
+  const uint64_t tiles = (uint64_t)grid_m * (uint64_t)grid_n, group = 8 * (uint64_t)grid_n, q = tiles / 8, r = tiles % 8;
+  TileMap m = {div_factor(group, tiles), div_factor((uint64_t)(grid_m & 7), group), 0, 0};
   if (((grid_m | grid_n) & 15) == 0 && tiles >= 1024 && (grid_m % 32 == 0 || tiles % 1024 == 0)) m.blocks = 1, m.div_last = div_factor((uint64_t)grid_n / 16, tiles / 256);
+  for (uint64_t x = 0; x < 8 && r != 0 && grid_m >= 8 && q >= 96 && q <= 2048; ++x) {
+    const uint64_t first = x * q + (x < r ? x : r), turn = (4 * x - first % group / 8) & 15;
+    if (8 * turn < q) m.turns |= (uint32_t)turn << (4 * x);
+  }
   return m;
 }
 
@@ -67,8 +77,9 @@ inline TileAt family_tile(uint32_t bid, int32_t grid_m, int32_t grid_n, const Ti
     t.tm = (int32_t)(16 * row + 8 * (xcd >> 2) + (pos & 7)), t.tn = (int32_t)(16 * (row & 1 ? per_row - 1 - at : at) + 4 * (xcd & 3) + (pos >> 3 & 3));
     return t;
   }
-  const uint32_t nwg = (uint32_t)grid_m * (uint32_t)grid_n, q = nwg >> 3, r = nwg & 7;
-  const uint32_t lin = xcd * q + (xcd < r ? xcd : r) + pos, per_group = grid_n < 1 << 28 ? 8u * (uint32_t)grid_n : ~0u;
+  const uint32_t nwg = (uint32_t)grid_m * (uint32_t)grid_n, q = nwg >> 3, r = nwg & 7, run = q + (xcd < r ? 1 : 0);
+  const uint32_t turned = pos + 8 * (map.turns >> (4 * xcd) & 15), lin = xcd * q + (xcd < r ? xcd : r) + (turned < run ? turned : turned - run);
+  const uint32_t per_group = grid_n < 1 << 28 ? 8u * (uint32_t)grid_n : ~0u;
   const uint32_t group = over(lin, per_group, map.div_group), in_group = lin - group * per_group, left = (uint32_t)grid_m - 8 * group;
   if (left >= 8) {
     t.tm = (int32_t)(8 * group + (in_group & 7)), t.tn = (int32_t)(in_group >> 3);

@@ -35,8 +35,12 @@ def test_every_tile_once_and_in_runs(grid_m, grid_n):
     assert sorted(tiles) == [(i, j) for i in range(grid_m) for j in range(grid_n)]
     if (grid_m, grid_n) == (16, 64):                       # runs that would all start at one column of their 16 (see below)
         return
-    # in the order of the XCDs: groups of 8 tile rows, inside them column by column
-    order = [tiles[i] for x in range(8) for i in range(x, n, 8)]
+    # in the order of the XCDs: groups of 8 tile rows, inside them column by column; a run may begin further on and end with what it skipped
+    key = lambda t: (t[0] // 8, t[1], t[0])
+    runs = [tiles[x::8] for x in range(8)]
+    starts = [r.index(min(r, key=key)) if r else 0 for r in runs]
+    order = [t for r, s in zip(runs, starts) for t in r[s:] + r[:s]]
+    assert not any(starts) or (n % 8 and n >= 768)
     assert order == sorted(order, key=lambda t: (t[0] // 8, t[1], t[0]))
 
 
@@ -57,6 +61,20 @@ def test_which_grids_go_in_blocks(grid_m, grid_n, blocks):
         for x in range(8):
             i, j = zip(*tiles[x:256:8])
             assert (max(i) - min(i), max(j) - min(j)) == (7, 3)
+
+
+# Grids that 8 does not divide, of three rounds and more, and neighbours that keep their starts
+@pytest.mark.parametrize("grid_m,grid_n,turned", [(31, 31, True), (31, 33, True), (29, 29, True), (13, 61, True), (11, 70, True), (35, 74, True), (9, 101, True), (250, 61, True),
+                                                  (13, 59, False), (15, 34, False), (7, 200, False), (28, 32, False), (15, 64, False)])
+def test_starts_of_runs(grid_m, grid_n, turned):
+    tiles = tile_map(grid_m, grid_n, range(grid_m * grid_n))
+    assert sorted(tiles) == [(i, j) for i in range(grid_m) for j in range(grid_n)]
+    key = lambda t: (t[0] // 8, t[1], t[0])
+    runs = [tiles[x::8] for x in range(8)]
+    assert any(r[0] != min(r, key=key) for r in runs) == turned
+    if turned:
+        # the 4 columns of 8 tiles that each takes first: together they lie on nearly all of the 16
+        assert len({(r[0][1] + d) % 16 for r in runs for d in range(4)}) >= 14, [r[0][1] % 16 for r in runs]
 
 
 def test_large_grids_divide():
@@ -84,9 +102,9 @@ def test_c_through_a_descriptor(member, dt, out, scale, rows):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("grid_m,grid_n", [(32, 32), (16, 64)])
+@pytest.mark.parametrize("grid_m,grid_n", [(32, 32), (16, 64), (31, 31), (13, 61)])
 @pytest.mark.parametrize("member", [0, 3])
-def test_grids_in_blocks(member, grid_m, grid_n):
+def test_grids_in_blocks_and_turned_runs(member, grid_m, grid_n):
     check(member, grid_m * MEMBERS[member][0] - 3, grid_n * MEMBERS[member][1] - 4, 128, "bf16", "bf16", None, 0, pad=1)
 
 
