@@ -317,7 +317,10 @@ hipError_t launch_relayout_generic(const GenericRelayoutPlan& p, int unit, const
 
 static int g_member = -2;         // of the tile family in the last dense GEMM; -1: the 64 x 64 kernel, -2: none yet
 static GemmArgs g_family;         // what the last dense launch of the tile family was given
-static hipError_t family_launch(int m, const GemmArgs& g) { return g_member = m, g_family = g, hipErrorNotSupported; }
+static int g_placed = -1;         // whether its reads and loads would have had places of their own
+static hipError_t family_launch(int m, const GemmArgs& g) {
+  return g_member = m, g_family = g, g_placed = family_placed(m, !g.scale_a ? 0 : (g.scale_e8m0 ? 2 : 1), g.K), hipErrorNotSupported;
+}
 hipError_t launch_gemm_tiles_16bit(int m, const GemmArgs& g, hipStream_t) { return family_launch(m, g); }
 hipError_t launch_gemm_tiles_grouped(const GemmArgs&, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_gemm_tiles_fp8(int m, const GemmArgs& g, hipStream_t) { return family_launch(m, g); }
@@ -350,6 +353,7 @@ extern "C" int axe_hostcheck_eval_by_blocks(void) { return axe::g_blocks; }
 extern "C" int axe_hostcheck_gemm_member(void) { return axe::g_member; }
 extern "C" int axe_hostcheck_grouped_narrow(void) { return axe::g_narrow; }
 extern "C" int axe_hostcheck_narrow_rows(void) { return axe::g_narrow_rows; }
+extern "C" int axe_hostcheck_family_placed(void) { return axe::g_placed; }
 // Tile of a workgroup of that launch, by the arguments the planner gave it.
 extern "C" void axe_hostcheck_family_tile(uint32_t bid, int32_t* tm, int32_t* tn) {
   const axe::TileAt t = axe::family_tile(bid, axe::g_family.grid_m, axe::g_family.grid_n, axe::g_family.map);

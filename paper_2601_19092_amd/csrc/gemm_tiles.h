@@ -95,10 +95,11 @@ __device__ __forceinline__ void wait_loads() {                     // all but th
 
 // DT: 0 bf16, 1 fp16, 2 fp8 e4m3.  SC (fp8): 0 unscaled, 1 fp32 scales, 2 E8M0 codes, 3 E8M0 codes multiplied as floats.
 // GRP: 0 dense; 1, 2 grouped (A's scales one per row), 2 with the gated epilogue.  A grouped launch finds its workgroup's
-// tiles on the device (grouped_tiles.h) and walks them one after the other.  ONCE: B is loaded past the caches.
+// tiles on the device (grouped_tiles.h) and walks them one after the other.  ONCE: B is loaded past the caches.  PLACED: reads and
+// loads have their places between the matrix instructions (launch_member).
 // Where AXE_TILES_BODY is defined this is a function, for kernels with more than one body (which hand it the workgroup's LDS and the table).  Not
 // everywhere: as a function inside a kernel it compiles to other code (a decode step of 16 rows 11.41 -> 11.46 us).
-template <int DT, int SC, int TM, int TN, int WM, int WN, int WK, int NST, int GRP = 0, bool ONCE = false>
+template <int DT, int SC, int TM, int TN, int WM, int WN, int WK, int NST, int GRP = 0, bool ONCE = false, bool PLACED = false>
 #ifdef AXE_TILES_BODY
 __device__ __forceinline__ void gemm_tiles_body(GemmArgs g, lds_u8 lds3, int t_row0, int t_desc) {
 #else
@@ -112,11 +113,6 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_tiles_kernel(GemmArgs 
   constexpr int kLoads = PA + PB;
   constexpr int kGroup = (TM + TN) * kRow, kStage = WK * kGroup;   // bytes of a group's K-tile, of a stage
   constexpr int U = SC ? 4 : 2;                                    // stages per trip of the main loop
-  // The 256 x 128 tile's sixteen fragments a wave: left to the compiler, a stage's reads gather behind its products and the next barrier waits for
-  // them.  Said to alternate, us: bf16 2048 x 4096 x 2048 36.8 -> 34.9, fp16 to fp32 2299 x 2950 x 4040 72.1 -> 68.5, fp8 2048 x 4096 x 4096 36.5 -> 34.3 (E8M0
-  // 42.1 -> 40.5).  Smaller tiles are level either way (128 x 128 at 2000 x 2000 x 2048 18.8 / 18.7, 1024 x 3584 x 8192 57.9 / 58.7), and so is this one with
-  // fp32 scales, whose fold stands between the products (1000 x 3584 x 8192 63.0 / 66.4).
-  constexpr bool kInterleave = GRP == 0 && TM * TN >= 256 * 128 && SC != 1;
   constexpr int NB = GRP == 2 ? 2 : 1;                             // column blocks of B's scales that a wave needs
   static_assert(TM % (16 * WM) == 0 && TN % (16 * WN) == 0 && (TM / 8) % NG == 0 && (TN / 8) % NG == 0, "whole fragments and pieces");
   static_assert(NST * kStage <= 160 * 1024 && (WK - 1) * TM * TN * 4 <= NST * kStage, "the ring, and then the partial sums, fit LDS");
@@ -419,7 +415,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_tiles_kernel(GemmArgs 
     else wait_loads<(NST - 2) * kLoads>();
     if constexpr (NG > 1) wg_barrier();
     AXE_PARANOID_SYNC();
-    if constexpr (kInterleave) __builtin_amdgcn_sched_barrier(0);
+    if constexpr (PLACED) __builtin_amdgcn_sched_barrier(0);
     const int nxt = cur + 1 == NST ? 0 : cur + 1;
     read_frags(f[(u + 1) & 1], nxt);
     if (u == 0) {
@@ -429,7 +425,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_tiles_kernel(GemmArgs 
     }
     issue(cur);
     multiply(f[u & 1], u, far);
-    if constexpr (kInterleave) {                                   // one matrix instruction, then its share of the reads and, after them, of the loads
+    if constexpr (PLACED) {                                        // one matrix instruction, then its share of the reads and, after them, of the loads
       constexpr int kReads = (MF + NF) * 2, kProducts = MF * NF * (DT == 2 ? 1 : 2), kOthers = kReads + kLoads;
 #pragma unroll
       for (int m = 0; m < kProducts; ++m) {
@@ -576,9 +572,15 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_tiles_kernel(GemmArgs 
 template <int DT, int SC, int F>
 hipError_t launch_member(const GemmArgs& g, hipStream_t s) {
   constexpr TileShape t = kTileFamily[F];
-  hipLaunchKernelGGL((gemm_tiles_kernel<DT, SC, t.tm, t.tn, t.wm, t.wn, t.wk, t.nst>), dim3((unsigned)(g.grid_m * g.grid_n)),
-                     dim3(64 * t.wm * t.wn * t.wk), 0, s, g);
-  return hipGetLastError();
+  auto launch = [&](auto placed) {
+    hipLaunchKernelGGL((gemm_tiles_kernel<DT, SC, t.tm, t.tn, t.wm, t.wn, t.wk, t.nst, 0, false, decltype(placed)::value>), dim3((unsigned)(g.grid_m * g.grid_n)),
+                       dim3(64 * t.wm * t.wn * t.wk), 0, s, g);
+    return hipGetLastError();
+  };
+  constexpr bool shortest = family_placed(F, SC, 0), longest = family_placed(F, SC, INT64_MAX);
+  if constexpr (shortest != longest)
+    if (!family_placed(F, SC, g.K)) return launch(std::false_type{});
+  return launch(std::bool_constant<longest>{});
 }
 
 template <int DT, int SC>

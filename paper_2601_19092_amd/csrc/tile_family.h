@@ -90,6 +90,18 @@ inline TileAt family_tile(uint32_t bid, int32_t grid_m, int32_t grid_n, const Ti
   return t;
 }
 
+// Whether a member's reads and loads have places of their own between the matrix instructions (gemm_tiles.h; sc: 0 unscaled, 1 fp32 scales, 2 E8M0 codes).
+// The 256 x 128 tile's sixteen fragments a wave: left to the compiler, a stage's reads gather behind its products and the next barrier waits for
+// them.  Placed, us: bf16 2048 x 4096 x 2048 36.8 -> 34.9, fp16 to fp32 2299 x 2950 x 4040 72.1 -> 68.5, fp8 2048 x 4096 x 4096 36.5 -> 34.3.  Smaller tiles are level either
+// way (128 x 128 at 2000 x 2000 x 2048 18.8 / 18.7, 1024 x 3584 x 8192 57.9 / 58.7), and so is this one with fp32 scales, whose fold stands between the products
+// (1000 x 3584 x 8192 63.0 / 66.4).  E8M0 codes have their products added up behind them: unplaced / placed K 512 4080 x 12288 69.2 / 71.6, 2040 x 4096 12.0 / 12.2, K 1024 and 1536
+// level, K 2048 4080 x 4092 41.6 / 41.3, K 4096 2000 x 4096 37.7 / 37.1, K 8192 3000 x 5000 128 / 123.
+// (Unscaled, two rounds of tiles and 6 to 10 K-tiles: it goes by the card.  bf16 4080 x 4092 x 512 unplaced / placed 25.5 / 24.3 on one, 27.0 / 28.1 on another.)
+constexpr bool family_placed(int member, int sc, int64_t K) {
+  const TileShape t = kTileFamily[member];
+  return t.tm * t.tn >= 256 * 128 && (sc == 0 || (sc == 2 && K >= 2048));
+}
+
 // The member that serves grouped problems (one wave group: the pipeline runs on from tile to tile), and the problems it takes:
 // whole tiles along N, counted in 11 bits, and at least as many K-tiles of 128 as its ring has stages.
 constexpr int kGroupedMember = 7;

@@ -90,6 +90,34 @@ def test_large_grids_divide():
         assert (tm, tn) == (8 * group + at % rows, at // rows)
 
 
+class At:
+    """An address for a scale array that nothing reads."""
+
+    def __init__(self, dtype):
+        self.dtype = dtype
+
+    def data_ptr(self):
+        return 1 << 43
+
+
+@pytest.mark.parametrize("K,placed", [(512, 0), (1024, 0), (1920, 0), (2048, 1), (4096, 1)])
+@pytest.mark.parametrize("scales", [None, torch.float32, torch.uint8])
+def test_placed_schedule_by_k(K, placed, scales):
+    """The 256 x 128 tile: E8M0 codes by K, unscaled always, fp32 scales never (both sides timed)."""
+    hc = C.CDLL(os.environ.get("AXE_TEST_HOST_LIB") or os.path.join(os.path.dirname(B.LIB_PATH), "libaxe_hostcheck.so"))
+    hc.axe_gemm.argtypes = [C.POINTER(B.axe_gemm_desc_t)] + [C.c_void_p] * 4
+    d = descriptor(2000, 4096, K, "fp8", scales=scales and (At(scales), At(scales)))
+    assert hc.axe_gemm(C.byref(d.c), 1 << 40, 1 << 41, 1 << 42, None) < 0
+    assert hc.axe_hostcheck_gemm_member() == 8
+    assert hc.axe_hostcheck_family_placed() == {None: 1, torch.float32: 0, torch.uint8: placed}[scales]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("K", [1920, 2048])
+def test_e8m0_either_side_of_the_placed_schedule(K):
+    check(8, 300, 260, K, "fp8", "bf16", "e8m0", 1, pad=1)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("member", range(len(MEMBERS)))
 @pytest.mark.parametrize("dt,out,scale,rows", [("bf16", "bf16", None, 0), ("f16", "f32", None, 0), ("fp8", "bf16", "f32", 1), ("fp8", "f32", "f32", 0)])
