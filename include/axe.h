@@ -284,6 +284,10 @@ int axe_gemm_grouped_check(const axe_gemm_grouped_desc_t* g);
  *       tile height only, both K multiples of 128 and at least 256, first problem gated, H's rows starting on
  *       128-byte boundaries (pitch and buffer), and few enough tiles that one workgroup per compute unit holds
  *       them (64 per workgroup and problem).
+ *   A kernel that either problem asks for is what runs: row blocks of the height that the hints name (AXE_GROUPED_TILES and
+ *   AXE_GROUPED_TILE128_ROWS as for one problem).  With AXE_GROUPED_AUTO on both and no such threshold set the one launch may take row
+ *   blocks of 192, which a single problem never does: the same bits, and axe_gemm_grouped_kernel and axe_gemm_grouped_describe, which
+ *   answer for axe_gemm_grouped, don't tell.
  *   Every wait inside the kernel is bounded (a number of polls, AXE_GROUPED_PAIR_POLLS, default 2^20, each a few
  *   microseconds): a wait that gives up is counted in d_sync[M] and the tile is computed from what is there.
  *   axe_gemm_grouped_pair_status(d_sync, M, stream) synchronises the stream and returns AXE_ETIMEOUT if any wait of

@@ -330,7 +330,8 @@ hipError_t launch_gemm_bf16_256_grouped(const GemmArgs&, hipStream_t) { return h
 hipError_t launch_gemm_bf16_256_ragged(const GemmArgs&, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_pair_sync_clear(int32_t*, int64_t, hipStream_t) { return hipErrorNotSupported; }
 hipError_t pair_static_workspace(int32_t**) { return hipErrorNotSupported; }
-hipError_t launch_gemm_bf16_256_grouped_pair(const GemmArgs&, const GemmArgs&, int32_t*, int, int, hipStream_t) { return hipErrorNotSupported; }
+static int g_pair_rows = 0;       // rows of a tile of the last fused pair
+hipError_t launch_gemm_bf16_256_grouped_pair(const GemmArgs&, const GemmArgs&, int rows, int32_t*, int, int, hipStream_t) { return g_pair_rows = rows, hipErrorNotSupported; }
 static int g_narrow = -1;         // whether the last grouped GEMM of few rows per group would have gone to the narrow tiles; -1: none yet
 static int g_narrow_rows = 0;     // and the rows of their tile, or 0
 hipError_t launch_gemm_grouped_stream(const GemmArgs& g, hipStream_t) { return g_narrow = narrow_fits(g), g_narrow_rows = g_narrow ? narrow_rows(g) : 0, hipErrorNotSupported; }
@@ -352,6 +353,7 @@ extern "C" void axe_hostcheck_set_buffers(int64_t src_bytes, int64_t dst_bytes) 
 extern "C" int axe_hostcheck_eval_by_blocks(void) { return axe::g_blocks; }
 extern "C" int axe_hostcheck_gemm_member(void) { return axe::g_member; }
 extern "C" int axe_hostcheck_grouped_narrow(void) { return axe::g_narrow; }
+extern "C" int axe_hostcheck_pair_rows(void) { return axe::g_pair_rows; }
 extern "C" int axe_hostcheck_narrow_rows(void) { return axe::g_narrow_rows; }
 extern "C" int axe_hostcheck_family_placed(void) { return axe::g_placed; }
 // Tile of a workgroup of that launch, by the arguments the planner gave it.

@@ -56,7 +56,8 @@ hipError_t launch_gemm_bf16_256_grouped(const GemmArgs& g, hipStream_t s);
 constexpr int64_t kPairStaticRows = int64_t(1) << 20;
 hipError_t pair_static_workspace(int32_t** out);
 hipError_t launch_pair_sync_clear(int32_t* p, int64_t n, hipStream_t s);   // p[0 .. n) = 0, by a small kernel
-hipError_t launch_gemm_bf16_256_grouped_pair(const GemmArgs& g1, const GemmArgs& g2, int32_t* sync, int spin_limit, int need_extra,
+// rows: of a tile, 128, 192 or 256 (pair_tile_rows)
+hipError_t launch_gemm_bf16_256_grouped_pair(const GemmArgs& g1, const GemmArgs& g2, int rows, int32_t* sync, int spin_limit, int need_extra,
                                              hipStream_t s);
 // dense with ragged edges through the grouped kernel (g.groups = 1, g.group_rows null): any M, N % 8 == 0, K % 64 == 0
 hipError_t launch_gemm_bf16_256_ragged(const GemmArgs& g, hipStream_t s);
@@ -64,10 +65,17 @@ hipError_t launch_gemm_bf16_256_ragged(const GemmArgs& g, hipStream_t s);
 // group sizes) or tile_m says otherwise.  Measured on an MoE layer (128 groups, N = 1536, K = 2048 and N = 2048,
 // K = 768): 128-row tiles win by 2 - 11 % up to 64 rows per group on average, draw at 256, and lose 3 - 4 % at 512 and
 // 7 - 8 % from 1024 on (AXE_GROUPED_TILE128_ROWS overrides the threshold for experiments).
+struct Tile128Rows {
+  int avg;
+  bool set;
+};
+inline Tile128Rows grouped_tile128_rows() {
+  static const Tile128Rows r = [] { const char* v = getenv("AXE_GROUPED_TILE128_ROWS"); return Tile128Rows{v ? atoi(v) : 384, v != nullptr}; }();
+  return r;
+}
 inline int grouped_tile_rows(int64_t M, int groups, int tile_m) {
-  static const int small_avg = [] { const char* v = getenv("AXE_GROUPED_TILE128_ROWS"); return v ? atoi(v) : 384; }();
   if (tile_m) return tile_m == 128 ? 128 : 256;
-  return M <= (int64_t)small_avg * groups ? 128 : 256;
+  return M <= (int64_t)grouped_tile128_rows().avg * groups ? 128 : 256;
 }
 // The same choice for the fp8 grouped tile kernel (AXE_GROUPED_FP8_TILE128_ROWS overrides the threshold).  Measured on
 // the same layer with E8M0 scales (gemm1 + gemm2, us, 256-row against 128-row tiles): 16 rows per group 158 against 136,
@@ -148,10 +156,8 @@ inline int narrow_rows(const GemmArgs& g) {
   return g.M <= (g.fp8 ? 12 : 16) * G ? 32 : 64;
 }
 
-// Whether two planned grouped problems (the second reading what the first writes) can run as one launch: both on
-// the chained tile pipeline with the same tile height, and few enough tiles in the worst case that one workgroup per
-// compute unit holds them all (a wave keeps 64 per GEMM) -- the workgroups must all be resident for the waits to end.
-// Rows of a tile of the fused pair, 128, 192 or 256, where the caller asks for none: by the rows per group on average.  Measured, us, 128 / 192 / 256 rows,
+// Rows of a tile of the fused pair: what its two problems ask for (128 or 256, the same for both: grouped_pair_fusable), or, where both leave it to
+// the library (left: no kernel asked for, and no threshold set for experiments), 128, 192 or 256 by the rows per group on average.  Measured, us, 128 / 192 / 256 rows,
 // fp16, groups drawn around the average (experts x hidden x intermediate).
 //   - With three tiles of 128 x 256 and more for every compute unit the height with the least weights loaded per compute unit wins: 128 x 2048 x 768 at 112 rows
 //     287 / 288 / 315, 144 306 / 296 / 324, 162 330 / 310 / 332, 219 385 / 362 / 367, 256 433 / 419 / 425, 300 480 / 461 / 449, 350 528 / 508 / 511; 256 x 2048 x 512 at
@@ -159,14 +165,18 @@ inline int narrow_rows(const GemmArgs& g) {
 //   - Fewer tiles are a round or two, and what counts is how many blocks most groups have: 16 x 4096 x 2048 at 180 204 / 237 / 266, 220 267 / 238 / 280, 256 277 / 249 / 290,
 //     300 286 / 288 / 295; 32 x 2048 x 1024 at 180 116 / 128 / 153, 256 153 / 135 / 165, 300 156 / 177 / 162; 8 x 4096 x 4096 at 180 197 / 238 / 243, 256 287 / 239 / 285;
 //     64 x 1024 x 512 at 180 70 / 79 / 97, 220 94 / 80 / 96, 300 98 / 103 / 102.
-inline int pair_tile_rows(const GemmArgs& g1) {
+inline int pair_tile_rows(const GemmArgs& g1, bool left) {
   const int rows = grouped_tile_rows(g1.M, g1.groups, g1.tile_m);
-  if (g1.tile_m || rows != 128) return rows;
+  if (!left || rows != 128 || grouped_tile128_rows().set) return rows;
   const int64_t G = g1.groups;
   const bool many = G * g1.grid_n >= 3 * (int64_t)cu_count();
   if (g1.M > 288 * G) return many ? 256 : 128;
   return g1.M > (many ? 136 : 208) * G ? 192 : 128;
 }
+// Whether two planned grouped problems (the second reading what the first writes) can run as one launch: both on
+// the chained tile pipeline, asking for the same tile height, and few enough tiles in the worst case that one workgroup per
+// compute unit holds them all (a wave keeps 64 per GEMM) -- the workgroups must all be resident for the waits to end.  (Judged on the height
+// asked for: pair_tile_rows takes none lower.)
 inline bool grouped_pair_fusable(const GemmArgs& g1, const GemmArgs& g2) {
   const int cus = cu_count();
   const int tm = grouped_tile_rows(g1.M, g1.groups, g1.tile_m);

@@ -772,10 +772,9 @@ hipError_t pair_static_workspace(int32_t** out) {
 }
 
 // sync: M + 1 words of device memory (cleared here, on the stream, by a small kernel: a caller may be capturing a graph)
-hipError_t launch_gemm_bf16_256_grouped_pair(const GemmArgs& g1, const GemmArgs& g2, int32_t* sync, int spin_limit, int need_extra,
+hipError_t launch_gemm_bf16_256_grouped_pair(const GemmArgs& g1, const GemmArgs& g2, int rows, int32_t* sync, int spin_limit, int need_extra,
                                              hipStream_t s) {
-  if (!grouped_pair_fusable(g1, g2) || !sync) return hipErrorInvalidValue;
-  const int rows = pair_tile_rows(g1);
+  if (!grouped_pair_fusable(g1, g2) || rows < grouped_tile_rows(g1.M, g1.groups, g1.tile_m) || !sync) return hipErrorInvalidValue;
   if (hipError_t e = launch_pair_sync_clear(sync, g1.M + 1, s); e != hipSuccess) return e;
   PairSync ps;
   ps.done = sync;
