@@ -1332,7 +1332,7 @@ int axe_gemm_grouped_pair(const axe_gemm_grouped_desc_t* g1, const axe_gemm_grou
   hipStream_t st = (hipStream_t)stream;
   if (d_sync && pair_runs_fused(g1, g2, a1, a2)) {
     const bool left = g1->kernel_hint == AXE_GROUPED_AUTO && g2->kernel_hint == AXE_GROUPED_AUTO;
-    hipError_t e = launch_gemm_bf16_256_grouped_pair(a1, a2, pair_tile_rows(a1, left), d_sync, env_int("AXE_GROUPED_PAIR_POLLS", 1 << 20),
+    hipError_t e = launch_gemm_bf16_256_grouped_pair(a1, a2, pair_tile_rows(a1, a2, left), d_sync, env_int("AXE_GROUPED_PAIR_POLLS", 1 << 20),
                                                      env_int("AXE_GROUPED_PAIR_TEST_NEVER", 0) ? 1 : 0, st);
     return e == hipSuccess ? AXE_OK : hip_fail(e, "axe_gemm_grouped_pair");
   }

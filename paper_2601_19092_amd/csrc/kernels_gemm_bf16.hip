@@ -136,10 +136,9 @@ __device__ __forceinline__ lds_u8 tile_lds() {
 // 2 x 64 and moves half as much of A (4 pieces per wave and K-step), so that the weights stream past twice as
 // fast -- with few rows per group the time is that of reading B from HBM.  The A blocks in LDS keep their
 // places (half of each is used); loads per K-step 12 instead of 16 (the wait count at the barrier is the same).
-// 6 (192 rows) in the fused pair: with some 250 rows per group a compute unit's time is that of its loads -- 256 lines in flight, each for a
-// trip to HBM, whether a neighbour asks for the same line or not -- and a group's 1.8 row blocks read its weights into LDS 1.8 times
-// instead of 2.5, for a tenth more matrix work (256 rows: 1.5 times, a fifth more).  us, 128 / 192 / 256 rows, the layer of 128 groups: 4096 tokens fp16
-// 433 / 419 / 425, bf16 422 / 407 / 411, 2600 tokens 330 / 310 / 332.  Which: pair_tile_rows.
+// 6 (192 rows) in the fused pair: a group of 129 to 192 rows is one row block instead of two, so its weights are read into LDS once instead of twice, for
+// a quarter less matrix work (192 rows of it against 256).  us, 128 / 192 / 256 rows, the layer of 128 groups in fp16 with 180 rows in each 345 / 297 / 306, drawn
+// around 180 350 / 347 / 341.  Which: pair_tile_rows.
 //
 // RAGGED: a dense GEMM whose M is no multiple of the tile height and whose N is no multiple of 256 (but of 8:
 // a lane stores 8 columns at once), run as a grouped one with a single group of all rows.  What M leaves over
@@ -478,7 +477,7 @@ __device__ __forceinline__ void gemm_bf16_256_body(const GemmArgs& g, int tb_row
     // (16 of them, 256 cycles) into sub-step 1: the wave reaches it with the last LDS read of sub-step 0 long
     // complete and a little more time for its loads to land, instead of draining the matrix pipe while it waits
     // for that read.  Everything that needs the barrier -- reads of step kt + 1, loads into what step kt
-    // occupied -- is scheduled into rows 2..7 of sub-step 1; rows 0 and 1 only multiply what is in registers.
+    // occupied -- is scheduled into rows 2..7 (192 rows: 2..5) of sub-step 1; rows 0 and 1 only multiply what is in registers.
     constexpr bool LATE = MR != 4;
     auto step_barrier = [&]() __attribute__((always_inline)) {
       // Own reads of step kt are complete, and so are own loads of step kt+1 (the 8 younger loads may still
@@ -502,7 +501,7 @@ __device__ __forceinline__ void gemm_bf16_256_body(const GemmArgs& g, int tb_row
         mfma_16x16x32<F16>(acc[mi][mj], fb[CUR][mj], fa[mi]);
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (LATE && S == 1) {
-          // side work of sub-step 1, rows 2..7 (NJ = 8, or 7 with the 224-wide tile: nothing sits at j = 7 but
+          // side work of sub-step 1, rows 2..7, or 2..5 of six (NJ = 8, or 7 with the 224-wide tile: nothing sits at j = 7 but
           // the reload of the row's own A fragment, which goes with the row's last MFMA)
           if (i == 1 && j == NJ - 1) step_barrier();
           if (i >= 2 && i < 6 && (j == 1 || j == 5) && 2 * (i - 2) + (j == 5) < NJ)
@@ -631,7 +630,8 @@ __device__ __forceinline__ void gemm_bf16_256_body(const GemmArgs& g, int tb_row
 }
 
 // A grouped kernel's tiles, worked out on the device, and its body on them.  128-row tiles come in both cache policies for B: the
-// table says which (larger tiles go with groups of several row blocks).
+// table says which.  256-row tiles go with groups of several row blocks.  192-row tiles (the pair) have mostly one in a group, but load through
+// the caches all the same: a body past them has not been measured.
 template <bool GATED, bool F16, int MR, bool RAGGED = false, bool OUT32 = false, int PAIR = 0>
 __device__ __forceinline__ void gemm_bf16_256_grouped_body(const GemmArgs& g, const PairSync ps = PairSync{}) {
   int row0, desc;
