@@ -956,7 +956,7 @@ int plan_gemm(const axe_gemm_desc_t* g, const void* dA, const void* dB, void* dC
   P.args.grid_n = (int32_t)((g->N + bn - 1) / bn);
   P.args.tile_n = (int32_t)bn;
   if (P.member >= 0) {
-    P.args.map = family_map(P.args.grid_m, P.args.grid_n);
+    P.args.map = family_map(P.args.grid_m, P.args.grid_n, bm, bn, cu_count());
     // (a tile's part of C within 32-bit offsets; whole dwords)
     P.args.c_vec = g->N % 4 == 0 && ldc * ob % 4 == 0 && 256 * ldc * ob < (int64_t(1) << 30);
   }

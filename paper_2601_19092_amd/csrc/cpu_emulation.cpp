@@ -356,9 +356,13 @@ extern "C" int axe_hostcheck_grouped_narrow(void) { return axe::g_narrow; }
 extern "C" int axe_hostcheck_pair_rows(void) { return axe::g_pair_rows; }
 extern "C" int axe_hostcheck_narrow_rows(void) { return axe::g_narrow_rows; }
 extern "C" int axe_hostcheck_family_placed(void) { return axe::g_placed; }
-// Tile of a workgroup of that launch, by the arguments the planner gave it.
-extern "C" void axe_hostcheck_family_tile(uint32_t bid, int32_t* tm, int32_t* tn) {
+// Tile of a workgroup of that launch, by the arguments the planner gave it; and of any grid dealt in runs.
+extern "C" void axe_hostcheck_planned_tile(uint32_t bid, int32_t* tm, int32_t* tn) {
   const axe::TileAt t = axe::family_tile(bid, axe::g_family.grid_m, axe::g_family.grid_n, axe::g_family.map);
+  *tm = t.tm, *tn = t.tn;
+}
+extern "C" void axe_hostcheck_family_tile(int32_t bid, int32_t grid_m, int32_t grid_n, int32_t* tm, int32_t* tn) {
+  const axe::TileAt t = axe::family_tile((uint32_t)bid, grid_m, grid_n, axe::family_runs(grid_m, grid_n));
   *tm = t.tm, *tn = t.tn;
 }
 extern "C" void axe_hostcheck_plan_only(int on) { axe::g_plan_only = on; }

@@ -125,7 +125,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_tiles_kernel(GemmArgs 
   // the arguments in one fetch: left alone they come one by one, where each is first used, and every fetch is waited for
   if constexpr (GRP == 0) {
     asm volatile("" ::"s"(g.A), "s"(g.B), "s"(g.C), "s"(g.M), "s"(g.N), "s"(g.K), "s"(g.lda), "s"(g.ldb), "s"(g.ldc));
-    asm volatile("" ::"s"(g.grid_m), "s"(g.grid_n), "s"(g.map.div_group), "s"(g.map.div_last), "s"(g.map.blocks), "s"(g.map.turns), "s"(g.c_vec), "s"(g.out_bf16));
+    asm volatile("" ::"s"(g.grid_m), "s"(g.grid_n), "s"(g.map.div_group), "s"(g.map.div_last), "s"(g.map.deal), "s"(g.map.turns), "s"(g.c_vec), "s"(g.out_bf16));
     if constexpr (SC != 0) asm volatile("" ::"s"(g.scale_a), "s"(g.scale_b), "s"(g.scale_a_rows), "s"(g.nkb));
   }
   const int lane = threadIdx.x & 63;

@@ -30,9 +30,10 @@ inline uint32_t div_factor(uint64_t d, uint64_t most) {
 }
 
 // What the map below needs of a grid, worked out by the host.
+enum : uint32_t { kRuns = 0, kBlocks = 1, kInTurn = 2 };
 struct TileMap {
-  uint32_t div_group, div_last;   // div_factor() of the tiles of a group of 8 tile rows, and of the last group's tile rows (blocks: of the blocks of a row)
-  uint32_t blocks;                // 1: the tiles go to the XCDs in blocks of 16 x 16
+  uint32_t div_group, div_last;   // div_factor() of the tiles of a group of 8 tile rows, and of the last group's tile rows (kBlocks: of the blocks of a row)
+  uint32_t deal;                  // how the tiles go to the XCDs: kRuns, kBlocks (of 16 x 16) or kInTurn (tile by tile)
   uint32_t turns;                 // 4 bits for each XCD: the tile columns by which its run is turned
 };
 // Where a launch is four rounds of tiles and more, every XCD walks along its rows of C at the pace of the others.  Runs that start at one or two columns (grid_m a
@@ -45,10 +46,45 @@ struct TileMap {
 // columns) and ends with what it skipped.  Round robin / runs / turned, us: fp8 31 x 31 tiles 7842 x 3908 x 512 with fp32 scales 40.7 / 44.4 / 42.0, unscaled 7776 x 3968 x 768 52.3 /
 // 50.9 / 48.4, bf16 31 x 33 7840 x 4220 x 512 67.7 / 58.8 / 54.3; over 107 products of 18 such grids 1 / 0.934 / 0.925 of the time, the slowest turned 29 x 29 with scales
 // (7286 x 3652 x 512 36.7 / 38.2 / 38.0), the slowest run 1.09.  (Where 8 divides them the runs start as they always have.)
-inline TileMap family_map(int64_t grid_m, int64_t grid_n) {
+//
+// One round of tiles that 8 does not divide goes in turn unless the XCDs then read many more rows (rows_read; 15 % decide, since the count leaves out when they are read): an XCD
+// has one row of every group of 8 tile rows, all columns of it, so few XCDs read a panel of A, where a run that goes from one group into the next reads up to 16.  us, in turn / runs: bf16 6733 x 244 x 8128
+// (53 x 4 tiles of 128 x 64) 41.0 / 52.5, 3284 x 332 x 2088 (26 x 6) 13.2 / 18.0, f16 711 x 475 x 3208 (12 x 15 of 64 x 32) 11.1 / 13.6, 2578 x 67 x 6160 (81 x 3 of 32 x 32) 13.7 / 16.6, 15243 x 64 x 1216 (239 x 1 of
+// 64 x 64) 8.4 / 9.2, fp8 2275 x 793 x 2224 (18 x 13 of 128 x 64) 10.4 / 11.7; and bf16 3002 x 51 x 2088 (94 x 2) 7.0 / 6.5.  Of 815 such launches of all members 607 go in turn; 0.3 % slower than the faster way on average, always in runs
+// 1.8 %, always in turn 0.8 %.  With more rounds it decides less (three of 92 more than 3 % slower in runs), and a grid of up to 8 tile rows has a single group.
+//
+// Rows of A and B that the XCDs read between them, each panel once for every XCD that has a tile of it; grid_m > 8.
+inline int64_t rows_read(uint32_t deal, int64_t grid_m, int64_t grid_n, int64_t tm, int64_t tn) {
+  const int64_t group = 8 * grid_n, tiles = grid_m * grid_n, q = tiles / 8, r = tiles % 8, full = grid_m / 8, last = grid_m % 8;
+  int64_t rows = 0, cols = 0;
+  for (int64_t x = 0; x < 8; ++x) {
+    if (deal == kInTurn) {                                           // of the last group, position x and every 8th from there
+      const int64_t has = last ? (last * grid_n - x + 7) / 8 : 0, all = last % 4 == 0 ? 1 : (last % 2 ? last : last / 2);
+      rows += full + (has < all ? has : all), cols += grid_n;
+      continue;
+    }
+    int64_t at = x * q + (x < r ? x : r), end = at + q + (x < r), lo = 0, hi = 0, next = 0;   // its first piece has columns lo .. hi, the others 0 .. next - 1
+    for (bool first = true; at < end; first = false) {
+      const int64_t g = at / group, start = g * group, height = g < full ? 8 : last, stop = end < start + height * grid_n ? end : start + height * grid_n;
+      rows += stop - at < height ? stop - at : height;
+      const int64_t c = (stop - 1 - start) / height;
+      if (first) lo = (at - start) / height, hi = c;
+      else next = c + 1 > next ? c + 1 : next;
+      at = stop;
+    }
+    cols += next <= lo ? next + hi - lo + 1 : (next > hi + 1 ? next : hi + 1);
+  }
+  return rows * tm + cols * tn;
+}
+inline TileMap family_runs(int64_t grid_m, int64_t grid_n) {
+  const uint64_t group = 8 * (uint64_t)grid_n;
+  return {div_factor(group, (uint64_t)grid_m * (uint64_t)grid_n), div_factor((uint64_t)(grid_m & 7), group), kRuns, 0};
+}
+inline TileMap family_map(int64_t grid_m, int64_t grid_n, int64_t tm, int64_t tn, int64_t round) {   // tiles of tm x tn, round of them at a time
   const uint64_t tiles = (uint64_t)grid_m * (uint64_t)grid_n, group = 8 * (uint64_t)grid_n, q = tiles / 8, r = tiles % 8;
-  TileMap m = {div_factor(group, tiles), div_factor((uint64_t)(grid_m & 7), group), 0, 0};
-  if (((grid_m | grid_n) & 15) == 0 && tiles >= 1024 && (grid_m % 32 == 0 || tiles % 1024 == 0)) m.blocks = 1, m.div_last = div_factor((uint64_t)grid_n / 16, tiles / 256);
+  TileMap m = family_runs(grid_m, grid_n);
+  if (((grid_m | grid_n) & 15) == 0 && tiles >= 1024 && (grid_m % 32 == 0 || tiles % 1024 == 0)) m.deal = kBlocks, m.div_last = div_factor((uint64_t)grid_n / 16, tiles / 256);
+  if (r != 0 && grid_m > 8 && tiles <= (uint64_t)round && 20 * rows_read(kInTurn, grid_m, grid_n, tm, tn) < 23 * rows_read(kRuns, grid_m, grid_n, tm, tn)) m.deal = kInTurn;
   for (uint64_t x = 0; x < 8 && r != 0 && grid_m >= 8 && q >= 96 && q <= 2048; ++x) {
     const uint64_t first = x * q + (x < r ? x : r), turn = (4 * x - first % group / 8) & 15;
     if (8 * turn < q) m.turns |= (uint32_t)turn << (4 * x);
@@ -72,13 +108,14 @@ inline TileAt family_tile(uint32_t bid, int32_t grid_m, int32_t grid_n, const Ti
   const uint32_t xcd = bid & 7, pos = bid >> 3;
   auto over = [](uint32_t n, uint32_t d, uint32_t f) -> uint32_t { return f ? (uint32_t)(((uint64_t)(2 * n) * f) >> 32) : n / d; };
   TileAt t;
-  if (map.blocks) {
+  if (map.deal == kBlocks) {
     const uint32_t per_row = (uint32_t)grid_n >> 4, block = pos >> 5, row = over(block, per_row, map.div_last), at = block - row * per_row;
     t.tm = (int32_t)(16 * row + 8 * (xcd >> 2) + (pos & 7)), t.tn = (int32_t)(16 * (row & 1 ? per_row - 1 - at : at) + 4 * (xcd & 3) + (pos >> 3 & 3));
     return t;
   }
   const uint32_t nwg = (uint32_t)grid_m * (uint32_t)grid_n, q = nwg >> 3, r = nwg & 7, run = q + (xcd < r ? 1 : 0);
-  const uint32_t turned = pos + 8 * (map.turns >> (4 * xcd) & 15), lin = xcd * q + (xcd < r ? xcd : r) + (turned < run ? turned : turned - run);
+  const uint32_t turned = pos + 8 * (map.turns >> (4 * xcd) & 15), in_run = xcd * q + (xcd < r ? xcd : r) + (turned < run ? turned : turned - run);
+  const uint32_t lin = map.deal == kInTurn ? bid : in_run;
   const uint32_t per_group = grid_n < 1 << 28 ? 8u * (uint32_t)grid_n : ~0u;
   const uint32_t group = over(lin, per_group, map.div_group), in_group = lin - group * per_group, left = (uint32_t)grid_m - 8 * group;
   if (left >= 8) {
