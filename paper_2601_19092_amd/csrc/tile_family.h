@@ -93,9 +93,9 @@ inline TileMap family_map(int64_t grid_m, int64_t grid_n, int64_t tm, int64_t tn
 }
 
 // Workgroup id -> tile of a dense launch.  Workgroup ids go round the 8 XCDs one by one, and each XCD takes a run of the tile sequence (they
-// differ by one tile at most), in which columns of 8 tile rows follow one another: its 32 workgroups share 8 panels of A and 4 of B.  Grids of a
-// number of tiles that 8 does not divide used to go to the XCDs tile by tile, so that every L2 read every panel; us, before -> with this map and what the
-// kernel no longer spends ahead of its first load: bf16 321 x 1164 x 8064 (19 x 37 tiles) 24.3 -> 19.5, 393 x 7991 x 1432 23.0 -> 20.1, fp16 310 x 2432 x
+// differ by one tile at most; other deals above), in which columns of 8 tile rows follow one another: its 32 workgroups share 8 panels of A and 4 of B.  Grids of a
+// number of tiles that 8 does not divide used to go to the XCDs tile by tile, all of them; us, before -> with this map and what the
+// kernel no longer spends ahead of its first load: bf16 321 x 1164 x 8064 (6 x 37 tiles) 24.3 -> 19.5, 393 x 7991 x 1432 23.0 -> 20.1, fp16 310 x 2432 x
 // 1408 10.0 -> 7.7; grids that 8 divides gain 0.3 - 0.6 us (1 x 896 x 1664 fp8 3.9 -> 3.4, 512 x 1792 x 1792 fp16 9.05 -> 8.6): two divisions, three fetches of
 // arguments one after the other and, at the end, a third of the instructions per stored fragment.
 struct TileAt {
