@@ -157,23 +157,23 @@ inline int narrow_rows(const GemmArgs& g) {
 }
 
 // Rows of a tile of the fused pair: what its two problems ask for (128 or 256, the same for both: grouped_pair_fusable), or, where both leave it to
-// the library (left: no kernel asked for, and no threshold set for experiments), 192 for 177 to 192 rows per group on average and at least one and a half
-// tiles of 256 columns per compute unit in either product.  The host knows the average, not the sizes, and the best height goes by the sizes: a group
+// the library (left: no kernel asked for, and no threshold set for experiments), 192 for 177 to 192 rows per group on average and at least one and three
+// quarter columns of tiles, 256 wide, per compute unit in either product (all groups).  The host knows the average, not the sizes, and the best height goes by the sizes: a group
 // of 129 to 192 rows is one row block of 192 or two of 128, one of 193 to 256 two of either.  So 192 is taken only where it was not slower whatever the sizes; time on 192 rows
 // over that on 128, fp16, groups drawn around the average with weights exp(N(0, 1/2)) (three draws) / all equal / a quarter of the rows in one group, the others equal:
 //   - 180 rows per group (experts x hidden x intermediate): 128 x 2048 x 768 0.99 / 0.86 / 0.71, 256 x 2048 x 512 0.96 / 0.81 / 0.67, 64 x 2048 x 1024 0.97 / 0.82 / 0.75, 60 x 2048 x 1408 0.92 / 0.81 /
-//     0.83, 128 x 4096 x 1536 0.99 / 0.81 / 0.57, 160 x 5120 x 1536 0.95 / 0.83 / 0.76, 64 x 2048 x 768 1.05 / 0.92 / 0.82; at 192 0.96 / 0.85 / 0.78, 0.96 / 0.84 / 0.66, 0.93 / 0.85 / 0.79, 0.91 / 0.80 / 0.83,
-//     0.99 / 0.80 / 0.57, 1.01 / 0.82 / 0.79, 0.99 / 0.92 / 0.86.
-//   - fewer rows: with a quarter of them in one group the others have at most 128: at 150 1.05 / 0.99 / 1.08 / 1.07 / 1.06 / 1.00 / 1.09 (the same seven).
+//     0.83, 128 x 4096 x 1536 0.99 / 0.81 / 0.57, 160 x 5120 x 1536 0.95 / 0.83 / 0.76; at 192 0.96 / 0.85 / 0.78, 0.96 / 0.84 / 0.66, 0.93 / 0.85 / 0.79, 0.91 / 0.80 / 0.83,
+//     0.99 / 0.80 / 0.57, 1.01 / 0.82 / 0.79.
+//   - fewer rows: with a quarter of them in one group the others have at most 128: at 150 1.05 / 0.99 / 1.08 / 1.07 / 1.06 / 1.00 (the same six).
 //   - more rows: equal groups have two row blocks either way.  At 200 128 x 2048 x 768 0.94 / 1.34 / 0.77, 64 x 2048 x 1024 0.83 / 1.23 / 0.78, 160 x 5120 x 1536 1.03 / 1.47 / 0.74; at 256 0.95 / 1.15 / 1.28, 1.01 / 1.15 /
 //     1.21, 1.03 / 1.41 / 1.36; at 320 0.95 / 0.90 / 1.17, 1.00 / 0.94 / 1.05, 1.00 / 1.02 / 1.33.  (256 rows, at 320: 1.01 / 1.10 / 0.87, 1.02 / 1.13 / 0.84, 1.01 / 1.21 / 0.81.)
-//   - fewer tiles: whole rounds decide.  At 180 16 x 4096 x 2048 (256 columns of tiles in both products) 1.12 / 0.84 / 0.82, 64 x 1024 x 512 (256) 1.13 / 0.83 / 0.97, 8 x 4096 x 1792 (112, 128) 1.11 / 1.17 / 0.95, 8 x 2048 x 1024 (64)
+//   - fewer tiles: whole rounds decide.  At 180 64 x 2048 x 768 (384 columns of tiles, 512) 1.05 / 0.92 / 0.82, 16 x 4096 x 2048 (256 columns of tiles in both products) 1.12 / 0.84 / 0.82, 64 x 1024 x 512 (256) 1.13 / 0.83 / 0.97, 8 x 4096 x 1792 (112, 128) 1.11 / 1.17 / 0.95, 8 x 2048 x 1024 (64)
 //     1.11 / 1.18 / 1.09, 32 x 2048 x 768 (192, 256) 1.13 / 0.81 / 0.86, 8 x 4096 x 14336 (896, 128) 1.05 / 1.07 / 0.73.
 inline int pair_tile_rows(const GemmArgs& g1, const GemmArgs& g2, bool left) {
   const int rows = grouped_tile_rows(g1.M, g1.groups, g1.tile_m);
   if (!left || rows != 128 || grouped_tile128_rows().set) return rows;
   const int64_t G = g1.groups, columns = G * (g1.grid_n < g2.grid_n ? g1.grid_n : g2.grid_n);
-  return g1.M > 176 * G && g1.M <= 192 * G && 2 * columns >= 3 * (int64_t)cu_count() ? 192 : 128;
+  return g1.M > 176 * G && g1.M <= 192 * G && 4 * columns >= 7 * (int64_t)cu_count() ? 192 : 128;
 }
 // Whether two planned grouped problems (the second reading what the first writes) can run as one launch: both on
 // the chained tile pipeline, asking for the same tile height, and few enough tiles in the worst case that one workgroup per

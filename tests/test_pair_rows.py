@@ -53,8 +53,8 @@ def test_the_threshold_for_experiments_counts_in_a_pair(threshold, rows):
 @pytest.mark.parametrize("shape,M,rows", [
     (LAYER, 128 * 176, 128), (LAYER, 128 * 176 + 1, 192), (LAYER, 128 * 192, 192), (LAYER, 128 * 192 + 1, 128),
     (LAYER, 128 * 137, 128), (LAYER, 128 * 209, 128), (LAYER, 128 * 256, 128), (LAYER, 128 * 289, 128), (LAYER, 128 * 384, 128), (LAYER, 128 * 384 + 1, 256),
-    ((256, 2048, 512), 256 * 184, 192), ((64, 2048, 768), 64 * 184, 192), ((60, 2048, 1408), 60 * 184, 192),             # 384 columns and more in both
-    ((192, 512, 256), 192 * 184, 192), ((191, 512, 256), 191 * 184, 128), ((48, 2048, 1024), 48 * 184, 192), ((47, 2048, 1024), 47 * 184, 128),
+    ((256, 2048, 512), 256 * 184, 192), ((64, 2048, 1024), 64 * 184, 192), ((60, 2048, 1408), 60 * 184, 192),             # 448 columns and more in both
+    ((224, 512, 256), 224 * 184, 192), ((223, 512, 256), 223 * 184, 128), ((56, 2048, 1024), 56 * 184, 192), ((55, 2048, 1024), 55 * 184, 128), ((64, 2048, 768), 64 * 184, 128),
     ((8, 4096, 14336), 8 * 184, 128), ((128, 512, 768), 128 * 184, 128), ((12, 4096, 3584), 12 * 184, 128), ((128, 2048, 256), 128 * 184, 128),   # few in one of them
     ((16, 4096, 2048), 16 * 256, 128), ((8, 4096, 1792), 8 * 220, 128), ((8, 2048, 1024), 8 * 240, 128), ((4, 2048, 768), 4 * 240, 128), ((1, 4096, 4096), 180, 128)])
 def test_the_librarys_own_choice(shape, M, rows):
