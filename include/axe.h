@@ -249,7 +249,8 @@ typedef struct {
  * launches that don't fill the chip.  AUTO takes AXE_GROUPED_STREAM when M <= 13 G, or M <= 19 G when K <= 1024 (the host knows M, not the group sizes; measured
  * crossovers on the two GEMMs of the benchmark's MoE layer).  In a pair the second GEMM follows the first. */
 enum { AXE_GROUPED_AUTO = 0, AXE_GROUPED_TILES = 1, AXE_GROUPED_STREAM = 2,
-       /* the tile kernel with tiles of 256 or 128 rows (AXE_GROUPED_TILES takes 128 while M <= 384 G) */
+       /* the tile kernel with tiles of 256 or 128 rows (AXE_GROUPED_TILES takes 128 while M <= 384 G), in a pair
+        * as well; a pair with AXE_GROUPED_AUTO on both may run on 192 rows (axe_gemm_grouped_pair) */
        AXE_GROUPED_TILES_256 = 3, AXE_GROUPED_TILES_128 = 4 };
 
 /* AXE_EPI_SWIGLU: the gated activation between the two group GEMMs, fused into the first.  The logical
